@@ -1,5 +1,5 @@
-// tANS encoder on the GPU: compresses one layer whose symbols are in device memory into the
-// container anszp_decode reads, word for word what the host packer (anszp_pack_layer) writes.
+// tANS encoder on the GPU: compresses layers whose symbols are in device memory into the container
+// anszp_decode reads, word for word what the host packer (anszp_pack_layer) writes.
 //
 // Encoding (Sec. II-A) walks a stream's symbols backwards: to encode symbol s in state x (in
 // [L, 2L)) the low bits of x are dropped, and written out, until x lies in [f_s, 2 f_s); the new
@@ -9,43 +9,57 @@
 //
 // Three launches, nothing allocated and no scratch memory: sizes (every stream's final state and
 // word count into the stream headers, every chunk's descriptor but for its payload offset), a scan
-// over the chunks (payload offsets, total), the writing pass.  One lane per stream, one wavefront
-// per chunk at a time; every workgroup builds the encoding tables in LDS for itself from the
-// frequencies: the states of a symbol in increasing order are the ranks of its occurrences in the
-// merged position sequences (the spread this library chose; Sec. II-A says only that the rate depends
-// on how the states are initialised), and a rank is a sum of integer quotients.
+// over the chunks (payload offsets, total), the writing pass.  What the writing pass needs to know of
+// the sizes pass beyond that (how many bits of a stream's last word are used) travels in fields that
+// the writing pass puts right: four of the five bits in bits 12..15 of the stream's header (a state has
+// at most 12 bits), the fifth bit of all the chunk's streams as one word in the descriptor's out_offset.
+//
+// One lane per stream, one wavefront per chunk.  A workgroup of eight wavefronts takes up to eight
+// consecutive chunks (as few as leave every CU two workgroups); all of it builds the encoding tables of
+// a layer in LDS (anszp_spread.h), then its wavefronts walk the layer's chunks.
+//
+// What bounds it: a walk is a chain, per symbol one LDS read and three instructions between the state and the next
+// one; a wavefront has its SIMD nearly for itself.  Whether a symbol drops k or k - 1 bits is one addition
+// (x + (k << 16) - (f_s << k): the upper half is the count), symbols are asked for two batches of sixteen
+// ahead, a symbol's constants half a batch ahead.  Measured on 369 chunks of 65,536 symbols (2^12 states, 64
+// streams): sizes 70 us, writing 98 us (54 and 83 ns a symbol, 9 us for the tables); with a search for the bit count
+// bit by bit, symbols waited for batch by batch, a second walk in the writing pass for the stream's bits and the
+// tables by divisions the two took 1.55 ms.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
 
 #include "anszp.h"
+#include "anszp_spread.h"
 
 namespace {
 
 constexpr uint32_t kWave = 64;
-constexpr uint32_t kThreads = 256;
+constexpr uint32_t kThreads = 512;          // two workgroups fit a CU at once (128 registers a lane)
 constexpr uint32_t kWaves = kThreads / kWave;
-constexpr uint32_t kStates = 1u << ANSZP_MAX_TABLE_LOG;
-constexpr uint32_t kBatch = 8;              // symbols a lane asks for at a time
+constexpr uint32_t kBatch = 16;             // symbols a lane asks for at a time
 
 struct EncParams {
     const uint8_t* symbols;
-    const uint32_t* freqs;
+    const uint32_t* freqs;                  // one row of 256 per layer
+    const anszp_pack_job_t* jobs;           // null: one layer, `one`
+    anszp_pack_job_t one;
     anszp_chunk_t* chunks;
     uint32_t* stream_hdr;
     uint32_t* payload;
     unsigned long long* used;
     uint32_t* status;
-    uint64_t n_symbols, n_chunks, out_offset, payload_word_offset, payload_cap_words;
-    uint32_t table_log, n_streams, chunk_size, layer_id, stream_offset;
+    uint64_t n_chunks, out_offset, payload_word_offset, payload_cap_words;
+    uint32_t n_layers, table_log, n_streams, layer_id, stream_offset, chunks_per_group;
 };
 
-struct EncTables {
-    uint32_t f[ANSZP_ALPHABET];
-    uint32_t first[ANSZP_ALPHABET];        // index of the symbol's first state in `states`
-    uint16_t states[kStates];              // the states of each symbol in increasing order
-    uint32_t used_sym[ANSZP_ALPHABET];     // symbols with f > 0, in increasing order
-    uint32_t n_used, total;
+// A layer's encoding tables.  info[s]: what x + info.x has in its upper half is the number of bits symbol s drops
+// in state x; 2 * (x >> that) + info.y is the byte of `next` that holds the new state plus L.  A symbol without a
+// frequency has info.x = 0 (no other symbol has), drops nothing and leads to some state.
+struct EncLds {
+    SpreadLds spread;
+    uint2 info[ANSZP_ALPHABET];
+    uint16_t next[kSpreadStates];
 };
 
 __device__ __forceinline__ void report(uint32_t* status, uint32_t bits) {
@@ -53,169 +67,257 @@ __device__ __forceinline__ void report(uint32_t* status, uint32_t bits) {
     atomicAdd(&status[1], 1u);
 }
 
-__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
-#pragma unroll
-    for (int d = 1; d < int(kWave); d <<= 1) v += __shfl_xor(v, d, kWave);
-    return v;
-}
-
-__device__ __forceinline__ uint32_t wave_exclusive_sum(uint32_t v, uint32_t lane) {
-    uint32_t s = v;
-#pragma unroll
-    for (int d = 1; d < int(kWave); d <<= 1) {
-        const uint32_t t = __shfl_up(s, d, kWave);
-        if (lane >= uint32_t(d)) s += t;
-    }
-    return s - v;
-}
-
 // The workgroup's encoding tables.  False (for every thread) when the frequencies do not sum to L.
-__device__ bool build_tables(const uint32_t* freqs, uint32_t table_log, EncTables& t) {
-    const uint32_t tid = threadIdx.x;
-    const uint32_t L = 1u << table_log;
-    if (tid < ANSZP_ALPHABET) t.f[tid] = freqs[tid];
-    __syncthreads();
-    if (tid == 0) {
-        uint32_t n = 0, acc = 0;
-        for (uint32_t s = 0; s < ANSZP_ALPHABET; ++s) {
-            const uint32_t fs = t.f[s];
-            t.first[s] = min(acc, L);
-            if (fs) t.used_sym[n++] = s;
-            acc = min(acc + min(fs, L + 1u), L + 1u);           // saturating
-        }
-        t.n_used = n;
-        t.total = acc;
-    }
-    __syncthreads();
-    if (t.total != L) return false;
-    const uint32_t used = t.n_used;
-    // occurrence i of symbol s sits at (2i + 1) / (2 f_s) (Sec. II-A), ties going to the smaller symbol: its
-    // rank among all occurrences is i plus, for every other symbol, the number of its occurrences before it
-    for (uint32_t g = tid; g < L; g += kThreads) {
-        uint32_t lo = 0, hi = used;                              // first[used_sym[lo]] <= g
-        while (hi - lo > 1u) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (t.first[t.used_sym[mid]] <= g) lo = mid; else hi = mid;
-        }
-        const uint32_t s = t.used_sym[lo], fs = t.f[s], i = g - t.first[s];
-        uint32_t rank = i;
-        for (uint32_t k = 0; k < used; ++k) {
-            if (k == lo) continue;
-            const uint32_t fo = t.f[t.used_sym[k]];
-            const int32_t q = static_cast<int32_t>((2u * i + 1u) * fo) - static_cast<int32_t>(fs);   // below 2^26
-            uint32_t before;
-            if (k < lo) before = q < 0 ? 0u : static_cast<uint32_t>(q) / (2u * fs) + 1u;
-            else before = q <= 0 ? 0u : (static_cast<uint32_t>(q) + 2u * fs - 1u) / (2u * fs);
-            rank += min(before, fo);
-        }
-        t.states[g] = static_cast<uint16_t>(rank);
+__device__ __forceinline__ bool build_tables(const uint32_t* freqs, uint32_t table_log, EncLds& t) {
+    const uint32_t tid = threadIdx.x, L = 1u << table_log;
+    const bool ok = spread_states<kThreads>(freqs, table_log, t.spread, [&](uint32_t g, uint32_t, uint32_t, uint32_t, uint32_t state) {
+        t.next[g] = static_cast<uint16_t>(L + state);
+    });
+    if (!ok) return false;
+    if (tid < ANSZP_ALPHABET) {
+        const uint32_t f = t.spread.f[tid];
+        // x in [L, 2L) drops k or k - 1 bits, k = table_log - floor(log2 f): k when x >= f << k
+        const uint32_t k = f ? table_log - (31u - static_cast<uint32_t>(__clz(f))) : 0u;
+        t.info[tid] = f ? make_uint2((k << 16) - (f << k), 2u * (t.spread.first[tid] - f)) : make_uint2(0u, 0u - 2u * L);
     }
     __syncthreads();
     return true;
 }
 
-// One stream, backwards (Sec. II-A).  WRITE: lay the bits down in `words` (the stream's n_words words);
-// otherwise only count them.  Returns the number of bits; x_out: the final state plus L.
+// A chunk's streams as its wavefront walks them: symbol number r of this lane's stream is chunk[r * n_streams + lane_off].
+typedef const __attribute__((address_space(1))) uint8_t global_uint8_t;   // (a flat load would be waited for with the LDS reads)
+struct ChunkStreams {
+    global_uint8_t* chunk;                                      // uniform
+    uint32_t cn, max_len;                                       // symbols of the chunk, of its longest stream (uniform)
+    uint32_t lane_off;                                          // 0 for a lane without symbols: it walks along, never counted
+    bool has_any, has_last;                                     // any symbol; one in row max_len - 1 (every lane has all rows before it)
+};
+
+// One stream, backwards (Sec. II-A).  WRITE: lay the bits down in `words` (the stream's n_words words, `pad` zero bits
+// behind its last one); otherwise only count them.  Returns the number of bits; x: the final state plus L.
 // The bits a symbol adds precede, in the stream, everything written so far; the stream is therefore built
 // in reverse, padded at its start so that whole reversed words are whole words of the stream, and each
 // finished word is bit-reversed into its place, from the stream's last word down to its first.
 template <bool WRITE>
-__device__ uint32_t walk_stream(const EncParams& p, const EncTables& t, uint64_t begin, uint32_t cn, uint32_t k,
-                                uint32_t* words, uint32_t n_words, uint32_t n_bits, uint32_t& x_out, bool& bad_symbol) {
-    const uint32_t N = p.n_streams, L = 1u << p.table_log;
-    const uint32_t len = (k < N && cn > k) ? (cn - k + N - 1u) / N : 0u;
-    uint32_t x = L, bits = 0;
+__device__ __forceinline__ uint32_t walk_stream(const EncLds& t, const ChunkStreams& s, uint32_t N, uint32_t L, uint32_t* words, uint32_t n_words,
+                                uint32_t pad, uint32_t& x_out, bool& bad_symbol) {
+    uint32_t x = L, bits = 0, lowest = 0xFFFFFFFFu;           // lowest: the smallest info.x met
     uint64_t acc = 0;
-    uint32_t cnt = WRITE ? 32u * n_words - n_bits : 0u;       // zero bits behind the stream's last bit
-    uint32_t at = n_words;                                    // words still to be written
-    for (uint32_t hi = len; hi > 0;) {
-        const uint32_t batch = min(hi, kBatch);
-        uint32_t sym[kBatch];
+    uint32_t pair = 0, pair_bits = 0;                         // the bits of the last two symbols, on their way into acc
+    uint32_t cnt = pad, at = n_words;                         // bits in acc; words still to be written
+    const uint8_t* next = reinterpret_cast<const uint8_t*>(t.next);
+    constexpr uint32_t kHalf = kBatch / 2u;
+    auto load = [&](uint32_t hi, uint32_t (&sym)[kBatch]) {   // rows hi - 1, hi - 2, ... (hi >= kBatch)
+        global_uint8_t* const row = s.chunk + uint64_t(hi - kBatch) * N;
 #pragma unroll
-        for (uint32_t j = 0; j < kBatch; ++j)                  // from a clamped, valid index: no load under a condition
-            sym[j] = p.symbols[begin + k + uint64_t(hi - 1u - min(j, batch - 1u)) * N];
+        for (uint32_t j = 0; j < kBatch; ++j) sym[j] = (row + (kBatch - 1u - j) * N)[s.lane_off];
+    };
+    auto look_up = [&](const uint32_t (&sym)[kBatch], uint32_t from, uint2 (&info)[kHalf]) {
 #pragma unroll
-        for (uint32_t j = 0; j < kBatch; ++j) {
-            if (j < batch) {
-                const uint32_t s = sym[j], fs = t.f[s];
-                if (fs == 0) { bad_symbol = true; continue; }
-                uint32_t drop = 0;
-                while ((x >> drop) >= 2u * fs) ++drop;          // bring x into [f_s, 2 f_s)
-                if (WRITE) {
-                    acc |= uint64_t(x & ((1u << drop) - 1u)) << cnt;
-                    cnt += drop;
-                    if (cnt >= 32u) {
-                        if (at) words[--at] = __brev(static_cast<uint32_t>(acc));
-                        acc >>= 32;
-                        cnt -= 32u;
-                    }
-                }
-                bits += drop;
-                x = L + t.states[t.first[s] + (x >> drop) - fs];
+        for (uint32_t j = 0; j < kHalf; ++j) info[j] = t.info[sym[from + j]];
+    };
+    auto step = [&](const uint2 i) {
+        const uint32_t sum = x + i.x, nb = sum >> 16;
+        lowest = min(lowest, i.x);
+        if constexpr (WRITE) {
+            pair |= __builtin_amdgcn_ubfe(x, 0u, nb) << pair_bits;
+            pair_bits += nb;
+        } else {
+            bits += nb;
+        }
+        uint32_t kept;                                        // x >> nb, the count taken from the sum's upper half as it is
+        asm("v_lshrrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:DWORD" : "=v"(kept) : "v"(sum), "v"(x));
+        x = *reinterpret_cast<const uint16_t*>(next + (2u * kept + i.y));
+    };
+    auto flush = [&]() {                                      // at least every two symbols: 24 bits, and 31 + 24 of them, fit
+        if constexpr (WRITE) {
+            acc |= uint64_t(pair) << cnt;
+            cnt += pair_bits;
+            pair = pair_bits = 0u;
+            if (cnt >= 32u) {
+                if (at) words[--at] = __brev(static_cast<uint32_t>(acc));
+                acc >>= 32;
+                cnt -= 32u;
             }
         }
-        hi -= batch;
+    };
+    auto walk = [&](const uint2 (&info)[kHalf]) {
+#pragma unroll
+        for (uint32_t j = 0; j < kHalf; ++j) {
+            step(info[j]);
+            if (j & 1u) flush();
+        }
+    };
+    // the first batch makes the number of symbols left a multiple of a batch; only its first symbol may be missing
+    // in a lane
+    const uint32_t top = (s.max_len - 1u) % kBatch + 1u;
+    uint32_t hi = s.max_len - top;                            // rows still to be asked for: a multiple of kBatch from here on
+    uint32_t sym_a[kBatch], sym_b[kBatch] = {};
+    uint2 info_0[kHalf], info_1[kHalf];
+    sym_a[0] = s.chunk[(s.has_last ? (s.max_len - 1u) * N : 0u) + s.lane_off];
+#pragma unroll
+    for (uint32_t j = 1; j < kBatch; ++j) sym_a[j] = (s.chunk + (j < top ? uint64_t(s.max_len - 1u - j) * N : 0u))[s.lane_off];
+    uint32_t left = hi;                                       // rows still to be walked behind the first batch
+    if (hi) { load(hi, sym_b); hi -= kBatch; }
+    look_up(sym_a, 0u, info_0);
+    look_up(sym_a, kHalf, info_1);
+    if (hi) { load(hi, sym_a); hi -= kBatch; }
+    if (s.has_last) step(info_0[0]);
+#pragma unroll
+    for (uint32_t j = 1; j < kBatch; ++j) {
+        if (j < top) step(j < kHalf ? info_0[j % kHalf] : info_1[j % kHalf]);         // (uniform)
+        if (j & 1u) flush();
     }
+    // a batch: the first half's constants are in info_0; `sym` holds the batch, `then` the one after it
+    auto batch = [&](uint32_t (&sym)[kBatch], uint32_t (&then)[kBatch]) {
+        look_up(sym, kHalf, info_1);
+        if (hi) { load(hi, sym); hi -= kBatch; }
+        walk(info_0);
+        look_up(then, 0u, info_0);                            // (behind the last batch: symbols walked before, not used)
+        walk(info_1);
+        left -= kBatch;
+    };
+    look_up(sym_b, 0u, info_0);
+    while (left) {
+        batch(sym_b, sym_a);
+        if (!left) break;
+        batch(sym_a, sym_b);
+    }
+    if (lowest == 0u) bad_symbol = true;
     x_out = x;
     return bits;
 }
 
-__global__ __launch_bounds__(kThreads) void encode_sizes(EncParams p) {
-    __shared__ EncTables t;
-    if (!build_tables(p.freqs, p.table_log, t)) {
-        if (threadIdx.x == 0 && blockIdx.x == 0) report(p.status, ANSZP_ST_BAD_FREQ);
-        return;
+// The layer chunk c belongs to (jobs are in chunk order: the last one whose first_chunk is not beyond c) and the
+// chunk's number within it.  False when c belongs to no layer.
+__device__ bool layer_of_chunk(const EncParams& p, uint64_t c, uint32_t& layer, anszp_pack_job_t& job, uint64_t& local) {
+    layer = 0;
+    if (!p.jobs) {
+        job = p.one;
+    } else {
+        uint32_t lo = 0, hi = p.n_layers;
+        if (hi == 0 || p.jobs[0].first_chunk > c) return false;
+        while (hi - lo > 1u) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (p.jobs[mid].first_chunk <= c) lo = mid; else hi = mid;
+        }
+        layer = lo;
+        job = p.jobs[lo];
     }
-    const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    local = c - job.first_chunk;
+    return job.chunk_size != 0 && local < (job.n_symbols + job.chunk_size - 1) / job.chunk_size;
+}
+
+// What both passes do with a workgroup's chunks: run after run of chunks of one layer, the layer's tables, then
+// chunk(job, layer, local, c, tables_ok) by one wavefront per chunk; none(c) by all threads for a chunk of no layer.
+template <class CHUNK, class NONE>
+__device__ __forceinline__ void for_each_chunk(const EncParams& p, EncLds& t, CHUNK&& chunk, NONE&& none) {
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint64_t c = uint64_t(blockIdx.x) * p.chunks_per_group;
+    const uint64_t end = min(c + p.chunks_per_group, (unsigned long long)p.n_chunks);
+    while (c < end) {                                           // (alike for every thread)
+        uint32_t layer;
+        anszp_pack_job_t job;
+        uint64_t local;
+        if (!layer_of_chunk(p, c, layer, job, local)) {
+            none(c);
+            ++c;
+            continue;
+        }
+        uint64_t run = (job.n_symbols + job.chunk_size - 1) / job.chunk_size - local;   // chunks of this layer from c on
+        if (p.jobs && layer + 1u < p.n_layers && p.jobs[layer + 1u].first_chunk > c) run = min(run, (unsigned long long)(p.jobs[layer + 1u].first_chunk - c));
+        run = min(run, (unsigned long long)(end - c));
+        const bool ok = build_tables(p.freqs + size_t(layer) * ANSZP_ALPHABET, p.table_log, t);
+        for (uint64_t i = wave; i < run; i += kWaves) chunk(job, layer, local + i, c + i, ok);
+        c += run;
+        // (behind the last run a wavefront is done as soon as its own chunks are: the registers of the idle ones let the
+        // next workgroup onto the CU)
+        if (c < end) __syncthreads();                           // the tables have been read
+    }
+}
+
+__device__ __forceinline__ ChunkStreams streams_of(const EncParams& p, const anszp_pack_job_t& job, uint64_t local, uint32_t lane) {
+    ChunkStreams s;
+    const uint32_t N = p.n_streams;
+    const uint64_t begin = local * job.chunk_size, rest = job.n_symbols - begin;
+    s.cn = __builtin_amdgcn_readfirstlane(rest < job.chunk_size ? static_cast<uint32_t>(rest) : job.chunk_size);
+    s.max_len = (s.cn - 1u) / N + 1u;
+    s.has_any = lane < N && lane < s.cn;
+    s.has_last = s.has_any && (s.cn - lane - 1u) / N + 1u == s.max_len;
+    s.lane_off = s.has_any ? lane : 0u;
+    const uintptr_t at = reinterpret_cast<uintptr_t>(p.symbols) + job.first_symbol + begin;
+    s.chunk = reinterpret_cast<global_uint8_t*>(uintptr_t(uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(at)))) |
+                                               uintptr_t(uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(at >> 32)))) << 32);
+    return s;
+}
+
+__global__ __launch_bounds__(kThreads, 4) void encode_sizes(EncParams p) {
+    __shared__ EncLds t;
+    const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t N = p.n_streams, L = 1u << p.table_log;
-    for (uint64_t c = uint64_t(blockIdx.x) * kWaves + wave; c < p.n_chunks; c += uint64_t(gridDim.x) * kWaves) {
-        const uint64_t begin = c * p.chunk_size;
-        const uint64_t rest = p.n_symbols - begin;
-        const uint32_t cn = rest < p.chunk_size ? static_cast<uint32_t>(rest) : p.chunk_size;
-        uint32_t x = L;
+    for_each_chunk(p, t, [&](const anszp_pack_job_t& job, uint32_t layer, uint64_t local, uint64_t c, bool ok) {
+        if (!ok && lane == 0 && local == 0) report(p.status, ANSZP_ST_BAD_FREQ);
+        if (!ok && !p.jobs) return;                             // (one layer: nothing is written)
+        const ChunkStreams s = streams_of(p, job, local, lane);
+        uint32_t x = L, nw = 0, bits = 0;
         bool bad = false;
-        const uint32_t bits = walk_stream<false>(p, t, begin, cn, lane, nullptr, 0u, 0u, x, bad);
-        const uint32_t nw = (bits + 31u) >> 5;
+        if (ok) {
+            bits = walk_stream<false>(t, s, N, L, nullptr, 0u, 0u, x, bad);
+            if (!s.has_any) { bits = 0; x = L; bad = false; }   // no stream, or one without symbols
+            nw = (bits + 31u) >> 5;
+        }
         const bool too_long = nw > 0xFFFFu;
-        if (lane < N) p.stream_hdr[c * N + lane] = (x - L) | (min(nw, 0xFFFFu) << 16);
-        const uint32_t chunk_words = wave_sum(lane < N ? min(nw, 0xFFFFu) : 0u);
+        nw = min(nw, 0xFFFFu);
+        // (bits 12..15 and out_offset: how many bits there are beyond whole words, for the writing pass)
+        const uint64_t fifth = __ballot((bits & 16u) != 0u);
+        if (lane < N) p.stream_hdr[c * N + lane] = (x - L) | (bits & 15u) << 12 | nw << 16;
+        const uint32_t chunk_words = __builtin_amdgcn_readlane(spread_wave_sum(nw), kWave - 1);
         if (__ballot(bad) && lane == 0) report(p.status, ANSZP_ST_BAD_SYMBOL);
         if (__ballot(too_long) && lane == 0) report(p.status, ANSZP_ST_NO_SPACE);
         if (lane == 0) {
             anszp_chunk_t d;
-            d.layer_id = p.layer_id;
-            d.n_symbols = cn;
-            d.out_offset = p.out_offset + begin;
+            d.layer_id = p.jobs ? layer : p.layer_id;
+            d.n_symbols = ok ? s.cn : 0u;
+            d.out_offset = ok ? fifth : job.first_symbol + local * job.chunk_size;
             d.payload_offset = 0;                               // by the scan
             d.payload_words = chunk_words;
             d.stream_offset = p.stream_offset + static_cast<uint32_t>(c) * N;
             p.chunks[c] = d;
         }
-    }
+    }, [&](uint64_t c) {                                        // the jobs do not cover the chunks the caller counted
+        if (threadIdx.x == 0) {
+            report(p.status, ANSZP_ST_BAD_DESC);
+            anszp_chunk_t d = {};
+            p.chunks[c] = d;
+        }
+        if (threadIdx.x < N) p.stream_hdr[c * N + threadIdx.x] = 0u;
+    });
 }
 
-// Payload offsets: every chunk starts on a multiple of four words.  One workgroup, chunks in order.
+// Payload offsets: every chunk starts on a multiple of four words.  One workgroup, chunks in order, as many at a time
+// as it has threads.
 __global__ __launch_bounds__(kThreads) void encode_scan(EncParams p) {
-    __shared__ unsigned long long part[kThreads];
-    __shared__ unsigned long long carry;
-    const uint32_t tid = threadIdx.x;
-    if (tid == 0) carry = 0;
-    __syncthreads();
-    for (uint64_t base = 0; base < p.n_chunks; base += kThreads) {
+    __shared__ unsigned long long part[2][kWaves];
+    const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+    unsigned long long carry = 0;
+    for (uint64_t base = 0, turn = 0; base < p.n_chunks; base += kThreads, ++turn) {
         const uint64_t c = base + tid;
-        const unsigned long long mine = c < p.n_chunks ? ((unsigned long long)(p.chunks[c].payload_words) + 3ull) & ~3ull : 0ull;
-        part[tid] = mine;
-        __syncthreads();
-        for (uint32_t d = 1; d < kThreads; d <<= 1) {           // inclusive scan
-            const unsigned long long v = tid >= d ? part[tid - d] : 0ull;
-            __syncthreads();
-            part[tid] += v;
-            __syncthreads();
+        unsigned long long mine = c < p.n_chunks ? ((unsigned long long)(p.chunks[c].payload_words) + 3ull) & ~3ull : 0ull;
+        unsigned long long upto = mine;
+#pragma unroll
+        for (int d = 1; d < int(kWave); d <<= 1) {
+            const unsigned long long v = __shfl_up(upto, d, kWave);
+            if (lane >= uint32_t(d)) upto += v;
         }
-        if (c < p.n_chunks) p.chunks[c].payload_offset = p.payload_word_offset + carry + part[tid] - mine;
+        if (lane == kWave - 1) part[turn & 1][wave] = upto;     // (two rows: one barrier per turn)
         __syncthreads();
-        if (tid == kThreads - 1) carry += part[tid];
-        __syncthreads();
+        unsigned long long before = carry;
+        for (uint32_t w = 0; w < kWaves; ++w) {
+            const unsigned long long v = part[turn & 1][w];
+            if (w < wave) before += v;
+            carry += v;
+        }
+        if (c < p.n_chunks) p.chunks[c].payload_offset = p.payload_word_offset + before + upto - mine;
     }
     if (tid == 0) {
         *p.used = carry;
@@ -223,128 +325,50 @@ __global__ __launch_bounds__(kThreads) void encode_scan(EncParams p) {
     }
 }
 
-__global__ __launch_bounds__(kThreads) void encode_write(EncParams p) {
-    __shared__ EncTables t;
-    if (!build_tables(p.freqs, p.table_log, t)) return;          // reported by the first pass
-    const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+__global__ __launch_bounds__(kThreads, 4) void encode_write(EncParams p) {
+    __shared__ EncLds t;
+    const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t N = p.n_streams, L = 1u << p.table_log;
-    for (uint64_t c = uint64_t(blockIdx.x) * kWaves + wave; c < p.n_chunks; c += uint64_t(gridDim.x) * kWaves) {
+    for_each_chunk(p, t, [&](const anszp_pack_job_t& job, uint32_t, uint64_t local, uint64_t c, bool ok) {
+        if (!ok) return;                                        // reported by the first pass
+        const ChunkStreams s = streams_of(p, job, local, lane);
         const anszp_chunk_t d = p.chunks[c];
+        const uint32_t hdr = lane < N ? p.stream_hdr[c * N + lane] : 0u;
+        const uint32_t nw = hdr >> 16;
+        const uint32_t beyond = ((hdr >> 12) & 15u) | ((d.out_offset >> lane) & 1u ? 16u : 0u);   // bits of the last word, 0: all
+        if (lane < N) p.stream_hdr[c * N + lane] = hdr & 0xFFFF0FFFu;
+        if (lane == 0) p.chunks[c].out_offset = p.out_offset + job.first_symbol + local * job.chunk_size;
         const uint64_t at = d.payload_offset - p.payload_word_offset;          // in the caller's payload region
         const uint64_t padded = (uint64_t(d.payload_words) + 3ull) & ~3ull;
-        if (at > p.payload_cap_words || padded > p.payload_cap_words - at) continue;   // no room: reported by the scan
-        const uint64_t begin = c * p.chunk_size;
-        const uint32_t nw = lane < N ? p.stream_hdr[c * N + lane] >> 16 : 0u;
-        uint32_t* words = p.payload + at + wave_exclusive_sum(nw, lane);
-        uint32_t x = L;
+        if (at > p.payload_cap_words || padded > p.payload_cap_words - at) return;     // no room: reported by the scan
+        uint32_t* words = p.payload + at + (spread_wave_sum(nw) - nw);
+        uint32_t x = L, room = nw;
         bool bad = false;
-        const uint32_t bits = walk_stream<false>(p, t, begin, d.n_symbols, lane, nullptr, 0u, 0u, x, bad);
-        if (((bits + 31u) >> 5) == nw)                             // (a stream too long for its header is not written)
-            walk_stream<true>(p, t, begin, d.n_symbols, lane, words, nw, bits, x, bad);
-        if (lane < padded - d.payload_words) p.payload[at + d.payload_words + lane] = 0u;   // up to three pad words
-    }
-}
-
-// ---- a whole set of layers in three launches.  One workgroup per chunk: all of it builds the chunk's layer's
-// tables, its first wavefront walks the chunk's streams.
-struct BatchParams {
-    EncParams p;                       // what all layers share (symbols: the set's first symbol; freqs: the first row)
-    const anszp_pack_job_t* jobs;
-    uint32_t n_layers;
-};
-
-// The layer of chunk c (jobs are in chunk order: the last one whose first_chunk is not beyond c), as EncParams
-// of that layer alone; local: the chunk's number within its layer.  False when c belongs to no layer.
-__device__ bool layer_of_chunk(const BatchParams& b, uint64_t c, EncParams& q, uint64_t& local) {
-    uint32_t lo = 0, hi = b.n_layers;
-    if (hi == 0 || b.jobs[0].first_chunk > c) return false;
-    while (hi - lo > 1u) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (b.jobs[mid].first_chunk <= c) lo = mid; else hi = mid;
-    }
-    const anszp_pack_job_t j = b.jobs[lo];
-    local = c - j.first_chunk;
-    if (j.chunk_size == 0 || local >= (j.n_symbols + j.chunk_size - 1) / j.chunk_size) return false;
-    q = b.p;
-    q.symbols = b.p.symbols + j.first_symbol;
-    q.freqs = b.p.freqs + size_t(lo) * ANSZP_ALPHABET;
-    q.n_symbols = j.n_symbols;
-    q.chunk_size = j.chunk_size;
-    q.layer_id = lo;
-    q.out_offset = j.first_symbol;
-    return true;
-}
-
-__global__ __launch_bounds__(kThreads) void encode_sizes_batch(BatchParams b) {
-    __shared__ EncTables t;
-    const uint64_t c = blockIdx.x;
-    EncParams q;
-    uint64_t local;
-    const bool mine = layer_of_chunk(b, c, q, local);           // (alike for every thread)
-    if (!mine) {
-        if (threadIdx.x == 0) {
-            report(b.p.status, ANSZP_ST_BAD_DESC);               // the jobs do not cover the chunks the caller counted
-            anszp_chunk_t d = {};
-            b.p.chunks[c] = d;
+        if (__ballot(nw == 0xFFFFu) != 0ull) {                  // a stream too long for its header is not written
+            const uint32_t bits = walk_stream<false>(t, s, N, L, nullptr, 0u, 0u, x, bad);
+            if (((bits + 31u) >> 5) != nw) room = 0u;
         }
-        if (threadIdx.x < b.p.n_streams) b.p.stream_hdr[c * b.p.n_streams + threadIdx.x] = 0u;
-        return;
-    }
-    const bool tables_ok = build_tables(q.freqs, q.table_log, t);
-    const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-    if (wave != 0) return;
-    const uint32_t N = q.n_streams, L = 1u << q.table_log;
-    const uint64_t begin = local * q.chunk_size;
-    const uint64_t rest = q.n_symbols - begin;
-    const uint32_t cn = rest < q.chunk_size ? static_cast<uint32_t>(rest) : q.chunk_size;
-    uint32_t x = L, nw = 0;
-    bool bad = false, too_long = false;
-    if (tables_ok) {
-        const uint32_t bits = walk_stream<false>(q, t, begin, cn, lane, nullptr, 0u, 0u, x, bad);
-        nw = (bits + 31u) >> 5;
-        too_long = nw > 0xFFFFu;
-    } else if (lane == 0 && local == 0) {
-        report(q.status, ANSZP_ST_BAD_FREQ);
-    }
-    if (lane < N) q.stream_hdr[c * N + lane] = (x - L) | (min(nw, 0xFFFFu) << 16);
-    const uint32_t chunk_words = wave_sum(lane < N ? min(nw, 0xFFFFu) : 0u);
-    if (__ballot(bad) && lane == 0) report(q.status, ANSZP_ST_BAD_SYMBOL);
-    if (__ballot(too_long) && lane == 0) report(q.status, ANSZP_ST_NO_SPACE);
-    if (lane == 0) {
-        anszp_chunk_t d;
-        d.layer_id = q.layer_id;
-        d.n_symbols = tables_ok ? cn : 0u;
-        d.out_offset = q.out_offset + begin;
-        d.payload_offset = 0;                                   // by the scan
-        d.payload_words = chunk_words;
-        d.stream_offset = static_cast<uint32_t>(c) * N;
-        q.chunks[c] = d;
-    }
+        if (!s.has_any) room = 0u;
+        walk_stream<true>(t, s, N, L, words, room, (32u - beyond) & 31u, x, bad);
+        if (lane < padded - d.payload_words) p.payload[at + d.payload_words + lane] = 0u;   // up to three pad words
+    }, [&](uint64_t) {});                                       // reported by the first pass
 }
 
-__global__ __launch_bounds__(kThreads) void encode_write_batch(BatchParams b) {
-    __shared__ EncTables t;
-    const uint64_t c = blockIdx.x;
-    EncParams q;
-    uint64_t local;
-    if (!layer_of_chunk(b, c, q, local)) return;                 // reported by the first pass
-    if (!build_tables(q.freqs, q.table_log, t)) return;
-    const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-    if (wave != 0) return;
-    const uint32_t N = q.n_streams, L = 1u << q.table_log;
-    const anszp_chunk_t d = q.chunks[c];
-    const uint64_t at = d.payload_offset;
-    const uint64_t padded = (uint64_t(d.payload_words) + 3ull) & ~3ull;
-    if (at > q.payload_cap_words || padded > q.payload_cap_words - at) return;     // no room: reported by the scan
-    const uint64_t begin = local * q.chunk_size;
-    const uint32_t nw = lane < N ? q.stream_hdr[c * N + lane] >> 16 : 0u;
-    uint32_t* words = q.payload + at + wave_exclusive_sum(nw, lane);
-    uint32_t x = L;
-    bool bad = false;
-    const uint32_t bits = walk_stream<false>(q, t, begin, d.n_symbols, lane, nullptr, 0u, 0u, x, bad);
-    if (((bits + 31u) >> 5) == nw)                               // (a stream too long for its header is not written)
-        walk_stream<true>(q, t, begin, d.n_symbols, lane, words, nw, bits, x, bad);
-    if (lane < padded - d.payload_words) q.payload[at + d.payload_words + lane] = 0u;   // up to three pad words
+// Chunks per workgroup: one as long as every CU gets no more than two (a walk is a chain: the fewer wavefronts share a
+// SIMD the better), then as many as keep it at two, so that a layer's tables are built by few workgroups; no more
+// than a workgroup has wavefronts.
+uint32_t chunks_per_group(uint64_t n_chunks) {
+    const uint64_t want = (n_chunks + 511u) / 512u;
+    return uint32_t(want < 1u ? 1u : want > kWaves ? kWaves : want);
+}
+
+int launch(EncParams& p, hipStream_t s) {
+    p.chunks_per_group = chunks_per_group(p.n_chunks);
+    const uint64_t groups = (p.n_chunks + p.chunks_per_group - 1u) / p.chunks_per_group;
+    if (groups) hipLaunchKernelGGL(encode_sizes, dim3(uint32_t(groups)), dim3(kThreads), 0, s, p);
+    hipLaunchKernelGGL(encode_scan, dim3(1), dim3(kThreads), 0, s, p);
+    if (groups) hipLaunchKernelGGL(encode_write, dim3(uint32_t(groups)), dim3(kThreads), 0, s, p);
+    return hipGetLastError() == hipSuccess ? ANSZP_OK : ANSZP_E_HIP;
 }
 
 }  // namespace
@@ -360,17 +384,13 @@ extern "C" int anszp_pack_layers_device(const uint8_t* symbols_dev, const anszp_
     if (table_log < 1 || table_log > ANSZP_MAX_TABLE_LOG || n_streams < 1 || n_streams > ANSZP_MAX_STREAMS ||
         n_chunks >= (1ull << 31) || uint64_t(n_chunks) * uint64_t(n_streams) >= (1ull << 32) || (n_chunks && n_layers == 0))
         return ANSZP_E_RANGE;
-    BatchParams b{};
-    b.p.symbols = symbols_dev; b.p.freqs = freqs_dev; b.p.chunks = chunks_dev; b.p.stream_hdr = stream_hdr_dev;
-    b.p.payload = payload_dev; b.p.used = reinterpret_cast<unsigned long long*>(payload_words_used_dev); b.p.status = status_dev;
-    b.p.n_chunks = n_chunks; b.p.payload_word_offset = 0; b.p.payload_cap_words = payload_cap_words;
-    b.p.table_log = uint32_t(table_log); b.p.n_streams = uint32_t(n_streams);
-    b.jobs = jobs_dev; b.n_layers = n_layers;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    if (n_chunks) hipLaunchKernelGGL(encode_sizes_batch, dim3(uint32_t(n_chunks)), dim3(kThreads), 0, s, b);
-    hipLaunchKernelGGL(encode_scan, dim3(1), dim3(kThreads), 0, s, b.p);
-    if (n_chunks) hipLaunchKernelGGL(encode_write_batch, dim3(uint32_t(n_chunks)), dim3(kThreads), 0, s, b);
-    return hipGetLastError() == hipSuccess ? ANSZP_OK : ANSZP_E_HIP;
+    EncParams p{};
+    p.symbols = symbols_dev; p.freqs = freqs_dev; p.chunks = chunks_dev; p.stream_hdr = stream_hdr_dev;
+    p.payload = payload_dev; p.used = reinterpret_cast<unsigned long long*>(payload_words_used_dev); p.status = status_dev;
+    p.n_chunks = n_chunks; p.payload_cap_words = payload_cap_words;
+    p.table_log = uint32_t(table_log); p.n_streams = uint32_t(n_streams);
+    p.jobs = jobs_dev; p.n_layers = n_layers;
+    return launch(p, static_cast<hipStream_t>(stream));
 }
 
 extern "C" int anszp_pack_layer_device(const uint8_t* symbols_dev, uint64_t n_symbols, const uint32_t* freqs_dev,
@@ -388,16 +408,11 @@ extern "C" int anszp_pack_layer_device(const uint8_t* symbols_dev, uint64_t n_sy
     EncParams p{};
     p.symbols = symbols_dev; p.freqs = freqs_dev; p.chunks = chunks_dev; p.stream_hdr = stream_hdr_dev;
     p.payload = payload_dev; p.used = reinterpret_cast<unsigned long long*>(payload_words_used_dev); p.status = status_dev;
-    p.n_symbols = n_symbols; p.n_chunks = (n_symbols + chunk_size - 1) / chunk_size;
+    p.one.n_symbols = n_symbols; p.one.chunk_size = chunk_size;
+    p.n_chunks = (n_symbols + chunk_size - 1) / chunk_size;
     p.out_offset = out_offset; p.payload_word_offset = payload_word_offset; p.payload_cap_words = payload_cap_words;
-    p.table_log = uint32_t(table_log); p.n_streams = uint32_t(n_streams); p.chunk_size = chunk_size;
+    p.n_layers = 1; p.table_log = uint32_t(table_log); p.n_streams = uint32_t(n_streams);
     p.layer_id = layer_id; p.stream_offset = stream_offset;
     if (p.n_chunks >= (1ull << 32)) return ANSZP_E_RANGE;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    const uint64_t wanted = (p.n_chunks + kWaves - 1) / kWaves;
-    const uint32_t grid = uint32_t(wanted < 1 ? 1 : wanted > 2048 ? 2048 : wanted);
-    hipLaunchKernelGGL(encode_sizes, dim3(grid), dim3(kThreads), 0, s, p);
-    hipLaunchKernelGGL(encode_scan, dim3(1), dim3(kThreads), 0, s, p);
-    hipLaunchKernelGGL(encode_write, dim3(grid), dim3(kThreads), 0, s, p);
-    return hipGetLastError() == hipSuccess ? ANSZP_OK : ANSZP_E_HIP;
+    return launch(p, static_cast<hipStream_t>(stream));
 }

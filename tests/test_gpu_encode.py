@@ -169,3 +169,33 @@ def test_whole_set_error_bits_and_rate(orc):
     st = small[4].cpu().numpy().view(np.uint32)
     assert st[0] & B.ST_NO_SPACE and int(small[3].item()) == len(c.payload)
     assert np.all(small[2].cpu().numpy().view(np.uint32)[len(c.payload) // 2:] == 0xFFFFFFFF)
+
+
+# A walk takes a stream's symbols in batches of sixteen, the first of them short; a workgroup takes several chunks, of
+# several layers, once there are more than 512.  Whole words are compared: no tolerance.
+@pytest.mark.parametrize("rows", [1, 2, 15, 16, 17, 31, 32, 33, 47, 48, 49, 64, 65])
+def test_stream_lengths_around_the_walks_batches(orc, rows):
+    for N, tail in ((64, 0), (64, 1), (64, 63), (5, 2), (1, 0)):      # tail: symbols beyond whole rows, in the last chunk
+        n = 2 * rows * N + (rows - 1) * N + tail
+        _compare(orc, W.tiny(seed=n, n=n, bitwidth=5, table_log=12, p0=0.5).symbols()[0], 12, N, rows * N)
+
+
+@pytest.mark.parametrize("n_layers,n,chunk", [(40, 3001, 192), (3, 65 * 1500, 65), (700, 130, 64)])
+def test_workgroups_of_several_chunks_and_layers(orc, n_layers, n, chunk):
+    layers = [W.tiny(seed=s, n=n - s % 7, bitwidth=2 + s % 7, n_streams=64, chunk_size=chunk, table_log=9, p0=0.4 + 0.01 * (s % 50)).layers[0]
+              for s in range(n_layers)]
+    w = W.Workload("many", layers, 9, 64, chunk, "bf16")
+    from helpers import oracle_encode
+    c = oracle_encode(orc, w)
+    chunks, hdr, payload, used, status = _pack_set(w, c)
+    assert status == (0, 0) and used == len(c.payload) and c.n_chunks > 512
+    assert np.array_equal(chunks["out_offset"][:c.n_chunks], c.chunk_out_off) and np.array_equal(chunks["payload_offset"][:c.n_chunks], c.chunk_payload_off)
+    assert np.array_equal(hdr[:c.n_chunks * 64], c.stream_hdr) and np.array_equal(payload[:used], c.payload)
+
+
+def test_descriptors_and_headers_are_complete_where_the_payload_has_no_room(orc):
+    sym = W.tiny(n=20000, bitwidth=6, table_log=12, p0=0.4).symbols()[0]
+    c = orc.encode_layers([sym], 12, 64, 4096)
+    chunks, hdr, payload, used, status = _pack(sym, c.freqs[0], 12, 64, 4096, payload_cap_words=1500)
+    assert status[0] == B.ST_NO_SPACE and used == len(c.payload) and np.all(payload[1500:] == 0xFFFFFFFF)
+    assert np.array_equal(chunks["out_offset"][:c.n_chunks], c.chunk_out_off) and np.array_equal(hdr[:c.n_chunks * 64], c.stream_hdr)
