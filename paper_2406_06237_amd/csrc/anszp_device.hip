@@ -28,6 +28,7 @@
 // element to be 16-byte aligned; other chunks take the step-wise path inside the same launch.
 #include "anszp.h"
 #include "anszp_layout.h"
+#include "anszp_spread.h"
 
 #include <hip/hip_runtime.h>
 
@@ -1903,110 +1904,71 @@ void decode_merged_small(DecodeParams p) { decode_lookahead<OUT, PER_CHANNEL, Sm
 // Decode tables built on the device (Sec. II-A table, Sec. III-A one table per layer): one workgroup
 // per table, same words as anszp_build_tables_host.
 //
-// The host merges the per-symbol position sequences (this library's choice of spread, which Sec. II-A
-// leaves open: occurrence i of a symbol of frequency f sits at (2i+1)/(2f); ties go to the smaller
-// symbol) with a heap.  Here every occurrence computes its
-// own rank instead: the number of occurrences of every other symbol that come before it, in exact
-// integer arithmetic, is a quotient.  The rank is the state X; the occurrence index gives the
-// sub-state f + i, hence nb_bits and newX; the look-ahead entries then follow the step table in LDS.
+// The host merges the per-symbol position sequences with a heap; here a counting sort gives every occurrence of
+// every symbol its state (anszp_spread.h), the occurrence index gives the sub-state f + i, hence nb_bits and newX;
+// the look-ahead entries then follow the step table in LDS.
 constexpr uint32_t kBuildThreads = 1024u;
 
 __global__ __launch_bounds__(kBuildThreads) void build_tables_kernel(const uint32_t* freqs, int table_log, uint32_t* tables,
                                                                      uint32_t* status) {
     constexpr uint32_t kStates = 1u << ANSZP_MAX_TABLE_LOG;
-    __shared__ uint32_t freq[ANSZP_ALPHABET];           // of every symbol
-    __shared__ uint32_t used_sym[ANSZP_ALPHABET];       // symbols with f > 0, in increasing order
-    __shared__ uint32_t used_first[ANSZP_ALPHABET + 1]; // occurrences of the symbols before each of them
-    __shared__ uint32_t n_used, total, dominant_sym;
-    __shared__ uint8_t st_sym[kStates], st_nb[kStates];
-    __shared__ uint16_t st_newX[kStates];
+    __shared__ SpreadLds spread;
+    __shared__ uint32_t dominant_sym;
+    __shared__ uint32_t triple[kStates];                // newX | nb_bits << 16 | symbol << 24 of every state
     const uint32_t tid = threadIdx.x;
     const uint32_t L = 1u << table_log;
     const uint32_t* f = freqs + size_t(blockIdx.x) * ANSZP_ALPHABET;
     uint32_t* out = tables + size_t(blockIdx.x) * table_stride_words(table_log);
-    if (tid < ANSZP_ALPHABET) freq[tid] = f[tid];
-    __syncthreads();
-    if (tid == 0) {
-        uint32_t n = 0, acc = 0, dom = 0xFFFFFFFFu;
-        for (uint32_t sy = 0; sy < ANSZP_ALPHABET; ++sy) {
-            const uint32_t fs = freq[sy];
-            if (fs > L / 2) dom = sy;
-            if (fs) {
-                used_sym[n] = sy;
-                used_first[n] = acc;
-                ++n;
-            }
-            acc = min(acc + min(fs, L + 1u), L + 1u);   // saturating: a row that overshoots is rejected below
-        }
-        used_first[n] = acc;
-        n_used = n;
-        total = acc;
-        dominant_sym = dom;
-    }
-    __syncthreads();
-    if (total != L) {                                   // not a normalised row: an all-zero table and a status bit
-        for (uint32_t i = tid; i < 8u * L; i += kBuildThreads) out[i] = 0u;
-        if (tid == 0 && status) report(status, ANSZP_ST_BAD_FREQ);
-        return;
-    }
-    const uint32_t used = n_used;
-    for (uint32_t g = tid; g < L; g += kBuildThreads) {
-        // occurrence g in symbol order: symbol used_sym[k], its i-th occurrence
-        uint32_t lo = 0, hi = used;                     // used_first[lo] <= g < used_first[hi]
-        while (hi - lo > 1u) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (used_first[mid] <= g) lo = mid; else hi = mid;
-        }
-        const uint32_t sy = used_sym[lo], fs = freq[sy], i = g - used_first[lo];
-        uint32_t rank = i;
-        for (uint32_t k = 0; k < used; ++k) {
-            if (k == lo) continue;
-            const uint32_t fo = freq[used_sym[k]];
-            // occurrences i' of the other symbol with (2i'+1) fs < (2i+1) fo, or <= when it is the smaller symbol
-            // (all quantities are below 2^26: i < fs <= L, fo <= L <= 4096)
-            const int32_t q = static_cast<int32_t>((2u * i + 1u) * fo) - static_cast<int32_t>(fs);
-            uint32_t before;
-            if (k < lo) before = q < 0 ? 0u : static_cast<uint32_t>(q) / (2u * fs) + 1u;
-            else before = q <= 0 ? 0u : (static_cast<uint32_t>(q) + 2u * fs - 1u) / (2u * fs);
-            rank += min(before, fo);
-        }
+    if (tid == 0) dominant_sym = 0xFFFFFFFFu;
+    const bool ok = spread_states<kBuildThreads>(f, static_cast<uint32_t>(table_log), spread, [&](uint32_t, uint32_t sy, uint32_t fs, uint32_t i, uint32_t rank) {
         // Sec. II-A: sub-state f + i, shifted left until it lies in [L, 2L)
         const uint32_t v = fs + i;
         const uint32_t shift = static_cast<uint32_t>(table_log) - (31u - static_cast<uint32_t>(__clz(v)));
-        st_sym[rank] = static_cast<uint8_t>(sy);
-        st_nb[rank] = static_cast<uint8_t>(shift);
-        st_newX[rank] = static_cast<uint16_t>((v << shift) - L);
+        triple[rank] = ((v << shift) - L) | shift << 16 | sy << 24;
+    });
+    // this workgroup's share of the table (gridDim.y of them build it together)
+    const uint32_t first = blockIdx.y * kBuildThreads + tid, stride = gridDim.y * kBuildThreads;
+    if (!ok) {                                          // not a normalised row: an all-zero table and a status bit
+        for (uint32_t i = first; i < 8u * L; i += stride) out[i] = 0u;
+        if (first == 0 && status) report(status, ANSZP_ST_BAD_FREQ);
+        return;
     }
+    if (tid < ANSZP_ALPHABET && spread.f[tid] > L / 2) dominant_sym = tid;      // at most one
     __syncthreads();
-    // every word the planes below do not fill is zero
-    for (uint32_t i = tid; i < 2u * L; i += kBuildThreads) { out[i] = 0u; if (i < L) out[3u * L + i] = 0u; }
-    __syncthreads();
-    for (uint32_t X = tid; X < L; X += kBuildThreads) {
-        out[table_triples_offset(table_log) + X] = uint32_t(st_newX[X]) | (uint32_t(st_nb[X]) << 16) | (uint32_t(st_sym[X]) << 24);
-        if (L <= 256u) {                                // Sec. II-A: three bytes per state
-            uint8_t* bytes = reinterpret_cast<uint8_t*>(out + table_bytes_offset(table_log));
-            bytes[3u * X] = st_sym[X];
-            bytes[3u * X + 1u] = st_nb[X];
-            bytes[3u * X + 2u] = static_cast<uint8_t>(st_newX[X]);
+    // every word the planes below do not fill is zero (the byte table fills 3 L of the first L words' bytes)
+    for (uint32_t i = first; i < L; i += stride) {
+        const uint32_t t = triple[i];
+        out[table_triples_offset(table_log) + i] = t;
+        out[L + i] = 0u;
+        out[3u * L + i] = 0u;
+        if (L > 256u) {
+            out[i] = 0u;
+        } else {                                        // Sec. II-A: three bytes per state, byte j of the plane is field j % 3 of state j / 3
+            uint32_t word = 0;
+            for (uint32_t j = 4u * i; j < 4u * i + 4u && j < 3u * L; ++j) {
+                const uint32_t e = triple[j / 3u], field = j % 3u;
+                word |= (field == 0u ? e >> 24 : field == 1u ? (e >> 16) & 0xFFu : e & 0xFFu) << 8u * (j & 3u);
+            }
+            out[table_bytes_offset(table_log) + i] = word;
         }
     }
     // look-ahead entries: up to kLookaheadMaxSymbols steps merged into one look-up, indexed by the state and
     // the next bit; a run never passes through state 0 (a stream then always ends where an entry ends)
     const uint32_t dominant = dominant_sym;
-    uint32_t* ahead = out + table_lookahead_offset(table_log);
-    for (uint32_t e = tid; e < 2u * L; e += kBuildThreads) {
+    uint2* ahead = reinterpret_cast<uint2*>(out + table_lookahead_offset(table_log));
+    for (uint32_t e = first; e < 2u * L; e += stride) {
         const uint32_t X = e >> 1, b = e & 1u;
         uint32_t Y = X, count = 0, bits = 0, last_sym = 0, saved_Y = 0, saved_count = 0;
         bool took_b = false, may_take_b = true;
         int32_t base = 0;
         for (;;) {
-            const uint32_t n = st_nb[Y];
+            const uint32_t t = triple[Y], n = (t >> 16) & 0xFFu, newX = t & 0xFFFFu;
             const bool room = count + 1u < kLookaheadMaxSymbols;       // another symbol may follow this one
-            const bool is_dominant = uint32_t(st_sym[Y]) == dominant;
-            if (is_dominant && room && n == 0u && st_newX[Y] != 0u) { ++count; Y = st_newX[Y]; continue; }
-            if (is_dominant && room && n == 1u && !took_b && may_take_b && (uint32_t(st_newX[Y]) | b) != 0u) {
+            const bool is_dominant = t >> 24 == dominant;
+            if (is_dominant && room && n == 0u && newX != 0u) { ++count; Y = newX; continue; }
+            if (is_dominant && room && n == 1u && !took_b && may_take_b && (newX | b) != 0u) {
                 saved_Y = Y; saved_count = count;
-                took_b = true; ++count; Y = uint32_t(st_newX[Y]) | b;
+                took_b = true; ++count; Y = newX | b;
                 continue;
             }
             if (took_b && 1u + n > uint32_t(ANSZP_MAX_TABLE_LOG)) {    // too many bits for one look-up: the 1-bit step is the last
@@ -2014,13 +1976,12 @@ __global__ __launch_bounds__(kBuildThreads) void build_tables_kernel(const uint3
                 continue;
             }
             bits = (took_b ? 1u : 0u) + n;
-            base = int32_t(2u * st_newX[Y]) - (took_b ? int32_t(b << (n + 1u)) : 0);
-            last_sym = st_sym[Y];
+            base = int32_t(2u * newX) - (took_b ? int32_t(b << (n + 1u)) : 0);
+            last_sym = t >> 24;
             ++count;
             break;
         }
-        ahead[2u * e] = lookahead_first_word(bits, count, last_sym, X == 0u);
-        ahead[2u * e + 1u] = lookahead_second_word(base);
+        ahead[e] = make_uint2(lookahead_first_word(bits, count, last_sym, X == 0u), lookahead_second_word(base));
     }
 }
 
@@ -2205,7 +2166,13 @@ int anszp_build_tables_device(const uint32_t* freqs_dev, int n_tables, int table
     if (!freqs_dev || !tables_dev) return ANSZP_E_NULL;
     if (table_log < 1 || table_log > ANSZP_MAX_TABLE_LOG || n_tables < 1) return ANSZP_E_RANGE;
     if (reinterpret_cast<uintptr_t>(tables_dev) & 15) return ANSZP_E_RANGE;
-    hipLaunchKernelGGL(build_tables_kernel, dim3(static_cast<uint32_t>(n_tables)), dim3(kBuildThreads), 0,
+    // Several workgroups per table while the tables alone do not fill the chip (each works out the states for itself and
+    // writes a share of the table); no more than there are rows of kBuildThreads look-ahead entries.  53 tables of 2^12
+    // states: 19 us with four workgroups each, 41 us with one (most of it the chains of steps an entry merges); one
+    // table: 16 us with eight, 36 us with one.
+    const uint32_t rows = std::max(1u, (2u << table_log) / kBuildThreads);
+    const uint32_t shares = std::max(1u, std::min(rows, device_cus() / static_cast<uint32_t>(n_tables)));
+    hipLaunchKernelGGL(build_tables_kernel, dim3(static_cast<uint32_t>(n_tables), shares), dim3(kBuildThreads), 0,
                        static_cast<hipStream_t>(hip_stream), freqs_dev, table_log, tables_dev, status_dev);
     return hipGetLastError() == hipSuccess ? ANSZP_OK : ANSZP_E_HIP;
 }

@@ -1,0 +1,49 @@
+"""Decode tables built on the device equal the host's word for word where the device kernel's split and its counting sort
+change: one and several workgroups per table, equal fractions (flat rows), one occurrence of many symbols, rejected rows."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2406_06237_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows(kind, n, R, rng):
+    L = 1 << R
+    rows = np.zeros((n, 256), dtype=np.uint32)
+    for r in rows:
+        if kind == "flat":                              # every symbol (or state) the same frequency: all fractions are shared
+            k = min(256, L)
+            r[:k] = L // k
+        elif kind == "rare":                            # as many symbols of frequency one as fit beside a dominant one
+            k = min(255, L // 3)
+            r[:k] = 1
+            r[k] = L - k
+        elif kind == "one":
+            r[rng.integers(256)] = L
+        else:
+            c = np.zeros(256, np.uint64)
+            k = int(rng.integers(2, min(256, L) + 1))
+            c[rng.permutation(256)[:k]] = rng.integers(1, 10 ** int(rng.integers(1, 6)), k)
+            r[:] = B.normalize_freqs(c, R)
+    return rows
+
+
+@pytest.mark.parametrize("R", [1, 2, 5, 8, 9, 10, 11, 12])
+@pytest.mark.parametrize("kind,n", [("random", 1), ("random", 5), ("random", 300), ("flat", 2), ("rare", 2), ("one", 2)])
+def test_device_tables_equal_the_hosts(kind, n, R):
+    rows = _rows(kind, n, R, np.random.default_rng(100 * R + n))
+    f = torch.from_numpy(rows.view(np.int32)).to("cuda:0")
+    status = torch.zeros(2, dtype=torch.int32, device="cuda:0")
+    got = B.build_tables_device(f, R, status).cpu().numpy().view(np.uint32).reshape(n, -1)
+    assert np.array_equal(got, B.build_tables_host(rows, R)) and not status.any().item()
+
+
+def test_a_rejected_row_is_reported_once_and_leaves_its_table_zero():
+    rows = _rows("random", 3, 12, np.random.default_rng(1))
+    rows[1, 7] += 1
+    status = torch.zeros(2, dtype=torch.int32, device="cuda:0")
+    got = B.build_tables_device(torch.from_numpy(rows.view(np.int32)).to("cuda:0"), 12, status).cpu().numpy().view(np.uint32).reshape(3, -1)
+    assert not got[1].any() and status.tolist() == [B.ST_BAD_FREQ, 1]
+    assert np.array_equal(got[[0, 2]], B.build_tables_host(rows[[0, 2]], 12))
