@@ -1985,7 +1985,7 @@ __global__ __launch_bounds__(kBuildThreads) void build_tables_kernel(const uint3
     }
 }
 
-// Sec. II-B alone.
+// Sec. II-B alone, one symbol per thread and step: any alignment.
 template <int OUT>
 __global__ __launch_bounds__(256) void dequant_kernel(const uint8_t* sym, uint64_t n, anszp_layer_t lay,
                                                       const float* scales, uint64_t n_scales, void* out) {
@@ -1997,6 +1997,64 @@ __global__ __launch_bounds__(256) void dequant_kernel(const uint8_t* sym, uint64
             scale = ch < n_scales ? scales[ch] : 0.0f;
         }
         store_weight<OUT>(out, i, sym[i], lay.zero_point, scale);
+    }
+}
+
+// The same for fewer than 2^32 symbols, symbols and weights on 16-byte boundaries.  Bound by memory: a thread takes
+// kDequantRun symbols with one load and writes them with 16-byte stores, and the channel is divided out once per run (a
+// 4096 x 11008 matrix to bf16, a scale per row: 22 us = 6.1 TB/s; 56 us with the kernel above).
+constexpr uint32_t kDequantRun = 8u;
+template <int OUT>
+__global__ __launch_bounds__(256) void dequant_runs_kernel(const uint8_t* sym, uint32_t n, anszp_layer_t lay,
+                                                           const float* scales, uint64_t n_scales, void* out) {
+    const uint32_t run = blockIdx.x * 256u + threadIdx.x, first = run * kDequantRun;
+    if (run > (n - 1u) / kDequantRun) return;
+    auto scale_of = [&](uint32_t channel) {
+        const uint64_t ch = lay.scales_offset + channel;
+        return ch < n_scales ? scales[ch] : 0.0f;
+    };
+    uint32_t channel = 0, left = 0xFFFFFFFFu;             // symbols of the channel from `first` on
+    float scale = lay.scale;
+    if (lay.channel_len) {
+        channel = first / lay.channel_len;
+        left = lay.channel_len - (first - channel * lay.channel_len);
+        scale = scale_of(channel);
+    }
+    auto weight = [&](uint32_t q) {                       // the next symbol's
+        if (left == 0u) {
+            scale = scale_of(++channel);
+            left = lay.channel_len;
+        }
+        --left;
+        return dequant(q, lay.zero_point, scale);
+    };
+    if (n - first < kDequantRun) {                        // behind the last whole run
+        for (uint32_t i = first; i < n; ++i) {
+            const float w = weight(sym[i]);
+            if constexpr (OUT == ANSZP_OUT_F32) static_cast<float*>(out)[i] = w;
+            else static_cast<uint16_t*>(out)[i] = static_cast<uint16_t>(bf16_rne(w));
+        }
+        return;
+    }
+    const uint2 q = *reinterpret_cast<const uint2*>(sym + first);
+    float w[kDequantRun];
+    if (left >= kDequantRun) {
+#pragma unroll
+        for (uint32_t j = 0; j < kDequantRun; ++j) w[j] = dequant(((j < 4u ? q.x : q.y) >> 8u * (j & 3u)) & 0xFFu, lay.zero_point, scale);
+    } else {
+#pragma unroll
+        for (uint32_t j = 0; j < kDequantRun; ++j) w[j] = weight(((j < 4u ? q.x : q.y) >> 8u * (j & 3u)) & 0xFFu);
+    }
+    typedef uint32_t out4 __attribute__((ext_vector_type(4)));
+    if constexpr (OUT == ANSZP_OUT_F32) {
+        out4* to = reinterpret_cast<out4*>(static_cast<float*>(out) + first);
+        to[0] = out4{__float_as_uint(w[0]), __float_as_uint(w[1]), __float_as_uint(w[2]), __float_as_uint(w[3])};
+        to[1] = out4{__float_as_uint(w[4]), __float_as_uint(w[5]), __float_as_uint(w[6]), __float_as_uint(w[7])};
+    } else {
+        out4 v;
+#pragma unroll
+        for (uint32_t j = 0; j < 4u; ++j) v[j] = bf16_rne(w[2u * j]) | bf16_rne(w[2u * j + 1u]) << 16;
+        *reinterpret_cast<out4*>(static_cast<uint16_t*>(out) + first) = v;
     }
 }
 
@@ -2219,6 +2277,15 @@ int anszp_dequant_zp(const uint8_t* symbols_dev, uint64_t n, const anszp_layer_t
     if (n == 0) return ANSZP_OK;
     if (!symbols_dev || !out_dev || (layer->channel_len && !scales_dev)) return ANSZP_E_NULL;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    if (n < (1ull << 32) - 256u && ((reinterpret_cast<uintptr_t>(symbols_dev) | reinterpret_cast<uintptr_t>(out_dev)) & 15u) == 0) {
+        const dim3 groups(static_cast<uint32_t>(((n + kDequantRun - 1u) / kDequantRun + 255u) / 256u));
+        const uint32_t m = static_cast<uint32_t>(n);
+        if (out_dtype == ANSZP_OUT_F32)
+            hipLaunchKernelGGL(dequant_runs_kernel<ANSZP_OUT_F32>, groups, dim3(256), 0, s, symbols_dev, m, *layer, scales_dev, n_scales, out_dev);
+        else
+            hipLaunchKernelGGL(dequant_runs_kernel<ANSZP_OUT_BF16>, groups, dim3(256), 0, s, symbols_dev, m, *layer, scales_dev, n_scales, out_dev);
+        return hipGetLastError() == hipSuccess ? ANSZP_OK : ANSZP_E_HIP;
+    }
     const uint64_t want = (n + 255) / 256;
     const dim3 grid(static_cast<uint32_t>(want < 65536 ? want : 65536)), block(256);
     if (out_dtype == ANSZP_OUT_F32)
