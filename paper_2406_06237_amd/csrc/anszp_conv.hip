@@ -46,6 +46,8 @@ constexpr uint32_t kRows = 16;              // output channels per MFMA row tile
 constexpr uint32_t kRowPad = 8;             // bytes between panel rows: rows start two LDS banks apart
 constexpr uint32_t kStageWords = 384;       // per wavefront: LDS room for one chunk's compressed words (2.6 bit per
                                             // weight at 4608 symbols; a larger chunk is read from global memory)
+constexpr uint32_t kStageBytes = kWaves * kStageWords * 4u;          // at the start of LDS; the table's entries follow
+constexpr uint32_t kStageMask = 0xFFFCu;    // whole words in the first 64 KiB of LDS
 constexpr uint32_t kWidenPieces = 7;        // 16-byte pieces of a byte panel one thread widens to bf16
 constexpr uint32_t kPatchTaps = 9;          // kTapsPatch: a 3 x 3 kernel
 constexpr uint32_t kPatchPieces = 4;        // kTapsPatch: 16-byte pieces of a patch per thread
@@ -76,6 +78,8 @@ struct ConvParams {
     uint32_t x_pixel, x_block, y_pixel, y_block;
     uint32_t y_bf16, K, row_stride, n_pixels, n_mtiles;   // n_mtiles: panels of 16 * MR rows
     uint32_t k_magic;                                     // floor(2^32 / K) + 1: i / K = mulhi(i, k_magic) for i * K < 2^32
+    uint32_t k_magic24, stage_words;                      // floor(2^24 / K) + 1: i / K = (i * k_magic24) >> 24 for i * K < 2^24; kStageWords where
+                                                          // that holds for all elements of a chunk (or a chunk is one row), else 0
     uint32_t panel_off;                                   // first byte of the panel in LDS (behind the table and the staging room)
     uint32_t wave_pixels, patch_off, patch_plane;         // kTapsPatch: pixels per wavefront and round (16..64); first byte of the
                                                           // patch; bytes of one of its four planes
@@ -125,19 +129,31 @@ struct ChunkDesc {
     bool ok, staged;             // staged: the chunk's words (and two zero words behind them) fit the wavefront's LDS room
 };
 
+// LDS byte addresses as numbers: a load or store through one is an LDS instruction with the rest of the address in
+// its offset field.
+template <class T>
+__device__ __forceinline__ T lds_load(uint32_t at) { return *reinterpret_cast<const __attribute__((address_space(3))) T*>(static_cast<uintptr_t>(at)); }
+template <class T>
+__device__ __forceinline__ void lds_store(uint32_t at, T v) { *reinterpret_cast<__attribute__((address_space(3))) T*>(static_cast<uintptr_t>(at)) = v; }
+
 // One chunk into the LDS panel: symbol i of the chunk belongs to panel row i / K, column i % K.  One lane per
 // stream (Sec. III-B) walks the automaton of Sec. II-A through the table's look-ahead entries (anszp_layout.h):
 // one look-up stands for up to eight symbols, all but the last the layer's dominant symbol, which the panel
-// already holds everywhere (the caller fills it), so a look-up writes one panel element.  The entry of index
-// 2X + b and the two stream words around the lane's bit position are read together; with T the bits the entry
-// consumes, the next index is base + (the next T + 1 stream bits, first bit most significant) and the bit
-// position moves on by T.  Returns the lane's error bits.
+// already holds everywhere (the caller fills it), so a look-up writes one panel element.  With T the bits the entry
+// of index 2X + b consumes, the next index is base + (the next T + 1 stream bits, first bit most significant) and the
+// bit position moves on by T.  Returns the lane's error bits.
+//
 // The chunk's words were fetched into `d` (16-byte loads issued long before) and go to `stage` (LDS, this
 // wavefront's own) when they fit, so that the loop waits for no global load; a larger chunk is read word by word
-// in place.  P16: the panel holds bf16 values q - z (two bytes per weight) instead of the symbols q.
+// in place.  What a look-up costs is instructions (three wavefronts share a SIMD) and LDS accesses (twelve share the
+// LDS), so the staged words are kept bit-reversed, the first word at the highest address: with c the bits left
+// down from there, words c / 32 + 1 and c / 32 funnel-shifted by c mod 32 are the next 32 stream bits, first bit
+// on top, and they last for two look-ups (2 * 12 + 1 bits).  14 vector instructions and 2.5 LDS accesses a look-up where
+// least significant bits first, a window per look-up and the clamps of every index took 28 and 3.
+// P16: the panel holds bf16 values q - z (two bytes per weight) instead of the symbols q.
 template <bool P16>
-__device__ uint32_t decode_chunk_to_panel(const ConvParams& p, const ChunkDesc& c, const ChunkData& d, const uint8_t* ahead,
-                                          uint32_t ahead_mask, uint32_t* stage, uint8_t* rows, uint32_t lane, int32_t zero_point) {
+__device__ uint32_t decode_chunk_to_panel(const ConvParams& p, const ChunkDesc& c, const ChunkData& d, const uint32_t ahead,
+                                          uint32_t ahead_mask, const uint32_t stage, const uint32_t rows, uint32_t lane, int32_t zero_point) {
     const uint32_t N = p.n_streams;
     const uint32_t L = 1u << p.table_log;
     const uint32_t X0 = d.hdr & (L - 1u);
@@ -146,72 +162,100 @@ __device__ uint32_t decode_chunk_to_panel(const ConvParams& p, const ChunkDesc& 
     const uint32_t first_word = wave_exclusive_sum(n_words, &total_words);
     uint32_t err = (total_words != c.payload_words) ? ANSZP_ST_BAD_DESC : 0u;
 
-    const uint32_t* words = p.payload + c.payload_offset;
     const uint32_t word_limit = c.payload_words;      // reads beyond the chunk see zeros
+    constexpr uint32_t kElem = P16 ? 2u : 1u;
+    const uint32_t n = lane < N ? c.n_symbols : 0u;   // a lane without a stream never runs
+    const float zf = static_cast<float>(zero_point);
+    // (|q - z| <= 255 has at most 8 significant bits: the upper half of its binary32 form is exact)
+    auto put = [&](uint32_t where, uint32_t entry) {
+        if constexpr (P16) lds_store<uint16_t>(where, static_cast<uint16_t>(__float_as_uint(static_cast<float>((entry >> 16) & 0xFFu) - zf) >> 16));
+        else lds_store<uint8_t>(where, static_cast<uint8_t>(entry >> 16));
+    };
+    // where what lies beyond the chunk goes (an entry that would carry a stream past its end: corrupt data only): the
+    // first column of padding behind the chunk's last row
+    const uint32_t beyond = rows + ((p.rows_per_chunk - 1u) * p.row_stride + p.K) * kElem;
+    // what the checks at a stream's end look at: the position behind its last symbol, index * 8 of the next entry, bits read
+    uint32_t ended_at = 0, at = 0, bits_read = 0;
     if (c.staged) {
-        const uint32_t quads = word_limit >> 2;
-        if (lane < quads) *reinterpret_cast<words4*>(stage + 4u * lane) = d.q0;
-        if (lane + kWave < quads) *reinterpret_cast<words4*>(stage + 4u * (lane + kWave)) = d.q1;
+        // word i at top - 4 - 4 * i
+        const uint32_t quads = word_limit >> 2, top = stage + 4u * kStageWords;
+        auto reversed = [](words4 q) { return words4{__brev(q.w), __brev(q.z), __brev(q.y), __brev(q.x)}; };
+        if (lane < quads) lds_store<words4>(top - 16u - 16u * lane, reversed(d.q0));
+        if (lane + kWave < quads) lds_store<words4>(top - 16u - 16u * (lane + kWave), reversed(d.q1));
         const uint32_t tail_at = (quads << 2) + lane;
-        if (lane < 3u && tail_at < word_limit) stage[tail_at] = d.tail;
-        if (lane < 2u) stage[word_limit + lane] = 0u;                // what a stream reads beyond the chunk
+        if (lane < 3u && tail_at < word_limit) lds_store<uint32_t>(top - 4u - 4u * tail_at, __brev(d.tail));
+        if (lane < 2u) lds_store<uint32_t>(top - 4u - 4u * (word_limit + lane), 0u);     // what a stream reads beyond the chunk
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");       // LDS serves a wavefront's accesses in order
         __builtin_amdgcn_wave_barrier();
-    }
-    const uint32_t n = lane < N ? c.n_symbols : 0u;   // a lane without a stream never runs
-    const uint32_t first_bit = first_word << 5;
-    uint32_t bit = first_bit;
-    uint32_t elem = lane;                             // the chunk element of the lane's next symbol
-    // A chunk of one panel row needs no division to find a symbol's row.  An entry that would carry a stream
-    // past its end (corrupt data only: a valid stream ends where an entry ends) writes the chunk's last element.
-    const uint32_t last_elem = c.n_symbols - 1u;
-    constexpr uint32_t kElem = P16 ? 2u : 1u;
-    const uint32_t row_gap_bytes = (p.row_stride - p.K) * kElem;
-    auto walk = [&](auto word_at, auto one_row) {
-        uint32_t at = ((2u * X0 + (word_at(min(first_word, word_limit)) & 1u)) * 8u) & ahead_mask;   // entry 2 X0 + first stream bit
-        bool active = elem < n;
-        if (__ballot(active) != 0) {
-            do {
-                if (active) {
-                    const uint32_t wi = min(bit >> 5, word_limit);
-                    const uint32_t w0 = word_at(wi), w1 = word_at(wi + 1u);
-                    const words2 e = *reinterpret_cast<const words2*>(ahead + at);
-                    const uint32_t window = __builtin_amdgcn_alignbit(w1, w0, bit);
-                    const uint32_t v = __brev(window) >> (e.x & 31u);       // the next T + 1 stream bits
-                    at = (e.y + 8u * v) & ahead_mask;
-                    bit += (e.x >> 24) & 15u;
-                    elem = __umul24((e.x >> 28) & 7u, N) + elem;            // past the entry's dominant symbols
-                    const uint32_t el = min(elem, last_elem);
-                    uint32_t where = el * kElem;                            // byte of the panel rows
-                    if constexpr (!decltype(one_row)::value)
-                        where = __umul24(p.K > 1u ? __umulhi(el, p.k_magic) : el, row_gap_bytes) + where;   // both factors below 2^24
-                    const uint32_t sym = (e.x >> 16) & 0xFFu;
-                    if constexpr (P16) {              // an integer of at most 8 bits: the upper half of its binary32 form is exact
-                        const float w = static_cast<float>(int32_t(sym) - zero_point);
-                        *reinterpret_cast<uint16_t*>(rows + where) = static_cast<uint16_t>(__float_as_uint(w) >> 16);
-                    } else {
-                        rows[where] = static_cast<uint8_t>(sym);
-                    }
-                    elem += N;
-                    active = elem < n;
+        // b bits into the chunk the next 32 bits, first bit on top, are the two words at and above (left / 32) * 4, funnel-
+        // shifted by left mod 32, with left = 8 * top - 32 - b.  (Corrupt data may run on below the staged words: the
+        // mask keeps every address in the first 64 KiB of LDS, which every launch has.)
+        const uint32_t begin = 8u * top - 32u - 32u * min(first_word, word_limit);
+        uint32_t left = begin;
+        at = ((2u * X0 + (lds_load<uint32_t>((begin >> 3) & kStageMask) >> 31)) * 8u) & ahead_mask;     // entry 2 X0 + first stream bit
+        auto walk = [&](auto one_row) {
+            // one row: positions are LDS addresses; several: elements of the chunk, put in their row by a division
+            constexpr bool kOneRow = decltype(one_row)::value;
+            const uint32_t step = kOneRow ? N * kElem : N;
+            const uint32_t end = kOneRow ? rows + n * kElem : n;
+            uint32_t pos = kOneRow ? rows + lane * kElem : lane;
+            const uint32_t gap = (p.row_stride - p.K) * kElem;
+            auto look_up = [&](uint32_t window, words2 e) {          // returns the bits it consumed
+                const uint32_t v = window >> (e.x & 31u);            // the next T + 1 stream bits
+                const uint32_t T = (e.x >> 24) & 15u;
+                at = (e.y + 8u * v) & ahead_mask;
+                pos = __umul24((e.x >> 28) & 7u, step) + pos;        // past the entry's dominant symbols
+                uint32_t where = pos;
+                if constexpr (!kOneRow) {                            // (a chunk's elements times K are below 2^24: see c.staged)
+                    uint32_t row;                                    // pos / K: upper 32 bits of the 48 of (pos << 8) * magic
+                    asm("v_mul_hi_u32_u24 %0, %1, %2" : "=v"(row) : "v"(pos << 8), "v"(p.k_magic24));
+                    where = __umul24(row, gap) + pos * kElem + rows;
                 }
-            } while (__ballot(active) != 0);
-        }
-        // a stream ends where an entry ends, in state 0 (the index of the next entry is 2 X + peeked bit),
-        // having read exactly its words
-        if (lane < N) {
-            // the lane's elements are lane, lane + N, ...: it has produced exactly its symbols if it stands on the
-            // first of them that is no element of the chunk
-            if (elem - c.n_symbols >= N) err |= ANSZP_ST_BAD_LENGTH;
-            if ((at >> 4) != 0u) err |= ANSZP_ST_BAD_STATE;
-            if (((bit - first_bit) + 31u) >> 5 != n_words) err |= ANSZP_ST_BAD_LENGTH;
-        }
-    };
-    if (c.staged) {
-        if (p.rows_per_chunk == 1u) walk([&](uint32_t i) { return stage[i]; }, std::true_type{});
-        else walk([&](uint32_t i) { return stage[i]; }, std::false_type{});
+                put(min(where, beyond), e.x);
+                pos += step;
+                return T;
+            };
+            while (pos < end) {
+                const uint32_t word = (left >> 3) & kStageMask;
+                const uint32_t lo = lds_load<uint32_t>(word), hi = lds_load<uint32_t>(word + 4u);
+                const words2 e = lds_load<words2>(ahead + at);
+                const uint32_t window = __builtin_amdgcn_alignbit(hi, lo, left);
+                const uint32_t T = look_up(window, e);
+                left -= T;
+                if (pos < end) left -= look_up(window << T, lds_load<words2>(ahead + at));
+            }
+            ended_at = kOneRow ? (pos - rows) / kElem : pos;
+        };
+        if (p.rows_per_chunk == 1u) walk(std::true_type{});
+        else walk(std::false_type{});
+        bits_read = begin - left;
     } else {
-        walk([&](uint32_t i) { return i < word_limit ? words[i] : 0u; }, std::false_type{});
+        const uint32_t* words = p.payload + c.payload_offset;
+        auto word_at = [&](uint32_t i) { return i < word_limit ? words[i] : 0u; };
+        uint32_t bit = first_word << 5, elem = lane;
+        at = ((2u * X0 + (word_at(min(first_word, word_limit)) & 1u)) * 8u) & ahead_mask;
+        while (elem < n) {
+            const uint32_t wi = min(bit >> 5, word_limit);
+            const words2 e = lds_load<words2>(ahead + at);
+            const uint32_t window = __builtin_amdgcn_alignbit(word_at(wi + 1u), word_at(wi), bit);
+            at = (e.y + 8u * (__brev(window) >> (e.x & 31u))) & ahead_mask;
+            bit += (e.x >> 24) & 15u;
+            elem += ((e.x >> 28) & 7u) * N;
+            const uint32_t row = p.K > 1u ? __umulhi(elem, p.k_magic) : elem;
+            put(min(rows + (row * (p.row_stride - p.K) + elem) * kElem, beyond), e.x);
+            elem += N;
+        }
+        ended_at = elem;
+        bits_read = bit - (first_word << 5);
+    }
+    // a stream ends where an entry ends, in state 0 (the index of the next entry is 2 X + peeked bit),
+    // having read exactly its words
+    if (lane < N) {
+        // the lane's elements are lane, lane + N, ...: it has produced exactly its symbols if it stands on the
+        // first of them that is no element of the chunk
+        if (ended_at - c.n_symbols >= N) err |= ANSZP_ST_BAD_LENGTH;
+        if ((at >> 4) != 0u) err |= ANSZP_ST_BAD_STATE;
+        if ((bits_read + 31u) >> 5 != n_words) err |= ANSZP_ST_BAD_LENGTH;
     }
     return err;                                       // this lane's
 }
@@ -310,9 +354,9 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const uint32_t L = 1u << p.table_log;
     const uint32_t ahead_bytes = 16u * L;                         // 2 L look-ahead entries of two words
-    uint8_t* ahead = lds;
-    uint32_t* stage = reinterpret_cast<uint32_t*>(lds + ahead_bytes);
+    uint8_t* ahead = lds + kStageBytes;
     uint8_t* panel = lds + p.panel_off;
+    const uint32_t lds_at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) uint8_t*)lds));   // 0
     constexpr uint32_t kElem = P16 ? 2u : 1u;                     // bytes per panel element
     const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -353,7 +397,7 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
         c.ok = layer_id == p.layer_id && c.n_symbols == p.rows_per_chunk * p.K && (c.payload_offset & 3u) == 0 &&
                c.payload_offset <= p.payload_words && c.payload_words <= p.payload_words - c.payload_offset &&
                uint64_t(c.stream_offset) + p.n_streams <= p.n_stream_hdr;
-        c.staged = c.payload_words + 2u <= kStageWords;           // two zero words behind the chunk's own
+        c.staged = c.payload_words + 2u <= p.stage_words;         // two zero words behind the chunk's own
         return c;
     };
     auto fetch = [&](const ChunkDesc& c, ChunkData& d) {          // from clamped, always valid addresses
@@ -410,8 +454,8 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
         }
         const uint32_t j = wave + i * kWaves;
         if (!cur.ok) err |= ANSZP_ST_BAD_DESC;                    // its rows stay the dominant symbol
-        else err |= decode_chunk_to_panel<P16>(p, cur, cur_data, ahead, ahead_bytes - 8u, stage + wave * kStageWords,
-                                               panel + j * p.rows_per_chunk * p.row_stride * kElem, lane, int32_t(lay.zero_point));
+        else err |= decode_chunk_to_panel<P16>(p, cur, cur_data, lds_at + kStageBytes, ahead_bytes - 8u, lds_at + wave * (kStageWords * 4u),
+                                               lds_at + p.panel_off + j * p.rows_per_chunk * p.row_stride * kElem, lane, int32_t(lay.zero_point));
         cur = nxt;
         cur_data = nxt_data;
     }
@@ -1292,7 +1336,7 @@ extern "C" int anszp_conv_fused(const anszp_conv_args_t* a, void* stream) {
     // beside the table and the staging buffers (more rows per activation vector loaded).
     const uint32_t row_stride = ((uint32_t(K) + 31u) & ~31u) + kRowPad;
     const uint32_t table_bytes = 16u << a->table_log;             // the look-ahead entries
-    const uint32_t fixed_bytes = table_bytes + kWaves * kStageWords * 4u + 64u;
+    const uint32_t fixed_bytes = kStageBytes + table_bytes + 64u;
     const bool p16 = K <= kMaxK16;                              // short rows: the panel as bf16
     const uint32_t elem = p16 ? 2u : 1u;
     uint32_t mr = 4;
@@ -1320,6 +1364,10 @@ extern "C" int anszp_conv_fused(const anszp_conv_args_t* a, void* stream) {
     p.y_block = a->y_layout == ANSZP_ACT_C8 ? 8u * out_h * out_w : 8u;
     p.K = uint32_t(K);
     p.k_magic = uint32_t((uint64_t(1) << 32) / K) + 1u;           // unused for K = 1
+    // (a look-up may step past the chunk's end by one entry: eight symbols of every stream)
+    const uint64_t reach = uint64_t(R) * K + 8u * a->n_streams;
+    p.k_magic24 = (1u << 24) / uint32_t(K) + 1u;
+    p.stage_words = R == 1u || (K > 1u && reach < 65536u && reach * K < (1u << 24)) ? kStageWords : 0u;
     p.row_stride = row_stride;
     p.chunks_per_panel = kRows * mr / R;
     p.n_pixels = uint32_t(n_pixels);
@@ -1360,7 +1408,7 @@ extern "C" int anszp_conv_fused(const anszp_conv_args_t* a, void* stream) {
     // pixels a wavefront takes per round are the most (of 64, 48, 32, 16, and no more than the workgroup's share
     // asks for) whose largest possible patch fits: in pieces per thread, and, with the slab of widened weights,
     // in the LDS below the panel.
-    p.panel_off = table_bytes + kWaves * kStageWords * 4u;
+    p.panel_off = kStageBytes + table_bytes;
     bool patch = patch_wanted;
     if (patch) {
         const uint32_t S = a->stride, Hp = a->in_h + 2u * a->pad, Wp = a->in_w + 2u * a->pad, Wh = (Wp + S - 1u) / S;
@@ -1386,7 +1434,7 @@ extern "C" int anszp_conv_fused(const anszp_conv_args_t* a, void* stream) {
                 break;
             }
         }
-        if (!patch) p.panel_off = table_bytes + kWaves * kStageWords * 4u;
+        if (!patch) p.panel_off = kStageBytes + table_bytes;
     }
     bool generic_patch = false;
     if (generic) {
@@ -1453,6 +1501,7 @@ extern "C" int anszp_conv_fused(const anszp_conv_args_t* a, void* stream) {
                                 int(kLdsLimit)) != hipSuccess) return ANSZP_E_HIP;
         lds_allowed[p16][kernel_no][slot][device].store(true, std::memory_order_relaxed);
     }
+    lds_total = std::max(lds_total, 65536u);                      // (what kStageMask leaves of an address is always there)
     hipLaunchKernelGGL(kernel, dim3(n_mtiles * splits), dim3(kThreads), lds_total, static_cast<hipStream_t>(stream), p);
     return hipGetLastError() == hipSuccess ? ANSZP_OK : ANSZP_E_HIP;
 }
