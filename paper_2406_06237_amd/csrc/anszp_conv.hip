@@ -17,14 +17,11 @@
 // v_mfma_f32_16x16x32_bf16: as many as fit in LDS) and a range of output pixels.  Phase 1: its twelve
 // wavefronts decode the chunks that hold those weight rows, one lane per stream (Sec. II-A, III-B),
 // through the table's look-ahead entries (one look-up per run of up to eight symbols) into a
-// [16 * MR][K] panel in LDS: symbols as bytes, or, for short rows, the bf16 values q - z.  Phase 2, by
-// kind of layer (see the enumeration in front of the kernel): 1 x 1 kernels read their activation
-// vectors from global memory through a ring of hand-issued loads; kernels three taps wide load the
-// three taps of a kernel row and 32 channels together, so that the L1 serves what they share; 3 x 3
-// kernels of stride 1 with long rows (K > 1152) stage the activations under all nine taps of a round
-// of pixels in LDS once per 32 input channels; layers like the first one (3 channels) stage whole
-// image rows in LDS and gather from there; other shapes use loops the compiler schedules.  fp32
-// accumulators; one store of four consecutive output channels per lane, row tile and column tile.
+// [16 * MR][K] panel in LDS: symbols as bytes, or, where they fit, the bf16 values q - z.  Phase 2, by
+// kind of layer: input channels that are multiples of 32 under 1 x 1 kernels without padding or kernels
+// three taps wide (nearly all layers of a network) have conv_sliced_kernel, which also slices the
+// reduction over the wavefronts; conv_fused_kernel has the others (see the enumeration in front of it).
+// fp32 accumulators; one store of four consecutive output channels per lane, row tile and column tile.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -49,8 +46,7 @@ constexpr uint32_t kStageWords = 384;       // per wavefront: LDS room for one c
 constexpr uint32_t kStageBytes = kWaves * kStageWords * 4u;          // at the start of LDS; the table's entries follow
 constexpr uint32_t kStageMask = 0xFFFCu;    // whole words in the first 64 KiB of LDS
 constexpr uint32_t kWidenPieces = 7;        // 16-byte pieces of a byte panel one thread widens to bf16
-constexpr uint32_t kPatchTaps = 9;          // kTapsPatch: a 3 x 3 kernel
-constexpr uint32_t kPatchPieces = 4;        // kTapsPatch: 16-byte pieces of a patch per thread
+constexpr uint32_t kPatchPieces = 4;        // kGenericPatch: 16-byte pieces of the staged rows per thread
 constexpr uint32_t kMaxMine = (4u * kRows + kWaves - 1u) / kWaves;   // chunks of a panel one wavefront may have to decode
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -81,9 +77,16 @@ struct ConvParams {
     uint32_t k_magic24, stage_words;                      // floor(2^24 / K) + 1: i / K = (i * k_magic24) >> 24 for i * K < 2^24; kStageWords where
                                                           // that holds for all elements of a chunk (or a chunk is one row), else 0
     uint32_t panel_off;                                   // first byte of the panel in LDS (behind the table and the staging room)
-    uint32_t wave_pixels, patch_off, patch_plane;         // kTapsPatch: pixels per wavefront and round (16..64); first byte of the
-                                                          // patch; bytes of one of its four planes
+    uint32_t patch_off;                                   // kGenericPatch: first byte of the staged rows
     uint32_t row_pitch;                                   // kGenericPatch: bytes from one staged image row to the next
+    // conv_sliced_kernel: slices of the reduction; wavefronts that share one (k_groups * t_groups = 12) and wave / t_groups =
+    // wave * t_groups_inv >> 16; column tiles of a wavefront (the first wave_tiles_rest have one more), of a round; units of a
+    // slice; bytes of x and y
+    uint32_t k_groups, t_groups, t_groups_inv, wave_tiles, wave_tiles_rest, round_tiles, slice_units, x_bytes, y_bytes;
+    uint32_t x_image, y_image;                            // elements of an image
+    // n / d = mulhi(2 n, magic) >> shift for n < 2^31 (d: output columns, output rows, panels, blocks of 32 input channels)
+    uint32_t out_w_magic, out_w_shift, out_h_magic, out_h_shift, n_mtiles_magic, n_mtiles_shift, blocks_magic, blocks_shift;
+    __device__ __forceinline__ uint32_t n_mtiles_by(uint32_t n) const { return __umulhi(2u * n, n_mtiles_magic) >> n_mtiles_shift; }
     uint32_t pixels_per_split, block_pixels;              // multiples of 16: the pixels of a workgroup; of one block (<= 64)
 };
 
@@ -135,6 +138,10 @@ template <class T>
 __device__ __forceinline__ T lds_load(uint32_t at) { return *reinterpret_cast<const __attribute__((address_space(3))) T*>(static_cast<uintptr_t>(at)); }
 template <class T>
 __device__ __forceinline__ void lds_store(uint32_t at, T v) { *reinterpret_cast<__attribute__((address_space(3))) T*>(static_cast<uintptr_t>(at)) = v; }
+
+__device__ __forceinline__ uint32_t lds_address(const void* shared) {
+    return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) void*)shared));
+}
 
 // One chunk into the LDS panel: symbol i of the chunk belongs to panel row i / K, column i % K.  One lane per
 // stream (Sec. III-B) walks the automaton of Sec. II-A through the table's look-ahead entries (anszp_layout.h):
@@ -312,7 +319,7 @@ __device__ __forceinline__ void store_tiles(const ConvParams& p, const anszp_lay
 // What a kernel tap outside the image reads (kTapsRing: every load is unconditional).
 __device__ __attribute__((aligned(64))) const uint32_t zero_page[16] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
 
-// kPointwiseRing, kTapsRing: the loads of one ring slot (QT activation vectors) issued by hand, and the wait for them.  When a
+// kTapsRing: the loads of one ring slot (QT activation vectors) issued by hand, and the wait for them.  When a
 // slot is used, LATER loads have been asked for after its own, so the wait is for all but LATER loads; it names the
 // slot's registers as its results, so that nothing which uses them can be moved ahead of it.  (The compiler, left
 // to count loads that cross the loop's back edge, waits for every load at the head of the loop.)
@@ -333,42 +340,29 @@ __device__ __forceinline__ void ring_arrived(words4 (&slot)[QT]) {
     if constexpr (QT == 4) asm volatile("s_waitcnt vmcnt(%4)" : "+v"(slot[0]), "+v"(slot[1]), "+v"(slot[2]), "+v"(slot[3]) : "n"(LATER) : "memory");
 }
 
-// MR: MFMA row tiles per workgroup.  Every wavefront multiplies all 16 * MR panel rows with its columns, so
-// an activation vector loaded once feeds MR MFMAs.
-// P16: the panel is kept as bf16 (short rows: K <= 576), so that the contraction reads its A operands as they are.
-// KIND: how the contraction addresses the activations.
-enum { kTaps = 0,        // input channels a multiple of 8: a lane's 8 consecutive k lie under one kernel tap
-       kPointwise = 1,   // as kTaps with a 1 x 1 kernel and no padding: one pixel per column, nothing outside the image
-       kGeneric = 2,     // any number of input channels (NHWC): every activation is addressed on its own
-       kPointwiseRing = 3,     // as kPointwise with input channels a multiple of 32 * D: D steps' activations in flight
-       kTapsPatch = 4,         // as kTaps with input channels a multiple of 32: the activations under all kernel taps of a
-                               // round of pixels are staged in LDS once per 32 input channels
-       kTapsRing = 5,          // as kTaps with input channels a multiple of 32 * D: D steps' activations in flight
-       kGenericPatch = 6,      // as kGeneric when whole image rows are multiples of 16 bytes: the image rows under a round
-                               // of pixels are staged in LDS, zero padding included, and gathered from there
-       kTapsRows = 7 };        // as kTapsRing for kernels three taps wide: the three taps of a kernel row and 32 channels
-                               // are loaded together, so that the L1 serves what they share
-// D (kPointwiseRing only): steps of 32 input channels whose activation loads are in flight at any time.
-template <int KIND, uint32_t MR, bool P16, uint32_t D>
-__global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+// The panel and the range of pixels of this workgroup.
+// The chip hands consecutive workgroups to its eight dies in turn and every die has its own L2: workgroup
+// blockIdx.x is the (blockIdx.x / 8)-th of die blockIdx.x % 8.  Numbering the workgroups die after die, the
+// panels of one range of pixels follow each other on one die, whose L2 then fetches those activations once
+// for all of them.  (Any one-to-one numbering is correct; this one is for the cache.)
+__device__ __forceinline__ uint32_t unit_of_workgroup() {
+    constexpr uint32_t kDies = 8;
+    const uint32_t per_die = gridDim.x / kDies, extra = gridDim.x % kDies, die = blockIdx.x % kDies;
+    return die * per_die + min(die, extra) + blockIdx.x / kDies;
+}
+
+// Phase 1: panel `mtile` (16 * MR weight rows) into LDS; the caller's barrier follows.  meanwhile(): called while the
+// first loads are on their way.  Returns the layer's quantizer.
+template <uint32_t MR, bool P16, class MEANWHILE>
+__device__ __forceinline__ anszp_layer_t decode_panel(const ConvParams& p, uint8_t* lds, uint32_t mtile, MEANWHILE&& meanwhile) {
     const uint32_t L = 1u << p.table_log;
     const uint32_t ahead_bytes = 16u * L;                         // 2 L look-ahead entries of two words
     uint8_t* ahead = lds + kStageBytes;
     uint8_t* panel = lds + p.panel_off;
-    const uint32_t lds_at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) uint8_t*)lds));   // 0
+    const uint32_t lds_at = lds_address(lds);                     // 0
     constexpr uint32_t kElem = P16 ? 2u : 1u;                     // bytes per panel element
     const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // The chip hands consecutive workgroups to its eight dies in turn and every die has its own L2: workgroup
-    // blockIdx.x is the (blockIdx.x / 8)-th of die blockIdx.x % 8.  Numbering the workgroups die after die, the
-    // panels of one range of pixels follow each other on one die, whose L2 then fetches those activations once
-    // for all of them.  (Any one-to-one numbering is correct; this one is for the cache.)
-    constexpr uint32_t kDies = 8;
-    const uint32_t per_die = gridDim.x / kDies, extra = gridDim.x % kDies, die = blockIdx.x % kDies;
-    const uint32_t unit = die * per_die + min(die, extra) + blockIdx.x / kDies;
-    const uint32_t mtile = unit % p.n_mtiles, split = unit / p.n_mtiles;
-
     // ---- phase 1: the layer's look-ahead entries into LDS, then this workgroup's 16 * MR weight rows.
     // Every global read that depends only on the kernel's arguments is issued before any is waited for: the
     // descriptors of this wavefront's chunks (lane i: its i-th chunk, panel chunk wave + i * kWaves), the layer's
@@ -424,6 +418,7 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
         cur = desc_of(0u);
         fetch(cur, cur_data);
     }
+    meanwhile();
     {
         // (done while the table is still on its way: only the quantizer and the last state's triple are needed)
         // The panel starts as the layer's dominant symbol everywhere (decoding writes only the other symbols);
@@ -461,6 +456,54 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
     }
     err = wave_or(err);
     if (err && lane == 0) report(p.status, err);
+    return lay;
+}
+
+// A panel of symbol bytes widened in place to bf16 values q - z (the table and the staging room are free by then; the
+// widened panel starts at the beginning of LDS): every thread takes its 16-byte pieces into registers, all wait, then
+// every piece is written back as 32 bytes, all wait.
+template <uint32_t MR>
+__device__ __forceinline__ void widen_panel(const ConvParams& p, uint8_t* lds, const anszp_layer_t& lay) {
+    const uint32_t tid = threadIdx.x;
+    const uint32_t n_pieces = (kRows * MR * p.row_stride + 64u) / 16u;     // the host made sure: <= kWidenPieces * kThreads
+    const float zf = static_cast<float>(lay.zero_point);
+    words4 held_q[kWidenPieces];
+#pragma unroll
+    for (uint32_t u = 0; u < kWidenPieces; ++u)
+        held_q[u] = reinterpret_cast<const words4*>(lds + p.panel_off)[min(tid + u * kThreads, n_pieces - 1u)];
+    __syncthreads();
+#pragma unroll
+    for (uint32_t u = 0; u < kWidenPieces; ++u) {
+        const uint32_t i = tid + u * kThreads;
+        if (i < n_pieces) {
+            bf16x8* dst = reinterpret_cast<bf16x8*>(lds + 32u * i);
+            dst[0] = weights_of(words2{held_q[u].x, held_q[u].y}, zf);
+            dst[1] = weights_of(words2{held_q[u].z, held_q[u].w}, zf);
+        }
+    }
+    __syncthreads();
+}
+
+// MR: MFMA row tiles per workgroup.  Every wavefront multiplies all 16 * MR panel rows with its columns, so
+// an activation vector loaded once feeds MR MFMAs.
+// P16: the panel is kept as bf16 (short rows: K <= 576), so that the contraction reads its A operands as they are.
+// KIND: how the contraction addresses the activations.
+enum { kTaps = 0,        // input channels a multiple of 8: a lane's 8 consecutive k lie under one kernel tap
+       kPointwise = 1,   // as kTaps with a 1 x 1 kernel and no padding: one pixel per column, nothing outside the image
+       kGeneric = 2,     // any number of input channels (NHWC): every activation is addressed on its own
+       kTapsRing = 3,          // as kTaps with input channels a multiple of 32 * D: D steps' activations in flight
+       kGenericPatch = 4 };    // as kGeneric when whole image rows are multiples of 16 bytes: the image rows under a round
+                               // of pixels are staged in LDS, zero padding included, and gathered from there
+// D (kTapsRing only): steps of 32 input channels whose activation loads are in flight at any time.
+template <int KIND, uint32_t MR, bool P16, uint32_t D>
+__global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    uint8_t* panel = lds + p.panel_off;
+    constexpr uint32_t kElem = P16 ? 2u : 1u;                     // bytes per panel element
+    const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t unit = unit_of_workgroup(), mtile = unit % p.n_mtiles, split = unit / p.n_mtiles;
+    const anszp_layer_t lay = decode_panel<MR, P16>(p, lds, mtile, [] {});
     __syncthreads();
     // kGeneric: what every k of the reduction means, worked out once (the table and the staging room are free now):
     // two words per k, the offset of its activation from the one under the first tap's first channel, and its
@@ -476,134 +519,9 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
         __syncthreads();
     }
 
-    // kPointwiseRing, kTapsRing (which need no other LDS in phase 2): a panel of symbol bytes is first widened in
-    // place to bf16 values q - z (the table and the staging room are free now and the widened panel starts at the
-    // beginning of LDS): every thread takes its 16-byte pieces into registers, all wait, then every piece is
-    // written back as 32 bytes.  Returns where the bf16 panel starts.
-    [[maybe_unused]] auto widened_panel = [&]() -> const uint8_t* {
-        if constexpr (P16) {
-            return panel;
-        } else {
-            const uint32_t n_pieces = (kRows * MR * p.row_stride + 64u) / 16u;     // the host made sure: <= kWidenPieces * kThreads
-            const float zf = static_cast<float>(lay.zero_point);
-            words4 held_q[kWidenPieces];
-#pragma unroll
-            for (uint32_t u = 0; u < kWidenPieces; ++u)
-                held_q[u] = reinterpret_cast<const words4*>(panel)[min(tid + u * kThreads, n_pieces - 1u)];
-            __syncthreads();
-#pragma unroll
-            for (uint32_t u = 0; u < kWidenPieces; ++u) {
-                const uint32_t i = tid + u * kThreads;
-                if (i < n_pieces) {
-                    bf16x8* dst = reinterpret_cast<bf16x8*>(lds + 32u * i);
-                    dst[0] = weights_of(words2{held_q[u].x, held_q[u].y}, zf);
-                    dst[1] = weights_of(words2{held_q[u].z, held_q[u].w}, zf);
-                }
-            }
-            __syncthreads();
-            return lds;
-        }
-    };
-    if constexpr (KIND == kPointwiseRing) {
-        // ---- phase 2 for 1 x 1 kernels without padding whose input channels are a multiple of 32 * D.
-        const uint8_t* a_base = widened_panel();
-        const uint32_t col = lane & 15u, kg = lane >> 4;          // MFMA operand layout: row or column, group of 8 k
-        const uint8_t* a_row = a_base + (col * p.row_stride + 8u * kg) * 2u;
-        const uint32_t tile_stride = kRows * p.row_stride * 2u;
-        const uint32_t n_steps = p.cin / 32u;                     // a multiple of D
-        const uint32_t step_elems = 4u * p.x_block;               // from one step's activation vector to the next's
-        const uint32_t split_begin = split * p.pixels_per_split;
-        const uint32_t split_end = min(split_begin + p.pixels_per_split, p.n_pixels);
-        // The workgroup's column tiles of 16 pixels are dealt out in rounds of at most 4 * kWaves, and a round's tiles
-        // evenly over the wavefronts: every wavefront has one to four neighbouring tiles (as many loads in flight
-        // on as many SIMDs as possible: the loop is bound by the activations' way from the L2).
-        const uint32_t tiles = (split_end - split_begin + 15u) / 16u;
-        const uint32_t n_rounds = (tiles + 4u * kWaves - 1u) / (4u * kWaves);
-        const uint32_t round_tiles = n_rounds ? (tiles + n_rounds - 1u) / n_rounds : 0u;
-        auto block = [&](uint32_t pix0, uint32_t block_end, auto tiles_here) {
-            constexpr uint32_t QT = decltype(tiles_here)::value;
-            // B: lane holds column lane % 16 of each of the block's QT column tiles; a column beyond the block
-            // reads the block's first pixel (every load is unconditional) and is not stored
-            bool valid[4] = {false, false, false, false};
-            uint32_t out_at[4] = {0u, 0u, 0u, 0u};
-            const uint16_t* px[QT];
-#pragma unroll
-            for (uint32_t q = 0; q < QT; ++q) {
-                const uint32_t pix = pix0 + q * 16u + col;
-                valid[q] = pix < block_end;
-                const uint32_t n = valid[q] ? pix : pix0;
-                const uint32_t wo = n % p.out_w, t = n / p.out_w;
-                const uint32_t ho = t % p.out_h, b = t / p.out_h;
-                px[q] = p.x + (b * p.in_h * p.in_w * p.cin + (ho * p.stride * p.in_w + wo * p.stride) * p.x_pixel + kg * p.x_block);
-                out_at[q] = b * p.out_h * p.out_w * p.cout + (ho * p.out_w + wo) * p.y_pixel;
-            }
-            floatx4 acc[MR][4];
-#pragma unroll
-            for (uint32_t m = 0; m < MR; ++m)
-#pragma unroll
-                for (uint32_t q = 0; q < 4; ++q) acc[m][q] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-            // A ring of D steps' activation vectors: a step's slot is refilled, for the step D later, as soon as its
-            // MFMAs are issued (ring_request / ring_arrived: by hand).
-            words4 ring[D][QT];
-            auto multiply = [&](uint32_t step, uint32_t d) {
-#pragma unroll
-                for (uint32_t m = 0; m < MR; ++m) {
-                    const bf16x8 a = *reinterpret_cast<const bf16x8*>(a_row + m * tile_stride + step * 64u);
-#pragma unroll
-                    for (uint32_t q = 0; q < QT; ++q)
-                        acc[m][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, ring[d][q]), acc[m][q], 0, 0, 0);
-                }
-            };
-#pragma unroll
-            for (uint32_t d = 0; d < D; ++d) ring_request<QT>(ring[d], px, d * step_elems);
-            uint32_t base = 0;
-            for (; base + D < n_steps; base += D) {               // every group of D steps but the last
-#pragma unroll
-                for (uint32_t d = 0; d < D; ++d) {
-                    ring_arrived<QT, (D - 1u) * QT>(ring[d]);
-                    multiply(base + d, d);
-                    ring_request<QT>(ring[d], px, (base + d + D) * step_elems);
-                }
-            }
-            // the last group: nothing is asked for any more, so fewer loads follow a slot's own
-            static_assert(D == 2 || D == 4, "written out for two and four slots");
-            if constexpr (D == 2) {
-                ring_arrived<QT, QT>(ring[0]);
-                multiply(base, 0u);
-                ring_arrived<QT, 0u>(ring[1]);
-                multiply(base + 1u, 1u);
-            } else {
-                ring_arrived<QT, 3u * QT>(ring[0]);
-                multiply(base, 0u);
-                ring_arrived<QT, 2u * QT>(ring[1]);
-                multiply(base + 1u, 1u);
-                ring_arrived<QT, QT>(ring[2]);
-                multiply(base + 2u, 2u);
-                ring_arrived<QT, 0u>(ring[3]);
-                multiply(base + 3u, 3u);
-            }
-            store_tiles<MR>(p, lay, mtile, kg, acc, valid, out_at);
-        };
-        for (uint32_t round = 0; round < n_rounds; ++round) {
-            const uint32_t t0 = round * round_tiles;
-            if (t0 >= tiles) break;
-            const uint32_t tn = min(round_tiles, tiles - t0);
-            const uint32_t w_begin = t0 + tn * wave / kWaves, w_end = t0 + tn * (wave + 1u) / kWaves;   // this wavefront's tiles
-            const uint32_t pix0 = split_begin + 16u * w_begin, block_end = min(split_begin + 16u * w_end, split_end);
-            switch (w_end - w_begin) {                            // uniform
-                case 1: block(pix0, block_end, std::integral_constant<uint32_t, 1>{}); break;
-                case 2: block(pix0, block_end, std::integral_constant<uint32_t, 2>{}); break;
-                case 3: block(pix0, block_end, std::integral_constant<uint32_t, 3>{}); break;
-                case 4: block(pix0, block_end, std::integral_constant<uint32_t, 4>{}); break;
-                default: break;
-            }
-        }
-        return;
-    }
-
     if constexpr (KIND == kGenericPatch) {
         // ---- phase 2 for any number of input channels (NHWC) when an image row is a multiple of 16 bytes: the
-        // workgroup's column tiles are taken in rounds (dealt out as for kPointwiseRing); the image rows under a
+        // workgroup's column tiles are taken in rounds of up to four per wavefront, dealt out evenly; the image rows under a
         // round's pixels go to LDS as they are, 16 bytes at a time, each behind 32 bytes whose upper part is the
         // left zero padding, followed by the right one; rows above and below an image are zeros.  A lane then
         // gathers its 8 k per column from LDS: the pixel's place plus an offset per k that is worked out once (a
@@ -731,143 +649,14 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
         return;
     }
 
-    if constexpr (KIND == kTapsRows) {
-        // ---- phase 2 for kernels three taps wide whose input channels are a multiple of 64 (and that stage no patch).
-        // A step is a kernel row, 32 input channels and the row's three taps; two steps' activation vectors are in
-        // flight (hand-issued loads as for kPointwiseRing, each tap of a step waited for on its own).  Kernel rows
-        // outermost, channels next, the three taps innermost: the taps of a row read the same pixels shifted by one
-        // (stride 1) or alternate halves of the same lines (stride 2), and asked for together they cost the L1 one
-        // fetch of a line instead of up to three.  A column whose pixel lies outside the image under a tap reads
-        // zero_page with a step stride of zero.
-        const uint32_t col = lane & 15u, kg = lane >> 4;          // MFMA operand layout: row or column, group of 8 k
-        const uint8_t* a_row = widened_panel() + (col * p.row_stride + 8u * kg) * 2u;
-        const uint32_t tile_stride = kRows * p.row_stride * 2u;
-        const uint32_t steps_per_row = p.cin / 32u;               // even
-        const uint32_t n_steps = p.kh * steps_per_row;
-        const uint32_t split_begin = split * p.pixels_per_split;
-        const uint32_t split_end = min(split_begin + p.pixels_per_split, p.n_pixels);
-        const uint32_t tiles = (split_end - split_begin + 15u) / 16u;
-        constexpr uint32_t kTilesMost = MR == 4 ? 2u : 3u;        // column tiles per wavefront and round: what the registers hold
-        const uint32_t n_rounds = (tiles + kTilesMost * kWaves - 1u) / (kTilesMost * kWaves);
-        const uint32_t round_tiles = n_rounds ? (tiles + n_rounds - 1u) / n_rounds : 0u;
-        const uint16_t* zeros = reinterpret_cast<const uint16_t*>(zero_page);
-        auto block = [&](uint32_t pix0, uint32_t block_end, auto tiles_here) {
-            constexpr uint32_t QT = decltype(tiles_here)::value;
-            bool valid[4] = {false, false, false, false};
-            uint32_t out_at[4] = {0u, 0u, 0u, 0u};
-            int32_t h0[QT], w0[QT];
-            uint32_t img[QT];
-#pragma unroll
-            for (uint32_t q = 0; q < QT; ++q) {
-                const uint32_t pix = pix0 + q * 16u + col;
-                valid[q] = pix < block_end;
-                const uint32_t n = valid[q] ? pix : pix0;         // a column beyond the block stands on its first pixel
-                const uint32_t wo = n % p.out_w, t = n / p.out_w;
-                const uint32_t ho = t % p.out_h, b = t / p.out_h;
-                h0[q] = int32_t(ho * p.stride) - int32_t(p.pad);
-                w0[q] = int32_t(wo * p.stride) - int32_t(p.pad);
-                img[q] = b * p.in_h * p.in_w * p.cin;
-                out_at[q] = b * p.out_h * p.out_w * p.cout + (ho * p.out_w + wo) * p.y_pixel;
-            }
-            floatx4 acc[MR][4];
-#pragma unroll
-            for (uint32_t m = 0; m < MR; ++m)
-#pragma unroll
-                for (uint32_t q = 0; q < 4; ++q) acc[m][q] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-            // where the requests of the kernel row being asked for read, per tap and column
-            const uint16_t* tap_ptr[3][QT];
-            uint32_t tap_step[3][QT];
-            auto enter_row = [&](uint32_t r) {
-#pragma unroll
-                for (uint32_t q = 0; q < QT; ++q) {
-                    const int32_t h = h0[q] + int32_t(r);
-                    const bool row_inside = uint32_t(h) < p.in_h;
-#pragma unroll
-                    for (uint32_t sx = 0; sx < 3; ++sx) {
-                        const int32_t w = w0[q] + int32_t(sx);
-                        const bool inside = row_inside && uint32_t(w) < p.in_w;
-                        tap_ptr[sx][q] = inside ? p.x + (img[q] + (uint32_t(h) * p.in_w + uint32_t(w)) * p.x_pixel + kg * p.x_block) : zeros;
-                        tap_step[sx][q] = inside ? 4u * p.x_block : 0u;
-                    }
-                }
-            };
-            words4 ring[2][3][QT];
-            auto request = [&](uint32_t slot, uint32_t step_in_row) {
-#pragma unroll
-                for (uint32_t sx = 0; sx < 3; ++sx) {
-                    const uint16_t* from[QT];
-#pragma unroll
-                    for (uint32_t q = 0; q < QT; ++q) from[q] = tap_ptr[sx][q] + __umul24(step_in_row, tap_step[sx][q]);
-                    ring_request<QT>(ring[slot][sx], from, 0u);
-                }
-            };
-            auto multiply = [&](uint32_t k_first, const words4 (&b)[QT]) {   // k_first: the step's first k under this tap (its panel column)
-#pragma unroll
-                for (uint32_t m = 0; m < MR; ++m) {
-                    const bf16x8 a = *reinterpret_cast<const bf16x8*>(a_row + m * tile_stride + k_first * 2u);
-#pragma unroll
-                    for (uint32_t q = 0; q < QT; ++q)
-                        acc[m][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, b[q]), acc[m][q], 0, 0, 0);
-                }
-            };
-            // the cursor of the requests runs two steps ahead of the cursor of the multiplications
-            uint32_t req_row = 0, req_step = 0;
-            auto request_next = [&](uint32_t slot) {
-                request(slot, req_step);
-                if (++req_step == steps_per_row) {                // uniform
-                    req_step = 0;
-                    ++req_row;
-                    if (req_row < p.kh) enter_row(req_row);
-                }
-            };
-            enter_row(0u);
-            request_next(0u);
-            request_next(1u);
-            uint32_t row = 0, step = 0;                           // of the step being multiplied
-            auto use = [&](uint32_t slot, auto other_slot_pending) {
-                constexpr uint32_t kOther = decltype(other_slot_pending)::value ? 3u * QT : 0u;   // loads asked for after this slot's
-                const uint32_t k_row = row * 3u * p.cin + step * 32u;
-                ring_arrived<QT, 2u * QT + kOther>(ring[slot][0]);
-                multiply(k_row, ring[slot][0]);
-                ring_arrived<QT, QT + kOther>(ring[slot][1]);
-                multiply(k_row + p.cin, ring[slot][1]);
-                ring_arrived<QT, kOther>(ring[slot][2]);
-                multiply(k_row + 2u * p.cin, ring[slot][2]);
-                if (++step == steps_per_row) { step = 0; ++row; }
-            };
-            for (uint32_t t = 0; t + 2u < n_steps; t += 2u) {     // every pair of steps but the last
-                use(0u, std::true_type{});
-                request_next(0u);
-                use(1u, std::true_type{});
-                request_next(1u);
-            }
-            use(0u, std::true_type{});
-            use(1u, std::false_type{});
-            store_tiles<MR>(p, lay, mtile, kg, acc, valid, out_at);
-        };
-        for (uint32_t round = 0; round < n_rounds; ++round) {
-            const uint32_t t0 = round * round_tiles;
-            if (t0 >= tiles) break;
-            const uint32_t tn = min(round_tiles, tiles - t0);
-            const uint32_t w_begin = t0 + tn * wave / kWaves, w_end = t0 + tn * (wave + 1u) / kWaves;   // this wavefront's tiles
-            const uint32_t pix0 = split_begin + 16u * w_begin, block_end = min(split_begin + 16u * w_end, split_end);
-            switch (w_end - w_begin) {                            // uniform
-                case 1: block(pix0, block_end, std::integral_constant<uint32_t, 1>{}); break;
-                case 2: block(pix0, block_end, std::integral_constant<uint32_t, 2>{}); break;
-                case 3: if constexpr (kTilesMost >= 3) block(pix0, block_end, std::integral_constant<uint32_t, 3>{}); break;
-                default: break;
-            }
-        }
-        return;
-    }
-
     if constexpr (KIND == kTapsRing) {
         // ---- phase 2 for kernels of several taps whose input channels are a multiple of 32 * D: steps of 32 k, kernel
-        // taps outermost, in groups of D steps that never straddle a tap; tiles dealt out and loads issued as for
-        // kPointwiseRing.  A column whose pixel lies outside the image under a tap reads zero_page for that tap (with a
+        // taps outermost, in groups of D steps that never straddle a tap; rounds of up to four column tiles per wavefront,
+        // dealt out evenly.  A column whose pixel lies outside the image under a tap reads zero_page for that tap (with a
         // step stride of zero), so every load is unconditional.
         const uint32_t col = lane & 15u, kg = lane >> 4;          // MFMA operand layout: row or column, group of 8 k
-        const uint8_t* a_row = widened_panel() + (col * p.row_stride + 8u * kg) * 2u;   // (the host keeps this kind for panels that can be widened)
+        if constexpr (!P16) widen_panel<MR>(p, lds, lay);         // (the host keeps this kind for panels that can be widened)
+        const uint8_t* a_row = (P16 ? panel : lds) + (col * p.row_stride + 8u * kg) * 2u;
         const uint32_t tile_stride = kRows * p.row_stride * 2u;
         const uint32_t groups_per_tap = p.cin / (32u * D);
         const uint32_t n_groups = p.kh * p.kw * groups_per_tap;
@@ -983,145 +772,6 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
                 case 4: block(pix0, block_end, std::integral_constant<uint32_t, 4>{}); break;
                 default: break;
             }
-        }
-        return;
-    }
-
-    if constexpr (KIND == kTapsPatch) {
-        // ---- phase 2 for kernels of several taps whose input channels are a multiple of 32.
-        // The workgroup's pixels are taken in rounds of kWaves * wave_pixels; for a round and 32 input channels
-        // the activations under every kernel tap of every pixel of the round (the "patch": the rows of the
-        // zero-padded input images from the first pixel's first tap to the last pixel's last, each row with its
-        // padding columns) are copied to LDS once, zeros included, and every tap's B operands are read from
-        // there: a lane's address is its pixel's place in the patch plus an offset that only depends on the tap,
-        // and nothing in the loop tests for the image's border.  The patch is four planes, one per block of 8 of
-        // the 32 channels; patch element (row pr, column pc) is the 16 bytes number
-        // (pr * stride + pc % stride) * Wh + pc / stride of each plane, Wh = ceil(padded width / stride): the 16
-        // lanes that read the same 8 channels of a column tile's 16 pixels read 256 consecutive bytes for every
-        // tap and stride (no two of them the same LDS bank).
-        // A panel of symbol bytes is widened, 32 input channels of every tap at a time, into a slab of bf16
-        // values beside the patch.  The next 32 channels' activations are on their way (in registers) while
-        // the current ones are multiplied.
-        const uint32_t S = p.stride, Hp = p.in_h + 2u * p.pad, Wp = p.in_w + 2u * p.pad, Wh = (Wp + S - 1u) / S;
-        constexpr uint32_t taps = kPatchTaps;                     // 3 x 3 kernels only (the host sees to it)
-        constexpr uint32_t slab_row = taps * 64u + 16u;           // bytes; rows start four banks apart
-        uint8_t* slab = lds;
-        uint8_t* patch = lds + p.patch_off;
-        const uint32_t col = lane & 15u, kg = lane >> 4;          // MFMA operand layout: row or column, group of 8 k
-        uint32_t tap_off[taps];                                   // from a pixel's place in the patch to what lies under a tap
-#pragma unroll
-        for (uint32_t tap = 0; tap < taps; ++tap) {
-            const uint32_t r = tap / 3u, sx = tap % 3u;
-            tap_off[tap] = ((r * S + sx % S) * Wh + sx / S) * 16u;
-        }
-        // A: lane holds row lane % 16 of a row tile, k = 8 * (lane / 16) + 0..7 of a step
-        const uint8_t* a_lane = P16 ? panel + (col * p.row_stride + 8u * kg) * 2u : slab + col * slab_row + kg * 16u;
-        const float zf = static_cast<float>(lay.zero_point);
-        const uint32_t split_begin = split * p.pixels_per_split;
-        const uint32_t split_end = min(split_begin + p.pixels_per_split, p.n_pixels);
-        constexpr uint32_t kPieces = kPatchPieces;                // 16-byte pieces of a patch one thread may have to copy
-        for (uint32_t round0 = split_begin; round0 < split_end; round0 += kWaves * p.wave_pixels) {
-            const uint32_t round_end = min(round0 + kWaves * p.wave_pixels, split_end);
-            // the patch's rows: flat index b * Hp + padded row
-            const uint32_t first_row = round0 / p.out_w, last_row = (round_end - 1u) / p.out_w;   // flat output rows b * out_h + ho
-            const uint32_t pr0 = (first_row / p.out_h) * Hp + (first_row % p.out_h) * S;
-            const uint32_t pr_last = (last_row / p.out_h) * Hp + (last_row % p.out_h) * S + p.kh - 1u;
-            const uint32_t n_pieces = (pr_last - pr0 + 1u) * 4u * Wp;
-            if (n_pieces > kPieces * kThreads) {                  // the host sized the rounds so that this cannot happen
-                if (tid == 0) report(p.status, ANSZP_ST_INTERNAL);
-                return;                                           // uniform
-            }
-            uint32_t src[kPieces], dst[kPieces];                  // element of x (none: zeros), byte of the patch (none: no piece)
-#pragma unroll
-            for (uint32_t u = 0; u < kPieces; ++u) {
-                const uint32_t i = tid + u * kThreads;            // piece (row, block of 8 channels, column), column fastest
-                src[u] = dst[u] = 0xFFFFFFFFu;
-                if (i < n_pieces) {
-                    const uint32_t pc = i % Wp, t = i / Wp;
-                    const uint32_t j = t & 3u, prl = t >> 2;
-                    const uint32_t pra = pr0 + prl;
-                    const uint32_t b = pra / Hp, h = pra % Hp - p.pad, w = pc - p.pad;   // unsigned: outside the image wraps around
-                    if (h < p.in_h && w < p.in_w) src[u] = b * p.in_h * p.in_w * p.cin + (h * p.in_w + w) * p.x_pixel + j * p.x_block;
-                    dst[u] = ((prl * S + pc % S) * Wh + pc / S) * 16u + j * p.patch_plane;
-                }
-            }
-            // this wavefront's pixels: up to four column tiles; a column beyond them stands on the round's first pixel
-            const uint32_t mine_begin = round0 + wave * p.wave_pixels;
-            const uint32_t mine_end = min(mine_begin + p.wave_pixels, round_end);
-            const uint32_t qt = mine_begin < mine_end ? (mine_end - mine_begin + 15u) / 16u : 0u;   // uniform
-            bool valid[4];
-            uint32_t out_at[4], at_patch[4];
-            valid[3] = false;                                     // at most three column tiles (48 pixels) per wavefront and round
-            out_at[3] = at_patch[3] = 0u;
-#pragma unroll
-            for (uint32_t q = 0; q < 3; ++q) {
-                const uint32_t pix = mine_begin + q * 16u + col;
-                valid[q] = pix < mine_end;
-                const uint32_t n = valid[q] ? pix : round0;
-                const uint32_t wo = n % p.out_w, t = n / p.out_w;
-                const uint32_t ho = t % p.out_h, b = t / p.out_h;
-                at_patch[q] = (((b * Hp + ho * S - pr0) * S) * Wh + wo) * 16u + kg * p.patch_plane;
-                out_at[q] = b * p.out_h * p.out_w * p.cout + (ho * p.out_w + wo) * p.y_pixel;
-            }
-            floatx4 acc[MR][4];
-#pragma unroll
-            for (uint32_t m = 0; m < MR; ++m)
-#pragma unroll
-                for (uint32_t q = 0; q < 4; ++q) acc[m][q] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-
-            words4 held_x[kPieces];
-            auto fetch_x = [&](uint32_t c0) {                     // the pieces of input channels c0 .. c0 + 31
-#pragma unroll
-                for (uint32_t u = 0; u < kPieces; ++u) {
-                    held_x[u] = words4{0u, 0u, 0u, 0u};
-                    if (src[u] != 0xFFFFFFFFu) held_x[u] = *reinterpret_cast<const words4*>(p.x + src[u] + (c0 >> 3) * p.x_block);
-                }
-            };
-            fetch_x(0u);
-            for (uint32_t c0 = 0; c0 < p.cin; c0 += 32u) {
-                __syncthreads();                                  // the previous step's patch and slab have been read
-#pragma unroll
-                for (uint32_t u = 0; u < kPieces; ++u)
-                    if (dst[u] != 0xFFFFFFFFu) *reinterpret_cast<words4*>(patch + dst[u]) = held_x[u];
-                if constexpr (!P16) {
-                    // slab[row][tap][32] = bf16(panel[row][tap * cin + c0 + 0..31] - z), 16 symbols per piece
-                    const uint32_t n_quads = kRows * MR * taps * 2u;
-                    for (uint32_t i = tid; i < n_quads; i += kThreads) {
-                        const uint32_t half = i & 1u, t = i >> 1;
-                        const uint32_t tap = t % taps, row = t / taps;
-                        const uint8_t* from = panel + row * p.row_stride + tap * p.cin + c0 + half * 16u;
-                        bf16x8* to = reinterpret_cast<bf16x8*>(slab + row * slab_row + tap * 64u + half * 32u);
-                        to[0] = weights_of(*reinterpret_cast<const words2*>(from), zf);
-                        to[1] = weights_of(*reinterpret_cast<const words2*>(from + 8), zf);
-                    }
-                }
-                if (c0 + 32u < p.cin) fetch_x(c0 + 32u);
-                __syncthreads();
-                // the nine taps, unrolled, with as many column tiles as this wavefront has (uniform)
-                auto multiply = [&](auto tiles) {
-                    constexpr uint32_t QT = decltype(tiles)::value;
-#pragma unroll
-                    for (uint32_t tap = 0; tap < kPatchTaps; ++tap) {
-                        bf16x8 a[MR];
-#pragma unroll
-                        for (uint32_t m = 0; m < MR; ++m) {
-                            if constexpr (P16) a[m] = *reinterpret_cast<const bf16x8*>(a_lane + (m * kRows * p.row_stride + tap * p.cin + c0) * 2u);
-                            else a[m] = *reinterpret_cast<const bf16x8*>(a_lane + m * kRows * slab_row + tap * 64u);
-                        }
-#pragma unroll
-                        for (uint32_t q = 0; q < QT; ++q) {
-                            const bf16x8 b = *reinterpret_cast<const bf16x8*>(patch + at_patch[q] + tap_off[tap]);
-#pragma unroll
-                            for (uint32_t m = 0; m < MR; ++m)
-                                acc[m][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], b, acc[m][q], 0, 0, 0);
-                        }
-                    }
-                };
-                if (qt == 3u) multiply(std::integral_constant<uint32_t, 3>{});
-                else if (qt == 2u) multiply(std::integral_constant<uint32_t, 2>{});
-                else if (qt == 1u) multiply(std::integral_constant<uint32_t, 1>{});
-            }
-            store_tiles<MR>(p, lay, mtile, kg, acc, valid, out_at);
         }
         return;
     }
@@ -1303,8 +953,401 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
     }
 }
 
+// The convolution of layers whose input channels are a multiple of 32 and whose kernels are 1 x 1 without padding
+// (kPoint) or three taps wide (kRow; stride 1 and padding 1: kShift): nearly all of a network's.
+//
+// Phase 2: a step is a kernel tap and 32 input channels, a unit the steps of a kernel row with the same 32 channels.
+// kRow asks for the row's three taps together: they read the same pixels shifted by one, or alternate halves of the
+// same lines (stride 2), and the L1 then fetches a line once for them.  kShift asks for the middle tap only (and one
+// vector that holds the pixels before the first and behind the last): the other two are the neighbouring lanes' values,
+// moved by one lane, zero at the image's left and right edge.  A load of 64 lanes of 16 bytes keeps a CU's address path busy for about
+// 34 clocks, more than the multiplications it feeds take when a panel has one row tile (K = 4608): 3 x 3 x 512 at 7 x 7
+// loads 4 vectors where kRow loads 9.  The workgroup's column tiles are dealt to t_groups
+// wavefronts, QT or one fewer each, the units to k_groups slices; t_groups * k_groups = 12.  A wavefront multiplies its
+// tiles with its slice, and the slices' sums are added up through LDS (the panel is no longer needed then).  What the
+// slices are for: a panel row tile read from LDS serves all of a wavefront's column tiles, so fewer tile ranges mean
+// fewer LDS reads, and with fewer tiles than wavefronts none of them idles.
+//
+// What bounds these launches (12 to 25 us each) is largely code that runs for the first time: a CU fetches it 64 bytes at
+// a time from the L2, about 85 ns each, which is as long as ten instructions take once they are there (measured: 2.5 us
+// for the tiles' addresses, 0.35 us the second time).  So the code is kept short: no divisions (the host passes
+// reciprocals), no tails (loads go through a buffer descriptor: what lies outside the image, belongs to no pixel or to no unit has an
+// offset beyond the buffer or an empty buffer and reads as zero without memory traffic; stores that belong to no pixel are
+// dropped the same way), one kernel per number of tiles, the slices' sums in a loop.
+//
+// Measured against rings of loads without slices (a call among others, MI355X): 3 x 3 x 512 channels, one 7 x 7 image 21.8 ->
+// 14.1 us; 1 x 1 from 1024 channels, 64 14 x 14 images 21.4 -> 18.3; 3 x 3 x 128 channels, 64 28 x 28 images 28.5 -> 27.2; a
+// ResNet-50's 53 convolutions on 16 images, one call each 900 -> 727.
+enum { kPoint = 1, kShift = 2, kRow = 3 };
+constexpr uint32_t units_in_flight(uint32_t mr, uint32_t mode, uint32_t qt) { return mode == kRow ? 2u : mr * qt > 8u || mode == kShift ? 3u : 4u; }
+
+// Every lane's neighbour's words within rows of 16 lanes: of the lane before (BEFORE) or after, the first (last) lane's
+// from `beyond`, which holds them in the row's last (first) lane if it is a tile of its own (ROTATE), else in the lane
+// itself; and-ed with `mask`.  (Moves and masks in one: the lane without a source keeps what the first instruction
+// wrote.  The wait states are those between writing a register and reading it from another lane or
+// in a matrix instruction.)
+template <bool BEFORE, bool ROTATE>
+__device__ __forceinline__ words4 neighbours(const words4& tile, const words4& beyond, uint32_t mask) {
+    words4 v;
+#define ANSZP_NEIGHBOURS(FIRST, FIRST_MOVE, MOVE)                                                                          \
+    asm("s_nop 1\n"                                                                                                        \
+        FIRST " %0, %8, %12" FIRST_MOVE FIRST " %1, %9, %12" FIRST_MOVE FIRST " %2, %10, %12" FIRST_MOVE FIRST " %3, %11, %12" FIRST_MOVE   \
+        "v_and_b32_dpp %0, %4, %12" MOVE "v_and_b32_dpp %1, %5, %12" MOVE "v_and_b32_dpp %2, %6, %12" MOVE "v_and_b32_dpp %3, %7, %12" MOVE \
+        "s_nop 1\n"                                                                                                        \
+        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])                                                                \
+        : "v"(tile[0]), "v"(tile[1]), "v"(tile[2]), "v"(tile[3]), "v"(beyond[0]), "v"(beyond[1]), "v"(beyond[2]), "v"(beyond[3]), "v"(mask))
+#define ANSZP_MOVE(HOW) " " HOW " row_mask:0xf bank_mask:0xf\n"
+    if constexpr (BEFORE && ROTATE) ANSZP_NEIGHBOURS("v_and_b32_dpp", ANSZP_MOVE("row_ror:1"), ANSZP_MOVE("row_shr:1"));
+    if constexpr (BEFORE && !ROTATE) ANSZP_NEIGHBOURS("v_and_b32", "\n", ANSZP_MOVE("row_shr:1"));
+    if constexpr (!BEFORE && ROTATE) ANSZP_NEIGHBOURS("v_and_b32_dpp", ANSZP_MOVE("row_ror:15"), ANSZP_MOVE("row_shl:1"));
+    if constexpr (!BEFORE && !ROTATE) ANSZP_NEIGHBOURS("v_and_b32", "\n", ANSZP_MOVE("row_shl:1"));
+#undef ANSZP_MOVE
+#undef ANSZP_NEIGHBOURS
+    return v;
+}
+
+template <uint32_t MR, bool P16, uint32_t MODE, uint32_t QT>
+__global__ __launch_bounds__(kThreads) void conv_sliced_kernel(ConvParams p) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    constexpr uint32_t NS = MODE == kPoint ? 1u : 3u;             // steps of a unit
+    constexpr uint32_t NF = MODE == kRow ? 3u : 1u;               // vectors of a unit that are loaded per column tile
+    constexpr uint32_t kSlots = units_in_flight(MR, MODE, QT);
+    constexpr uint32_t kOutside = 0x80000000u;                    // an offset beyond any x or y (the host: fewer than 2^31 bytes)
+    const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t unit = unit_of_workgroup(), split = p.n_mtiles_by(unit), mtile = unit - split * p.n_mtiles;
+    const uint32_t col = lane & 15u, kg = lane >> 4;              // MFMA operand layout: row or column, group of 8 k
+    const uint32_t wk = (wave * p.t_groups_inv) >> 16, wt = wave - wk * p.t_groups;
+    const uint32_t split_begin = split * p.pixels_per_split;
+    const uint32_t split_end = min(split_begin + p.pixels_per_split, p.n_pixels);
+
+    // B: lane holds column lane % 16 of each of the wavefront's QT column tiles.  Where the taps of the first kernel row read
+    // (byte of x; kOutside: outside the image), that row, byte of y (kOutside: no pixel)
+    uint32_t from[NF][QT], out_at[QT];
+    int32_t h0[QT];
+    [[maybe_unused]] uint32_t edge_from = kOutside;               // kShift: of the pixel before the first column (lanes 0) and
+    [[maybe_unused]] int32_t edge_h0 = 0;                         // behind the last (lanes 15)
+    [[maybe_unused]] uint32_t not_left[QT], not_right[QT];        // all bits, or none in the image's first, last column
+    const uint32_t y_elem = p.y_bf16 ? 1u : 2u;                   // log2 bytes
+    auto pixel_of = [&](uint32_t pix, uint32_t end, uint32_t& b, uint32_t& ho, uint32_t& wo) {    // returns the pixel's byte of y
+        const uint32_t t = __umulhi(2u * pix, p.out_w_magic) >> p.out_w_shift;
+        wo = pix - t * p.out_w;
+        b = __umulhi(2u * t, p.out_h_magic) >> p.out_h_shift;
+        ho = t - b * p.out_h;
+        // D: lane holds column lane % 16, rows 4 * (lane / 16) + 0..3 of a row tile
+        const uint32_t at = (b * p.y_image + (ho * p.out_w + wo) * p.y_pixel + (kg >> 1) * p.y_block + 4u * (kg & 1u)) << y_elem;
+        return pix < end ? at : kOutside;
+    };
+    // a round's tiles dealt evenly: QT or one fewer each
+    auto first_tile = [&](uint32_t g) { return g * p.wave_tiles + min(g, p.wave_tiles_rest); };
+    const bool has_last = first_tile(wt + 1u) - first_tile(wt) == QT;
+    auto place = [&](uint32_t t0) {                               // of the round from tile t0 on
+        const uint32_t pix0 = split_begin + 16u * (t0 + first_tile(wt)), end = min(split_begin + 16u * (t0 + first_tile(wt + 1u)), split_end);
+#pragma unroll
+        for (uint32_t q = 0; q < QT; ++q) {
+            const uint32_t pix = pix0 + q * 16u + col;
+            uint32_t b, ho, wo;
+            out_at[q] = pixel_of(pix, end, b, ho, wo);
+            h0[q] = int32_t(ho * p.stride) - int32_t(p.pad);
+            const int32_t w0 = int32_t(wo * p.stride) - int32_t(p.pad);
+            const uint32_t corner = (b * p.x_image + uint32_t(h0[q] * int32_t(p.in_w) + w0) * p.x_pixel + kg * p.x_block) * 2u;
+            if constexpr (MODE == kShift) {                       // (a column that is not stored may be a neighbour's neighbour)
+                from[0][q] = pix < p.n_pixels ? corner + p.x_pixel * 2u : kOutside;
+                not_left[q] = wo != 0u ? 0xFFFFFFFFu : 0u;
+                not_right[q] = wo + 1u != p.out_w ? 0xFFFFFFFFu : 0u;
+            } else {
+#pragma unroll
+                for (uint32_t sx = 0; sx < NS; ++sx)
+                    from[sx][q] = ((uint32_t(w0 + int32_t(sx)) < p.in_w) & (pix < end)) ? corner + sx * p.x_pixel * 2u : kOutside;
+            }
+        }
+        if constexpr (MODE == kShift) {
+            const uint32_t pix = col == 0u ? pix0 - 1u : pix0 + 16u * QT;      // (before pixel 0: beyond all; a tile that is not there
+                                                                  // is loaded all the same)
+            uint32_t b, ho, wo;
+            pixel_of(min(pix, p.n_pixels - 1u), 0u, b, ho, wo);
+            edge_h0 = int32_t(ho) - 1;
+            const bool is_edge = (col == 0u) | (col == 15u);
+            edge_from = is_edge && pix < p.n_pixels
+                            ? (b * p.x_image + uint32_t(edge_h0 * int32_t(p.in_w) + int32_t(wo)) * p.x_pixel + kg * p.x_block) * 2u : kOutside;
+        }
+    };
+    const anszp_layer_t lay = decode_panel<MR, P16>(p, lds, mtile, [&] { place(0u); });
+    __syncthreads();
+    if constexpr (!P16) widen_panel<MR>(p, lds, lay);
+
+    const uint32_t a_at = lds_address(lds) + (P16 ? p.panel_off : 0u) + (col * p.row_stride + 8u * kg) * 2u;
+    const uint32_t tile_stride = kRows * p.row_stride * 2u;
+    const uint32_t blocks = p.cin / 32u, units = (MODE != kPoint ? p.kh : 1u) * blocks;
+    const uint32_t u_begin = wk * p.slice_units, n = min(p.slice_units, units - min(u_begin, units));
+    const uint32_t row0 = MODE != kPoint ? __umulhi(2u * u_begin, p.blocks_magic) >> p.blocks_shift : 0u;
+    const __amdgpu_buffer_rsrc_t y_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, p.y_bytes, 0x00020000);
+    const bool per_channel = lay.channel_len != 0;
+    auto store = [&](uint32_t m, uint32_t at, const floatx4 sum) {
+        const uint32_t tile = mtile * MR + m;                     // (o = 16 * tile + 4 * kg + i)
+        float sc[4] = {lay.scale, lay.scale, lay.scale, lay.scale};
+        if (per_channel) {
+#pragma unroll 1
+            for (uint32_t i = 0; i < 4; ++i) {
+                const uint64_t ch = lay.scales_offset + tile * kRows + 4u * kg + i;
+                const float v = ch < p.n_scales ? p.scales[ch] : 0.0f;
+                sc[0] = i == 0u ? v : sc[0]; sc[1] = i == 1u ? v : sc[1]; sc[2] = i == 2u ? v : sc[2]; sc[3] = i == 3u ? v : sc[3];
+            }
+        }
+        const floatx4 out = {sum[0] * sc[0], sum[1] * sc[1], sum[2] * sc[2], sum[3] * sc[3]};
+        const uint32_t tile_at = (2u * tile * p.y_block) << y_elem;
+        if (p.y_bf16) {                                           // round to nearest even (v_cvt_pk_bf16_f32)
+            typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+            const bf16x4 r = {static_cast<__bf16>(out[0]), static_cast<__bf16>(out[1]), static_cast<__bf16>(out[2]), static_cast<__bf16>(out[3])};
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(words2, r), y_rsrc, at, tile_at, 0);
+        } else {
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(words4, out), y_rsrc, at, tile_at, 0);
+        }
+    };
+    for (uint32_t t0 = 0;;) {
+        floatx4 acc[MR][QT];
+#pragma unroll
+        for (uint32_t m = 0; m < MR; ++m)
+#pragma unroll
+            for (uint32_t q = 0; q < QT; ++q) acc[m][q] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        // the cursors of the loads and of the multiplications: kernel row and block of 32 channels of the next unit
+        uint32_t row = row0, cb = u_begin - row0 * blocks, use_cb = cb, k_use = row0 * NS * p.cin + cb * 32u, asked = 0;
+        words4 ring[kSlots][NF][QT];
+        [[maybe_unused]] words4 edge[kSlots];
+        auto request = [&](uint32_t slot) {
+            const __amdgpu_buffer_rsrc_t x = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.x), 0, asked < n ? p.x_bytes : 0u, 0x00020000);
+            const uint32_t at = asked < n ? cb * 8u * p.x_block : 0u;      // (an empty buffer's check must not overflow)
+            // (what is outside stays beyond the buffer: no row is 2^31 bytes away)
+            const uint32_t row_at = MODE == kPoint ? 0u : row * p.in_w * p.x_pixel * 2u;
+            auto in_row = [&](int32_t first_row, uint32_t where) {
+                return MODE == kPoint ? where : uint32_t(first_row + int32_t(row)) < p.in_h ? where + row_at : kOutside;
+            };
+#pragma unroll
+            for (uint32_t q = 0; q < QT; ++q)
+#pragma unroll
+                for (uint32_t f = 0; f < NF; ++f) ring[slot][f][q] = __builtin_amdgcn_raw_buffer_load_b128(x, in_row(h0[q], from[f][q]), at, 0);
+            if constexpr (MODE == kShift) edge[slot] = __builtin_amdgcn_raw_buffer_load_b128(x, in_row(edge_h0, edge_from), at, 0);
+            ++asked;
+            ++cb;
+            if constexpr (MODE != kPoint) {
+                const bool next_row = cb == blocks;               // (without a branch)
+                cb = next_row ? 0u : cb;
+                row += next_row ? 1u : 0u;
+            }
+        };
+#pragma unroll
+        for (uint32_t d = 0; d < kSlots; ++d) request(d);
+#pragma unroll 1
+        for (uint32_t done = 0; done < n; done += kSlots) {
+#pragma unroll
+            for (uint32_t d = 0; d < kSlots; ++d) {
+                uint32_t a_step = a_at + k_use * 2u;
+#pragma unroll
+                for (uint32_t sx = 0; sx < NS; ++sx) {
+                    auto operand = [&](uint32_t q) {              // (q is a constant once unrolled)
+                        if constexpr (MODE != kShift) return ring[d][sx][q];
+                        if (sx == 1u) return ring[d][0][q];
+                        if (sx == 0u) return q ? neighbours<true, true>(ring[d][0][q], ring[d][0][q ? q - 1u : 0u], not_left[q])
+                                               : neighbours<true, false>(ring[d][0][q], edge[d], not_left[q]);
+                        return q + 1u < QT ? neighbours<false, true>(ring[d][0][q], ring[d][0][q + 1u < QT ? q + 1u : q], not_right[q])
+                                           : neighbours<false, false>(ring[d][0][q], edge[d], not_right[q]);
+                    };
+                    bf16x8 a[MR];
+#pragma unroll
+                    for (uint32_t m = 0; m < MR; ++m) a[m] = lds_load<bf16x8>(a_step + m * tile_stride);
+                    auto multiply = [&](uint32_t q) {
+                        const bf16x8 b = __builtin_bit_cast(bf16x8, operand(q));
+#pragma unroll
+                        for (uint32_t m = 0; m < MR; ++m) acc[m][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], b, acc[m][q], 0, 0, 0);
+                    };
+#pragma unroll
+                    for (uint32_t q = 0; q + 1u < QT; ++q) multiply(q);
+                    if (has_last) multiply(QT - 1u);              // (uniform)
+                    a_step += p.cin * 2u;
+                }
+                // (behind the slice's last unit: that one's weights times zeros)
+                const bool more = done + d + 1u < n;
+                use_cb += more ? 1u : 0u;
+                k_use += more ? 32u : 0u;
+                if constexpr (MODE != kPoint) {
+                    const bool next_row = use_cb == blocks;
+                    use_cb = next_row ? 0u : use_cb;
+                    k_use += next_row ? 2u * p.cin : 0u;
+                }
+                request(d);
+            }
+        }
+        if (p.k_groups == 1u) {
+#pragma unroll
+            for (uint32_t m = 0; m < MR; ++m)
+#pragma unroll
+                for (uint32_t q = 0; q < QT; ++q) store(m, out_at[q], acc[m][q]);
+            t0 += p.round_tiles;
+            if (split_begin + 16u * t0 >= split_end) break;
+            place(t0);
+        } else {
+            // One round.  Every wavefront leaves its sums in LDS, 1 KiB per tile and row tile ([slice][tile range][q][m]);
+            // the wavefronts then take the blocks in turn, add up the slices' and store.
+            const uint32_t block_bytes = kWave * 16u, slice_bytes = p.t_groups * QT * MR * block_bytes;
+            __syncthreads();                                      // every wavefront has read what it needs of the panel
+            const uint32_t mine = lds_address(lds) + wk * slice_bytes + wt * (QT * MR * block_bytes) + lane * 16u;
+#pragma unroll
+            for (uint32_t q = 0; q < QT; ++q)
+#pragma unroll
+                for (uint32_t m = 0; m < MR; ++m) lds_store<floatx4>(mine + (q * MR + m) * block_bytes, acc[m][q]);
+            __syncthreads();
+            const uint32_t n_blocks = p.t_groups * QT * MR;
+#pragma unroll 1
+            for (uint32_t i = wave; i < n_blocks; i += kWaves) {
+                const uint32_t m = i % MR, tq = i / MR, g = tq / QT, q = tq - g * QT;        // (constants)
+                const uint32_t tile = first_tile(g) + q, pix = split_begin + 16u * tile + col;
+                uint32_t b, ho, wo;
+                const uint32_t at = pixel_of(pix, tile < first_tile(g + 1u) ? split_end : 0u, b, ho, wo);
+                uint32_t part = lds_address(lds) + i * block_bytes + lane * 16u;
+                floatx4 sum = lds_load<floatx4>(part);
+#pragma unroll 1
+                for (uint32_t j = 1; j < p.k_groups; ++j) {
+                    part += slice_bytes;
+                    sum += lds_load<floatx4>(part);
+                }
+                store(m, at, sum);
+            }
+            break;
+        }
+    }
+}
+
 constexpr uint32_t kMaxK = 4608;           // reduction length whose 16-row panel (72 KiB) fits LDS beside the table
 constexpr uint32_t kLdsLimit = 160u * 1024u;
+
+// The most column tiles per wavefront the registers hold.
+constexpr uint32_t most_tiles(uint32_t mr, uint32_t mode) { return mode == kRow ? (mr == 1u ? 4u : 3u) : mr == 4u ? 3u : 4u; }
+
+template <uint32_t MR, bool P16, uint32_t MODE>
+void (*sliced_kernel(uint32_t qt))(ConvParams) {
+    if constexpr (most_tiles(MR, MODE) == 4u) {
+        if (qt == 4u) return conv_sliced_kernel<MR, P16, MODE, 4>;
+    }
+    return qt == 3u ? conv_sliced_kernel<MR, P16, MODE, 3> : qt == 2u ? conv_sliced_kernel<MR, P16, MODE, 2> : conv_sliced_kernel<MR, P16, MODE, 1>;
+}
+template <uint32_t MR, bool P16>
+void (*sliced_kernel(uint32_t mode, uint32_t qt))(ConvParams) {
+    return mode == kPoint ? sliced_kernel<MR, P16, kPoint>(qt) : mode == kShift ? sliced_kernel<MR, P16, kShift>(qt) : sliced_kernel<MR, P16, kRow>(qt);
+}
+
+template <uint32_t MR, bool P16>
+bool allow_all_lds(uint32_t mode) {
+    for (uint32_t qt = 1; qt <= most_tiles(MR, mode); ++qt)
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(sliced_kernel<MR, P16>(mode, qt)), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+            return false;
+    return true;
+}
+
+int launch_sliced(const ConvParams& p, uint32_t mr, bool p16, uint32_t mode, uint32_t qt, int device, uint32_t groups, uint32_t lds_bytes, hipStream_t s) {
+    void (*const kernel)(ConvParams) =
+        p16 ? (mr == 4 ? sliced_kernel<4, true>(mode, qt) : mr == 2 ? sliced_kernel<2, true>(mode, qt) : sliced_kernel<1, true>(mode, qt))
+            : (mr == 4 ? sliced_kernel<4, false>(mode, qt) : mr == 2 ? sliced_kernel<2, false>(mode, qt) : sliced_kernel<1, false>(mode, qt));
+    // the kernels may use all of the CU's LDS: said for all of them by a device's first call, because which one a layer gets
+    // depends on the batch too, and a call may be captured whose layer ran before with another batch (concurrent first callers
+    // at worst both say it)
+    static std::atomic<bool> allowed[64];
+    if (device < 0 || device >= 64) return ANSZP_E_HIP;
+    if (!allowed[device].load(std::memory_order_acquire)) {
+        for (uint32_t every = kPoint; every <= kRow; ++every)
+            if (!allow_all_lds<4, true>(every) || !allow_all_lds<2, true>(every) || !allow_all_lds<1, true>(every) ||
+                !allow_all_lds<4, false>(every) || !allow_all_lds<2, false>(every) || !allow_all_lds<1, false>(every)) return ANSZP_E_HIP;
+        allowed[device].store(true, std::memory_order_release);
+    }
+    hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), std::max(lds_bytes, 65536u), s, p);
+    return hipGetLastError() == hipSuccess ? ANSZP_OK : ANSZP_E_HIP;
+}
+
+// conv_sliced_kernel's row tiles, column tiles, slices and panel form for a call: the fewest clocks by an estimate, all its constants in clocks
+// and fitted to 28 layers of a ResNet-50 at batches of 16 and 64 with every choice forced in turn (on average the choice is 2 %
+// slower than the best one).  Decoding: rounds of chunks over the twelve wavefronts, 2500 and half a clock per symbol each.
+// Widening a panel of bytes: 5000.  A unit of a wavefront: whichever takes longest of its SIMD's wavefronts' matrix
+// instructions (16 each), all wavefronts' panel reads (8), all wavefronts' activation loads (24) and a load's latency over
+// the units in flight (2400).  Rounds of tiles: that latency again.  Slices: 1500 and 64 bytes of sums a clock.
+struct SlicedPlan {
+    uint32_t mr = 0, qt = 0, k_groups = 0, round_tiles = 0, slice_units = 0, splits = 0, tiles_per_split = 0, lds_bytes = 0;
+    bool p16 = false;
+};
+SlicedPlan plan_sliced(const anszp_conv_args_t& a, uint32_t mode, uint32_t K, uint32_t row_stride, uint32_t n_tiles, uint32_t cus) {
+    const uint32_t table_bytes = 16u << a.table_log, fixed = kStageBytes + table_bytes + 64u;
+    const uint32_t taps = mode == kPoint ? 1u : 3u, units = (mode == kPoint ? 1u : a.kh) * (a.cin / 32u);
+    SlicedPlan best;
+    uint64_t fewest = ~0ull;
+    for (const uint32_t mr : {4u, 2u, 1u}) {
+        if (a.cout % (kRows * mr)) continue;
+        const uint32_t elems = kRows * mr * row_stride;
+        const bool p16 = fixed + 2u * elems <= kLdsLimit;         // the panel decoded as bf16 values; else as bytes, widened in place
+        if (!p16 && (fixed + elems > kLdsLimit || 2u * (elems + 64u) > kLdsLimit || elems + 64u > kWidenPieces * kThreads * 16u)) continue;
+        const uint32_t n_mtiles = a.cout / (kRows * mr), most = most_tiles(mr, mode);
+        // few, long-lived workgroups, as many as are resident at once (one per CU): each decodes its panel once
+        uint32_t splits = std::max(1u, std::min((cus + n_mtiles - 1u) / n_mtiles, n_tiles));
+        const uint32_t tiles = (n_tiles + splits - 1u) / splits;
+        splits = (n_tiles + tiles - 1u) / tiles;
+        const uint32_t chunk_rounds = (kRows * mr / a.rows_per_chunk + kWaves - 1u) / kWaves;
+        const uint64_t decode = chunk_rounds * (2500u + uint64_t(a.rows_per_chunk) * K / 2u) + (p16 ? 0u : 5000u);
+        for (const uint32_t ks : {1u, 2u, 3u, 4u, 6u, 12u}) {
+            const uint32_t ts = kWaves / ks, rounds = (tiles + most * ts - 1u) / (most * ts);
+            const uint32_t per_round = (tiles + rounds - 1u) / rounds, qt = (per_round + ts - 1u) / ts;
+            const uint64_t sums = ks > 1u ? uint64_t(kWaves) * qt * mr * 1024u : 0u;
+            if (ks > 1u && (rounds > 1u || units < ks || sums > kLdsLimit)) continue;
+            const uint32_t busy = (per_round + qt - 1u) / qt * ks, slots = units_in_flight(mr, mode, qt);
+            const uint64_t mfma = uint64_t((busy + 3u) / 4u) * qt * mr * taps * 16u, reads = uint64_t(busy) * mr * taps * 8u;
+            const uint64_t loads = uint64_t(busy) * (mode == kRow ? 3u * qt : mode == kShift ? qt + 1u : qt) * 24u;
+            const uint64_t unit = std::max(std::max(mfma, reads), std::max<uint64_t>(loads, 2400u / slots));
+            const uint64_t clocks = decode + rounds * ((units + ks - 1u) / ks * unit + 2400u) + (ks > 1u ? 1500u + sums / 64u : 0u);
+            if (clocks >= fewest) continue;
+            fewest = clocks;
+            best.mr = mr; best.p16 = p16; best.qt = qt; best.k_groups = ks; best.round_tiles = per_round;
+            best.slice_units = (units + ks - 1u) / ks; best.splits = splits; best.tiles_per_split = tiles;
+            best.lds_bytes = std::max(std::max(fixed + elems * (p16 ? 2u : 1u), p16 ? 0u : 2u * (elems + 64u)), uint32_t(sums));
+        }
+    }
+    return best;                                                  // (one row tile always fits: K <= 4608)
+}
+
+// The whole call in launches of at most `images` images.
+int conv_sliced(ConvParams p, const anszp_conv_args_t& a, uint32_t images, uint32_t cus, int device, hipStream_t s) {
+    const uint32_t mode = a.kw != 3 ? kPoint : a.stride == 1 && a.pad == 1 ? kShift : kRow;
+    p.x_image = a.in_h * a.in_w * a.cin;
+    p.y_image = p.out_h * p.out_w * a.cout;
+    p.panel_off = kStageBytes + (16u << a.table_log);
+    auto magic = [](uint32_t d, uint32_t& m, uint32_t& shift) {
+        for (shift = 0; (1ull << shift) < d; ++shift) {}
+        m = uint32_t((1ull << (31 + shift)) / d + 1u);
+    };
+    magic(p.out_w, p.out_w_magic, p.out_w_shift);
+    magic(p.out_h, p.out_h_magic, p.out_h_shift);
+    magic(a.cin / 32u, p.blocks_magic, p.blocks_shift);
+    for (uint32_t first = 0; first < a.batch; first += images) {
+        const uint32_t n = std::min(images, a.batch - first);
+        p.x = a.x + uint64_t(first) * p.x_image;
+        p.y = static_cast<uint8_t*>(a.y) + uint64_t(first) * p.y_image * (p.y_bf16 ? 2u : 4u);
+        p.x_bytes = uint32_t(uint64_t(n) * p.x_image * 2u);
+        p.y_bytes = uint32_t(uint64_t(n) * p.y_image * (p.y_bf16 ? 2u : 4u));
+        p.n_pixels = n * p.out_h * p.out_w;
+        const SlicedPlan plan = plan_sliced(a, mode, p.K, p.row_stride, (p.n_pixels + 15u) / 16u, cus);
+        if (!plan.mr) return ANSZP_E_RANGE;
+        p.n_mtiles = a.cout / (kRows * plan.mr);
+        magic(p.n_mtiles, p.n_mtiles_magic, p.n_mtiles_shift);
+        p.chunks_per_panel = kRows * plan.mr / a.rows_per_chunk;
+        p.pixels_per_split = 16u * plan.tiles_per_split;
+        p.k_groups = plan.k_groups;
+        p.t_groups = kWaves / plan.k_groups;
+        p.t_groups_inv = 65536u / p.t_groups + 1u;
+        p.wave_tiles = plan.round_tiles / p.t_groups;
+        p.wave_tiles_rest = plan.round_tiles % p.t_groups;
+        p.round_tiles = plan.round_tiles;
+        p.slice_units = plan.slice_units;
+        const int rc = launch_sliced(p, plan.mr, plan.p16, mode, plan.qt, device, p.n_mtiles * plan.splits, plan.lds_bytes, s);
+        if (rc != ANSZP_OK) return rc;
+    }
+    return ANSZP_OK;
+}
+
 constexpr uint32_t kMaxK16 = 576;          // up to here 64 rows fit as bf16 (73 KiB), and no conversion is left in the loop
 
 }  // namespace
@@ -1332,20 +1375,6 @@ extern "C" int anszp_conv_fused(const anszp_conv_args_t* a, void* stream) {
     if (a->x_layout > ANSZP_ACT_C8 || a->y_layout > ANSZP_ACT_C8) return ANSZP_E_RANGE;
     if (a->x_layout == ANSZP_ACT_C8 && (a->cin % 8u) != 0) return ANSZP_E_RANGE;
     if (a->n_chunks < a->cout / R) return ANSZP_E_RANGE;
-    // Row tiles per workgroup: as many of 4, 2, 1 as divide the output channels and leave the panel room in LDS
-    // beside the table and the staging buffers (more rows per activation vector loaded).
-    const uint32_t row_stride = ((uint32_t(K) + 31u) & ~31u) + kRowPad;
-    const uint32_t table_bytes = 16u << a->table_log;             // the look-ahead entries
-    const uint32_t fixed_bytes = kStageBytes + table_bytes + 64u;
-    const bool p16 = K <= kMaxK16;                              // short rows: the panel as bf16
-    const uint32_t elem = p16 ? 2u : 1u;
-    uint32_t mr = 4;
-    while (mr > 1 && ((a->cout % (kRows * mr)) != 0 || fixed_bytes + kRows * mr * row_stride * elem > kLdsLimit)) mr >>= 1;
-    // A 3 x 3 kernel of stride 1 stages its activations in LDS where at most two row tiles fit anyway (K > 1152): with
-    // four, the loads of a kernel row's three taps issued together do as well through the L1 (measured), and the
-    // accumulators and operands in flight of four row tiles would not fit the patch kernel's registers.
-    const bool patch_wanted = (a->cin % 32u) == 0 && a->cin >= 128u && a->kh == 3 && a->kw == 3 && a->stride == 1 && mr <= 2;
-    const uint32_t n_mtiles = a->cout / (kRows * mr);
     if ((reinterpret_cast<uintptr_t>(a->x) | reinterpret_cast<uintptr_t>(a->y) | reinterpret_cast<uintptr_t>(a->payload) |
          reinterpret_cast<uintptr_t>(a->tables)) & 15u) return ANSZP_E_RANGE;
 
@@ -1368,14 +1397,31 @@ extern "C" int anszp_conv_fused(const anszp_conv_args_t* a, void* stream) {
     const uint64_t reach = uint64_t(R) * K + 8u * a->n_streams;
     p.k_magic24 = (1u << 24) / uint32_t(K) + 1u;
     p.stage_words = R == 1u || (K > 1u && reach < 65536u && reach * K < (1u << 24)) ? kStageWords : 0u;
+    const uint32_t row_stride = ((uint32_t(K) + 31u) & ~31u) + kRowPad, table_bytes = 16u << a->table_log;      // (the look-ahead entries)
     p.row_stride = row_stride;
-    p.chunks_per_panel = kRows * mr / R;
     p.n_pixels = uint32_t(n_pixels);
-    p.n_mtiles = n_mtiles;
 
     int device = 0, cus = 0;
     if (hipGetDevice(&device) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) return ANSZP_E_HIP;
+    const bool generic = (a->cin % 8u) != 0;
+    const bool pointwise = !generic && a->kh == 1 && a->kw == 1 && a->pad == 0;
+    if ((a->cin % 32u) == 0 && (pointwise || a->kw == 3)) {
+        // buffer offsets are 31 bits: as many images at a time as x and y of that size allow (all of them, but for very large calls)
+        const uint64_t x_image = uint64_t(a->in_h) * a->in_w * a->cin, y_image = uint64_t(out_h) * out_w * a->cout;
+        const uint64_t most = ((1ull << 31) - 1u) / std::max(2u * x_image, (p.y_bf16 ? 2u : 4u) * y_image);
+        if (most) return conv_sliced(p, *a, uint32_t(std::min<uint64_t>(most, a->batch)), uint32_t(cus > 0 ? cus : 256), device, static_cast<hipStream_t>(stream));
+    }
+    // Row tiles per workgroup: as many of 4, 2, 1 as divide the output channels and leave the panel room in LDS
+    // beside the table and the staging buffers (more rows per activation vector loaded).
+    const uint32_t fixed_bytes = kStageBytes + table_bytes + 64u;
+    const bool p16 = K <= kMaxK16;                              // short rows: the panel as bf16
+    const uint32_t elem = p16 ? 2u : 1u;
+    uint32_t mr = 4;
+    while (mr > 1 && ((a->cout % (kRows * mr)) != 0 || fixed_bytes + kRows * mr * row_stride * elem > kLdsLimit)) mr >>= 1;
+    const uint32_t n_mtiles = a->cout / (kRows * mr);
+    p.chunks_per_panel = kRows * mr / R;
+    p.n_mtiles = n_mtiles;
     // Every workgroup decodes its panel once, so few, long-lived workgroups: as many as are resident at once,
     // which is one per CU (twelve wavefronts of more than 128 VGPRs fill a CU's four SIMDs whatever the LDS
     // would allow).  A panel's pixels are dealt out in column tiles of 16, evenly over the workgroups that
@@ -1392,50 +1438,9 @@ extern "C" int anszp_conv_fused(const anszp_conv_args_t* a, void* stream) {
     p.block_pixels = 16u * (tiles_per_wave < 4u ? tiles_per_wave : 4u);
 
     // (fixed_bytes counts 64 bytes beyond the panel: the last 32 k of a kernel tap may reach past the end of the last row)
-    const bool generic = (a->cin % 8u) != 0;
-    const bool pointwise = !generic && a->kh == 1 && a->kw == 1 && a->pad == 0;
     const uint32_t panel_bytes = kRows * mr * row_stride * elem;
     uint32_t lds_total = lds_bytes;
-    // 1 x 1 kernels whose input channels are a multiple of 64: the contraction with several steps' loads in flight;
-    // a panel of bytes is widened to bf16 in place first, which needs twice its room from the start of LDS
-    bool ring = pointwise && (a->cin % 64u) == 0;
-    if (ring && !p16) {
-        ring = panel_bytes + 64u <= kWidenPieces * kThreads * 16u && 2u * (panel_bytes + 64u) <= kLdsLimit;
-        if (ring && lds_total < 2u * (panel_bytes + 64u)) lds_total = 2u * (panel_bytes + 64u);
-    }
-    const uint32_t depth = ring ? ((a->cin % 128u) == 0 ? 4u : 2u) : 0u;
-    // Kernels of several taps (or with padding) whose input channels are a multiple of 32: the patch in LDS.  The
-    // pixels a wavefront takes per round are the most (of 64, 48, 32, 16, and no more than the workgroup's share
-    // asks for) whose largest possible patch fits: in pieces per thread, and, with the slab of widened weights,
-    // in the LDS below the panel.
     p.panel_off = kStageBytes + table_bytes;
-    bool patch = patch_wanted;
-    if (patch) {
-        const uint32_t S = a->stride, Hp = a->in_h + 2u * a->pad, Wp = a->in_w + 2u * a->pad, Wh = (Wp + S - 1u) / S;
-        const uint32_t taps = a->kh * a->kw;
-        const uint32_t slab_bytes = p16 ? 0u : ((kRows * mr * (taps * 64u + 16u) + 63u) & ~63u);
-        const int64_t gap = int64_t(Hp) - int64_t(out_h) * S;     // patch rows between the last output row of an image and the next image's first
-        uint32_t wave_pixels = std::min(p.block_pixels, 48u);
-        patch = false;
-        for (; wave_pixels >= 16u; wave_pixels -= 16u) {
-            const uint64_t round = std::min<uint64_t>(uint64_t(kWaves) * wave_pixels, p.pixels_per_split);
-            const uint64_t rows_out = (round + out_w - 2u) / out_w + 1u;                   // output rows a round can touch
-            const uint64_t crossings = std::min<uint64_t>(a->batch - 1u, (rows_out + out_h - 2u) / out_h);
-            const uint64_t rows = (rows_out - 1u) * S + a->kh + crossings * uint64_t(gap > 0 ? gap : 0);
-            const uint64_t patch_bytes = rows * S * Wh * 64u;
-            const uint64_t below = std::max<uint64_t>(p.panel_off, slab_bytes + patch_bytes);
-            if (rows * 4u * Wp <= kPatchPieces * kThreads && below + panel_bytes + 64u <= kLdsLimit) {
-                patch = true;
-                p.wave_pixels = wave_pixels;
-                p.patch_off = slab_bytes;
-                p.patch_plane = uint32_t(rows * S * Wh * 16u);
-                p.panel_off = uint32_t((below + 15u) & ~uint64_t(15));
-                lds_total = p.panel_off + panel_bytes + 64u;
-                break;
-            }
-        }
-        if (!patch) p.panel_off = kStageBytes + table_bytes;
-    }
     bool generic_patch = false;
     if (generic) {
         // image rows that are multiples of 16 bytes (NHWC): the rows under a round of pixels staged in LDS, if the most
@@ -1473,28 +1478,24 @@ extern "C" int anszp_conv_fused(const anszp_conv_args_t* a, void* stream) {
     }
     // other kernels of several taps: the ring of loads, if the channels allow whole groups of steps per tap and a
     // step's stride fits a 24-bit multiplication
-    const bool taps_ring = !generic && !pointwise && !patch && (a->cin % 64u) == 0 && 4ull * p.x_block < (1u << 24) &&
+    const bool taps_ring = !generic && !pointwise && (a->cin % 64u) == 0 && 4ull * p.x_block < (1u << 24) &&
                            (p16 || (panel_bytes + 64u <= kWidenPieces * kThreads * 16u && 2u * (panel_bytes + 64u) <= kLdsLimit));
     if (taps_ring && !p16 && lds_total < 2u * (panel_bytes + 64u)) lds_total = 2u * (panel_bytes + 64u);
     const uint32_t taps_depth = taps_ring ? ((a->cin % 128u) == 0 ? 4u : 2u) : 0u;
-    const bool taps_rows = taps_ring && a->kw == 3;
-    const int kind = generic_patch ? kGenericPatch : generic ? kGeneric : ring ? kPointwiseRing : pointwise ? kPointwise : patch ? kTapsPatch
-                   : taps_rows ? kTapsRows : taps_ring ? kTapsRing : kTaps;
+    const int kind = generic_patch ? kGenericPatch : generic ? kGeneric : taps_ring ? kTapsRing : pointwise ? kPointwise : kTaps;
     void (*kernel)(ConvParams) = nullptr;
 #define ANSZP_CONV_PICK(KIND, D)                                                                                       \
     (p16 ? (mr == 4 ? conv_fused_kernel<KIND, 4, true, D> : mr == 2 ? conv_fused_kernel<KIND, 2, true, D> : conv_fused_kernel<KIND, 1, true, D>) \
          : (mr == 4 ? conv_fused_kernel<KIND, 4, false, D> : mr == 2 ? conv_fused_kernel<KIND, 2, false, D> : conv_fused_kernel<KIND, 1, false, D>))
     kernel = kind == kGeneric ? ANSZP_CONV_PICK(kGeneric, 0) : kind == kPointwise ? ANSZP_CONV_PICK(kPointwise, 0)
-           : kind == kTaps ? ANSZP_CONV_PICK(kTaps, 0) : kind == kTapsPatch ? ANSZP_CONV_PICK(kTapsPatch, 0)
-           : kind == kGenericPatch ? ANSZP_CONV_PICK(kGenericPatch, 0) : kind == kTapsRows ? ANSZP_CONV_PICK(kTapsRows, 0)
-           : kind == kTapsRing ? (taps_depth == 4 ? ANSZP_CONV_PICK(kTapsRing, 4) : ANSZP_CONV_PICK(kTapsRing, 2))
-           : depth == 4 ? ANSZP_CONV_PICK(kPointwiseRing, 4) : ANSZP_CONV_PICK(kPointwiseRing, 2);
+           : kind == kTaps ? ANSZP_CONV_PICK(kTaps, 0) : kind == kGenericPatch ? ANSZP_CONV_PICK(kGenericPatch, 0)
+           : taps_depth == 4 ? ANSZP_CONV_PICK(kTapsRing, 4) : ANSZP_CONV_PICK(kTapsRing, 2);
 #undef ANSZP_CONV_PICK
     // the kernels may use all of the CU's LDS: said once per kernel and device (a table of atomics:
     // concurrent callers at worst both say it)
-    static std::atomic<bool> lds_allowed[2][10][3][64];
+    static std::atomic<bool> lds_allowed[2][6][3][64];
     const uint32_t slot = mr == 4 ? 2u : mr == 2 ? 1u : 0u;
-    const uint32_t kernel_no = kind == kPointwiseRing && depth == 4 ? 8u : kind == kTapsRing && taps_depth == 4 ? 9u : uint32_t(kind);
+    const uint32_t kernel_no = kind == kTapsRing && taps_depth == 4 ? 5u : uint32_t(kind);
     if (device < 0 || device >= 64) return ANSZP_E_HIP;
     if (!lds_allowed[p16][kernel_no][slot][device].load(std::memory_order_relaxed)) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -333,3 +333,70 @@ def test_launches_replayed_from_a_captured_graph(orc):
         torch.cuda.synchronize()
     for d, _ in calls:
         assert d.read_status() == (0, 0)
+
+
+# The kernel for input channels that are multiples of 32 (1 x 1 without padding; three taps wide): the edges of its tiles,
+# slices, rounds and images.  Same bound as everywhere in this file (fp32 sums of exact products, in any order).
+@pytest.mark.parametrize("shape,B_,H,Wd,stride,pad", [
+    ((16, 32, 1, 1), 1, 1, 1, 1, 0),          # one pixel, one unit
+    ((16, 4608, 1, 1), 1, 3, 5, 1, 0),        # 144 units over twelve slices, fewer pixels than a tile
+    ((64, 1024, 1, 1), 3, 5, 7, 1, 0),
+    ((128, 2304, 1, 1), 2, 9, 9, 1, 0),
+    ((48, 96, 1, 1), 2, 6, 6, 3, 0),          # three channel blocks, stride 3
+    ((16, 32, 1, 1), 40, 64, 64, 1, 0),       # ten thousand tiles: several rounds, one row tile
+    ((64, 64, 1, 1), 30, 56, 56, 1, 0),       # several rounds, four row tiles
+    ((64, 32, 3, 3), 70, 40, 40, 1, 1),       # several rounds of shifted columns
+    ((16, 32, 3, 3), 5, 1, 1, 1, 1),          # images of one pixel: every neighbour is outside
+    ((16, 32, 3, 3), 3, 1, 20, 1, 1),         # one row
+    ((32, 64, 3, 3), 3, 20, 1, 1, 1),         # one column
+    ((32, 64, 3, 3), 9, 2, 2, 1, 1),
+    ((64, 128, 3, 3), 5, 15, 17, 1, 1),       # image edges inside and at the ends of tiles
+    ((48, 256, 3, 3), 4, 16, 16, 1, 1),
+    ((32, 512, 3, 3), 3, 8, 8, 2, 1),
+    ((32, 64, 3, 3), 2, 12, 12, 1, 0),        # no padding: not the shifted form
+    ((32, 64, 3, 3), 2, 12, 12, 1, 2),
+    ((32, 64, 3, 3), 2, 13, 11, 3, 1),
+    ((16, 64, 1, 3), 2, 9, 9, 1, 1),          # kernels three wide that are not square, rows above and below the image
+    ((16, 32, 5, 3), 2, 9, 9, 1, 1),
+    ((16, 32, 5, 3), 2, 9, 9, 2, 2),
+])
+@pytest.mark.parametrize("layout", ["nhwc", "c8"])
+def test_sliced_contraction_at_its_edges(orc, shape, B_, H, Wd, stride, pad, layout):
+    _check(*_case(orc, shape, B_, H, Wd, stride, pad, x_layout=layout, y_layout=layout))
+
+
+# How a chunk's rows, streams and elements decide between the staged decode loops and the one from global memory.
+@pytest.mark.parametrize("shape,rows,n_streams", [
+    ((16, 1152, 1, 1), 16, 64),               # 18,432 elements a chunk: beyond the reciprocal's reach
+    ((16, 128, 3, 3), 4, 64), ((16, 128, 3, 3), 1, 33), ((16, 32, 1, 1), 16, 64), ((32, 32, 3, 3), 2, 1), ((16, 8, 1, 1), 8, 5),
+])
+def test_chunks_of_every_number_of_rows(orc, shape, rows, n_streams):
+    cout, cin, kh, kw = shape
+    K = cin * kh * kw
+    lay = _layer(shape, 4, 0.8, 11)
+    w = W.Workload("rows", [lay], 11, n_streams, rows * K, "bf16")
+    d = B.to_device(host_from_oracle(oracle_encode(orc, w), w))
+    codes, values = W.bf16_activations(2 * 6 * 6 * cin, 5)
+    x = torch.from_numpy(codes.view(np.int16).reshape(2, 6, 6, cin)).to("cuda:0").view(torch.bfloat16)
+    y = B.conv_fused(d, 0, 0, rows, x, shape, 1, kh // 2)
+    sym = lay.symbols().reshape(cout, kh, kw, cin)
+    x64 = values.astype(np.float64).reshape(2, 6, 6, cin)
+    wts = CO.dequantized_weights(sym, lay.zero_point, lay.scale, sym.shape)
+    _check(d.read_status(), y.cpu().numpy().astype(np.float64), CO.conv2d_nhwc(x64, wts, 1, kh // 2),
+           CO.conv2d_nhwc(np.abs(x64), np.abs(wts), 1, kh // 2))
+
+
+def test_activations_of_more_than_two_gibibytes(orc):
+    # 31-bit buffer offsets: such calls are split into several launches; the sums of 32 products have one order only
+    shape, n = (16, 32, 1, 1), 8300
+    lay = _layer(shape, 4, 0.7, 3)
+    w = W.Workload("large", [lay], 10, 64, 512, "bf16")
+    d = B.to_device(host_from_oracle(oracle_encode(orc, w), w))
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(1)
+    x = torch.randn((n, 64, 64, 32), generator=g, device="cuda:0", dtype=torch.bfloat16)
+    assert x.numel() * 2 > 1 << 31
+    y = B.conv_fused(d, 0, 0, 16, x, shape, 1, 0)
+    for first in (0, n // 2, n - 3):
+        assert torch.equal(y[first:first + 3], B.conv_fused(d, 0, 0, 16, x[first:first + 3].contiguous(), shape, 1, 0))
+    assert d.read_status() == (0, 0)
