@@ -428,7 +428,13 @@ __host__ __device__ __forceinline__ uint32_t stream_group_begin(uint32_t g, uint
     return static_cast<uint32_t>(uint64_t(g) * n / groups);
 }
 
-template <int OUT>
+// AHEAD: the words of a decoder's next block are asked for while the current one's last two entries are on their way.  For
+// workgroups of at most kStreamAheadDecoders decoders, which are mostly alone on their SIMDs: the chain of a step binds them
+// (seven matrices, 772 chunks of 262,144 symbols, three or four per CU: 270 -> 208 us; six per CU: 146 -> 120 us per 772).
+// Fuller workgroups are bound by what their SIMDs issue, where the fifth word and its shifts cost more than they give
+// (6,176 chunks, twelve per CU: 1.043 ms without, 1.065 with).
+constexpr uint32_t kStreamAheadDecoders = 8u;
+template <int OUT, bool AHEAD>
 __global__ __launch_bounds__(kStreamWaves * kWave) void decode_streaming(DecodeParams p, uint32_t n_chunks, uint32_t n_groups) {
     constexpr uint32_t kStates = 1u << ANSZP_MAX_TABLE_LOG;
     // one object, the tables first: their entries are then within reach of an LDS instruction's offset field
@@ -543,10 +549,18 @@ __global__ __launch_bounds__(kStreamWaves * kWave) void decode_streaming(DecodeP
         ring[s0 + 12][lane] = f.d.x; ring[s0 + 13][lane] = f.d.y; ring[s0 + 14][lane] = f.d.z; ring[s0 + 15][lane] = f.d.w;
         if (s0 == 0u) ring[kStreamRingWords][lane] = f.a.x;              // so that a pair of neighbouring words never wraps
     };
+    // AHEAD: the words of decoders that a loading wavefront feeds are kept with the stream's first bit on top, and counted from 32
+    constexpr uint32_t kFirstWord = AHEAD ? kStreamRingWords : 0u;
+    auto first_bit_on_top = [](Fetched& f) {
+        auto turn = [](words4& v) { v = words4{__brev(v.x), __brev(v.y), __brev(v.z), __brev(v.w)}; };
+        turn(f.a); turn(f.b); turn(f.c); turn(f.d);
+    };
 
     if (wave >= uint32_t(kStreamDecoders)) {
-        // ---- loading wavefront: decoders wave - 14, + 2, + 4, ... (little to issue, and others wait for it: first in line)
-        __builtin_amdgcn_s_setprio(3);
+        // ---- loading wavefront: decoders wave - 14, + 2, + 4, ...  Little to issue, and in a full workgroup others wait for
+        // it: first in line.  Else it is the decoders' chains of look-ups that the launch waits for (772 chunks: 226 us with
+        // the loading wavefronts first in line, 212 with all alike)
+        if constexpr (!AHEAD) __builtin_amdgcn_s_setprio(3);
         const uint32_t mine_index = wave - uint32_t(kStreamDecoders);
         const uint32_t* where[kStreamServed];             // all indexed by constants once the loops are unrolled
         uint32_t readable[kStreamServed], fetched[kStreamServed];
@@ -556,7 +570,7 @@ __global__ __launch_bounds__(kStreamWaves * kWave) void decode_streaming(DecodeP
             const uint32_t d = mine_index + uint32_t(j * kStreamLoaders);
             where[j] = p.payload;
             readable[j] = 0u;
-            fetched[j] = kStreamRingWords;                // the decoding wavefront fills its ring once itself
+            fetched[j] = kFirstWord + kStreamRingWords;   // the decoding wavefront fills its ring once itself
             alive[j] = false;
             if (d < count) {
                 const anszp_chunk_t cj = p.chunks[first + d];
@@ -592,7 +606,7 @@ __global__ __launch_bounds__(kStreamWaves * kWave) void decode_streaming(DecodeP
                             const bool started = at < kStreamNotStarted;
                             if (__ballot(started && ahead <= kStreamUrgentWords) != 0ull) {
                                 want[i] = started && ahead <= kStreamRingWords - kStreamFetchWords;
-                                if (want[i]) fetch(where[j], readable[j], fetched[j], f[i]);
+                                if (want[i]) fetch(where[j], readable[j], fetched[j] - kFirstWord, f[i]);
                             }
                         }
                     }
@@ -603,6 +617,7 @@ __global__ __launch_bounds__(kStreamWaves * kWave) void decode_streaming(DecodeP
                     if (j < kStreamServed) {
                         const uint32_t d = mine_index + uint32_t(j * kStreamLoaders);
                         if (want[i]) {
+                            if constexpr (AHEAD) first_bit_on_top(f[i]);
                             land(lds.rings[d], fetched[j], f[i]);
                             fetched[j] += kStreamFetchWords;
                             asm volatile("" ::: "memory");
@@ -667,9 +682,12 @@ __global__ __launch_bounds__(kStreamWaves * kWave) void decode_streaming(DecodeP
     uint32_t err = sums_up ? 0u : ANSZP_ST_BAD_DESC;
     const uint32_t full_steps = c.n_symbols / N;          // steps every stream of the chunk takes
 
+    const bool aligned = !per_channel || (lay.channel_len % kWave == 0u && in_channel0 % kWave == 0u);
+    const bool fed = fast && aligned && uint64_t(c.n_symbols) * kElemBytes < (1ull << 31);      // fast: all 64 lanes have a stream
     for (uint32_t at = 0; at < kStreamRingWords; at += kStreamFetchWords) {
         Fetched f;
         fetch(mine, readable, at, f);
+        if (AHEAD && fed) first_bit_on_top(f);
         land(ring, at, f);
     }
     uint32_t fetched = kStreamRingWords;                  // words of the stream that are in the ring or before it (when this wavefront fetches itself)
@@ -740,15 +758,13 @@ __global__ __launch_bounds__(kStreamWaves * kWave) void decode_streaming(DecodeP
         }
     };
 
-    const bool aligned = !per_channel || (lay.channel_len % kWave == 0u && in_channel0 % kWave == 0u);
-    const bool fed = fast && aligned && uint64_t(c.n_symbols) * kElemBytes < (1ull << 31);      // fast: all 64 lanes have a stream
     if (!fed) no_more_positions();
     if (lane < N) {
         if (fed) {
             // every wavefront-step lies inside one channel: one scale per run of steps, weights of
             // step k at chunk_out + at + k * 64 * kElemBytes; the stream words come from a loading wavefront
-            filled[lane] = kStreamRingWords;
-            position[lane] = abit >> 5;
+            filled[lane] = kFirstWord + kStreamRingWords;
+            position[lane] = kFirstWord + (abit >> 5);
             char* const chunk_out = static_cast<char*>(p.out) + c.out_offset * kElemBytes;
             uint32_t at = lane * kElemBytes;
             // The scale of a channel comes through the scalar cache: a vector load would have to be waited
@@ -762,7 +778,15 @@ __global__ __launch_bounds__(kStreamWaves * kWave) void decode_streaming(DecodeP
                 asm volatile("s_load_dword %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(v) : "s"(address) : "memory");
                 return __uint_as_float(v);
             };
-            float scale = per_channel ? uniform_scale(0) : lay.scale;
+            // AHEAD: not with a scalar load per channel, which the chain would wait for, but the scales of 64 channels at a time,
+            // one per lane (a wait for the stores in flight every 64 channels)
+            float scales_here = lay.scale;
+            auto scale_of_next = [&](uint32_t channel_in_chunk) {
+                if constexpr (!AHEAD) return uniform_scale(channel_in_chunk);
+                if ((channel_in_chunk & (kWave - 1u)) == 0u) scales_here = scale_of(channel_in_chunk + lane);
+                return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(scales_here), channel_in_chunk & (kWave - 1u)));
+            };
+            float scale = per_channel ? scale_of_next(0) : lay.scale;
             uint32_t channel = 0;                                          // within the chunk
             uint32_t left = uniform(per_channel ? (lay.channel_len - in_channel0) / kWave : 0xFFFFFFFFu);   // steps left under this scale
             const uint32_t steps = uniform(full_steps);
@@ -790,7 +814,7 @@ __global__ __launch_bounds__(kStreamWaves * kWave) void decode_streaming(DecodeP
             };
             // K steps from the ring as the loading wavefront fills it: the window's four words must be there
             const uint32_t filled_at = lds_address(&lds.filled[wave][lane]);
-            auto block_fed = [&](auto count_tag) {
+            auto block_at_once = [&](auto count_tag) {
                 uint32_t w0, w1, w2, w3, e0;
                 for (uint32_t spins = 0;;) {
                     // how far the ring is filled, read before the words themselves, and the entry of the current
@@ -814,6 +838,80 @@ __global__ __launch_bounds__(kStreamWaves * kWave) void decode_streaming(DecodeP
                 }
                 steps_fast(count_tag, w0, w1, w2, emit, [&]() { return e0; });
                 position[lane] = abit >> 5;
+            };
+            // A block of K steps.  The stream's next 96 bits are in w0..w2, the first on top, and the entry of the current state
+            // in e or on its way.  What a lone wavefront waits for is the chain of entries, so everything else happens while
+            // an entry is on its way: the words of the next block are asked for two steps ahead (five words, from the one that
+            // holds bit `before`, the last one read by then: the words behind it make the window whatever its place in its
+            // word) and then shifted by what the two steps read.
+            // (How far the ring is filled is read before the words: LDS accesses of a wavefront are performed in order.)
+            uint32_t w0, w1, w2, e, have, n0, n1, n2, n3, n4;
+            uint32_t before = abit + 32u * kStreamRingWords - 1u, sum = 0;     // sum: 32 - nb_bits (low bits) over the steps since `before`
+            uint32_t steps_since = 0;
+            auto ask = [&]() {
+                auto row_of = [&](uint32_t word) {
+                    return reinterpret_cast<const lds_uint32_t*>(static_cast<uintptr_t>(my_words + (((before + 32u * word) << 3) & ((kStreamRingWords - 1u) << 8))));
+                };
+                const lds_uint32_t *const p01 = row_of(0), *const p23 = row_of(2), *const p4 = row_of(4);
+                have = filled[lane];
+                asm volatile("" ::: "memory");
+                n0 = p01[0]; n1 = p01[kWave]; n2 = p23[0]; n3 = p23[kWave]; n4 = *p4;
+            };
+            auto missing = [&]() { return __ballot(have - (before >> 5) < 5u) != 0ull; };
+            auto wait_for_words = [&]() {
+                for (uint32_t spins = 0; missing(); ask()) {
+                    if (uniform(*gave_up) || ++spins > p.spin_limit) { stuck = true; return; }
+                    __builtin_amdgcn_s_sleep(1);
+                }
+            };
+            auto block_ahead = [&](auto count_tag) {
+                constexpr int K = static_cast<int>(decltype(count_tag)::value), kAsk = K > 2 ? K - 2 : 0;
+                static_assert(K * ANSZP_MAX_TABLE_LOG <= 96 && (K - kAsk) * ANSZP_MAX_TABLE_LOG <= 31, "the windows of K steps and of the last two");
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    if (k == kAsk) {
+                        before += 32u * (steps_since + kAsk) - (sum & 0x7FFFFu);
+                        ask();
+                        position[lane] = before >> 5;
+                        sum = 0;
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    // next_entry_offset of w0 >> (here & 31) (the first bit read is the top bit), in one piece: between pieces
+                    // the compiler puts wait states
+                    const uint32_t here = e;
+                    uint32_t index;
+                    asm("v_bfe_u32 %0, %2, 5, 13\n\tv_lshrrev_b32 %1, %2, %3\n\tv_add_lshl_u32 %1, %0, %1, 2"
+                        : "=&v"(index), "=&v"(X) : "v"(here), "v"(w0));
+                    e = entry_at(X);
+                    __builtin_amdgcn_sched_barrier(0);                     // nothing ahead of it that it does not need
+                    // of the 96 bits only those a later step of the K can still reach are kept in place
+                    if (k <= K - 2) w0 = __builtin_amdgcn_alignbit(w0, w1, here);
+                    if (k <= K - 4) w1 = __builtin_amdgcn_alignbit(w1, w2, here);
+                    if (k <= K - 7) w2 = __builtin_amdgcn_alignbit(w2, 0u, here);
+                    const uint32_t cleared = here & 0xFFF8001Fu;           // as in steps_fast
+                    sum += cleared;
+                    emit(k, cleared, k == K - 1);
+                    if (k == kAsk && __builtin_expect(missing(), 0)) wait_for_words();
+                }
+                n0 = __builtin_amdgcn_alignbit(n0, n1, ~before);
+                n1 = __builtin_amdgcn_alignbit(n1, n2, ~before);
+                n2 = __builtin_amdgcn_alignbit(n2, n3, ~before);
+                n3 = __builtin_amdgcn_alignbit(n3, n4, ~before);
+                w0 = __builtin_amdgcn_alignbit(n0, n1, sum);
+                w1 = __builtin_amdgcn_alignbit(n1, n2, sum);
+                w2 = __builtin_amdgcn_alignbit(n2, n3, sum);
+                steps_since = K - kAsk;
+            };
+            if constexpr (AHEAD) {
+                e = entry_at(X);
+                ask();                                        // (the ring was filled above)
+                w0 = __builtin_amdgcn_alignbit(n0, n1, ~before);
+                w1 = __builtin_amdgcn_alignbit(n1, n2, ~before);
+                w2 = __builtin_amdgcn_alignbit(n2, n3, ~before);
+            }
+            auto block_fed = [&](auto count_tag) {
+                if constexpr (AHEAD) block_ahead(count_tag);
+                else block_at_once(count_tag);
             };
             // Wavefronts go to the four SIMDs round robin, and a SIMD serves the oldest of its wavefronts
             // first: left alone, the decoders of a workgroup finish in the order of their age, 15 % apart,
@@ -846,10 +944,11 @@ __global__ __launch_bounds__(kStreamWaves * kWave) void decode_streaming(DecodeP
                 if (left == 0u) {
                     ++channel;
                     left = uniform(lay.channel_len / kWave);
-                    scale = uniform_scale(channel);
+                    scale = scale_of_next(channel);
                 }
             }
             if (len > full_steps && !stuck) block_fed(std::integral_constant<int, 1>{});   // ragged tail: streams 0 .. n mod N - 1
+            if constexpr (AHEAD) abit = before + 1u - 32u * kStreamRingWords + 32u * steps_since - (sum & 0x7FFFFu);
             if (stuck) {
                 if (lane == 0) { *gave_up = 1u; report(p.status, ANSZP_ST_INTERNAL); }
                 no_more_positions();
@@ -2084,7 +2183,10 @@ void launch_decode(const DecodeParams& p, uint32_t n_chunks, bool per_channel, b
         const uint32_t per_round = device_cus() * uint32_t(kStreamDecoders);
         const uint32_t rounds = (n_chunks + per_round - 1u) / per_round;
         const uint32_t groups = std::min(n_chunks, device_cus() * rounds);
-        hipLaunchKernelGGL(decode_streaming<OUT>, dim3(groups), dim3(kStreamWaves * kWave), 0, s, p, n_chunks, groups);
+        if ((n_chunks + groups - 1u) / groups <= kStreamAheadDecoders)
+            hipLaunchKernelGGL((decode_streaming<OUT, true>), dim3(groups), dim3(kStreamWaves * kWave), 0, s, p, n_chunks, groups);
+        else
+            hipLaunchKernelGGL((decode_streaming<OUT, false>), dim3(groups), dim3(kStreamWaves * kWave), 0, s, p, n_chunks, groups);
     } else if (stepwise && shared)
         hipLaunchKernelGGL(decode_stepwise_shared<OUT>, dim3((n_chunks + kSharedWaves - 1) / kSharedWaves),
                            dim3(kSharedWaves * kWave), 0, s, p, n_chunks);
