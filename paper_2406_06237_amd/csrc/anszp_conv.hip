@@ -33,18 +33,16 @@
 
 #include "anszp.h"
 #include "anszp_layout.h"
+#include "anszp_panel.h"
 
 namespace {
 
 constexpr uint32_t kWave = 64;
 constexpr uint32_t kThreads = 768;
 constexpr uint32_t kWaves = kThreads / kWave;
+static_assert(kWaves == kPanelWaves, "the staging room is counted in wavefronts");
 constexpr uint32_t kRows = 16;              // output channels per MFMA row tile
 constexpr uint32_t kRowPad = 8;             // bytes between panel rows: rows start two LDS banks apart
-constexpr uint32_t kStageWords = 384;       // per wavefront: LDS room for one chunk's compressed words (2.6 bit per
-                                            // weight at 4608 symbols; a larger chunk is read from global memory)
-constexpr uint32_t kStageBytes = kWaves * kStageWords * 4u;          // at the start of LDS; the table's entries follow
-constexpr uint32_t kStageMask = 0xFFFCu;    // whole words in the first 64 KiB of LDS
 constexpr uint32_t kWidenPieces = 7;        // 16-byte pieces of a byte panel one thread widens to bf16
 constexpr uint32_t kPatchPieces = 4;        // kGenericPatch: 16-byte pieces of the staged rows per thread
 constexpr uint32_t kMaxMine = (4u * kRows + kWaves - 1u) / kWaves;   // chunks of a panel one wavefront may have to decode
@@ -195,11 +193,10 @@ __device__ uint32_t decode_chunk_to_panel(const ConvParams& p, const ChunkDesc& 
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");       // LDS serves a wavefront's accesses in order
         __builtin_amdgcn_wave_barrier();
         // b bits into the chunk the next 32 bits, first bit on top, are the two words at and above (left / 32) * 4, funnel-
-        // shifted by left mod 32, with left = 8 * top - 32 - b.  (Corrupt data may run on below the staged words: the
-        // mask keeps every address in the first 64 KiB of LDS, which every launch has.)
+        // shifted by left mod 32, with left = 8 * top - 32 - b (anszp_panel.h)
         const uint32_t begin = 8u * top - 32u - 32u * min(first_word, word_limit);
         uint32_t left = begin;
-        at = ((2u * X0 + (lds_load<uint32_t>((begin >> 3) & kStageMask) >> 31)) * 8u) & ahead_mask;     // entry 2 X0 + first stream bit
+        at = ((2u * X0 + (lds_load<uint32_t>(stage_address(begin)) >> 31)) * 8u) & ahead_mask;     // entry 2 X0 + first stream bit
         auto walk = [&](auto one_row) {
             // one row: positions are LDS addresses; several: elements of the chunk, put in their row by a division
             constexpr bool kOneRow = decltype(one_row)::value;
@@ -223,7 +220,7 @@ __device__ uint32_t decode_chunk_to_panel(const ConvParams& p, const ChunkDesc& 
                 return T;
             };
             while (pos < end) {
-                const uint32_t word = (left >> 3) & kStageMask;
+                const uint32_t word = stage_address(left);
                 const uint32_t lo = lds_load<uint32_t>(word), hi = lds_load<uint32_t>(word + 4u);
                 const words2 e = lds_load<words2>(ahead + at);
                 const uint32_t window = __builtin_amdgcn_alignbit(hi, lo, left);
@@ -1258,7 +1255,7 @@ int launch_sliced(const ConvParams& p, uint32_t mr, bool p16, uint32_t mode, uin
                 !allow_all_lds<4, false>(every) || !allow_all_lds<2, false>(every) || !allow_all_lds<1, false>(every)) return ANSZP_E_HIP;
         allowed[device].store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), std::max(lds_bytes, 65536u), s, p);
+    hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), std::max(lds_bytes, kLeastLds), s, p);
     return hipGetLastError() == hipSuccess ? ANSZP_OK : ANSZP_E_HIP;
 }
 
@@ -1502,7 +1499,7 @@ extern "C" int anszp_conv_fused(const anszp_conv_args_t* a, void* stream) {
                                 int(kLdsLimit)) != hipSuccess) return ANSZP_E_HIP;
         lds_allowed[p16][kernel_no][slot][device].store(true, std::memory_order_relaxed);
     }
-    lds_total = std::max(lds_total, 65536u);                      // (what kStageMask leaves of an address is always there)
+    lds_total = std::max(lds_total, kLeastLds);                   // (what kStageMask leaves of an address is always there)
     hipLaunchKernelGGL(kernel, dim3(n_mtiles * splits), dim3(kThreads), lds_total, static_cast<hipStream_t>(stream), p);
     return hipGetLastError() == hipSuccess ? ANSZP_OK : ANSZP_E_HIP;
 }
