@@ -72,8 +72,7 @@ struct ConvParams {
     uint32_t x_pixel, x_block, y_pixel, y_block;
     uint32_t y_bf16, K, row_stride, n_pixels, n_mtiles;   // n_mtiles: panels of 16 * MR rows
     uint32_t k_magic;                                     // floor(2^32 / K) + 1: i / K = mulhi(i, k_magic) for i * K < 2^32
-    uint32_t k_magic24, stage_words;                      // floor(2^24 / K) + 1: i / K = (i * k_magic24) >> 24 for i * K < 2^24; kStageWords where
-                                                          // that holds for all elements of a chunk (or a chunk is one row), else 0
+    RowReciprocal row_of;                                 // the same with 24-bit factors, for all elements of a chunk
     uint32_t panel_off;                                   // first byte of the panel in LDS (behind the table and the staging room)
     uint32_t patch_off;                                   // kGenericPatch: first byte of the staged rows
     uint32_t row_pitch;                                   // kGenericPatch: bytes from one staged image row to the next
@@ -210,9 +209,9 @@ __device__ uint32_t decode_chunk_to_panel(const ConvParams& p, const ChunkDesc& 
                 at = (e.y + 8u * v) & ahead_mask;
                 pos = __umul24((e.x >> 28) & 7u, step) + pos;        // past the entry's dominant symbols
                 uint32_t where = pos;
-                if constexpr (!kOneRow) {                            // (a chunk's elements times K are below 2^24: see c.staged)
-                    uint32_t row;                                    // pos / K: upper 32 bits of the 48 of (pos << 8) * magic
-                    asm("v_mul_hi_u32_u24 %0, %1, %2" : "=v"(row) : "v"(pos << 8), "v"(p.k_magic24));
+                if constexpr (!kOneRow) {
+                    uint32_t row;                                    // pos / K (anszp_panel.h)
+                    asm("v_mul_hi_u32_u24 %0, %1, %2" : "=v"(row) : "v"(pos << p.row_of.shift), "v"(p.row_of.magic));
                     where = __umul24(row, gap) + pos * kElem + rows;
                 }
                 put(min(where, beyond), e.x);
@@ -388,7 +387,7 @@ __device__ __forceinline__ anszp_layer_t decode_panel(const ConvParams& p, uint8
         c.ok = layer_id == p.layer_id && c.n_symbols == p.rows_per_chunk * p.K && (c.payload_offset & 3u) == 0 &&
                c.payload_offset <= p.payload_words && c.payload_words <= p.payload_words - c.payload_offset &&
                uint64_t(c.stream_offset) + p.n_streams <= p.n_stream_hdr;
-        c.staged = c.payload_words + 2u <= p.stage_words;         // two zero words behind the chunk's own
+        c.staged = c.payload_words + 2u <= kStageWords;           // two zero words behind the chunk's own
         return c;
     };
     auto fetch = [&](const ChunkDesc& c, ChunkData& d) {          // from clamped, always valid addresses
@@ -1390,10 +1389,7 @@ extern "C" int anszp_conv_fused(const anszp_conv_args_t* a, void* stream) {
     p.y_block = a->y_layout == ANSZP_ACT_C8 ? 8u * out_h * out_w : 8u;
     p.K = uint32_t(K);
     p.k_magic = uint32_t((uint64_t(1) << 32) / K) + 1u;           // unused for K = 1
-    // (a look-up may step past the chunk's end by one entry: eight symbols of every stream)
-    const uint64_t reach = uint64_t(R) * K + 8u * a->n_streams;
-    p.k_magic24 = (1u << 24) / uint32_t(K) + 1u;
-    p.stage_words = R == 1u || (K > 1u && reach < 65536u && reach * K < (1u << 24)) ? kStageWords : 0u;
+    p.row_of = row_reciprocal(uint32_t(K));
     const uint32_t row_stride = ((uint32_t(K) + 31u) & ~31u) + kRowPad, table_bytes = 16u << a->table_log;      // (the look-ahead entries)
     p.row_stride = row_stride;
     p.n_pixels = uint32_t(n_pixels);

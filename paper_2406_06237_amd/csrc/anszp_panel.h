@@ -25,4 +25,21 @@ constexpr uint32_t kStageMask = 0x7FFCu;
 ANSZP_PANEL_HD uint32_t stage_address(uint32_t left) { return (left >> 3) & kStageMask; }
 static_assert(kStageBytes <= kStageMask + 4u && kStageMask + 8u <= kLeastLds, "all of the room is reached, and nothing outside LDS");
 
+// The row of a chunk's element `pos`, pos / K, as one 24-bit multiplication: the upper 32 of the 48 bits of
+// (pos << shift) * magic, magic = floor(2^(32 - shift) / K) + 1.  Both factors must be below 2^24 and the error
+// pos * (magic * K - 2^(32 - shift)) <= pos * K below 2^(32 - shift): K >= 257 takes shift 0 (pos * K < 2^32), 2 <= K <= 256
+// shift 8 (pos < 2^16, pos * K < 2^24), K = 1 shift 9 and 2^23 exactly (pos < 2^15).  A chunk has at most 16 rows, and a
+// look-up may step past its end by eight symbols of each of 64 streams: pos < 16 K + 512, within all three.
+// (With 2^24 for every K, chunks of 4 rows of 2304 or 16 of 1152 were beyond it and read their words from global memory: a
+// call of 256 x 2304 weights on sixteen 7 x 7 images took 13.4 us, 11.8 staged; 256 x 1152 in chunks of 16 rows 15.4, 12.3.)
+struct RowReciprocal {
+    uint32_t magic, shift;
+};
+ANSZP_PANEL_HD RowReciprocal row_reciprocal(uint32_t K) {
+    RowReciprocal r;
+    r.shift = K >= 257u ? 0u : K >= 2u ? 8u : 9u;
+    r.magic = K >= 2u ? uint32_t((uint64_t(1) << (32u - r.shift)) / K) + 1u : 1u << 23;
+    return r;
+}
+
 #endif

@@ -367,13 +367,26 @@ def test_sliced_contraction_at_its_edges(orc, shape, B_, H, Wd, stride, pad, lay
 
 # How a chunk's rows, streams and elements decide between the staged decode loops and the one from global memory.
 @pytest.mark.parametrize("shape,rows,n_streams", [
-    ((16, 1152, 1, 1), 16, 64),               # 18,432 elements a chunk: beyond the reciprocal's reach
+    ((16, 1152, 1, 1), 16, 64),               # 18,432 elements a chunk
     ((16, 128, 3, 3), 4, 64), ((16, 128, 3, 3), 1, 33), ((16, 32, 1, 1), 16, 64), ((32, 32, 3, 3), 2, 1), ((16, 8, 1, 1), 8, 5),
 ])
 def test_chunks_of_every_number_of_rows(orc, shape, rows, n_streams):
+    _rows_case(orc, shape, rows, n_streams, 0.8)
+
+
+# Staged chunks (at most 382 words) of several long rows, and the reduction lengths around which the reciprocal changes its form.
+@pytest.mark.parametrize("shape,rows,n_streams", [
+    ((16, 2304, 1, 1), 4, 64), ((16, 2304, 1, 1), 8, 64), ((32, 4608, 1, 1), 2, 64), ((16, 512, 3, 3), 16, 64), ((16, 4608, 1, 1), 16, 1),
+    ((16, 1024, 1, 1), 16, 64), ((16, 257, 1, 1), 16, 64), ((16, 256, 1, 1), 16, 64), ((16, 1, 1, 1), 16, 64), ((16, 2, 1, 1), 16, 3),
+])
+def test_staged_chunks_of_long_rows(orc, shape, rows, n_streams):
+    _rows_case(orc, shape, rows, n_streams, 0.97)
+
+
+def _rows_case(orc, shape, rows, n_streams, p0):
     cout, cin, kh, kw = shape
     K = cin * kh * kw
-    lay = _layer(shape, 4, 0.8, 11)
+    lay = _layer(shape, 4, p0, 11)
     w = W.Workload("rows", [lay], 11, n_streams, rows * K, "bf16")
     d = B.to_device(host_from_oracle(oracle_encode(orc, w), w))
     codes, values = W.bf16_activations(2 * 6 * 6 * cin, 5)

@@ -30,3 +30,19 @@ def test_staged_words_are_read_inside_lds_whatever_the_stream_says(tmp_path):
         if (left < 8u * kStageBytes && a != left / 32u * 4u) { std::printf("left %u: address %u", left, a); return 1; }
         if (left == 0xFFFFFFF8u) break;
     }""")
+
+
+def test_rows_of_a_chunks_elements_for_every_reduction_length(tmp_path):
+    # pos / K for every K a panel may have and every element a look-up can reach in a chunk of up to 16 rows, with the
+    # factors the 24-bit multiplication takes
+    _run(tmp_path, """
+    for (uint32_t K = 1; K <= 4608u; ++K) {
+        const RowReciprocal r = row_reciprocal(K);
+        const uint32_t reach = 16u * K + 8u * 64u;
+        if (r.magic >= 1u << 24 || (uint64_t(reach) << r.shift) >= 1u << 24) { std::printf("K %u: factors", K); return 1; }
+        uint32_t row = 0, next = K;
+        for (uint32_t pos = 0; pos < reach; ++pos) {
+            if (pos == next) { ++row; next += K; }
+            if (uint32_t((uint64_t(pos << r.shift) * r.magic) >> 32) != row) { std::printf("K %u, element %u", K, pos); return 1; }
+        }
+    }""")
