@@ -293,8 +293,8 @@ int anszp_pack_layer_device(const uint8_t* symbols_dev, uint64_t n_symbols, cons
                             uint64_t payload_cap_words, uint64_t* payload_words_used_dev,
                             uint32_t* status_dev, void* hip_stream);
 
-/* The same for a whole set of layers in three launches (one workgroup per chunk, so every chunk of every layer is
- * encoded at once).  symbols_dev [device]: the layers' symbols, layer after layer; jobs_dev [device] n_layers
+/* The same for a whole set of layers in three launches (a wavefront per chunk at a time, chunks of all layers side by
+ * side).  symbols_dev [device]: the layers' symbols, layer after layer; jobs_dev [device] n_layers
  * entries in layer order; freqs_dev [device] n_layers rows of 256 frequencies summing to 2^table_log each;
  * n_chunks: the sum over the layers of ceil(n_symbols / chunk_size) (anszp_pack_bound gives each term).
  * Layer l becomes layer_id l; its chunks follow those of layer l-1 in chunks_dev and stream_hdr_dev

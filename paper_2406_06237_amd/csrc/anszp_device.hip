@@ -27,6 +27,7 @@
 // The look-ahead path needs the chunk's words to fit its LDS window and the chunk's first output
 // element to be 16-byte aligned; other chunks take the step-wise path inside the same launch.
 #include "anszp.h"
+#include "anszp_cus.h"
 #include "anszp_layout.h"
 #include "anszp_spread.h"
 
@@ -2155,22 +2156,6 @@ __global__ __launch_bounds__(256) void dequant_runs_kernel(const uint8_t* sym, u
         for (uint32_t j = 0; j < 4u; ++j) v[j] = bf16_rne(w[2u * j]) | bf16_rne(w[2u * j + 1u]) << 16;
         *reinterpret_cast<out4*>(static_cast<uint16_t*>(out) + first) = v;
     }
-}
-
-// Compute units of the current device (queried once per device; the cache is a table of atomics, so
-// concurrent callers at worst both query).
-uint32_t device_cus() {
-    static std::atomic<uint32_t> cached[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256u;
-    uint32_t n = cached[dev].load(std::memory_order_relaxed);
-    if (!n) {
-        int count = 0;
-        if (hipDeviceGetAttribute(&count, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || count <= 0) count = 256;
-        n = static_cast<uint32_t>(count);
-        cached[dev].store(n, std::memory_order_relaxed);
-    }
-    return n;
 }
 
 template <int OUT>

@@ -199,3 +199,48 @@ def test_descriptors_and_headers_are_complete_where_the_payload_has_no_room(orc)
     chunks, hdr, payload, used, status = _pack(sym, c.freqs[0], 12, 64, 4096, payload_cap_words=1500)
     assert status[0] == B.ST_NO_SPACE and used == len(c.payload) and np.all(payload[1500:] == 0xFFFFFFFF)
     assert np.array_equal(chunks["out_offset"][:c.n_chunks], c.chunk_out_off) and np.array_equal(hdr[:c.n_chunks * 64], c.stream_hdr)
+
+
+# More chunks than two workgroups per CU have wavefronts: a wavefront then takes several chunks of a run, one after the other.
+@pytest.mark.parametrize("n_chunks,per,N", [(4097, 64, 64), (5003, 130, 64), (20000, 33, 7), (70001, 3, 1)])
+def test_more_chunks_than_wavefronts(orc, n_chunks, per, N):
+    n = n_chunks * per - (per - 1)                                 # the last chunk has one symbol
+    _compare(orc, W.tiny(seed=n, n=n, bitwidth=4, table_log=9, p0=0.6).symbols()[0], 9, N, per)
+
+
+def test_many_layers_of_more_chunks_than_wavefronts(orc):
+    layers = [W.tiny(seed=s, n=1700 + 31 * s, bitwidth=2 + s % 5, n_streams=16, chunk_size=32, table_log=8, p0=0.5).layers[0] for s in range(90)]
+    w = W.Workload("many", layers, 8, 16, 32, "bf16")
+    from helpers import oracle_encode
+    c = oracle_encode(orc, w)
+    chunks, hdr, payload, used, status = _pack_set(w, c)
+    assert status == (0, 0) and used == len(c.payload) and c.n_chunks > 8 * 512
+    assert np.array_equal(chunks["out_offset"][:c.n_chunks], c.chunk_out_off) and np.array_equal(chunks["payload_offset"][:c.n_chunks], c.chunk_payload_off)
+    assert np.array_equal(hdr[:c.n_chunks * 16], c.stream_hdr) and np.array_equal(payload[:used], c.payload)
+
+
+def test_more_chunks_than_a_grid_of_workgroups_of_eight_could_hold(orc):
+    """2^26 chunks and a few: eight per workgroup of 512 would be more than 2^32 work-items.  Chunks of two symbols in one
+    stream, so that the headers and words the oracle gives the 64 pairs are those of all chunks."""
+    n, R = (1 << 26) + 5, 6
+    freqs = np.zeros(256, dtype=np.uint32)
+    freqs[:8] = (5, 3, 9, 7, 11, 13, 6, 10)
+    pairs = np.stack([np.arange(64) // 8, np.arange(64) % 8], axis=1).astype(np.uint8)
+    c = orc.encode_layers([pairs.reshape(-1)], R, 1, 2, freqs=[freqs])
+    assert len(c.payload) == 4 * 64 and np.all(c.chunk_payload_words == 1)
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(3)
+    sym = torch.randint(0, 8, (2 * n,), generator=g, device="cuda:0", dtype=torch.uint8)
+    chunks, hdr, payload, used, status = B.pack_layer_device(sym, torch.from_numpy(freqs.view(np.int32)).to("cuda:0"), R, 1, 2)
+    torch.cuda.synchronize()
+    assert status.tolist() == [0, 0] and int(used.item()) == 4 * n
+    pair = sym[0::2].long() * 8 + sym[1::2].long()
+    of_pair = lambda a: torch.from_numpy(np.ascontiguousarray(a).view(np.int32)).to("cuda:0")[pair]
+    assert torch.equal(hdr[:n], of_pair(c.stream_hdr))
+    words = payload[:4 * n].view(n, 4)
+    assert torch.equal(words[:, 0], of_pair(c.payload[::4])) and not bool(words[:, 1:].any())
+    rows, i = chunks.view(n, B.CHUNK_DTYPE.itemsize), torch.arange(n, device="cuda:0")
+    for field, want, dtype in (("out_offset", 2 * i, torch.int64), ("payload_offset", 4 * i, torch.int64), ("stream_offset", i.int(), torch.int32),
+                               ("n_symbols", torch.full_like(i, 2).int(), torch.int32), ("payload_words", torch.ones_like(i).int(), torch.int32)):
+        begin = B.CHUNK_DTYPE.fields[field][1]
+        assert torch.equal(rows[:, begin:begin + want.element_size()].contiguous().view(dtype)[:, 0], want), field
