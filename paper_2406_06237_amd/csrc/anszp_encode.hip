@@ -296,6 +296,15 @@ __global__ __launch_bounds__(kThreads, 4) void encode_sizes(EncParams p) {
     });
 }
 
+// A layer without symbols: what is left to do is to look at its frequencies (one wavefront).
+__global__ __launch_bounds__(kWave) void encode_nothing(EncParams p) {
+    const uint32_t L = 1u << p.table_log;
+    uint32_t sum = 0;
+    for (uint32_t s = threadIdx.x; s < ANSZP_ALPHABET; s += kWave) sum += min(p.freqs[s], L + 1u);   // (as in spread_states)
+    sum = spread_wave_sum(sum);
+    if (threadIdx.x == kWave - 1u && sum != L) report(p.status, ANSZP_ST_BAD_FREQ);
+}
+
 // Payload offsets: every chunk starts on a multiple of four words.  One workgroup, chunks in order, as many at a time
 // as it has threads.
 __global__ __launch_bounds__(kThreads) void encode_scan(EncParams p) {
@@ -370,6 +379,7 @@ int launch(EncParams& p, hipStream_t s) {
     p.chunks_per_group = chunks_per_group(p.n_chunks);
     const uint64_t groups = (p.n_chunks + p.chunks_per_group - 1u) / p.chunks_per_group;
     if (groups) hipLaunchKernelGGL(encode_sizes, dim3(uint32_t(groups)), dim3(kThreads), 0, s, p);
+    else if (!p.jobs) hipLaunchKernelGGL(encode_nothing, dim3(1), dim3(kWave), 0, s, p);
     hipLaunchKernelGGL(encode_scan, dim3(1), dim3(kThreads), 0, s, p);
     if (groups) hipLaunchKernelGGL(encode_write, dim3(uint32_t(groups)), dim3(kThreads), 0, s, p);
     return hipGetLastError() == hipSuccess ? ANSZP_OK : ANSZP_E_HIP;

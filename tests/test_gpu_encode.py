@@ -244,3 +244,16 @@ def test_more_chunks_than_a_grid_of_workgroups_of_eight_could_hold(orc):
                                ("n_symbols", torch.full_like(i, 2).int(), torch.int32), ("payload_words", torch.ones_like(i).int(), torch.int32)):
         begin = B.CHUNK_DTYPE.fields[field][1]
         assert torch.equal(rows[:, begin:begin + want.element_size()].contiguous().view(dtype)[:, 0], want), field
+
+
+def test_a_layer_without_symbols_still_has_its_frequencies_checked():
+    f = np.zeros(256, dtype=np.uint32)
+    f[3], f[255] = 1000, 24
+    empty = np.zeros(0, dtype=np.uint8)
+    chunks, hdr, payload, used, status = _pack(empty, f, 10, 64, 4096)
+    assert status == (0, 0) and used == 0 and np.all(payload == 0xFFFFFFFF)
+    for at, v in ((255, 25), (3, 0), (7, 0xFFFFFFFF)):             # one too many, too few, a sum that wraps around
+        g = f.copy()
+        g[at] = v
+        chunks, hdr, payload, used, status = _pack(empty, g, 10, 64, 4096)
+        assert status == (B.ST_BAD_FREQ, 1) and used == 0 and np.all(payload == 0xFFFFFFFF)
