@@ -7,10 +7,15 @@
 //
 // The rank is found by a counting sort: occurrence -> one of L buckets by the integer part of L (2i + 1) / (2f)
 // (equal fractions share a bucket and buckets are ordered as the fractions are), a prefix sum over the buckets, and an
-// exact comparison (products below 2^26) with the other occurrences of the same bucket: one division per state, and as
-// many comparisons as a bucket has members (a few on skewed tables, the number of symbols on a flat one).  Counting
-// the occurrences of every other symbol before each occurrence takes a division per state and symbol instead: with
-// 2^12 states a decode table took 57 us that way (16 symbols; 218 us with 256), 36 us (46 us) this way.
+// exact comparison with the other occurrences of the same bucket: one division per state, and as many comparisons as a
+// bucket has members.  On skewed tables these are a few, compared by their products (below 2^26).  Where symbols share a
+// frequency they share all fractions, and a bucket has as many members as there are such symbols: then (some bucket has
+// more than kSpreadFew) a second division gives every occurrence a number that orders the bucket by itself.  With r / 2f the
+// place in the bucket, that is the integer part of 2L r / 2f (different fractions, of frequencies f + g <= L, are
+// 1 / 2fg >= 2 / L^2 apart, so 4 apart here), the symbol below it.
+// Counting the occurrences of every other symbol before each occurrence takes a division per state and symbol instead: with
+// 2^12 states a decode table took 57 us that way (16 symbols; 218 us with 256), 36 us (46 us) this way by one workgroup.
+// A flat row of 2^12 states: 16 symbols 13 us, 256 symbols 56 us (by products in every bucket 25 and 230).
 #ifndef ANSZP_SPREAD_H
 #define ANSZP_SPREAD_H
 
@@ -21,13 +26,15 @@
 #include "anszp.h"
 
 constexpr uint32_t kSpreadStates = 1u << ANSZP_MAX_TABLE_LOG;
+constexpr uint32_t kSpreadFew = 8;             // members of a bucket that are compared by their products
 
 struct SpreadLds {
     uint32_t f[ANSZP_ALPHABET];
     uint32_t first[ANSZP_ALPHABET];        // occurrences of smaller symbols: occurrence i of symbol s is number first[s] + i
     uint32_t bucket[kSpreadStates];        // members of each bucket, then where each bucket's members start
-    uint32_t member[kSpreadStates];        // f - 1 | i << 12 | symbol << 24, bucket after bucket
+    uint32_t member[kSpreadStates];        // bucket after bucket: f - 1 | i << 12 | symbol << 24 (crowded: order in the bucket << 8 | symbol)
     uint32_t part[16];                     // a wavefront's share of a prefix sum
+    uint32_t crowded;                      // some bucket has more than kSpreadFew members
 };
 
 // Inclusive prefix sum over the 64 lanes of a wavefront.
@@ -58,6 +65,7 @@ __device__ __forceinline__ bool spread_states(const uint32_t* freqs, uint32_t ta
         if (lane == 63u) t.part[wave] = upto;
     }
     for (uint32_t b = tid; b < L; b += THREADS) t.bucket[b] = 0u;
+    if (tid == 0u) t.crowded = 0u;
     __syncthreads();
     uint32_t total = 0;
 #pragma unroll
@@ -103,10 +111,42 @@ __device__ __forceinline__ bool spread_states(const uint32_t* freqs, uint32_t ta
 #pragma unroll
         for (uint32_t u = 0; u < kPerThread; ++u) {
             if (u < per && b0 + u < L) t.bucket[b0 + u] = start;
+            if (n[u] > kSpreadFew) t.crowded = 1u;
             start += n[u];
         }
     }
     __syncthreads();
+    auto end_of = [&](uint32_t b) { return b + 1u < L ? t.bucket[b + 1u] : L; };
+    if (__builtin_amdgcn_readfirstlane(t.crowded)) {           // (uniform)
+        uint32_t key[kPerThread];
+#pragma unroll
+        for (uint32_t u = 0; u < kPerThread; ++u) {
+            if (tid + u * THREADS < L) {
+                const uint32_t b = at[u] & 0xFFFFu, f = (mine[u] & 0xFFFu) + 1u, i = (mine[u] >> 12) & 0xFFFu;
+                const uint32_t rest = ((2u * i + 1u) << table_log) - b * 2u * f;         // below 2 f
+                key[u] = (rest << (table_log + 1u)) / (2u * f) << 8 | mine[u] >> 24;     // (the division below 2^26)
+                t.member[t.bucket[b] + (at[u] >> 16)] = key[u];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t u = 0; u < kPerThread; ++u) {
+            if (tid + u * THREADS < L) {
+                const uint32_t begin = t.bucket[at[u] & 0xFFFFu], end = end_of(at[u] & 0xFFFFu);
+                uint32_t state = begin;
+                // (from another member in every lane: occurrences of one symbol are in buckets of like sizes, whose members
+                // in one place would share an LDS bank)
+                uint32_t m = begin + lane % (end - begin);
+#pragma unroll 8
+                for (uint32_t n = end - begin; n; --n) {
+                    state += t.member[m] < key[u] ? 1u : 0u;
+                    m = m + 1u < end ? m + 1u : begin;
+                }
+                place(tid + u * THREADS, mine[u] >> 24, (mine[u] & 0xFFFu) + 1u, (mine[u] >> 12) & 0xFFFu, state);
+            }
+        }
+        return true;
+    }
 #pragma unroll
     for (uint32_t u = 0; u < kPerThread; ++u)
         if (tid + u * THREADS < L) t.member[t.bucket[at[u] & 0xFFFFu] + (at[u] >> 16)] = mine[u];
@@ -116,7 +156,7 @@ __device__ __forceinline__ bool spread_states(const uint32_t* freqs, uint32_t ta
         const uint32_t g = tid + u * THREADS;
         if (g < L) {
             const uint32_t b = at[u] & 0xFFFFu;
-            const uint32_t begin = t.bucket[b], end = b + 1u < L ? t.bucket[b + 1u] : L;
+            const uint32_t begin = t.bucket[b], end = end_of(b);
             const uint32_t f = (mine[u] & 0xFFFu) + 1u, i = (mine[u] >> 12) & 0xFFFu, s = mine[u] >> 24;
             uint32_t state = begin;
 #pragma unroll 4

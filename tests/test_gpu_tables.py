@@ -47,3 +47,26 @@ def test_a_rejected_row_is_reported_once_and_leaves_its_table_zero():
     got = B.build_tables_device(torch.from_numpy(rows.view(np.int32)).to("cuda:0"), 12, status).cpu().numpy().view(np.uint32).reshape(3, -1)
     assert not got[1].any() and status.tolist() == [B.ST_BAD_FREQ, 1]
     assert np.array_equal(got[[0, 2]], B.build_tables_host(rows[[0, 2]], 12))
+
+
+# Buckets of the counting sort around the size from which its members are compared by their place in the bucket: `equal`
+# symbols of one frequency share every fraction; `near` ones of neighbouring frequencies lie close to each other.
+@pytest.mark.parametrize("R", [8, 10, 11, 12])
+@pytest.mark.parametrize("kind,k", [("equal", k) for k in (7, 8, 9, 10, 16, 63, 64, 65, 200)] + [("near", k) for k in (9, 30, 120, 250)])
+def test_buckets_of_few_and_of_many_members(kind, k, R):
+    L, rng = 1 << R, np.random.default_rng(k)
+    f = max(1, L // (k + 1))
+    row = np.zeros(256, dtype=np.int64)
+    at = np.sort(rng.permutation(256)[:k])
+    row[at] = f if kind == "equal" else np.maximum(1, f + rng.integers(-1, 2, k))
+    rest = L - int(row.sum())
+    free = np.setdiff1d(np.arange(256), at)[0]
+    if rest < 0:                                        # (near: a little too many)
+        over = np.nonzero(row > 1)[0][:-rest]
+        assert len(over) == -rest
+        row[over] -= 1
+    else:
+        row[free] = rest
+    rows = np.stack([row, row[::-1]]).astype(np.uint32)
+    got = B.build_tables_device(torch.from_numpy(rows.view(np.int32)).to("cuda:0"), R).cpu().numpy().view(np.uint32).reshape(2, -1)
+    assert np.array_equal(got, B.build_tables_host(rows, R))
