@@ -2364,7 +2364,8 @@ int anszp_dequant_zp(const uint8_t* symbols_dev, uint64_t n, const anszp_layer_t
     if (n == 0) return ANSZP_OK;
     if (!symbols_dev || !out_dev || (layer->channel_len && !scales_dev)) return ANSZP_E_NULL;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    if (n < (1ull << 32) - 256u && ((reinterpret_cast<uintptr_t>(symbols_dev) | reinterpret_cast<uintptr_t>(out_dev)) & 15u) == 0) {
+    // (a scale of its own for every symbol: the runs fetch them one after the other, 45 M symbols to bf16 114 us, 87 without)
+    if (n < (1ull << 32) - 256u && layer->channel_len != 1u && ((reinterpret_cast<uintptr_t>(symbols_dev) | reinterpret_cast<uintptr_t>(out_dev)) & 15u) == 0) {
         const dim3 groups(static_cast<uint32_t>(((n + kDequantRun - 1u) / kDequantRun + 255u) / 256u));
         const uint32_t m = static_cast<uint32_t>(n);
         if (out_dtype == ANSZP_OUT_F32)

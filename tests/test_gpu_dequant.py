@@ -17,7 +17,7 @@ def test_runs_and_channels(orc, channel_len, dtype):
     scales = rng.uniform(-0.1, 0.1, 4200).astype(np.float32)
     qd, sd = torch.from_numpy(q).cuda(), torch.from_numpy(scales).cuda()
     for n in (1, 7, 8, 9, 15, 16, 2047, 2048, 2049, 4100):
-        for first in (0, 1, 8, 16):                       # multiples of sixteen take the runs, the others one symbol at a time
+        for first in (0, 1, 8, 16):                       # multiples of sixteen take the runs (but for channels of one symbol), the others one symbol at a time
             want = orc.dequant(q[first:first + n], 100, 0.0173, dtype, channel_len, scales if channel_len else None)
             got = B.bits_of(B.dequant_zp(qd[first:first + n], 100, 0.0173, dtype, channel_len, sd if channel_len else None))
             assert np.array_equal(got, want.view(np.uint32) if dtype == "f32" else want), (n, first)
