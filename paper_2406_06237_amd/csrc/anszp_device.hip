@@ -683,8 +683,14 @@ __global__ __launch_bounds__(kStreamWaves * kWave) void decode_streaming(DecodeP
     uint32_t err = sums_up ? 0u : ANSZP_ST_BAD_DESC;
     const uint32_t full_steps = c.n_symbols / N;          // steps every stream of the chunk takes
 
-    const bool aligned = !per_channel || (lay.channel_len % kWave == 0u && in_channel0 % kWave == 0u);
-    const bool fed = fast && aligned && uint64_t(c.n_symbols) * kElemBytes < (1ull << 31);      // fast: all 64 lanes have a stream
+    // whether the stream words come from a loading wavefront (asked where each form needs it: before the ring is filled, the
+    // compiler keeps the other form's loops in vector registers; 6,176 chunks of 131,072 symbols took 425 us that way, 369 now)
+    auto is_fed = [&]() {
+        const bool aligned = !per_channel || (lay.channel_len % kWave == 0u && in_channel0 % kWave == 0u);
+        return fast && aligned && uint64_t(c.n_symbols) * kElemBytes < (1ull << 31);            // fast: all 64 lanes have a stream
+    };
+    bool fed = false;
+    if constexpr (AHEAD) fed = is_fed();
     for (uint32_t at = 0; at < kStreamRingWords; at += kStreamFetchWords) {
         Fetched f;
         fetch(mine, readable, at, f);
@@ -759,6 +765,7 @@ __global__ __launch_bounds__(kStreamWaves * kWave) void decode_streaming(DecodeP
         }
     };
 
+    if constexpr (!AHEAD) fed = is_fed();
     if (!fed) no_more_positions();
     if (lane < N) {
         if (fed) {
