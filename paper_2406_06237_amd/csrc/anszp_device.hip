@@ -430,11 +430,13 @@ __host__ __device__ __forceinline__ uint32_t stream_group_begin(uint32_t g, uint
 }
 
 // AHEAD: the words of a decoder's next block are asked for while the current one's last two entries are on their way.  For
-// workgroups of at most kStreamAheadDecoders decoders, which are mostly alone on their SIMDs: the chain of a step binds them
-// (seven matrices, 772 chunks of 262,144 symbols, three or four per CU: 270 -> 208 us; six per CU: 146 -> 120 us per 772).
-// Fuller workgroups are bound by what their SIMDs issue, where the fifth word and its shifts cost more than they give
-// (6,176 chunks, twelve per CU: 1.043 ms without, 1.065 with).
-constexpr uint32_t kStreamAheadDecoders = 8u;
+// workgroups of at most kStreamAheadDecoders decoders, in which the chain of a step binds; fuller ones are bound by what
+// their SIMDs issue, where the fifth word and its shifts cost more than they give.  Whole calls among others, us without ->
+// with, chunks of 131,072 symbols (64 streams, 2^12 states, a scale per 4,096) to bf16: 3 or 4 per workgroup 138 -> 108, 8
+// 152 -> 135, 9 151 -> 143, 10 161 -> 158, 11 173 -> 169, 12 182 -> 178, 13 194 -> 198, 14 201 -> 206; in two rounds of 7 or 8
+// 296 -> 244, of 9 301 -> 269, of 10 or 11 334 -> 322, of 12 or 13 373 -> 377.  To u8 alike, to f32 (the stores bind) no more
+// than 2 % either way.
+constexpr uint32_t kStreamAheadDecoders = 12u;
 template <int OUT, bool AHEAD>
 __global__ __launch_bounds__(kStreamWaves * kWave) void decode_streaming(DecodeParams p, uint32_t n_chunks, uint32_t n_groups) {
     constexpr uint32_t kStates = 1u << ANSZP_MAX_TABLE_LOG;
