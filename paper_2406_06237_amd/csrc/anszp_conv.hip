@@ -1279,27 +1279,32 @@ SlicedPlan plan_sliced(const anszp_conv_args_t& a, uint32_t mode, uint32_t K, ui
         const bool p16 = fixed + 2u * elems <= kLdsLimit;         // the panel decoded as bf16 values; else as bytes, widened in place
         if (!p16 && (fixed + elems > kLdsLimit || 2u * (elems + 64u) > kLdsLimit || elems + 64u > kWidenPieces * kThreads * 16u)) continue;
         const uint32_t n_mtiles = a.cout / (kRows * mr), most = most_tiles(mr, mode);
-        // few, long-lived workgroups, as many as are resident at once (one per CU): each decodes its panel once
-        uint32_t splits = std::max(1u, std::min((cus + n_mtiles - 1u) / n_mtiles, n_tiles));
-        const uint32_t tiles = (n_tiles + splits - 1u) / splits;
-        splits = (n_tiles + tiles - 1u) / tiles;
         const uint32_t chunk_rounds = (kRows * mr / a.rows_per_chunk + kWaves - 1u) / kWaves;
         const uint64_t decode = chunk_rounds * (2500u + uint64_t(a.rows_per_chunk) * K / 2u) + (p16 ? 0u : 5000u);
-        for (const uint32_t ks : {1u, 2u, 3u, 4u, 6u, 12u}) {
-            const uint32_t ts = kWaves / ks, rounds = (tiles + most * ts - 1u) / (most * ts);
-            const uint32_t per_round = (tiles + rounds - 1u) / rounds, qt = (per_round + ts - 1u) / ts;
-            const uint64_t sums = ks > 1u ? uint64_t(kWaves) * qt * mr * 1024u : 0u;
-            if (ks > 1u && (rounds > 1u || units < ks || sums > kLdsLimit)) continue;
-            const uint32_t busy = (per_round + qt - 1u) / qt * ks, slots = units_in_flight(mr, mode, qt);
-            const uint64_t mfma = uint64_t((busy + 3u) / 4u) * qt * mr * taps * 16u, reads = uint64_t(busy) * mr * taps * 8u;
-            const uint64_t loads = uint64_t(busy) * (mode == kRow ? 3u * qt : mode == kShift ? qt + 1u : qt) * 24u;
-            const uint64_t unit = std::max(std::max(mfma, reads), std::max<uint64_t>(loads, 2400u / slots));
-            const uint64_t clocks = decode + rounds * ((units + ks - 1u) / ks * unit + 2400u) + (ks > 1u ? 1500u + sums / 64u : 0u);
-            if (clocks >= fewest) continue;
-            fewest = clocks;
-            best.mr = mr; best.p16 = p16; best.qt = qt; best.k_groups = ks; best.round_tiles = per_round;
-            best.slice_units = (units + ks - 1u) / ks; best.splits = splits; best.tiles_per_split = tiles;
-            best.lds_bytes = std::max(std::max(fixed + elems * (p16 ? 2u : 1u), p16 ? 0u : 2u * (elems + 64u)), uint32_t(sums));
+        // few, long-lived workgroups, as many as are resident at once (one per CU): each decodes its panel once.  Where the panels
+        // do not divide the CUs: a few CUs left over, or a few workgroups that wait for a CU.
+        for (uint32_t more = 0; more < 2u; ++more) {
+            uint32_t splits = more ? (cus + n_mtiles - 1u) / n_mtiles : cus / n_mtiles;
+            splits = std::max(1u, std::min(splits, n_tiles));
+            const uint32_t tiles = (n_tiles + splits - 1u) / splits;
+            splits = (n_tiles + tiles - 1u) / tiles;
+            const uint64_t turns = (uint64_t(n_mtiles) * splits + cus - 1u) / cus;
+            for (const uint32_t ks : {1u, 2u, 3u, 4u, 6u, 12u}) {
+                const uint32_t ts = kWaves / ks, rounds = (tiles + most * ts - 1u) / (most * ts);
+                const uint32_t per_round = (tiles + rounds - 1u) / rounds, qt = (per_round + ts - 1u) / ts;
+                const uint64_t sums = ks > 1u ? uint64_t(kWaves) * qt * mr * 1024u : 0u;
+                if (ks > 1u && (rounds > 1u || units < ks || sums > kLdsLimit)) continue;
+                const uint32_t busy = (per_round + qt - 1u) / qt * ks, slots = units_in_flight(mr, mode, qt);
+                const uint64_t mfma = uint64_t((busy + 3u) / 4u) * qt * mr * taps * 16u, reads = uint64_t(busy) * mr * taps * 8u;
+                const uint64_t loads = uint64_t(busy) * (mode == kRow ? 3u * qt : mode == kShift ? qt + 1u : qt) * 24u;
+                const uint64_t unit = std::max(std::max(mfma, reads), std::max<uint64_t>(loads, 2400u / slots));
+                const uint64_t clocks = turns * (decode + rounds * ((units + ks - 1u) / ks * unit + 2400u) + (ks > 1u ? 1500u + sums / 64u : 0u));
+                if (clocks >= fewest) continue;
+                fewest = clocks;
+                best.mr = mr; best.p16 = p16; best.qt = qt; best.k_groups = ks; best.round_tiles = per_round;
+                best.slice_units = (units + ks - 1u) / ks; best.splits = splits; best.tiles_per_split = tiles;
+                best.lds_bytes = std::max(std::max(fixed + elems * (p16 ? 2u : 1u), p16 ? 0u : 2u * (elems + 64u)), uint32_t(sums));
+            }
         }
     }
     return best;                                                  // (one row tile always fits: K <= 4608)

@@ -413,3 +413,12 @@ def test_activations_of_more_than_two_gibibytes(orc):
     for first in (0, n // 2, n - 3):
         assert torch.equal(y[first:first + 3], B.conv_fused(d, 0, 0, 16, x[first:first + 3].contiguous(), shape, 1, 0))
     assert d.read_status() == (0, 0)
+
+
+# Panels that do not divide the CUs: workgroups in one turn with CUs left over, in two turns, more panels than CUs.
+@pytest.mark.parametrize("shape,B_,H,Wd,stride,pad", [
+    ((80, 32, 1, 1), 9, 40, 40, 1, 0), ((176, 64, 3, 3), 6, 30, 30, 1, 1), ((2064, 32, 1, 1), 1, 20, 20, 1, 0), ((4112, 32, 1, 1), 1, 9, 9, 1, 0),
+    ((1360, 64, 1, 3), 1, 12, 40, 2, 1),
+])
+def test_panels_that_do_not_divide_the_cus(orc, shape, B_, H, Wd, stride, pad):
+    _check(*_case(orc, shape, B_, H, Wd, stride, pad, x_layout="c8", y_layout="c8"))
