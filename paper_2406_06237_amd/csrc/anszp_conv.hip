@@ -81,8 +81,10 @@ struct ConvParams {
     // slice; bytes of x and y
     uint32_t k_groups, t_groups, t_groups_inv, wave_tiles, wave_tiles_rest, round_tiles, slice_units, x_bytes, y_bytes;
     uint32_t x_image, y_image;                            // elements of an image
-    // n / d = mulhi(2 n, magic) >> shift for n < 2^31 (d: output columns, output rows, panels, blocks of 32 input channels)
-    uint32_t out_w_magic, out_w_shift, out_h_magic, out_h_shift, n_mtiles_magic, n_mtiles_shift, blocks_magic, blocks_shift;
+    uint32_t columns, first_column;                       // pixels in a row of them; the one that is the first output column (kShift
+                                                          // without padding: 1, with a pixel on either side that has no output)
+    // n / d = mulhi(2 n, magic) >> shift for n < 2^31 (d: columns, output rows, panels, blocks of 32 input channels)
+    uint32_t columns_magic, columns_shift, out_h_magic, out_h_shift, n_mtiles_magic, n_mtiles_shift, blocks_magic, blocks_shift;
     __device__ __forceinline__ uint32_t n_mtiles_by(uint32_t n) const { return __umulhi(2u * n, n_mtiles_magic) >> n_mtiles_shift; }
     uint32_t pixels_per_split, block_pixels;              // multiples of 16: the pixels of a workgroup; of one block (<= 64)
 };
@@ -950,13 +952,14 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
 }
 
 // The convolution of layers whose input channels are a multiple of 32 and whose kernels are 1 x 1 without padding
-// (kPoint) or three taps wide (kRow; stride 1 and padding 1: kShift): nearly all of a network's.
+// (kPoint) or three taps wide (kRow; stride 1: kShift): nearly all of a network's.
 //
 // Phase 2: a step is a kernel tap and 32 input channels, a unit the steps of a kernel row with the same 32 channels.
 // kRow asks for the row's three taps together: they read the same pixels shifted by one, or alternate halves of the
 // same lines (stride 2), and the L1 then fetches a line once for them.  kShift asks for the middle tap only (and one
 // vector that holds the pixels before the first and behind the last): the other two are the neighbouring lanes' values,
-// moved by one lane, zero at the image's left and right edge.  A load of 64 lanes of 16 bytes keeps a CU's address path busy for about
+// moved by one lane, zero at the ends of a row of pixels.  With padding those are the zeros around the image; without,
+// a row has a pixel more on either side, whose middle tap is the image's first or last column and which has no output.  A load of 64 lanes of 16 bytes keeps a CU's address path busy for about
 // 34 clocks, more than the multiplications it feeds take when a panel has one row tile (K = 4608): 3 x 3 x 512 at 7 x 7
 // loads 4 vectors where kRow loads 9.  The workgroup's column tiles are dealt to t_groups
 // wavefronts, QT or one fewer each, the units to k_groups slices; t_groups * k_groups = 12.  A wavefront multiplies its
@@ -1023,13 +1026,19 @@ __global__ __launch_bounds__(kThreads) void conv_sliced_kernel(ConvParams p) {
     int32_t h0[QT];
     [[maybe_unused]] uint32_t edge_from = kOutside;               // kShift: of the pixel before the first column (lanes 0) and
     [[maybe_unused]] int32_t edge_h0 = 0;                         // behind the last (lanes 15)
-    [[maybe_unused]] uint32_t not_left[QT], not_right[QT];        // all bits, or none in the image's first, last column
+    [[maybe_unused]] uint32_t not_left[QT], not_right[QT];        // all bits, or none in a row's first, last column
     const uint32_t y_elem = p.y_bf16 ? 1u : 2u;                   // log2 bytes
-    auto pixel_of = [&](uint32_t pix, uint32_t end, uint32_t& b, uint32_t& ho, uint32_t& wo) {    // returns the pixel's byte of y
-        const uint32_t t = __umulhi(2u * pix, p.out_w_magic) >> p.out_w_shift;
-        wo = pix - t * p.out_w;
+    // returns the pixel's byte of y; kShift: wo is a column (p.first_column: output column 0)
+    auto pixel_of = [&](uint32_t pix, uint32_t end, uint32_t& b, uint32_t& ho, uint32_t& wo) {
+        const uint32_t t = __umulhi(2u * pix, p.columns_magic) >> p.columns_shift;
+        wo = pix - t * p.columns;
         b = __umulhi(2u * t, p.out_h_magic) >> p.out_h_shift;
         ho = t - b * p.out_h;
+        if constexpr (MODE == kShift) {
+            const uint32_t w = wo - p.first_column;
+            const uint32_t at = (b * p.y_image + (ho * p.out_w + w) * p.y_pixel + (kg >> 1) * p.y_block + 4u * (kg & 1u)) << y_elem;
+            return ((pix < end) & (w < p.out_w)) ? at : kOutside;
+        }
         // D: lane holds column lane % 16, rows 4 * (lane / 16) + 0..3 of a row tile
         const uint32_t at = (b * p.y_image + (ho * p.out_w + wo) * p.y_pixel + (kg >> 1) * p.y_block + 4u * (kg & 1u)) << y_elem;
         return pix < end ? at : kOutside;
@@ -1045,12 +1054,13 @@ __global__ __launch_bounds__(kThreads) void conv_sliced_kernel(ConvParams p) {
             uint32_t b, ho, wo;
             out_at[q] = pixel_of(pix, end, b, ho, wo);
             h0[q] = int32_t(ho * p.stride) - int32_t(p.pad);
-            const int32_t w0 = int32_t(wo * p.stride) - int32_t(p.pad);
+            // (kShift: stride 1; the middle tap's column, w0 of the others)
+            const int32_t w0 = MODE == kShift ? int32_t(wo - p.first_column) + 1 - int32_t(p.pad) : int32_t(wo * p.stride) - int32_t(p.pad);
             const uint32_t corner = (b * p.x_image + uint32_t(h0[q] * int32_t(p.in_w) + w0) * p.x_pixel + kg * p.x_block) * 2u;
             if constexpr (MODE == kShift) {                       // (a column that is not stored may be a neighbour's neighbour)
-                from[0][q] = pix < p.n_pixels ? corner + p.x_pixel * 2u : kOutside;
+                from[0][q] = ((pix < p.n_pixels) & (uint32_t(w0) < p.in_w)) ? corner : kOutside;
                 not_left[q] = wo != 0u ? 0xFFFFFFFFu : 0u;
-                not_right[q] = wo + 1u != p.out_w ? 0xFFFFFFFFu : 0u;
+                not_right[q] = wo + 1u != p.columns ? 0xFFFFFFFFu : 0u;
             } else {
 #pragma unroll
                 for (uint32_t sx = 0; sx < NS; ++sx)
@@ -1062,10 +1072,11 @@ __global__ __launch_bounds__(kThreads) void conv_sliced_kernel(ConvParams p) {
                                                                   // is loaded all the same)
             uint32_t b, ho, wo;
             pixel_of(min(pix, p.n_pixels - 1u), 0u, b, ho, wo);
-            edge_h0 = int32_t(ho) - 1;
+            edge_h0 = int32_t(ho) - int32_t(p.pad);
+            const int32_t w0 = int32_t(wo - p.first_column) + 1 - int32_t(p.pad);
             const bool is_edge = (col == 0u) | (col == 15u);
-            edge_from = is_edge && pix < p.n_pixels
-                            ? (b * p.x_image + uint32_t(edge_h0 * int32_t(p.in_w) + int32_t(wo)) * p.x_pixel + kg * p.x_block) * 2u : kOutside;
+            edge_from = (is_edge & (pix < p.n_pixels) & (uint32_t(w0) < p.in_w))
+                            ? (b * p.x_image + uint32_t(edge_h0 * int32_t(p.in_w) + w0) * p.x_pixel + kg * p.x_block) * 2u : kOutside;
         }
     };
     const anszp_layer_t lay = decode_panel<MR, P16>(p, lds, mtile, [&] { place(0u); });
@@ -1267,12 +1278,12 @@ int launch_sliced(const ConvParams& p, uint32_t mr, bool p16, uint32_t mode, uin
 struct SlicedPlan {
     uint32_t mr = 0, qt = 0, k_groups = 0, round_tiles = 0, slice_units = 0, splits = 0, tiles_per_split = 0, lds_bytes = 0;
     bool p16 = false;
+    uint64_t clocks = ~0ull;
 };
 SlicedPlan plan_sliced(const anszp_conv_args_t& a, uint32_t mode, uint32_t K, uint32_t row_stride, uint32_t n_tiles, uint32_t cus) {
     const uint32_t table_bytes = 16u << a.table_log, fixed = kStageBytes + table_bytes + 64u;
     const uint32_t taps = mode == kPoint ? 1u : 3u, units = (mode == kPoint ? 1u : a.kh) * (a.cin / 32u);
     SlicedPlan best;
-    uint64_t fewest = ~0ull;
     for (const uint32_t mr : {4u, 2u, 1u}) {
         if (a.cout % (kRows * mr)) continue;
         const uint32_t elems = kRows * mr * row_stride;
@@ -1299,8 +1310,8 @@ SlicedPlan plan_sliced(const anszp_conv_args_t& a, uint32_t mode, uint32_t K, ui
                 const uint64_t loads = uint64_t(busy) * (mode == kRow ? 3u * qt : mode == kShift ? qt + 1u : qt) * 24u;
                 const uint64_t unit = std::max(std::max(mfma, reads), std::max<uint64_t>(loads, 2400u / slots));
                 const uint64_t clocks = turns * (decode + rounds * ((units + ks - 1u) / ks * unit + 2400u) + (ks > 1u ? 1500u + sums / 64u : 0u));
-                if (clocks >= fewest) continue;
-                fewest = clocks;
+                if (clocks >= best.clocks) continue;
+                best.clocks = clocks;
                 best.mr = mr; best.p16 = p16; best.qt = qt; best.k_groups = ks; best.round_tiles = per_round;
                 best.slice_units = (units + ks - 1u) / ks; best.splits = splits; best.tiles_per_split = tiles;
                 best.lds_bytes = std::max(std::max(fixed + elems * (p16 ? 2u : 1u), p16 ? 0u : 2u * (elems + 64u)), uint32_t(sums));
@@ -1312,7 +1323,7 @@ SlicedPlan plan_sliced(const anszp_conv_args_t& a, uint32_t mode, uint32_t K, ui
 
 // The whole call in launches of at most `images` images.
 int conv_sliced(ConvParams p, const anszp_conv_args_t& a, uint32_t images, uint32_t cus, int device, hipStream_t s) {
-    const uint32_t mode = a.kw != 3 ? kPoint : a.stride == 1 && a.pad == 1 ? kShift : kRow;
+    const uint32_t widest = a.kw != 3 ? kPoint : a.stride == 1 ? kShift : kRow;
     p.x_image = a.in_h * a.in_w * a.cin;
     p.y_image = p.out_h * p.out_w * a.cout;
     p.panel_off = kStageBytes + (16u << a.table_log);
@@ -1320,7 +1331,6 @@ int conv_sliced(ConvParams p, const anszp_conv_args_t& a, uint32_t images, uint3
         for (shift = 0; (1ull << shift) < d; ++shift) {}
         m = uint32_t((1ull << (31 + shift)) / d + 1u);
     };
-    magic(p.out_w, p.out_w_magic, p.out_w_shift);
     magic(p.out_h, p.out_h_magic, p.out_h_shift);
     magic(a.cin / 32u, p.blocks_magic, p.blocks_shift);
     for (uint32_t first = 0; first < a.batch; first += images) {
@@ -1329,9 +1339,22 @@ int conv_sliced(ConvParams p, const anszp_conv_args_t& a, uint32_t images, uint3
         p.y = static_cast<uint8_t*>(a.y) + uint64_t(first) * p.y_image * (p.y_bf16 ? 2u : 4u);
         p.x_bytes = uint32_t(uint64_t(n) * p.x_image * 2u);
         p.y_bytes = uint32_t(uint64_t(n) * p.y_image * (p.y_bf16 ? 2u : 4u));
-        p.n_pixels = n * p.out_h * p.out_w;
-        const SlicedPlan plan = plan_sliced(a, mode, p.K, p.row_stride, (p.n_pixels + 15u) / 16u, cus);
+        // (without padding kShift takes two pixels more per row: narrow images are better off with kRow)
+        auto plan_of = [&](uint32_t mode) {
+            const uint32_t columns = p.out_w + (mode == kShift && a.pad == 0u ? 2u : 0u);
+            return plan_sliced(a, mode, p.K, p.row_stride, (n * p.out_h * columns + 15u) / 16u, cus);
+        };
+        uint32_t mode = widest;
+        SlicedPlan plan = plan_of(mode);
+        if (mode == kShift && a.pad == 0u) {
+            const SlicedPlan by_row = plan_of(kRow);
+            if (by_row.clocks < plan.clocks) { plan = by_row; mode = kRow; }
+        }
         if (!plan.mr) return ANSZP_E_RANGE;
+        p.first_column = mode == kShift && a.pad == 0u ? 1u : 0u;
+        p.columns = p.out_w + 2u * p.first_column;
+        magic(p.columns, p.columns_magic, p.columns_shift);
+        p.n_pixels = n * p.out_h * p.columns;
         p.n_mtiles = a.cout / (kRows * plan.mr);
         magic(p.n_mtiles, p.n_mtiles_magic, p.n_mtiles_shift);
         p.chunks_per_panel = kRows * plan.mr / a.rows_per_chunk;

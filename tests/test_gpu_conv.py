@@ -415,6 +415,20 @@ def test_activations_of_more_than_two_gibibytes(orc):
     assert d.read_status() == (0, 0)
 
 
+# Three taps wide, stride 1, any padding: rows of pixels that end inside and at the ends of column tiles, one-pixel rows,
+# padding beyond the kernel; narrow images without padding are the other form's.
+@pytest.mark.parametrize("shape,B_,H,Wd,pad", [
+    ((16, 32, 3, 3), 1, 3, 3, 0), ((16, 32, 3, 3), 5, 4, 4, 0), ((32, 64, 3, 3), 3, 9, 16, 0), ((32, 64, 3, 3), 2, 12, 17, 0), ((32, 64, 3, 3), 2, 12, 18, 0),
+    ((64, 128, 3, 3), 4, 15, 34, 0), ((16, 288, 3, 3), 9, 20, 12, 0), ((64, 32, 3, 3), 40, 40, 40, 0), ((16, 512, 3, 3), 2, 9, 33, 0),
+    ((16, 32, 1, 3), 2, 5, 40, 0), ((32, 32, 5, 3), 3, 11, 31, 0),
+    ((16, 32, 3, 3), 2, 1, 1, 2), ((32, 64, 3, 3), 3, 7, 15, 2), ((64, 64, 3, 3), 4, 14, 14, 2), ((16, 32, 3, 3), 2, 6, 5, 3), ((16, 64, 1, 3), 2, 9, 9, 2),
+    ((32, 96, 5, 3), 2, 9, 9, 2), ((64, 32, 3, 3), 30, 40, 38, 2), ((16, 512, 3, 3), 3, 8, 8, 2), ((16, 32, 3, 3), 2, 6, 5, 7),
+])
+@pytest.mark.parametrize("layout", ["nhwc", "c8"])
+def test_shifted_columns_with_any_padding(orc, shape, B_, H, Wd, pad, layout):
+    _check(*_case(orc, shape, B_, H, Wd, 1, pad, x_layout=layout, y_layout=layout))
+
+
 # Panels that do not divide the CUs: workgroups in one turn with CUs left over, in two turns, more panels than CUs.
 @pytest.mark.parametrize("shape,B_,H,Wd,stride,pad", [
     ((80, 32, 1, 1), 9, 40, 40, 1, 0), ((176, 64, 3, 3), 6, 30, 30, 1, 1), ((2064, 32, 1, 1), 1, 20, 20, 1, 0), ((4112, 32, 1, 1), 1, 9, 9, 1, 0),
