@@ -970,9 +970,13 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
 // What bounds these launches (12 to 25 us each) is largely code that runs for the first time: a CU fetches it 64 bytes at
 // a time from the L2, about 85 ns each, which is as long as ten instructions take once they are there (measured: 2.5 us
 // for the tiles' addresses, 0.35 us the second time).  So the code is kept short: no divisions (the host passes
-// reciprocals), no tails (loads go through a buffer descriptor: what lies outside the image, belongs to no pixel or to no unit has an
-// offset beyond the buffer or an empty buffer and reads as zero without memory traffic; stores that belong to no pixel are
-// dropped the same way), one kernel per number of tiles, the slices' sums in a loop.
+// reciprocals), no conditions on a pixel or unit (loads go through a buffer descriptor: what lies outside the image, belongs
+// to no pixel or to no unit has an offset beyond the buffer or an empty buffer and reads as zero without memory traffic;
+// stores that belong to no pixel are dropped the same way), one kernel per number of tiles, the slices' sums in a loop.
+// A load that reads nothing still takes its 25 to 34 clocks of the address path, though, so the last units of a slice have
+// code of their own that asks for no more (as many again as are in flight otherwise, and their multiplications: 840 calls
+// whose best choice takes 9 to 500 us became 4 to 20 % faster where a wavefront has few units or rounds, none slower; 1 x 1
+// from 32 channels to 592 on eight 59 x 59 images 31 -> 27 us).
 //
 // Measured against rings of loads without slices (a call among others, MI355X): 3 x 3 x 512 channels, one 7 x 7 image 21.8 ->
 // 14.1 us; 1 x 1 from 1024 channels, 64 14 x 14 images 21.4 -> 18.3; 3 x 3 x 128 channels, 64 28 x 28 images 28.5 -> 27.2; a
@@ -1144,46 +1148,52 @@ __global__ __launch_bounds__(kThreads) void conv_sliced_kernel(ConvParams p) {
         };
 #pragma unroll
         for (uint32_t d = 0; d < kSlots; ++d) request(d);
+        auto use = [&](uint32_t d) {                              // the unit in slot d
+            uint32_t a_step = a_at + k_use * 2u;
+#pragma unroll
+            for (uint32_t sx = 0; sx < NS; ++sx) {
+                auto operand = [&](uint32_t q) {                  // (q is a constant once unrolled)
+                    if constexpr (MODE != kShift) return ring[d][sx][q];
+                    if (sx == 1u) return ring[d][0][q];
+                    if (sx == 0u) return q ? neighbours<true, true>(ring[d][0][q], ring[d][0][q ? q - 1u : 0u], not_left[q])
+                                           : neighbours<true, false>(ring[d][0][q], edge[d], not_left[q]);
+                    return q + 1u < QT ? neighbours<false, true>(ring[d][0][q], ring[d][0][q + 1u < QT ? q + 1u : q], not_right[q])
+                                       : neighbours<false, false>(ring[d][0][q], edge[d], not_right[q]);
+                };
+                bf16x8 a[MR];
+#pragma unroll
+                for (uint32_t m = 0; m < MR; ++m) a[m] = lds_load<bf16x8>(a_step + m * tile_stride);
+                auto multiply = [&](uint32_t q) {
+                    const bf16x8 b = __builtin_bit_cast(bf16x8, operand(q));
+#pragma unroll
+                    for (uint32_t m = 0; m < MR; ++m) acc[m][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], b, acc[m][q], 0, 0, 0);
+                };
+#pragma unroll
+                for (uint32_t q = 0; q + 1u < QT; ++q) multiply(q);
+                if (has_last) multiply(QT - 1u);                  // (uniform)
+                a_step += p.cin * 2u;
+            }
+            ++use_cb;
+            k_use += 32u;
+            if constexpr (MODE != kPoint) {
+                const bool next_row = use_cb == blocks;
+                use_cb = next_row ? 0u : use_cb;
+                k_use += next_row ? 2u * p.cin : 0u;
+            }
+        };
+        uint32_t done = 0;
 #pragma unroll 1
-        for (uint32_t done = 0; done < n; done += kSlots) {
+        for (; done + kSlots < n; done += kSlots) {
 #pragma unroll
             for (uint32_t d = 0; d < kSlots; ++d) {
-                uint32_t a_step = a_at + k_use * 2u;
-#pragma unroll
-                for (uint32_t sx = 0; sx < NS; ++sx) {
-                    auto operand = [&](uint32_t q) {              // (q is a constant once unrolled)
-                        if constexpr (MODE != kShift) return ring[d][sx][q];
-                        if (sx == 1u) return ring[d][0][q];
-                        if (sx == 0u) return q ? neighbours<true, true>(ring[d][0][q], ring[d][0][q ? q - 1u : 0u], not_left[q])
-                                               : neighbours<true, false>(ring[d][0][q], edge[d], not_left[q]);
-                        return q + 1u < QT ? neighbours<false, true>(ring[d][0][q], ring[d][0][q + 1u < QT ? q + 1u : q], not_right[q])
-                                           : neighbours<false, false>(ring[d][0][q], edge[d], not_right[q]);
-                    };
-                    bf16x8 a[MR];
-#pragma unroll
-                    for (uint32_t m = 0; m < MR; ++m) a[m] = lds_load<bf16x8>(a_step + m * tile_stride);
-                    auto multiply = [&](uint32_t q) {
-                        const bf16x8 b = __builtin_bit_cast(bf16x8, operand(q));
-#pragma unroll
-                        for (uint32_t m = 0; m < MR; ++m) acc[m][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], b, acc[m][q], 0, 0, 0);
-                    };
-#pragma unroll
-                    for (uint32_t q = 0; q + 1u < QT; ++q) multiply(q);
-                    if (has_last) multiply(QT - 1u);              // (uniform)
-                    a_step += p.cin * 2u;
-                }
-                // (behind the slice's last unit: that one's weights times zeros)
-                const bool more = done + d + 1u < n;
-                use_cb += more ? 1u : 0u;
-                k_use += more ? 32u : 0u;
-                if constexpr (MODE != kPoint) {
-                    const bool next_row = use_cb == blocks;
-                    use_cb = next_row ? 0u : use_cb;
-                    k_use += next_row ? 2u * p.cin : 0u;
-                }
+                use(d);
                 request(d);
             }
         }
+#pragma unroll
+        for (uint32_t d = 0; d < kSlots; ++d)
+            if (done + d < n) use(d);                             // (uniform: between the loads a branch would cost the compiler
+                                                                  // its count of them, and every use would wait for all)
         if (p.k_groups == 1u) {
 #pragma unroll
             for (uint32_t m = 0; m < MR; ++m)
