@@ -32,18 +32,12 @@
 #include <cstdint>
 
 #include "anszp.h"
+#include "anszp_conv_plan.h"
 #include "anszp_layout.h"
 #include "anszp_panel.h"
 
 namespace {
 
-constexpr uint32_t kWave = 64;
-constexpr uint32_t kThreads = 768;
-constexpr uint32_t kWaves = kThreads / kWave;
-static_assert(kWaves == kPanelWaves, "the staging room is counted in wavefronts");
-constexpr uint32_t kRows = 16;              // output channels per MFMA row tile
-constexpr uint32_t kRowPad = 8;             // bytes between panel rows: rows start two LDS banks apart
-constexpr uint32_t kWidenPieces = 7;        // 16-byte pieces of a byte panel one thread widens to bf16
 constexpr uint32_t kPatchPieces = 4;        // kGenericPatch: 16-byte pieces of the staged rows per thread
 constexpr uint32_t kMaxMine = (4u * kRows + kWaves - 1u) / kWaves;   // chunks of a panel one wavefront may have to decode
 
@@ -979,11 +973,8 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
 // from 32 channels to 592 on eight 59 x 59 images 31 -> 27 us).
 //
 // Measured against rings of loads without slices (a call among others, MI355X): 3 x 3 x 512 channels, one 7 x 7 image 21.8 ->
-// 14.1 us; 1 x 1 from 1024 channels, 64 14 x 14 images 21.4 -> 18.3; 3 x 3 x 128 channels, 64 28 x 28 images 28.5 -> 27.2; a
-// ResNet-50's 53 convolutions on 16 images, one call each 900 -> 727.
-enum { kPoint = 1, kShift = 2, kRow = 3 };
-constexpr uint32_t units_in_flight(uint32_t mr, uint32_t mode, uint32_t qt) { return mode == kRow ? 2u : mr * qt > 8u || mode == kShift ? 3u : 4u; }
-
+// 13.0 us; 1 x 1 from 1024 channels, 64 14 x 14 images 21.4 -> 17.2; 3 x 3 x 128 channels, 64 28 x 28 images 28.5 -> 26.2; a
+// ResNet-50's 53 convolutions on 16 images, one call each 900 -> 696.
 // Every lane's neighbour's words within rows of 16 lanes: of the lane before (BEFORE) or after, the first (last) lane's
 // from `beyond`, which holds them in the row's last (first) lane if it is a tile of its own (ROTATE), else in the lane
 // itself; and-ed with `mask`.  (Moves and masks in one: the lane without a source keeps what the first instruction
@@ -1234,12 +1225,6 @@ __global__ __launch_bounds__(kThreads) void conv_sliced_kernel(ConvParams p) {
     }
 }
 
-constexpr uint32_t kMaxK = 4608;           // reduction length whose 16-row panel (72 KiB) fits LDS beside the table
-constexpr uint32_t kLdsLimit = 160u * 1024u;
-
-// The most column tiles per wavefront the registers hold.
-constexpr uint32_t most_tiles(uint32_t mr, uint32_t mode) { return mode == kRow ? (mr == 1u ? 4u : 3u) : mr == 4u ? 3u : 4u; }
-
 template <uint32_t MR, bool P16, uint32_t MODE>
 void (*sliced_kernel(uint32_t qt))(ConvParams) {
     if constexpr (most_tiles(MR, MODE) == 4u) {
@@ -1277,58 +1262,6 @@ int launch_sliced(const ConvParams& p, uint32_t mr, bool p16, uint32_t mode, uin
     }
     hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), std::max(lds_bytes, kLeastLds), s, p);
     return hipGetLastError() == hipSuccess ? ANSZP_OK : ANSZP_E_HIP;
-}
-
-// conv_sliced_kernel's row tiles, column tiles, slices and panel form for a call: the fewest clocks by an estimate, all its constants in clocks
-// and fitted to 28 layers of a ResNet-50 at batches of 16 and 64 with every choice forced in turn (on average the choice is 2 %
-// slower than the best one).  Decoding: rounds of chunks over the twelve wavefronts, 2500 and half a clock per symbol each.
-// Widening a panel of bytes: 5000.  A unit of a wavefront: whichever takes longest of its SIMD's wavefronts' matrix
-// instructions (16 each), all wavefronts' panel reads (8), all wavefronts' activation loads (24) and a load's latency over
-// the units in flight (2400).  Rounds of tiles: that latency again.  Slices: 1500 and 64 bytes of sums a clock.
-struct SlicedPlan {
-    uint32_t mr = 0, qt = 0, k_groups = 0, round_tiles = 0, slice_units = 0, splits = 0, tiles_per_split = 0, lds_bytes = 0;
-    bool p16 = false;
-    uint64_t clocks = ~0ull;
-};
-SlicedPlan plan_sliced(const anszp_conv_args_t& a, uint32_t mode, uint32_t K, uint32_t row_stride, uint32_t n_tiles, uint32_t cus) {
-    const uint32_t table_bytes = 16u << a.table_log, fixed = kStageBytes + table_bytes + 64u;
-    const uint32_t taps = mode == kPoint ? 1u : 3u, units = (mode == kPoint ? 1u : a.kh) * (a.cin / 32u);
-    SlicedPlan best;
-    for (const uint32_t mr : {4u, 2u, 1u}) {
-        if (a.cout % (kRows * mr)) continue;
-        const uint32_t elems = kRows * mr * row_stride;
-        const bool p16 = fixed + 2u * elems <= kLdsLimit;         // the panel decoded as bf16 values; else as bytes, widened in place
-        if (!p16 && (fixed + elems > kLdsLimit || 2u * (elems + 64u) > kLdsLimit || elems + 64u > kWidenPieces * kThreads * 16u)) continue;
-        const uint32_t n_mtiles = a.cout / (kRows * mr), most = most_tiles(mr, mode);
-        const uint32_t chunk_rounds = (kRows * mr / a.rows_per_chunk + kWaves - 1u) / kWaves;
-        const uint64_t decode = chunk_rounds * (2500u + uint64_t(a.rows_per_chunk) * K / 2u) + (p16 ? 0u : 5000u);
-        // few, long-lived workgroups, as many as are resident at once (one per CU): each decodes its panel once.  Where the panels
-        // do not divide the CUs: a few CUs left over, or a few workgroups that wait for a CU.
-        for (uint32_t more = 0; more < 2u; ++more) {
-            uint32_t splits = more ? (cus + n_mtiles - 1u) / n_mtiles : cus / n_mtiles;
-            splits = std::max(1u, std::min(splits, n_tiles));
-            const uint32_t tiles = (n_tiles + splits - 1u) / splits;
-            splits = (n_tiles + tiles - 1u) / tiles;
-            const uint64_t turns = (uint64_t(n_mtiles) * splits + cus - 1u) / cus;
-            for (const uint32_t ks : {1u, 2u, 3u, 4u, 6u, 12u}) {
-                const uint32_t ts = kWaves / ks, rounds = (tiles + most * ts - 1u) / (most * ts);
-                const uint32_t per_round = (tiles + rounds - 1u) / rounds, qt = (per_round + ts - 1u) / ts;
-                const uint64_t sums = ks > 1u ? uint64_t(kWaves) * qt * mr * 1024u : 0u;
-                if (ks > 1u && (rounds > 1u || units < ks || sums > kLdsLimit)) continue;
-                const uint32_t busy = (per_round + qt - 1u) / qt * ks, slots = units_in_flight(mr, mode, qt);
-                const uint64_t mfma = uint64_t((busy + 3u) / 4u) * qt * mr * taps * 16u, reads = uint64_t(busy) * mr * taps * 8u;
-                const uint64_t loads = uint64_t(busy) * (mode == kRow ? 3u * qt : mode == kShift ? qt + 1u : qt) * 24u;
-                const uint64_t unit = std::max(std::max(mfma, reads), std::max<uint64_t>(loads, 2400u / slots));
-                const uint64_t clocks = turns * (decode + rounds * ((units + ks - 1u) / ks * unit + 2400u) + (ks > 1u ? 1500u + sums / 64u : 0u));
-                if (clocks >= best.clocks) continue;
-                best.clocks = clocks;
-                best.mr = mr; best.p16 = p16; best.qt = qt; best.k_groups = ks; best.round_tiles = per_round;
-                best.slice_units = (units + ks - 1u) / ks; best.splits = splits; best.tiles_per_split = tiles;
-                best.lds_bytes = std::max(std::max(fixed + elems * (p16 ? 2u : 1u), p16 ? 0u : 2u * (elems + 64u)), uint32_t(sums));
-            }
-        }
-    }
-    return best;                                                  // (one row tile always fits: K <= 4608)
 }
 
 // The whole call in launches of at most `images` images.

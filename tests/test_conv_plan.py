@@ -1,0 +1,67 @@
+"""How the fused convolution's sliced kernel is launched (csrc/anszp_conv_plan.h), checked on the host over calls of every
+size: what the kernel takes for granted about tiles, slices and LDS, and that no few workgroups wait for a CU."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+DRIVER = r"""
+#include <cstdio>
+#include <random>
+#include "anszp_conv_plan.h"
+#define REQUIRE(what) do { if (!(what)) { std::printf("%s: mode %u, %u x %u x %u x %u, rows %u, 2^%u states, %u tiles, %u CUs: %u row tiles, %u tiles, %u slices, %u of %u tiles, %u LDS", \
+    #what, mode, a.cout, a.cin, a.kh, a.kw, a.rows_per_chunk, a.table_log, n_tiles, cus, p.mr, p.qt, p.k_groups, p.splits, p.tiles_per_split, p.lds_bytes); return 1; } } while (0)
+int main() {
+    std::mt19937 rng(1);
+    auto upto = [&](double most) { return uint32_t(std::exp(std::uniform_real_distribution<double>(0.0, std::log(most + 0.999))(rng))); };
+    for (uint32_t i = 0; i < 400000u; ++i) {
+        anszp_conv_args_t a{};
+        const uint32_t mode = 1u + rng() % 3u;
+        a.kw = mode == kPoint ? 1u : 3u;
+        a.kh = mode == kPoint ? 1u : 1u + rng() % 5u;
+        a.cin = 32u * upto(kMaxK / (32u * a.kh * a.kw));
+        if (rng() % 8u == 0u) a.cin = kMaxK / (a.kh * a.kw) / 32u * 32u;
+        a.cout = 16u * upto(300);
+        a.rows_per_chunk = 1u << rng() % 5u;
+        a.table_log = 1u + rng() % 12u;
+        a.x_layout = rng() % 2u; a.y_layout = rng() % 2u;
+        a.y_dtype = rng() % 2u ? ANSZP_OUT_BF16 : ANSZP_OUT_F32;
+        const uint32_t n_tiles = upto(1u << 27), cus = rng() % 4u ? 256u : 1u + rng() % 304u;
+        const uint32_t K = a.cin * a.kh * a.kw, row_stride = ((K + 31u) & ~31u) + kRowPad, units = (mode == kPoint ? 1u : a.kh) * (a.cin / 32u);
+        const SlicedPlan p = plan_sliced(a, mode, K, row_stride, n_tiles, cus);
+        REQUIRE(p.mr == 1u || p.mr == 2u || p.mr == 4u);
+        REQUIRE(a.cout % (kRows * p.mr) == 0u);
+        const uint32_t n_mtiles = a.cout / (kRows * p.mr), elems = kRows * p.mr * row_stride, front = kStageBytes + (16u << a.table_log);
+        // the decoded panel, widened if it is one of bytes, and the slices' sums fit what is asked for, and that the CU
+        REQUIRE(p.lds_bytes <= kLdsLimit && front + elems * (p.p16 ? 2u : 1u) + 64u <= p.lds_bytes);
+        REQUIRE(p.p16 || (2u * (elems + 64u) <= p.lds_bytes && elems + 64u <= kWidenPieces * kThreads * 16u));
+        REQUIRE(p.k_groups >= 1u && kWaves % p.k_groups == 0u);
+        const uint32_t t_groups = kWaves / p.k_groups;
+        REQUIRE(p.qt >= 1u && p.qt <= most_tiles(p.mr, mode));
+        REQUIRE(p.k_groups == 1u || (p.round_tiles == p.tiles_per_split && kWaves * p.qt * p.mr * 1024u <= p.lds_bytes && units >= p.k_groups));
+        // every range of tiles has p.qt of them or one fewer, all rounds and splits together all of them
+        REQUIRE(p.round_tiles >= 1u && (p.round_tiles + t_groups - 1u) / t_groups == p.qt);
+        REQUIRE(p.slice_units * p.k_groups >= units);
+        REQUIRE(uint64_t(p.splits) * p.tiles_per_split >= n_tiles && uint64_t(p.splits - 1u) * p.tiles_per_split < n_tiles);
+        REQUIRE(uint64_t(n_mtiles) * p.splits < (1u << 22));
+        // one workgroup per CU: with several shares a panel, one more each would make some wait for all others
+        REQUIRE(n_mtiles > cus / 8u || n_mtiles * p.splits <= cus);
+    }
+    std::puts("ok");
+    return 0;
+}
+"""
+
+
+def test_plans_of_every_size(tmp_path):
+    if shutil.which("g++") is None:
+        pytest.skip("no host compiler")
+    src, exe = tmp_path / "plan.cpp", tmp_path / "plan"
+    src.write_text("#include <cmath>\n" + DRIVER)
+    subprocess.check_call(["g++", "-std=c++17", "-O2", "-Wall", "-I", os.path.join(ROOT, "include"),
+                           "-I", os.path.join(ROOT, "paper_2406_06237_amd", "csrc"), str(src), "-o", str(exe)])
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout == "ok\n", r.stdout
