@@ -316,12 +316,9 @@ __device__ __attribute__((aligned(64))) const uint32_t zero_page[16] = {0u, 0u, 
 // slot's registers as its results, so that nothing which uses them can be moved ahead of it.  (The compiler, left
 // to count loads that cross the loop's back edge, waits for every load at the head of the loop.)
 template <uint32_t QT>
-__device__ __forceinline__ void ring_request(words4 (&slot)[QT], const uint16_t* const (&px)[QT], uint32_t element_offset) {
+__device__ __forceinline__ void ring_request(words4 (&slot)[QT], const uint16_t* const (&from)[QT]) {
 #pragma unroll
-    for (uint32_t q = 0; q < QT; ++q) {
-        const uint16_t* from = px[q] + element_offset;
-        asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(slot[q]) : "v"(from) : "memory");
-    }
+    for (uint32_t q = 0; q < QT; ++q) asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(slot[q]) : "v"(from[q]) : "memory");
 }
 template <uint32_t QT, uint32_t LATER>
 __device__ __forceinline__ void ring_arrived(words4 (&slot)[QT]) {
@@ -700,7 +697,7 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
                 const uint16_t* from[QT];
 #pragma unroll
                 for (uint32_t q = 0; q < QT; ++q) from[q] = tap_ptr[q] + __umul24(step_in_tap, tap_step[q]);
-                ring_request<QT>(ring[d], from, 0u);
+                ring_request<QT>(ring[d], from);
             };
             auto multiply = [&](uint32_t k_first, uint32_t d) {   // k_first: the step's first k (its panel column)
 #pragma unroll

@@ -87,21 +87,21 @@ def test_convolution_shapes(orc, shape, B_, H, Wd, stride, pad):
 
 
 @pytest.mark.parametrize("shape,B_,H,Wd,stride,pad,layout", [
-    ((64, 256, 1, 1), 2, 14, 14, 1, 0, "c8"),     # pointwise, four steps' loads in flight, bf16 panel of four row tiles
-    ((32, 1024, 1, 1), 1, 7, 7, 1, 0, "c8"),      # pointwise, byte panel widened to bf16 in place
-    ((64, 128, 1, 1), 2, 9, 9, 2, 0, "c8"),       # strided pointwise through the ring of loads
-    ((64, 64, 1, 1), 1, 30, 30, 1, 0, "nhwc"),    # 900 pixels, 57 column tiles: two rounds of tiles, two steps in flight
-    ((32, 128, 3, 3), 3, 9, 9, 2, 1, "c8"),       # several taps through the ring: stride 2, taps outside the image
-    ((64, 64, 3, 3), 2, 12, 12, 1, 1, "c8"),      # several taps through the ring: one group of two steps per tap
-    ((32, 128, 3, 3), 5, 7, 7, 1, 1, "c8"),       # patch in LDS: a round of pixels spans five images
-    ((16, 512, 3, 3), 9, 7, 7, 1, 1, "c8"),       # patch in LDS, K = 4608, sixteen steps, 441 pixels
-    ((64, 128, 3, 3), 2, 30, 30, 1, 1, "nhwc"),   # patch in LDS: 1800 pixels, several workgroups and rounds, rows of 30
-    ((32, 256, 3, 3), 1, 17, 5, 1, 1, "c8"),      # patch in LDS: narrow images, rows shorter than a column tile
+    ((64, 256, 1, 1), 2, 14, 14, 1, 0, "c8"),     # pointwise
+    ((32, 1024, 1, 1), 1, 7, 7, 1, 0, "c8"),      # pointwise, sliced reduction
+    ((64, 128, 1, 1), 2, 9, 9, 2, 0, "c8"),       # strided pointwise
+    ((64, 64, 1, 1), 1, 30, 30, 1, 0, "nhwc"),    # 900 pixels, 57 column tiles
+    ((32, 128, 3, 3), 3, 9, 9, 2, 1, "c8"),       # three taps from three loads: stride 2, taps outside the image
+    ((64, 64, 3, 3), 2, 12, 12, 1, 1, "c8"),      # three taps from one load
+    ((32, 128, 3, 3), 5, 7, 7, 1, 1, "c8"),       # column tiles that span images
+    ((16, 512, 3, 3), 9, 7, 7, 1, 1, "c8"),       # K = 4608, 441 pixels
+    ((64, 128, 3, 3), 2, 30, 30, 1, 1, "nhwc"),   # 1800 pixels, rows of 30
+    ((32, 256, 3, 3), 1, 17, 5, 1, 1, "c8"),      # narrow images, rows shorter than a column tile
     ((64, 3, 7, 7), 2, 24, 24, 2, 3, "nhwc"),     # 3 channels, image rows of 144 bytes staged in LDS with their padding
     ((32, 3, 3, 3), 3, 16, 16, 1, 1, "nhwc"),     # the same over three images, stride 1
     ((16, 5, 2, 2), 1, 9, 8, 1, 0, "nhwc"),       # 5 channels, no padding, a 2 x 2 kernel
     ((16, 12, 5, 5), 2, 40, 40, 3, 2, "nhwc"),    # 12 channels, stride 3, 392 pixels: K = 300 spans ten steps
-    ((32, 64, 1, 3), 2, 8, 9, 1, 1, "c8"),        # a kernel of one row of three taps (a kernel row's taps loaded together)
+    ((32, 64, 1, 3), 2, 8, 9, 1, 1, "c8"),        # a kernel of one row of three taps
     ((16, 128, 5, 3), 1, 9, 9, 2, 1, "c8"),       # five kernel rows of three taps, stride 2
     ((16, 64, 3, 5), 1, 9, 9, 1, 2, "c8"),        # five taps wide: the ring with the taps outermost
     ((128, 64, 3, 3), 1, 40, 40, 1, 1, "c8"),     # four row tiles, 1600 pixels: two column tiles per wavefront, several rounds
@@ -436,3 +436,21 @@ def test_shifted_columns_with_any_padding(orc, shape, B_, H, Wd, pad, layout):
 ])
 def test_panels_that_do_not_divide_the_cus(orc, shape, B_, H, Wd, stride, pad):
     _check(*_case(orc, shape, B_, H, Wd, stride, pad, x_layout="c8", y_layout="c8"))
+
+
+# Kernels of several taps that are not three wide, 1 x 1 with padding: channels that are multiples of 64 go through the ring of
+# hand-issued loads, two (64) or four (128) steps in flight, panels of bf16 values (K <= 576) or of bytes widened in place,
+# four, two and one row tiles; ragged pixel counts, taps outside the image, several rounds of tiles.
+@pytest.mark.parametrize("shape,B_,H,Wd,stride,pad", [
+    ((64, 128, 2, 2), 2, 13, 9, 1, 1), ((32, 128, 2, 2), 3, 11, 7, 1, 0), ((16, 128, 2, 2), 1, 9, 9, 2, 1),      # four in flight, bf16
+    ((64, 128, 1, 1), 2, 9, 7, 1, 1), ((128, 256, 1, 1), 1, 6, 6, 2, 1),
+    ((64, 64, 2, 2), 2, 17, 5, 1, 1), ((32, 64, 2, 4), 1, 12, 12, 1, 2), ((16, 64, 1, 5), 2, 7, 20, 1, 2),        # two in flight, bf16
+    ((64, 128, 1, 8), 1, 4, 30, 1, 4), ((32, 128, 4, 4), 2, 9, 10, 1, 2), ((32, 128, 5, 5), 1, 9, 9, 2, 2),      # four in flight, bytes
+    ((32, 256, 1, 5), 2, 3, 17, 1, 2),
+    ((64, 64, 4, 4), 2, 10, 9, 1, 2), ((32, 64, 5, 5), 2, 9, 8, 1, 2), ((16, 64, 7, 7), 1, 12, 12, 2, 3),        # two in flight, bytes
+    ((16, 64, 2, 2), 64, 60, 60, 1, 0), ((128, 64, 2, 2), 28, 60, 60, 1, 0), ((64, 128, 2, 2), 62, 60, 60, 2, 1),
+    ((128, 192, 1, 2), 33, 50, 50, 1, 1),
+])
+@pytest.mark.parametrize("layout", ["nhwc", "c8"])
+def test_ring_of_loads_for_several_taps(orc, shape, B_, H, Wd, stride, pad, layout):
+    _check(*_case(orc, shape, B_, H, Wd, stride, pad, x_layout=layout, y_layout=layout))
