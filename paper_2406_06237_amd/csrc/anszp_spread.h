@@ -8,14 +8,16 @@
 // The rank is found by a counting sort: occurrence -> one of L buckets by the integer part of L (2i + 1) / (2f)
 // (equal fractions share a bucket and buckets are ordered as the fractions are), a prefix sum over the buckets, and an
 // exact comparison with the other occurrences of the same bucket: one division per state, and as many comparisons as a
-// bucket has members.  On skewed tables these are a few, compared by their products (below 2^26).  Where symbols share a
-// frequency they share all fractions, and a bucket has as many members as there are such symbols: then (some bucket has
-// more than kSpreadFew) a second division gives every occurrence a number that orders the bucket by itself.  With r / 2f the
-// place in the bucket, that is the integer part of 2L r / 2f (different fractions, of frequencies f + g <= L, are
-// 1 / 2fg >= 2 / L^2 apart, so 4 apart here), the symbol below it.
+// bucket has members.  On most tables these are a few, compared by their products (below 2^26; all symbols of odd
+// frequency meet in the middle, but one bucket of a dozen is soon done).  Where symbols share a frequency they share all
+// fractions, and every bucket has as many members as there are such symbols: then a second division gives every
+// occurrence a number that orders its bucket by itself.  With r / 2f the place in the bucket, that is the integer part of
+// 2L r / 2f (different fractions, of frequencies f + g <= L, are 1 / 2fg >= 2 / L^2 apart, so 4 apart here), the symbol
+// below it.
 // Counting the occurrences of every other symbol before each occurrence takes a division per state and symbol instead: with
 // 2^12 states a decode table took 57 us that way (16 symbols; 218 us with 256), 36 us (46 us) this way by one workgroup.
-// A flat row of 2^12 states: 16 symbols 13 us, 256 symbols 56 us (by products in every bucket 25 and 230).
+// Flat rows of 2^12 states by several workgroups, by products -> by numbers: 16 symbols 25 -> 16 us, 256 symbols
+// 231 -> 60; tables with a crowded middle only as before.
 #ifndef ANSZP_SPREAD_H
 #define ANSZP_SPREAD_H
 
@@ -26,7 +28,8 @@
 #include "anszp.h"
 
 constexpr uint32_t kSpreadStates = 1u << ANSZP_MAX_TABLE_LOG;
-constexpr uint32_t kSpreadFew = 8;             // members of a bucket that are compared by their products
+constexpr uint32_t kSpreadFew = 8, kSpreadMany = 24;      // crowded: that many lanes of a wavefront have an occurrence that is not
+                                                          // among the first kSpreadFew of its bucket
 
 struct SpreadLds {
     uint32_t f[ANSZP_ALPHABET];
@@ -34,7 +37,7 @@ struct SpreadLds {
     uint32_t bucket[kSpreadStates];        // members of each bucket, then where each bucket's members start
     uint32_t member[kSpreadStates];        // bucket after bucket: f - 1 | i << 12 | symbol << 24 (crowded: order in the bucket << 8 | symbol)
     uint32_t part[16];                     // a wavefront's share of a prefix sum
-    uint32_t crowded;                      // some bucket has more than kSpreadFew members
+    uint32_t crowded;                      // many buckets have many members
 };
 
 // Inclusive prefix sum over the 64 lanes of a wavefront.
@@ -65,7 +68,6 @@ __device__ __forceinline__ bool spread_states(const uint32_t* freqs, uint32_t ta
         if (lane == 63u) t.part[wave] = upto;
     }
     for (uint32_t b = tid; b < L; b += THREADS) t.bucket[b] = 0u;
-    if (tid == 0u) t.crowded = 0u;
     __syncthreads();
     uint32_t total = 0;
 #pragma unroll
@@ -77,23 +79,34 @@ __device__ __forceinline__ bool spread_states(const uint32_t* freqs, uint32_t ta
     if (tid < ANSZP_ALPHABET) {
         t.f[tid] = fs;
         t.first[tid] = upto - fs;
+        t.crowded = 0u;
     }
     __syncthreads();
-    uint32_t mine[kPerThread], at[kPerThread];     // as in `member`; bucket | place within it << 16
+    // occurrence g: its symbol, frequency, number among the symbol's, bucket
+    auto occurrence = [&](uint32_t g, uint32_t& sy, uint32_t& f, uint32_t& i) {
+        sy = 0;                                                // the largest symbol with first[sy] <= g (it has a frequency)
+#pragma unroll
+        for (uint32_t step = ANSZP_ALPHABET / 2u; step; step >>= 1)
+            sy += t.first[sy + step] <= g ? step : 0u;
+        f = t.f[sy];
+        i = g - t.first[sy];
+        return ((2u * i + 1u) << table_log) / (2u * f);        // below 2^26; i < f, so below L
+    };
+    uint32_t mine[kPerThread], at[kPerThread] = {};     // as in `member`; bucket | place within it << 16
+    uint32_t places = 0;
 #pragma unroll
     for (uint32_t u = 0; u < kPerThread; ++u) {
         const uint32_t g = tid + u * THREADS;
         if (g < L) {
-            uint32_t s = 0;                                    // the largest symbol with first[s] <= g (it has a frequency)
-#pragma unroll
-            for (uint32_t step = ANSZP_ALPHABET / 2u; step; step >>= 1)
-                s += t.first[s + step] <= g ? step : 0u;
-            const uint32_t f = t.f[s], i = g - t.first[s];
-            const uint32_t b = ((2u * i + 1u) << table_log) / (2u * f);      // below 2^26; i < f, so b < L
-            mine[u] = (f - 1u) | i << 12 | s << 24;
+            uint32_t sy, f, i;
+            const uint32_t b = occurrence(g, sy, f, i);
+            mine[u] = (f - 1u) | i << 12 | sy << 24;
             at[u] = b | atomicAdd(&t.bucket[b], 1u) << 16;     // below 2^12 both
         }
+        places |= at[u];
     }
+    // (kSpreadFew is a power of two: a place beyond it has a bit that high)
+    if (__builtin_expect(__popcll(__ballot((places >> 16) >= kSpreadFew)) >= kSpreadMany, 0)) t.crowded = 1u;
     __syncthreads();
     {                                                          // counts -> starts: neighbouring buckets per thread
         const uint32_t per = max(L / THREADS, 1u), b0 = tid * per;
@@ -111,39 +124,36 @@ __device__ __forceinline__ bool spread_states(const uint32_t* freqs, uint32_t ta
 #pragma unroll
         for (uint32_t u = 0; u < kPerThread; ++u) {
             if (u < per && b0 + u < L) t.bucket[b0 + u] = start;
-            if (n[u] > kSpreadFew) t.crowded = 1u;
             start += n[u];
         }
     }
     __syncthreads();
-    auto end_of = [&](uint32_t b) { return b + 1u < L ? t.bucket[b + 1u] : L; };
-    if (__builtin_amdgcn_readfirstlane(t.crowded)) {           // (uniform)
-        uint32_t key[kPerThread];
-#pragma unroll
-        for (uint32_t u = 0; u < kPerThread; ++u) {
-            if (tid + u * THREADS < L) {
-                const uint32_t b = at[u] & 0xFFFFu, f = (mine[u] & 0xFFFu) + 1u, i = (mine[u] >> 12) & 0xFFFu;
-                const uint32_t rest = ((2u * i + 1u) << table_log) - b * 2u * f;         // below 2 f
-                key[u] = (rest << (table_log + 1u)) / (2u * f) << 8 | mine[u] >> 24;     // (the division below 2^26)
-                t.member[t.bucket[b] + (at[u] >> 16)] = key[u];
-            }
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(t.crowded), 0)) {      // (uniform)
+        // (loops that work everything out again: less code beside the other tables' than from registers)
+        auto key_of = [&](uint32_t g, uint32_t& sy, uint32_t& f, uint32_t& i, uint32_t& b) {
+            b = occurrence(g, sy, f, i);
+            const uint32_t rest = ((2u * i + 1u) << table_log) - b * 2u * f;             // below 2 f
+            return (rest << (table_log + 1u)) / (2u * f) << 8 | sy;                      // (the division below 2^26)
+        };
+        uint32_t sy, f, i, b;
+#pragma unroll 1
+        for (uint32_t g = tid; g < L; g += THREADS) {
+            const uint32_t key = key_of(g, sy, f, i, b);
+            t.member[atomicAdd(&t.bucket[b], 1u)] = key;       // (behind this loop every bucket's entry is its end)
         }
         __syncthreads();
-#pragma unroll
-        for (uint32_t u = 0; u < kPerThread; ++u) {
-            if (tid + u * THREADS < L) {
-                const uint32_t begin = t.bucket[at[u] & 0xFFFFu], end = end_of(at[u] & 0xFFFFu);
-                uint32_t state = begin;
-                // (from another member in every lane: occurrences of one symbol are in buckets of like sizes, whose members
-                // in one place would share an LDS bank)
-                uint32_t m = begin + lane % (end - begin);
+#pragma unroll 1
+        for (uint32_t g = tid; g < L; g += THREADS) {
+            const uint32_t key = key_of(g, sy, f, i, b), begin = b ? t.bucket[b - 1u] : 0u, end = t.bucket[b];
+            // (from another member in every lane: occurrences of one symbol are in buckets of like sizes, whose members
+            // in one place would share an LDS bank)
+            uint32_t state = begin, m = begin + lane % (end - begin);
 #pragma unroll 8
-                for (uint32_t n = end - begin; n; --n) {
-                    state += t.member[m] < key[u] ? 1u : 0u;
-                    m = m + 1u < end ? m + 1u : begin;
-                }
-                place(tid + u * THREADS, mine[u] >> 24, (mine[u] & 0xFFFu) + 1u, (mine[u] >> 12) & 0xFFFu, state);
+            for (uint32_t n = end - begin; n; --n) {
+                state += t.member[m] < key ? 1u : 0u;
+                m = m + 1u < end ? m + 1u : begin;
             }
+            place(g, sy, f, i, state);
         }
         return true;
     }
@@ -156,7 +166,7 @@ __device__ __forceinline__ bool spread_states(const uint32_t* freqs, uint32_t ta
         const uint32_t g = tid + u * THREADS;
         if (g < L) {
             const uint32_t b = at[u] & 0xFFFFu;
-            const uint32_t begin = t.bucket[b], end = end_of(b);
+            const uint32_t begin = t.bucket[b], end = b + 1u < L ? t.bucket[b + 1u] : L;
             const uint32_t f = (mine[u] & 0xFFFu) + 1u, i = (mine[u] >> 12) & 0xFFFu, s = mine[u] >> 24;
             uint32_t state = begin;
 #pragma unroll 4

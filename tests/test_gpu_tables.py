@@ -49,7 +49,7 @@ def test_a_rejected_row_is_reported_once_and_leaves_its_table_zero():
     assert np.array_equal(got[[0, 2]], B.build_tables_host(rows[[0, 2]], 12))
 
 
-# Buckets of the counting sort around the size from which its members are compared by their place in the bucket: `equal`
+# Buckets of the counting sort around the sizes from which its members are ordered by a number of their own: `equal`
 # symbols of one frequency share every fraction; `near` ones of neighbouring frequencies lie close to each other.
 @pytest.mark.parametrize("R", [8, 10, 11, 12])
 @pytest.mark.parametrize("kind,k", [("equal", k) for k in (7, 8, 9, 10, 16, 63, 64, 65, 200)] + [("near", k) for k in (9, 30, 120, 250)])
