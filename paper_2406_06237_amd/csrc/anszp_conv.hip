@@ -33,6 +33,7 @@
 
 #include "anszp.h"
 #include "anszp_conv_plan.h"
+#include "anszp_cus.h"
 #include "anszp_layout.h"
 #include "anszp_panel.h"
 
@@ -1268,7 +1269,7 @@ int conv_sliced(ConvParams p, const anszp_conv_args_t& a, uint32_t images, uint3
     p.y_image = p.out_h * p.out_w * a.cout;
     p.panel_off = kStageBytes + (16u << a.table_log);
     auto magic = [](uint32_t d, uint32_t& m, uint32_t& shift) {
-        for (shift = 0; (1ull << shift) < d; ++shift) {}
+        shift = d > 1u ? 32u - uint32_t(__builtin_clz(d - 1u)) : 0u;
         m = uint32_t((1ull << (31 + shift)) / d + 1u);
     };
     magic(p.out_h, p.out_h_magic, p.out_h_shift);
@@ -1362,16 +1363,16 @@ extern "C" int anszp_conv_fused(const anszp_conv_args_t* a, void* stream) {
     p.row_stride = row_stride;
     p.n_pixels = uint32_t(n_pixels);
 
-    int device = 0, cus = 0;
-    if (hipGetDevice(&device) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) return ANSZP_E_HIP;
+    int device = 0;
+    if (hipGetDevice(&device) != hipSuccess) return ANSZP_E_HIP;
+    const uint32_t cus = device_cus(device);
     const bool generic = (a->cin % 8u) != 0;
     const bool pointwise = !generic && a->kh == 1 && a->kw == 1 && a->pad == 0;
     if ((a->cin % 32u) == 0 && (pointwise || a->kw == 3)) {
         // buffer offsets are 31 bits: as many images at a time as x and y of that size allow (all of them, but for very large calls)
         const uint64_t x_image = uint64_t(a->in_h) * a->in_w * a->cin, y_image = uint64_t(out_h) * out_w * a->cout;
         const uint64_t most = ((1ull << 31) - 1u) / std::max(2u * x_image, (p.y_bf16 ? 2u : 4u) * y_image);
-        if (most) return conv_sliced(p, *a, uint32_t(std::min<uint64_t>(most, a->batch)), uint32_t(cus > 0 ? cus : 256), device, static_cast<hipStream_t>(stream));
+        if (most) return conv_sliced(p, *a, uint32_t(std::min<uint64_t>(most, a->batch)), cus, device, static_cast<hipStream_t>(stream));
     }
     // Row tiles per workgroup: as many of 4, 2, 1 as divide the output channels and leave the panel room in LDS
     // beside the table and the staging buffers (more rows per activation vector loaded).
@@ -1389,7 +1390,7 @@ extern "C" int anszp_conv_fused(const anszp_conv_args_t* a, void* stream) {
     // share the panel.
     const uint32_t lds_bytes = fixed_bytes + kRows * mr * row_stride * elem;
     const uint32_t n_tiles = uint32_t((n_pixels + 15u) / 16u);
-    uint32_t splits = (uint32_t(cus > 0 ? cus : 256) + n_mtiles - 1u) / n_mtiles;
+    uint32_t splits = (cus + n_mtiles - 1u) / n_mtiles;
     if (splits > n_tiles) splits = n_tiles;
     if (splits == 0) splits = 1;
     const uint32_t tiles_per_split = (n_tiles + splits - 1u) / splits;

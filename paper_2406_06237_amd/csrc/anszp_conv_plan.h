@@ -59,7 +59,8 @@ inline SlicedPlan plan_sliced(const anszp_conv_args_t& a, uint32_t mode, uint32_
             if (more && (splits * n_mtiles <= cus || cus % n_mtiles == 0u)) break;           // (no more than before, or too many)
             const uint32_t tiles = (n_tiles + splits - 1u) / splits;
             splits = (n_tiles + tiles - 1u) / tiles;
-            const uint64_t turns = (uint64_t(n_mtiles) * splits + cus - 1u) / cus;
+            const uint32_t turns = (n_mtiles * splits + cus - 1u) / cus;                     // (n_mtiles * splits < cus + n_mtiles)
+            if (turns * decode >= best.clocks) continue;
             for (const uint32_t ks : {1u, 2u, 3u, 4u, 6u, 12u}) {
                 const uint32_t ts = kWaves / ks, rounds = (tiles + most * ts - 1u) / (most * ts);
                 const uint32_t per_round = (tiles + rounds - 1u) / rounds, qt = (per_round + ts - 1u) / ts;

@@ -1,4 +1,4 @@
-// Compute units of the current device (host code, internal to the library): queried once per device; the cache is a
+// Compute units of a device (host code, internal to the library): queried once per device; the cache is a
 // table of atomics, so concurrent callers at worst both query.
 #ifndef ANSZP_CUS_H
 #define ANSZP_CUS_H
@@ -8,10 +8,9 @@
 #include <atomic>
 #include <cstdint>
 
-inline uint32_t device_cus() {
+inline uint32_t device_cus(int dev) {
     static std::atomic<uint32_t> cached[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256u;
+    if (dev < 0 || dev >= 64) return 256u;
     uint32_t n = cached[dev].load(std::memory_order_relaxed);
     if (!n) {
         int count = 0;
@@ -20,6 +19,12 @@ inline uint32_t device_cus() {
         cached[dev].store(n, std::memory_order_relaxed);
     }
     return n;
+}
+
+// of the current device
+inline uint32_t device_cus() {
+    int dev = 0;
+    return hipGetDevice(&dev) == hipSuccess ? device_cus(dev) : 256u;
 }
 
 #endif
