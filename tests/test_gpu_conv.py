@@ -454,3 +454,27 @@ def test_panels_that_do_not_divide_the_cus(orc, shape, B_, H, Wd, stride, pad):
 @pytest.mark.parametrize("layout", ["nhwc", "c8"])
 def test_ring_of_loads_for_several_taps(orc, shape, B_, H, Wd, stride, pad, layout):
     _check(*_case(orc, shape, B_, H, Wd, stride, pad, x_layout=layout, y_layout=layout))
+
+
+@pytest.mark.parametrize("shape,stride,pad", [
+    ((32, 64, 1, 1), 1, 0), ((32, 64, 1, 1), 2, 0), ((32, 64, 3, 3), 1, 0), ((32, 64, 3, 3), 1, 1), ((32, 64, 3, 3), 1, 2), ((32, 64, 3, 3), 2, 1),
+    ((16, 512, 3, 3), 1, 1), ((16, 64, 2, 2), 1, 1),
+])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_a_value_that_is_not_finite_reaches_its_own_windows_only(orc, shape, stride, pad, value):
+    cout, cin, kh, kw = shape
+    K, H, Wd = cin * kh * kw, 9, 17                            # rows that end inside a column tile
+    rows = B.conv_rows_per_chunk(K)
+    lay = W.Layer("conv", shape, 4, 16, 0.03125, np.full(16, 1 / 16), 3)     # zero-point beyond the symbols: no weight is zero
+    w = W.Workload("finite", [lay], 12, 64, rows * K, "bf16")
+    d = B.to_device(host_from_oracle(oracle_encode(orc, w), w))
+    codes, _ = W.bf16_activations(2 * H * Wd * cin, 9)
+    x = torch.from_numpy(codes.view(np.int16).reshape(2, H, Wd, cin)).to("cuda:0").view(torch.bfloat16)
+    hit = torch.zeros((2, 1, H, Wd), device="cuda:0")
+    for b, i, j, c in ((0, 0, 0, 5), (0, 4, 16, 40), (1, 8, 3, 0), (1, 5, 0, cin - 1)):
+        x[b, i, j, c] = value
+        hit[b, 0, i, j] = 1.0
+    y = B.from_c8(B.conv_fused(d, 0, 0, rows, B.to_c8(x), shape, stride, pad, x_layout="c8", y_layout="c8"))
+    assert d.read_status() == (0, 0)
+    reached = torch.nn.functional.conv2d(hit, torch.ones((1, 1, kh, kw), device="cuda:0"), stride=stride, padding=pad)[:, 0, :, :, None] > 0
+    assert torch.equal(~torch.isfinite(y), reached.expand_as(y))
