@@ -128,7 +128,11 @@ __device__ __forceinline__ bool spread_states(const uint32_t* freqs, uint32_t ta
         }
     }
     __syncthreads();
-    if (__builtin_expect(__builtin_amdgcn_readfirstlane(t.crowded), 0)) {      // (uniform)
+    uint32_t starts[kPerThread];                               // (asked for together with `crowded`, not behind the branch)
+    const uint32_t crowded = t.crowded;
+#pragma unroll
+    for (uint32_t u = 0; u < kPerThread; ++u) starts[u] = t.bucket[at[u] & 0xFFFFu];
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(crowded), 0)) {        // (uniform)
         // (loops that work everything out again: less code beside the other tables' than from registers)
         auto key_of = [&](uint32_t g, uint32_t& sy, uint32_t& f, uint32_t& i, uint32_t& b) {
             b = occurrence(g, sy, f, i);
@@ -159,7 +163,7 @@ __device__ __forceinline__ bool spread_states(const uint32_t* freqs, uint32_t ta
     }
 #pragma unroll
     for (uint32_t u = 0; u < kPerThread; ++u)
-        if (tid + u * THREADS < L) t.member[t.bucket[at[u] & 0xFFFFu] + (at[u] >> 16)] = mine[u];
+        if (tid + u * THREADS < L) t.member[starts[u] + (at[u] >> 16)] = mine[u];
     __syncthreads();
 #pragma unroll
     for (uint32_t u = 0; u < kPerThread; ++u) {
