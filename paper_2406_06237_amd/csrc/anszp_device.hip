@@ -561,8 +561,8 @@ __global__ __launch_bounds__(kStreamWaves * kWave) void decode_streaming(DecodeP
 
     if (wave >= uint32_t(kStreamDecoders)) {
         // ---- loading wavefront: decoders wave - 14, + 2, + 4, ...  Little to issue, and in a full workgroup others wait for
-        // it: first in line.  Else it is the decoders' chains of look-ups that the launch waits for (772 chunks: 226 us with
-        // the loading wavefronts first in line, 212 with all alike)
+        // it: first in line.  Else it is the decoders' chains of look-ups that the launch waits for (772 chunks of 262,144 symbols:
+        // 226 us with the loading wavefronts first in line, 212 with all alike in the same session)
         if constexpr (!AHEAD) __builtin_amdgcn_s_setprio(3);
         const uint32_t mine_index = wave - uint32_t(kStreamDecoders);
         const uint32_t* where[kStreamServed];             // all indexed by constants once the loops are unrolled
