@@ -210,8 +210,7 @@ int anszp_decode(const anszp_decode_args_t* args, void* hip_stream);
 /* The same call with the kernel chosen by hand; results are identical for every variant.
  *   0  automatic (what anszp_decode does)
  *   1  step-wise kernel: one look-up per symbol, exactly the loop of Sec. II-A / III-B; also the
- *      path any chunk takes whose compressed words exceed the on-chip window or whose first
- *      output element is not 16-byte aligned
+ *      path any chunk takes whose compressed words exceed the on-chip window
  *   2  look-ahead kernel: look-ups use the look-ahead entries of the table (entry 2X + b above),
  *      compressed words and decoded symbols are staged in LDS, and the work of a chunk is split
  *      over several wavefronts of its workgroup

@@ -24,8 +24,8 @@
 //                          of the ring and store them, 16 bytes per lane.  A workgroup serves one
 //                          chunk or two chunks of one layer; which, and in what order the
 //                          workgroups take them, is found per launch or read from a prepared plan.
-// The look-ahead path needs the chunk's words to fit its LDS window and the chunk's first output
-// element to be 16-byte aligned; other chunks take the step-wise path inside the same launch.
+// The look-ahead path needs the chunk's words to fit its LDS window; other chunks take the step-wise path
+// inside the same launch.
 #include "anszp.h"
 #include "anszp_cus.h"
 #include "anszp_layout.h"
@@ -1378,7 +1378,6 @@ __device__ __forceinline__ void decode_lookahead(const DecodeParams& p) {
     enum { kLogged = 0, kNext0 = 1, kOver = 3, kStored0 = 4, kGaveUp = 8 };
     constexpr uint32_t kMaxStorers = 4u;
     static_assert(kExpanders == 2u, "hand-over words 1 and 2");
-    constexpr uint32_t kElemBytes = OUT == ANSZP_OUT_U8 ? 1u : (OUT == ANSZP_OUT_F32 ? 4u : 2u);
     constexpr uint32_t kTableLoads = ((2u << G::kTableLog) / 2u + kBlock - 1u) / kBlock;          // 16-byte loads per thread
     constexpr uint32_t kWordLoads = (kPayloadWords / 4u + kBlock - 1u) / kBlock;                  // per chunk
     static_assert(kSoloWords <= 2u * kWordLoads * 4u * kBlock, "a single chunk's words are loaded by both chunks' loads");
@@ -1464,6 +1463,12 @@ __device__ __forceinline__ void decode_lookahead(const DecodeParams& p) {
     // are in flight (the plan names the dominant symbol); without one the LDS it touches is still in use by
     // the search for the unit, and the dominant symbol is on its way with the table.
     const uint32_t storers = single ? 4u : 3u;           // storing wavefronts per chunk
+    // Positions in a chunk's ring count from the multiple of 8 elements of the output at or below its first element, so
+    // that the eight symbols a lane stores lie on 16 bytes whatever the chunk's offset (an odd-sized layer moves every
+    // layer behind it).  Only the first eight of a chunk are then fewer: its first half slab is stored one by one.  (Such chunks
+    // took the plain loop before.  Measured, layers at odd offsets: 6 layers of 6.7 M symbols, 48 streams, chunks of 54,944
+    // symbols 314 -> 43 us; 16 of 1.1 M, 64 streams, 2^9 states 169 -> 34; 47 of 282,076, 17 streams 651 -> 80.)
+    auto skew_of = [](const anszp_chunk_t& ch) { return static_cast<uint32_t>(ch.out_offset) & 7u; };
     auto init_pipes = [&](uint32_t dominant) {
         if (tid < (single ? 16u : 2u * 16u)) {            // hand-over words (of both chunks)
             const uint32_t q = tid / 16u, i = tid % 16u;
@@ -1479,7 +1484,7 @@ __device__ __forceinline__ void decode_lookahead(const DecodeParams& p) {
         if (tid < (single ? 1u : 2u) * kExpanders * kWave) {   // where every stream is: its first element, or nothing to wait for
             const uint32_t q = tid / (kExpanders * kWave), l = tid % kWave;
             const uint32_t n_q = q ? (in1 ? c1.n_symbols : 0u) : (in0 ? c0.n_symbols : 0u);
-            reinterpret_cast<uint32_t*>(lds + kPipeOff + q * kPipeBytes + kProgOff)[tid % (kExpanders * kWave)] = (l < N && l < n_q) ? l : 0xFFFFFFF0u;
+            reinterpret_cast<uint32_t*>(lds + kPipeOff + q * kPipeBytes + kProgOff)[tid % (kExpanders * kWave)] = (l < N && l < n_q) ? l + skew_of(q ? c1 : c0) : 0xFFFFFFF0u;
         }
         const uint32_t fill = dominant * 0x01010101u;
         uint4* rdst = reinterpret_cast<uint4*>(lds + kRingOff);
@@ -1575,14 +1580,14 @@ __device__ __forceinline__ void decode_lookahead(const DecodeParams& p) {
     const uint32_t ring_mask = ring_elems - 1u;
     uint8_t* const ring8 = lds + kRingOff + pipe * kRingElems;
     lds_flag_t* const ctl = (lds_flag_t*)(lds + pipe_off + kCtlOff);
-    const uint32_t n = c.n_symbols;
-    const uint64_t layer_elem0 = c.out_offset - lay.out_base;
+    const uint32_t skew = skew_of(c);
+    const uint32_t n = c.n_symbols + skew;                           // (like every position: from `skew` elements before the chunk's first)
     const uint32_t n_words = hdr >> 16;
-    const uint32_t len = (lane < N && n > lane) ? (n - lane + N - 1u) / N : 0u;
-    const uint32_t lane_end = lane < N ? lane + len * N : n;         // first element of this lane at or beyond the chunk's end
+    const uint32_t len = (lane < N && c.n_symbols > lane) ? (c.n_symbols - lane + N - 1u) / N : 0u;
+    const uint32_t lane_end = lane < N ? skew + lane + len * N : n;  // first element of this lane at or beyond the chunk's end
     const bool merged_ok = p.table_log <= G::kTableLog && c.payload_words <= (single ? kSoloWords : kPayloadWords) &&
-                           ((c.out_offset * kElemBytes) & 15u) == 0 && n <= (1u << 24) && PER_CHANNEL == (lay.channel_len != 0) &&
-                           (!PER_CHANNEL || layer_elem0 + n < (1ull << 32));
+                           c.n_symbols <= (1u << 24) && PER_CHANNEL == (lay.channel_len != 0) &&
+                           (!PER_CHANNEL || c.out_offset - lay.out_base + c.n_symbols < (1ull << 32));
     if (!merged_ok) {                                     // the plain loop of Sec. II-A, table read from global memory
         if (task != kDecode) return;
         const uint32_t err = decode_chunk_stepwise<OUT>(p, c, lay, WordTable{src + table_triples_offset(p.table_log)}, lane);
@@ -1590,22 +1595,31 @@ __device__ __forceinline__ void decode_lookahead(const DecodeParams& p) {
         return;
     }
 
-    // Slabs of the ring are final once every unfinished lane's next symbol lies beyond them.  A lane
-    // takes elements 8*lane .. 8*lane+7 of each half of a slab, so that every store instruction writes
-    // one contiguous run; the slots go back to the background value.
-    auto store_slab = [&](uint32_t first_elem) {
-        uint8_t* q = ring8 + ((first_elem & ring_mask) + lane * 8u);         // the ring is a whole number of slabs
-        const uint2 lo = *reinterpret_cast<const uint2*>(q);
-        const uint2 hi = *reinterpret_cast<const uint2*>(q + kSlab / 2u);
-        *reinterpret_cast<uint2*>(q) = make_uint2(bg4, bg4);
-        *reinterpret_cast<uint2*>(q + kSlab / 2u) = make_uint2(bg4, bg4);
-        const uint32_t first = first_elem + lane * 8u;
-        Flusher<OUT, PER_CHANNEL>::store8(p, lay, c.out_offset + first, layer_elem0 + first, lo);
-        Flusher<OUT, PER_CHANNEL>::store8(p, lay, c.out_offset + first + kSlab / 2u, layer_elem0 + first + kSlab / 2u, hi);
-    };
-
     if (task == kStore) {
         // ---- storing wavefronts: wavefront `sub` takes every `storers`-th slab
+        const uint64_t out_elem0 = c.out_offset - skew;               // the output's and the layer's element at position 0 (the layer's may
+        const uint64_t layer_elem0 = out_elem0 - lay.out_base;        // wrap below 0: only positions from `skew` on are looked up)
+        // Slabs of the ring are final once every unfinished lane's next symbol lies beyond them.  A lane
+        // takes elements 8*lane .. 8*lane+7 of each half of a slab, so that every store instruction writes
+        // one contiguous run; the slots go back to the background value.
+        auto store_slab = [&](uint32_t first_elem) {
+            uint8_t* q = ring8 + ((first_elem & ring_mask) + lane * 8u);         // the ring is a whole number of slabs
+            const uint2 lo = *reinterpret_cast<const uint2*>(q);
+            const uint2 hi = *reinterpret_cast<const uint2*>(q + kSlab / 2u);
+            *reinterpret_cast<uint2*>(q) = make_uint2(bg4, bg4);
+            *reinterpret_cast<uint2*>(q + kSlab / 2u) = make_uint2(bg4, bg4);
+            const uint32_t first = first_elem + lane * 8u;
+            // (the usual case first and whole: a condition around the first of two stores cost 0.3 us of a ResNet-50's 21.7)
+            if (__builtin_expect(first_elem != 0u || skew == 0u, 1)) {
+                Flusher<OUT, PER_CHANNEL>::store8(p, lay, out_elem0 + first, layer_elem0 + first, lo);
+                Flusher<OUT, PER_CHANNEL>::store8(p, lay, out_elem0 + first + kSlab / 2u, layer_elem0 + first + kSlab / 2u, hi);
+                return;
+            }
+#pragma unroll 1
+            for (uint32_t j = lane == 0u ? skew : 0u; j < 8u; ++j)     // what lies before the chunk is not its own
+                Flusher<OUT, PER_CHANNEL>::store1(p, lay, out_elem0 + first + j, layer_elem0 + first + j, ((j < 4u ? lo.x : lo.y) >> (8u * (j & 3u))) & 0xFFu);
+            Flusher<OUT, PER_CHANNEL>::store8(p, lay, out_elem0 + first + kSlab / 2u, layer_elem0 + first + kSlab / 2u, hi);
+        };
         uint32_t mine = sub * kSlab, spins = 0;          // first element of the next slab this one takes
         for (;;) {
             uint32_t over_v, next_a, next_b;
@@ -1650,8 +1664,8 @@ __device__ __forceinline__ void decode_lookahead(const DecodeParams& p) {
         // the elements behind the last whole slab, by the wavefront whose turn that slab would have been
         const uint32_t rest = n / kSlab * kSlab;
         if ((rest / kSlab) % storers == sub)
-            for (uint32_t j = rest + lane; j < n; j += kWave)
-                Flusher<OUT, PER_CHANNEL>::store1(p, lay, c.out_offset + j, layer_elem0 + j, ring8[j & ring_mask]);
+            for (uint32_t j = max(rest, skew) + lane; j < n; j += kWave)
+                Flusher<OUT, PER_CHANNEL>::store1(p, lay, out_elem0 + j, layer_elem0 + j, ring8[j & ring_mask]);
         return;
     }
 
@@ -1667,12 +1681,12 @@ __device__ __forceinline__ void decode_lookahead(const DecodeParams& p) {
         // read after it is the block.
         __builtin_amdgcn_s_setprio(2);                   // ahead of the storing wavefronts
         uint32_t err = (sub == 0u && total_words != c.payload_words) ? ANSZP_ST_BAD_DESC : 0u;
-        if (sub == 0u && lane < N && !(lane < n)) {      // no symbols: the initial state must be the final one
+        if (sub == 0u && lane < N && len == 0u) {        // no symbols: the initial state must be the final one
             if ((hdr & (L - 1u)) != 0u) err |= ANSZP_ST_BAD_STATE;
             if (n_words != 0u) err |= ANSZP_ST_BAD_LENGTH;
         }
         uint32_t block = sub, spins = 0;
-        uint32_t ne = (lane < N && lane < n) ? lane : 0xFFFFFFF0u;          // as staged: after the last block (none yet)
+        uint32_t ne = len != 0u ? skew + lane : 0xFFFFFFF0u;                // as staged: after the last block (none yet)
         // the block a lane's stream ends in (of this wavefront's blocks), kept for the checks behind the loop
         uint32_t end_ent[kBlockLookups + 1u] = {}, end_bit_after = 0, end_ne_before = 0;
         bool ended_here = false;
@@ -1782,7 +1796,7 @@ __device__ __forceinline__ void decode_lookahead(const DecodeParams& p) {
     const uint32_t index0 = 2u * (hdr & (L - 1u)) + (lds_words[min(first_word, c.payload_words)] & 1u);
     uint2 e = reinterpret_cast<const uint2*>(lds + kTableOff)[index0];
     uint32_t abit = first_bit;                           // bit position, counted from the start of LDS
-    uint32_t ne = (lane < N && lane < n) ? lane : lane_end;
+    uint32_t ne = len != 0u ? skew + lane : lane_end;
     uint32_t logged = 0, spins = 0;
     bool gave_up = false;
     // the first eight hand-over words in two LDS reads
@@ -1873,6 +1887,7 @@ __device__ __forceinline__ void decode_lookahead(const DecodeParams& p) {
             "s_mov_b64 exec, s[42:43]\n"
             "s_waitcnt lgkmcnt(1)\n"
             "s_branch 3f\n"
+            ".p2align 6\n"
             "1:\n"
             "ds_write_b32 v47, v39 offset:%[posrow]\n"
             "s_mov_b64 exec, s[42:43]\n"
