@@ -24,6 +24,8 @@
 //                          of the ring and store them, 16 bytes per lane.  A workgroup serves one
 //                          chunk or two chunks of one layer; which, and in what order the
 //                          workgroups take them, is found per launch or read from a prepared plan.
+//   decode_split           one stream per chunk, long enough: the stream cut into segments that a workgroup's
+//                          wavefronts walk side by side from guessed states (anszp_split.h).
 // The look-ahead path needs the chunk's words to fit its LDS window; other chunks take the step-wise path
 // inside the same launch.
 #include "anszp.h"
@@ -1100,6 +1102,8 @@ struct Flusher {
         store_weight<OUT>(p.out, g, sym, lay.zero_point, sc);
     }
 };
+
+#include "anszp_split.h"
 
 // ---------------------------------------------------------------------------------------------
 // Which chunks a workgroup of the look-ahead kernel decodes.  A workgroup that has a CU to itself decodes a
@@ -2184,8 +2188,10 @@ __global__ __launch_bounds__(256) void dequant_runs_kernel(const uint8_t* sym, u
 
 template <int OUT>
 void launch_decode(const DecodeParams& p, uint32_t n_chunks, bool per_channel, bool stepwise, bool shared, bool streaming,
-                   bool small, bool byte_table, hipStream_t s) {
-    if (byte_table) {
+                   bool small, bool byte_table, bool split, hipStream_t s) {
+    if (split) {
+        hipLaunchKernelGGL(decode_split<OUT>, dim3(n_chunks), dim3(kSplitThreads), 0, s, p);
+    } else if (byte_table) {
         hipLaunchKernelGGL(decode_byte_table<OUT>, dim3((n_chunks + kByteWaves - 1) / kByteWaves), dim3(kByteWaves * kWave), 0, s, p);
     } else if (stepwise && streaming) {
         // chunks dealt evenly to as many workgroups as fill whole rounds of the device's CUs
@@ -2214,7 +2220,7 @@ void launch_decode(const DecodeParams& p, uint32_t n_chunks, bool per_channel, b
 std::atomic<uint32_t> spin_limit_for_tests{kSpinLimit};
 
 // What a launch would be: checks of the arguments, the kernel's parameters, which kernel.
-struct LaunchChoice { bool stepwise, byte_table, shared, streaming, small, per_channel; };
+struct LaunchChoice { bool stepwise, byte_table, shared, streaming, small, per_channel, split; };
 
 int choose_launch(const anszp_decode_args_t* a, int mode, DecodeParams& p, LaunchChoice& k);
 
@@ -2230,7 +2236,7 @@ int decode_impl(const anszp_decode_args_t* a, int mode, void* hip_stream, uint32
     if (rc != ANSZP_OK) return rc;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const uint32_t nc = static_cast<uint32_t>(a->n_chunks);
-    const bool lookahead = !k.stepwise && !k.byte_table;
+    const bool lookahead = !k.stepwise && !k.byte_table && !k.split;
     if (plan || plan_only) {
         if (!plan) return ANSZP_E_NULL;
         if ((reinterpret_cast<uintptr_t>(plan) & 15) || plan_bytes < 2u * uint64_t(mapped_workgroups(nc)) * sizeof(PlanRecord)) return ANSZP_E_RANGE;
@@ -2248,9 +2254,9 @@ int decode_impl(const anszp_decode_args_t* a, int mode, void* hip_stream, uint32
     }
     p.plan = lookahead ? plan : nullptr;
     switch (a->out_dtype) {
-        case ANSZP_OUT_U8: launch_decode<ANSZP_OUT_U8>(p, nc, k.per_channel, k.stepwise, k.shared, k.streaming, k.small, k.byte_table, s); break;
-        case ANSZP_OUT_F32: launch_decode<ANSZP_OUT_F32>(p, nc, k.per_channel, k.stepwise, k.shared, k.streaming, k.small, k.byte_table, s); break;
-        default: launch_decode<ANSZP_OUT_BF16>(p, nc, k.per_channel, k.stepwise, k.shared, k.streaming, k.small, k.byte_table, s); break;
+        case ANSZP_OUT_U8: launch_decode<ANSZP_OUT_U8>(p, nc, k.per_channel, k.stepwise, k.shared, k.streaming, k.small, k.byte_table, k.split, s); break;
+        case ANSZP_OUT_F32: launch_decode<ANSZP_OUT_F32>(p, nc, k.per_channel, k.stepwise, k.shared, k.streaming, k.small, k.byte_table, k.split, s); break;
+        default: launch_decode<ANSZP_OUT_BF16>(p, nc, k.per_channel, k.stepwise, k.shared, k.streaming, k.small, k.byte_table, k.split, s); break;
     }
     return hipGetLastError() == hipSuccess ? ANSZP_OK : ANSZP_E_HIP;
 }
@@ -2285,6 +2291,17 @@ int choose_launch(const anszp_decode_args_t* a, int mode, DecodeParams& p, Launc
     k.small = a->table_log <= SmallLds::kTableLog && 2u * mean_words <= SmallLds::kPayloadWords &&
               kBlockLookups * kLookaheadMaxSymbols * a->n_streams < SmallLds::kRingElems;     // a block must fit its ring
     k.per_channel = a->scales != nullptr && a->n_scales != 0;
+    // One stream per chunk: its chain split over a workgroup where the stream is long enough for walks started anywhere
+    // to meet it, i.e. as many bits as the table has states and 3,072, or twice as many and 2,048 (2^11 states: 2,048 bits
+    // 28.6 us as one chain, 32.0 split; 3,072 bits 40.7 and 28.9; 2^10 states: 2,048 bits 28.2 and 18.6), and either the
+    // chunks leave CUs idle otherwise or a chain is so long that four chunks at once on a CU do not make up for it (600
+    // chunks of 11,000 bits 148 us as chains, of 17,000 bits 146 split).  Longer than the kernel can hold: as before (the
+    // mean is exact for one chunk; several may differ, then the bound is the look-ahead kernel's).
+    const uint64_t bits = 32u * mean_words, states = 1ull << a->table_log;
+    k.split = mode == 0 && a->n_streams == 1 && bits >= kSplitMinBits && bits >= states && (bits >= 3072u || bits >= 2u * states) &&
+              mean_words <= (a->n_chunks == 1 ? kSplitWords : LargeLds::kPayloadWords) &&
+              (a->n_chunks <= p.n_cus || bits >= 16384u);
+    if (k.split) k.stepwise = k.streaming = false;
     return ANSZP_OK;
 }
 
