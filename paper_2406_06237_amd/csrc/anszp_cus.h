@@ -1,4 +1,6 @@
-// Compute units of a device (host code, internal to the library): queried once per device; the cache is a
+// Host state shared by the library's sources (internal to the library).
+//
+// Compute units of a device: queried once per device; the cache is a
 // table of atomics, so concurrent callers at worst both query.
 #ifndef ANSZP_CUS_H
 #define ANSZP_CUS_H
@@ -25,6 +27,13 @@ inline uint32_t device_cus(int dev) {
 inline uint32_t device_cus() {
     int dev = 0;
     return hipGetDevice(&dev) == hipSuccess ? device_cus(dev) : 256u;
+}
+
+// The bound of every wait between wavefronts or workgroups, in polls and one more; 0: each kernel's own.  Tests lower
+// it (anszp_test_set_spin_limit) to see what a wait that is given up leads to.
+inline std::atomic<uint32_t>& spin_limit_for_tests() {
+    static std::atomic<uint32_t> polls{0};
+    return polls;
 }
 
 #endif

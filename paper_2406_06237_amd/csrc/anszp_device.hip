@@ -2215,10 +2215,6 @@ void launch_decode(const DecodeParams& p, uint32_t n_chunks, bool per_channel, b
     }
 }
 
-// The bound of every wait between wavefronts, in polls.  Tests lower it (anszp_test_set_spin_limit) to see that a
-// hand-over that does not complete ends in ANSZP_ST_INTERNAL and a drained launch, not in a hang.
-std::atomic<uint32_t> spin_limit_for_tests{kSpinLimit};
-
 // What a launch would be: checks of the arguments, the kernel's parameters, which kernel.
 struct LaunchChoice { bool stepwise, byte_table, shared, streaming, small, per_channel, split; };
 
@@ -2278,7 +2274,8 @@ int choose_launch(const anszp_decode_args_t* a, int mode, DecodeParams& p, Launc
     p.n_cus = device_cus();
     p.n_chunks = static_cast<uint32_t>(a->n_chunks);
     p.plan = nullptr;
-    p.spin_limit = spin_limit_for_tests.load(std::memory_order_relaxed);
+    const uint32_t polls = spin_limit_for_tests().load(std::memory_order_relaxed);
+    p.spin_limit = polls ? polls - 1u : kSpinLimit;
     // chunks whose compressed words cannot fit the look-ahead kernel's LDS window would all take its
     // fallback: they go to the streaming kernel, whatever their number (measured on 772 to 24,704
     // chunks of 82 KB of words: 5 to 7 times faster than one step-wise wavefront per chunk)
@@ -2365,7 +2362,7 @@ int anszp_build_tables_device(const uint32_t* freqs_dev, int n_tables, int table
 
 int anszp_decode(const anszp_decode_args_t* args, void* hip_stream) { return decode_impl(args, 0, hip_stream); }
 
-void anszp_test_set_spin_limit(uint32_t polls) { spin_limit_for_tests.store(polls ? polls - 1u : kSpinLimit, std::memory_order_relaxed); }
+void anszp_test_set_spin_limit(uint32_t polls) { spin_limit_for_tests().store(polls, std::memory_order_relaxed); }
 
 uint64_t anszp_plan_bytes(uint64_t n_chunks) {
     if (n_chunks >= (1ull << 31)) return 0;

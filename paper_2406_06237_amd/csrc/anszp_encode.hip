@@ -7,7 +7,8 @@
 // bits of the first symbol first, so a stream's bits are laid down from its end: the walk is done
 // once to learn the stream's length and once to write.
 //
-// Three launches, nothing allocated and no scratch memory: sizes (every stream's final state and
+// As many chunks as the chip holds workgroups at once are walked once (encode_once, further down).  More of them take three
+// launches, like those nothing allocated and no scratch memory: sizes (every stream's final state and
 // word count into the stream headers, every chunk's descriptor but for its payload offset), a scan
 // over the chunks (payload offsets, total), the writing pass.  What the writing pass needs to know of
 // the sizes pass beyond that (how many bits of a stream's last word are used) travels in fields that
@@ -28,6 +29,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstddef>
 #include <cstdint>
 
 #include "anszp.h"
@@ -52,16 +54,18 @@ struct EncParams {
     unsigned long long* used;
     uint32_t* status;
     uint64_t n_chunks, out_offset, payload_word_offset, payload_cap_words;
-    uint32_t n_layers, table_log, n_streams, layer_id, stream_offset, chunks_per_group;
+    uint32_t n_layers, table_log, n_streams, layer_id, stream_offset, chunks_per_group, spin_limit;
 };
 
 // A layer's encoding tables.  info[s]: what x + info.x has in its upper half is the number of bits symbol s drops
 // in state x; 2 * (x >> that) + info.y is the byte of `next` that holds the new state plus L.  A symbol without a
 // frequency has info.x = 0 (no other symbol has), drops nothing and leads to some state.
-struct EncLds {
-    SpreadLds spread;
+struct EncTables {
     uint2 info[ANSZP_ALPHABET];
     uint16_t next[kSpreadStates];
+};
+struct EncLds : EncTables {
+    SpreadLds spread;
 };
 
 __device__ __forceinline__ void report(uint32_t* status, uint32_t bits) {
@@ -70,17 +74,17 @@ __device__ __forceinline__ void report(uint32_t* status, uint32_t bits) {
 }
 
 // The workgroup's encoding tables.  False (for every thread) when the frequencies do not sum to L.
-__device__ __forceinline__ bool build_tables(const uint32_t* freqs, uint32_t table_log, EncLds& t) {
+__device__ __forceinline__ bool build_tables(const uint32_t* freqs, uint32_t table_log, EncTables& t, SpreadLds& spread) {
     const uint32_t tid = threadIdx.x, L = 1u << table_log;
-    const bool ok = spread_states<kThreads>(freqs, table_log, t.spread, [&](uint32_t g, uint32_t, uint32_t, uint32_t, uint32_t state) {
+    const bool ok = spread_states<kThreads>(freqs, table_log, spread, [&](uint32_t g, uint32_t, uint32_t, uint32_t, uint32_t state) {
         t.next[g] = static_cast<uint16_t>(L + state);
     });
     if (!ok) return false;
     if (tid < ANSZP_ALPHABET) {
-        const uint32_t f = t.spread.f[tid];
+        const uint32_t f = spread.f[tid];
         // x in [L, 2L) drops k or k - 1 bits, k = table_log - floor(log2 f): k when x >= f << k
         const uint32_t k = f ? table_log - (31u - static_cast<uint32_t>(__clz(f))) : 0u;
-        t.info[tid] = f ? make_uint2((k << 16) - (f << k), 2u * (t.spread.first[tid] - f)) : make_uint2(0u, 0u - 2u * L);
+        t.info[tid] = f ? make_uint2((k << 16) - (f << k), 2u * (spread.first[tid] - f)) : make_uint2(0u, 0u - 2u * L);
     }
     __syncthreads();
     return true;
@@ -101,7 +105,7 @@ struct ChunkStreams {
 // in reverse, padded at its start so that whole reversed words are whole words of the stream, and each
 // finished word is bit-reversed into its place, from the stream's last word down to its first.
 template <bool WRITE>
-__device__ __forceinline__ uint32_t walk_stream(const EncLds& t, const ChunkStreams& s, uint32_t N, uint32_t L, uint32_t* words, uint32_t n_words,
+__device__ __forceinline__ uint32_t walk_stream(const EncTables& t, const ChunkStreams& s, uint32_t N, uint32_t L, uint32_t* words, uint32_t n_words,
                                 uint32_t pad, uint32_t& x_out, bool& bad_symbol) {
     uint32_t x = L, bits = 0, lowest = 0xFFFFFFFFu;           // lowest: the smallest info.x met
     uint64_t acc = 0;
@@ -190,19 +194,22 @@ __device__ __forceinline__ uint32_t walk_stream(const EncLds& t, const ChunkStre
     return bits;
 }
 
-// The layer chunk c belongs to (jobs are in chunk order: the last one whose first_chunk is not beyond c) and the
+// (Called by whole wavefronts, c alike for all lanes.)  The layer chunk c belongs to (jobs are in chunk order: the last one whose first_chunk is not beyond c) and the
 // chunk's number within it.  False when c belongs to no layer.
 __device__ bool layer_of_chunk(const EncParams& p, uint64_t c, uint32_t& layer, anszp_pack_job_t& job, uint64_t& local) {
     layer = 0;
     if (!p.jobs) {
         job = p.one;
     } else {
+        // (64 jobs at a look, one per lane: a look is a round trip to memory)
         uint32_t lo = 0, hi = p.n_layers;
-        if (hi == 0 || p.jobs[0].first_chunk > c) return false;
-        while (hi - lo > 1u) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (p.jobs[mid].first_chunk <= c) lo = mid; else hi = mid;
-        }
+        do {
+            const uint32_t stride = (hi - lo + kWave - 1u) / kWave, i = lo + (threadIdx.x & (kWave - 1u)) * stride;
+            const uint32_t below = static_cast<uint32_t>(__popcll(__ballot(i < hi && p.jobs[min(i, hi - 1u)].first_chunk <= c)));
+            if (below == 0u) return false;
+            lo += (below - 1u) * stride;
+            hi = min(hi, lo + stride);
+        } while (hi - lo > 1u);
         layer = lo;
         job = p.jobs[lo];
     }
@@ -229,7 +236,7 @@ __device__ __forceinline__ void for_each_chunk(const EncParams& p, EncLds& t, CH
         uint64_t run = (job.n_symbols + job.chunk_size - 1) / job.chunk_size - local;   // chunks of this layer from c on
         if (p.jobs && layer + 1u < p.n_layers && p.jobs[layer + 1u].first_chunk > c) run = min(run, (unsigned long long)(p.jobs[layer + 1u].first_chunk - c));
         run = min(run, (unsigned long long)(end - c));
-        const bool ok = build_tables(p.freqs + size_t(layer) * ANSZP_ALPHABET, p.table_log, t);
+        const bool ok = build_tables(p.freqs + size_t(layer) * ANSZP_ALPHABET, p.table_log, t, t.spread);
         for (uint64_t i = wave; i < run; i += kWaves) chunk(job, layer, local + i, c + i, ok);
         c += run;
         // (behind the last run a wavefront is done as soon as its own chunks are: the registers of the idle ones let the
@@ -336,33 +343,381 @@ __global__ __launch_bounds__(kThreads) void encode_scan(EncParams p) {
     }
 }
 
-__global__ __launch_bounds__(kThreads, 4) void encode_write(EncParams p) {
-    __shared__ EncLds t;
+// A chunk's words, by one wavefront, from a walk of its own.  fifth: see encode_sizes.
+__device__ __forceinline__ void write_chunk(const EncParams& p, const EncTables& t, const anszp_pack_job_t& job, uint64_t local, uint64_t c, uint32_t payload_words,
+                                            uint64_t payload_offset, uint64_t fifth) {
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t N = p.n_streams, L = 1u << p.table_log;
+    const ChunkStreams s = streams_of(p, job, local, lane);
+    const uint32_t hdr = lane < N ? p.stream_hdr[c * N + lane] : 0u;
+    const uint32_t nw = hdr >> 16;
+    const uint32_t beyond = ((hdr >> 12) & 15u) | ((fifth >> lane) & 1u ? 16u : 0u);   // bits of the last word, 0: all
+    if (lane < N) p.stream_hdr[c * N + lane] = hdr & 0xFFFF0FFFu;
+    if (lane == 0) p.chunks[c].out_offset = p.out_offset + job.first_symbol + local * job.chunk_size;
+    const uint64_t at = payload_offset - p.payload_word_offset;          // in the caller's payload region
+    const uint64_t padded = (uint64_t(payload_words) + 3ull) & ~3ull;
+    if (at > p.payload_cap_words || padded > p.payload_cap_words - at) return;     // no room: reported with the total
+    uint32_t* words = p.payload + at + (spread_wave_sum(nw) - nw);
+    uint32_t x = L, room = nw;
+    bool bad = false;
+    if (__ballot(nw == 0xFFFFu) != 0ull) {                  // a stream too long for its header is not written
+        const uint32_t bits = walk_stream<false>(t, s, N, L, nullptr, 0u, 0u, x, bad);
+        if (((bits + 31u) >> 5) != nw) room = 0u;
+    }
+    if (!s.has_any) room = 0u;
+    walk_stream<true>(t, s, N, L, words, room, (32u - beyond) & 31u, x, bad);
+    if (lane < padded - payload_words) p.payload[at + payload_words + lane] = 0u;   // up to three pad words
+}
+
+__global__ __launch_bounds__(kThreads, 4) void encode_write(EncParams p) {
+    __shared__ EncLds t;
     for_each_chunk(p, t, [&](const anszp_pack_job_t& job, uint32_t, uint64_t local, uint64_t c, bool ok) {
         if (!ok) return;                                        // reported by the first pass
-        const ChunkStreams s = streams_of(p, job, local, lane);
         const anszp_chunk_t d = p.chunks[c];
-        const uint32_t hdr = lane < N ? p.stream_hdr[c * N + lane] : 0u;
-        const uint32_t nw = hdr >> 16;
-        const uint32_t beyond = ((hdr >> 12) & 15u) | ((d.out_offset >> lane) & 1u ? 16u : 0u);   // bits of the last word, 0: all
-        if (lane < N) p.stream_hdr[c * N + lane] = hdr & 0xFFFF0FFFu;
-        if (lane == 0) p.chunks[c].out_offset = p.out_offset + job.first_symbol + local * job.chunk_size;
-        const uint64_t at = d.payload_offset - p.payload_word_offset;          // in the caller's payload region
-        const uint64_t padded = (uint64_t(d.payload_words) + 3ull) & ~3ull;
-        if (at > p.payload_cap_words || padded > p.payload_cap_words - at) return;     // no room: reported by the scan
-        uint32_t* words = p.payload + at + (spread_wave_sum(nw) - nw);
-        uint32_t x = L, room = nw;
-        bool bad = false;
-        if (__ballot(nw == 0xFFFFu) != 0ull) {                  // a stream too long for its header is not written
-            const uint32_t bits = walk_stream<false>(t, s, N, L, nullptr, 0u, 0u, x, bad);
-            if (((bits + 31u) >> 5) != nw) room = 0u;
-        }
-        if (!s.has_any) room = 0u;
-        walk_stream<true>(t, s, N, L, words, room, (32u - beyond) & 31u, x, bad);
-        if (lane < padded - d.payload_words) p.payload[at + d.payload_words + lane] = 0u;   // up to three pad words
+        write_chunk(p, t, job, local, c, d.payload_words, d.payload_offset, d.out_offset);
     }, [&](uint64_t) {});                                       // reported by the first pass
+}
+
+// ---- All chunks at once (no more than the chip holds workgroups): one walk of every stream.
+//
+// A workgroup takes one chunk.  Its wavefronts share the walk, sixteen rows of symbols at a time with a barrier between:
+//   load   (four) fetch the symbols, two steps ahead, and leave their constants in LDS in the order they are needed,
+//   walk   (one) goes from state to state and notes each with the symbol's constant added,
+//   pack   (one) works out from that which bits were dropped and lays them down, in the order of the walk.
+// What stands between two states is then all the walking wavefront does (one LDS read, three instructions: 40 ns a
+// symbol; 83 with the bits laid down in between, after 54 for a walk that only counts them).  A stream's bits stay in LDS
+// until it is known how many there are and where the chunk's words begin: every workgroup publishes its chunk's words
+// in the chunk's descriptor and adds up those of the chunks before it (the field reads kUnknown until then).  A workgroup only ever waits for lower-numbered
+// ones, which the chip has started before it; it gives up after a bounded number of looks all the same.  The
+// chunks of those that did, and chunks with a stream longer than its place in LDS, are written by the launch behind
+// this one, with a walk of their own.
+// Measured on 369 chunks of 65,536 symbols (2^12 states, 64 streams): 70 us, 11 of them the tables, 40 ns a symbol, and 1.4
+// and 4 us for the launches before and behind; with a pass for the sizes, a scan and a pass that writes 71, 5 and 97.  One
+// layer of 2.4 M symbols in 144 chunks 26 (23, 5, 29).  (A chunk whose streams do not fit is walked twice and costs what it
+// did: 200 chunks of 65,536 symbols at 4.9 bits 236, 240.)
+constexpr uint32_t kRows = 16u;                             // rows of symbols between two barriers
+constexpr uint32_t kRowsPerLoader = 4u;
+constexpr uint32_t kBitsStride = kWave + 1u;                // words from a stream's word to its next (read by streams and by words)
+constexpr uint32_t kUnknown = 0xFFFFFFFFu;                  // in a descriptor's payload_words: not published yet
+constexpr uint64_t kNotWritten = 1ull << 63;                // in its out_offset: to be written by the launch behind this one
+typedef __attribute__((address_space(3))) uint32_t lds_word_t;
+__device__ __forceinline__ uint32_t lds_offset(const void* shared) {
+    return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) void*)shared));
+}
+struct OnceLds {
+    EncTables tables;
+    union {
+        SpreadLds spread;
+        struct {
+            uint2 ring[2][kRows][kWave];                    // the symbols' constants: being loaded, being read by the walk
+            uint32_t sums[2][kRows][kWave];                 // state plus constant: being walked, packed
+        };
+    };
+    uint32_t first[kWave], n_words[kWave], pad[kWave], x[kWave];
+    uint32_t before, gave_up, bad, over;
+    uint64_t fifth;                                         // (with bits 12..15 of a header: the bits beyond whole words, for a chunk written later)
+    uint32_t bits[kBitsStride];                             // (as many rows as fit: see kBitRows)
+};
+constexpr uint32_t kOnceLds = 80u * 1024u;                  // two workgroups per CU
+constexpr uint32_t kBitRows = (kOnceLds - uint32_t(offsetof(OnceLds, bits))) / (4u * kBitsStride) - 1u;
+
+// True for every thread when the frequencies of the one layer sum to L.
+__device__ __forceinline__ bool one_layer_ok(const EncParams& p) {
+    __shared__ uint32_t part[ANSZP_ALPHABET / kWave];
+    const uint32_t tid = threadIdx.x, L = 1u << p.table_log;
+    if (tid < ANSZP_ALPHABET) {
+        const uint32_t sum = spread_wave_sum(min(p.freqs[tid], L + 1u));       // (as in spread_states)
+        if (tid % kWave == kWave - 1u) part[tid / kWave] = sum;
+    }
+    __syncthreads();
+    return part[0] + part[1] + part[2] + part[3] == L;
+}
+
+// Before it: nothing is published.  (One layer of bad frequencies: nothing is written at all.)
+__global__ __launch_bounds__(kThreads) void encode_begin(EncParams p) {
+    if (!p.jobs && !one_layer_ok(p)) return;
+    for (uint64_t c = threadIdx.x; c < p.n_chunks; c += kThreads) p.chunks[c].payload_words = kUnknown;
+}
+
+// Words of the chunks before c (each a multiple of four), once all are published.  False for every thread when one of
+// them was not by the `looks`-th look.
+__device__ __forceinline__ bool words_before(const EncParams& p, uint64_t c, uint32_t looks, uint32_t& before, uint32_t& gave_up, uint64_t& out) {
+    const uint32_t tid = threadIdx.x;
+    if (tid == 0) { before = 0u; gave_up = 0u; }
+    __syncthreads();
+    uint32_t sum = 0;
+    for (uint64_t i = tid; i < c; i += kThreads) {
+        uint32_t v, n = 0;
+        while ((v = __hip_atomic_load(&p.chunks[i].payload_words, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == kUnknown) {
+            if (n++ >= looks) { gave_up = 1u; v = 0u; break; }
+            __builtin_amdgcn_s_sleep(8);
+        }
+        sum += (v + 3u) & ~3u;
+    }
+    if (sum) atomicAdd(&before, sum);
+    __syncthreads();
+    out = before;                                           // (at most 2^9 chunks of at most 2^21 words)
+    return gave_up == 0u;
+}
+
+__global__ __launch_bounds__(kThreads, 4) void encode_once(EncParams p) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kOnceLds];
+    OnceLds& t = *reinterpret_cast<OnceLds*>(lds);
+    const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t N = p.n_streams, L = 1u << p.table_log;
+    const uint64_t c = blockIdx.x;
+    auto publish = [&](uint32_t words) { __hip_atomic_store(&p.chunks[c].payload_words, words, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    uint32_t layer;
+    anszp_pack_job_t job;
+    uint64_t local;
+    if (!layer_of_chunk(p, c, layer, job, local)) {         // the jobs do not cover the chunks the caller counted
+        if (tid == 0) {
+            report(p.status, ANSZP_ST_BAD_DESC);
+            anszp_chunk_t* const d = &p.chunks[c];
+            d->layer_id = d->n_symbols = d->stream_offset = 0u;
+            d->out_offset = kNotWritten;
+            publish(0u);
+        }
+        if (tid < N) p.stream_hdr[c * N + tid] = 0u;
+        return;
+    }
+    const bool ok = build_tables(p.freqs + size_t(layer) * ANSZP_ALPHABET, p.table_log, t.tables, t.spread);
+    const uint64_t out_offset = p.out_offset + job.first_symbol + local * job.chunk_size;
+    auto describe = [&](uint32_t n_symbols, bool later) {
+        anszp_chunk_t* const d = &p.chunks[c];
+        d->layer_id = p.jobs ? layer : p.layer_id;
+        d->n_symbols = n_symbols;
+        d->out_offset = out_offset | (later ? kNotWritten : 0u);
+        d->stream_offset = p.stream_offset + static_cast<uint32_t>(c) * N;
+    };
+    if (!ok) {
+        if (tid == 0 && local == 0) report(p.status, ANSZP_ST_BAD_FREQ);
+        if (!p.jobs) return;                                // (one layer: nothing is written)
+        if (tid < N) p.stream_hdr[c * N + tid] = 0u;
+        if (tid == 0) {
+            describe(0u, true);
+            publish(0u);
+        }
+        return;
+    }
+    const ChunkStreams s = streams_of(p, job, local, lane);
+    if (tid == 0) t.bad = t.over = 0u;
+    const uint32_t batches = (s.max_len + kRows - 1u) / kRows, skip = batches * kRows - s.max_len;   // the first batch's first `skip` places are empty
+    // (the tables have been built: what they were built with makes room for the ring)
+    __syncthreads();
+    auto next_phase = [] { asm volatile("s_waitcnt lgkmcnt(0)\n s_barrier" ::: "memory"); };     // (loads from global memory stay under way)
+    // Phase ph: batch ph is loaded, ph - 1 read by the walk, ph - 2 walked, ph - 3 packed.
+    const uint32_t phases = batches + 3u;
+    if (wave == 0u) {
+        __builtin_amdgcn_s_setprio(3);
+        uint32_t x = L;
+        const uint8_t* const next = reinterpret_cast<const uint8_t*>(t.tables.next);
+        // (the sum's upper half is the number of bits dropped, and as f_s << k ends in k zeros its lowest bits are the
+        // state's: all that the packing wavefront needs)
+        auto step = [&](const uint2 i, uint32_t& note) {
+            const uint32_t sum = x + i.x;
+            uint32_t kept;                                  // x >> (the count in the sum's upper half)
+            asm("v_lshrrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:DWORD" : "=v"(kept) : "v"(sum), "v"(x));
+            x = *reinterpret_cast<const uint16_t*>(next + (2u * kept + i.y));
+            note = sum;
+        };
+        auto walk = [&](uint32_t b, const uint2 (&info)[kRows], uint2 (&then)[kRows]) {
+            const uint2* const row = &t.ring[(b + 1u) & 1u][0][lane];           // (behind the last batch: read, and not used)
+            uint32_t* const note = &t.sums[b & 1u][0][lane];
+#pragma unroll
+            for (uint32_t j = 0; j < kRows; ++j) {
+                step(info[j], note[j * kWave]);
+                then[j] = row[j * kWave];
+            }
+            next_phase();
+        };
+        uint2 info_a[kRows], info_b[kRows];
+        next_phase();
+#pragma unroll
+        for (uint32_t j = 0; j < kRows; ++j) info_a[j] = t.ring[0][j][lane];
+        next_phase();
+#pragma unroll
+        for (uint32_t j = 0; j < kRows; ++j) {              // the first batch: its first `skip` places are empty, in some lanes one more
+            info_b[j] = t.ring[1][j][lane];
+            uint32_t note = 0u;
+            if (j > skip || (j == skip && s.has_last)) step(info_a[j], note);
+            t.sums[0][j][lane] = note;
+        }
+        next_phase();
+        for (uint32_t b = 1; b < batches; b += 2u) {
+            walk(b, info_b, info_a);
+            if (b + 1u >= batches) break;
+            walk(b + 1u, info_a, info_b);
+        }
+        t.x[lane] = s.has_any ? x - L : 0u;
+        next_phase();
+        __builtin_amdgcn_s_setprio(0);
+    } else if (wave == 1u) {
+        __builtin_amdgcn_s_setprio(2);
+        // A word is written to its place whenever bits have been added to it, whether it is full or not: no branch.
+        uint32_t low = 0, count = 0, bits = 0;              // the bits of the word being filled, how many; of the stream
+        uint32_t at = lds_offset(t.bits) + 4u * lane;
+        const uint32_t last = at + 4u * kBitsStride * kBitRows;         // (a row for what finds no room)
+        next_phase();
+        next_phase();
+        next_phase();
+        for (uint32_t b = 0; b < batches; ++b) {
+            const uint32_t* const note = &t.sums[b & 1u][0][lane];
+            uint32_t sum[kRows];
+#pragma unroll
+            for (uint32_t j = 0; j < kRows; ++j) sum[j] = note[j * kWave];
+#pragma unroll
+            for (uint32_t j = 0; j < kRows; j += 2u) {      // at most 24 bits
+                const uint32_t n0 = sum[j] >> 16, n1 = sum[j + 1u] >> 16, n = n0 + n1;
+                const uint32_t two = __builtin_amdgcn_ubfe(sum[j + 1u], 0u, n1) << n0 | __builtin_amdgcn_ubfe(sum[j], 0u, n0);
+                const uint32_t carry = (two >> 1) >> (~count & 31u);
+                low |= two << count;
+                *reinterpret_cast<lds_word_t*>(static_cast<uintptr_t>(at)) = low;
+                count += n;
+                bits += n;
+                const bool full = count >= 32u;
+                low = full ? carry : low;
+                at = min(full ? at + 4u * kBitsStride : at, last);
+                count &= 31u;
+            }
+            if (b + 1u < batches) next_phase();
+        }
+        *reinterpret_cast<lds_word_t*>(static_cast<uintptr_t>(at)) = low;
+        if (!s.has_any) bits = 0u;
+        uint32_t nw = (bits + 31u) >> 5;
+        const bool too_long = nw > 0xFFFFu;
+        nw = min(nw, 0xFFFFu);
+        const bool over = __ballot(nw > kBitRows) != 0ull;
+        const uint32_t upto = spread_wave_sum(nw), words = __builtin_amdgcn_readlane(upto, kWave - 1);
+        const uint64_t fifth = __ballot((bits & 16u) != 0u);
+        if (lane == 0) {
+            describe(s.cn, over);
+            publish(words);
+            t.fifth = fifth;
+            if (over) t.over = 1u;
+        }
+        if (__ballot(too_long) && lane == 0) report(p.status, ANSZP_ST_NO_SPACE);
+        t.first[lane] = upto - nw;
+        t.n_words[lane] = nw;
+        t.pad[lane] = (32u - bits) & 31u;
+        next_phase();
+    } else {
+        // loading wavefronts: 2, 3, 6 and 7 (the others share a SIMD with the wavefronts above, as SIMDs are dealt out)
+        const bool loads = (wave & 2u) != 0u;
+        const uint32_t from = ((wave & 1u) + (wave >> 2) * 2u) * kRowsPerLoader;
+        uint32_t sym_a[kRowsPerLoader] = {}, sym_b[kRowsPerLoader] = {}, lowest = 0xFFFFFFFFu;
+        auto fetch = [&](uint32_t b, uint32_t (&sym)[kRowsPerLoader]) {
+            if (b >= batches) return;
+#pragma unroll
+            for (uint32_t j = 0; j < kRowsPerLoader; ++j) {
+                const uint32_t place = max(b * kRows + from + j, skip);
+                // (a lane without a symbol in the last row takes another one there, which is neither walked nor packed)
+                const uint32_t row = s.max_len - 1u - (place - skip);
+                global_uint8_t* const at = s.chunk + uint64_t(row) * N;
+                sym[j] = place == skip && !s.has_last ? s.chunk[s.lane_off] : at[s.lane_off];
+            }
+        };
+        auto prepare = [&](uint32_t b, uint32_t slot, const uint32_t (&sym)[kRowsPerLoader]) {
+            if (b >= batches) return;
+            uint2 info[kRowsPerLoader];
+#pragma unroll
+            for (uint32_t j = 0; j < kRowsPerLoader; ++j) info[j] = t.tables.info[sym[j]];
+#pragma unroll
+            for (uint32_t j = 0; j < kRowsPerLoader; ++j) {
+                lowest = min(lowest, info[j].x);
+                t.ring[slot][from + j][lane] = info[j];
+            }
+        };
+        if (loads) { fetch(0u, sym_a); fetch(1u, sym_b); }
+        for (uint32_t ph = 0; ph < phases; ph += 2u) {
+            if (loads) {
+                prepare(ph, 0u, sym_a);
+                fetch(ph + 2u, sym_a);
+            }
+            next_phase();
+            if (ph + 1u >= phases) break;
+            if (loads) {
+                prepare(ph + 1u, 1u, sym_b);
+                fetch(ph + 3u, sym_b);
+            }
+            next_phase();
+        }
+        if (lowest == 0u) t.bad = 1u;
+    }
+    __syncthreads();
+    if (tid == 0 && t.bad) report(p.status, ANSZP_ST_BAD_SYMBOL);
+    const bool over = t.over != 0u;
+    uint64_t before = 0;
+    const bool known = !over && words_before(p, c, p.spin_limit, t.before, t.gave_up, before);
+    const uint32_t nw = t.n_words[lane], n_words = __builtin_amdgcn_readlane(t.first[lane] + nw, kWave - 1);
+    const uint64_t padded = (uint64_t(n_words) + 3ull) & ~3ull;
+    if (wave == 0u && lane < N)
+        p.stream_hdr[c * N + lane] = t.x[lane] | (known ? 0u : ((32u - t.pad[lane]) & 15u) << 12) | nw << 16;
+    if (!known) {
+        if (tid == 0) {
+            p.chunks[c].payload_offset = t.fifth;
+            p.chunks[c].out_offset = out_offset | kNotWritten;
+        }
+        return;
+    }
+    if (tid == 0) p.chunks[c].payload_offset = p.payload_word_offset + before;
+    if (before > p.payload_cap_words || padded > p.payload_cap_words - before) return;    // no room: reported by the launch behind this one
+    uint32_t* const out = p.payload + before;
+    // A wavefront takes a stream at a time, a lane every 64th word: the bits as laid down, moved up by the zero bits behind
+    // the stream's last one, are whole words of the stream from its last to its first, bit-reversed.
+    for (uint32_t k = wave; k < N; k += kWaves) {
+        const uint32_t n = __builtin_amdgcn_readfirstlane(t.n_words[k]), pad = __builtin_amdgcn_readfirstlane(t.pad[k]);
+        uint32_t* const words = out + __builtin_amdgcn_readfirstlane(t.first[k]);
+        for (uint32_t m = lane; m < n; m += kWave) {
+            const uint32_t hi = t.bits[m * kBitsStride + k], lo = m ? t.bits[(m - 1u) * kBitsStride + k] : 0u;
+            words[n - 1u - m] = __brev(static_cast<uint32_t>(((uint64_t(hi) << 32 | lo) << pad) >> 32));
+        }
+    }
+    if (tid < padded - n_words) out[n_words + tid] = 0u;        // up to three pad words
+}
+
+// Behind it: the total, and the chunks that were not written.
+__global__ __launch_bounds__(kThreads, 4) void encode_rest(EncParams p) {
+    __shared__ EncLds t;
+    __shared__ unsigned long long sum;
+    const uint32_t tid = threadIdx.x;
+    const uint64_t c = blockIdx.x;
+    const bool last = c + 1u == p.n_chunks;
+    if (!p.jobs && !one_layer_ok(p)) {
+        if (last && tid == 0) *p.used = 0ull;
+        return;
+    }
+    const anszp_chunk_t d = p.chunks[c];
+    const bool written = !(d.out_offset & kNotWritten);
+    if (!written || last) {                                     // words before this chunk
+        if (tid == 0) sum = 0ull;
+        __syncthreads();
+        unsigned long long mine = 0;
+        for (uint64_t i = tid; i < c; i += kThreads) mine += (uint64_t(p.chunks[i].payload_words) + 3ull) & ~3ull;
+        if (mine) atomicAdd(&sum, mine);
+        __syncthreads();
+    }
+    if (last && tid == 0) {
+        const uint64_t used = sum + ((uint64_t(d.payload_words) + 3ull) & ~3ull);
+        *p.used = used;
+        if (used > p.payload_cap_words) report(p.status, ANSZP_ST_NO_SPACE);
+    }
+    uint32_t layer;
+    anszp_pack_job_t job;
+    uint64_t local;
+    if (written) return;
+    const bool has_layer = layer_of_chunk(p, c, layer, job, local);
+    if (d.n_symbols == 0u) {                                    // no layer, or one of bad frequencies
+        if (tid == 0) {
+            p.chunks[c].out_offset = has_layer ? p.out_offset + job.first_symbol + local * job.chunk_size : 0u;
+            p.chunks[c].payload_offset = p.payload_word_offset + sum;
+        }
+        return;
+    }
+    if (!build_tables(p.freqs + size_t(layer) * ANSZP_ALPHABET, p.table_log, t, t.spread)) return;      // (they were there: the chunk has symbols)
+    if (tid >= kWave) return;
+    if (tid == 0) p.chunks[c].payload_offset = p.payload_word_offset + sum;
+    write_chunk(p, t, job, local, c, d.payload_words, p.payload_word_offset + sum, d.payload_offset);
 }
 
 // Chunks per workgroup: one as long as every CU gets no more than two workgroups (a walk is a chain: the fewer wavefronts
@@ -377,6 +732,16 @@ uint32_t chunks_per_group(uint64_t n_chunks) {
 
 int launch(EncParams& p, hipStream_t s) {
     p.chunks_per_group = chunks_per_group(p.n_chunks);
+    if (p.n_chunks && p.chunks_per_group == 1u) {
+        // (a look at the others' words takes about 0.4 us: some 25 ms)
+        const uint32_t looks = spin_limit_for_tests().load(std::memory_order_relaxed);
+        p.spin_limit = looks ? looks - 1u : 1u << 16;
+        const dim3 groups(uint32_t(p.n_chunks)), threads(kThreads);
+        hipLaunchKernelGGL(encode_begin, dim3(1), threads, 0, s, p);
+        hipLaunchKernelGGL(encode_once, groups, threads, 0, s, p);
+        hipLaunchKernelGGL(encode_rest, groups, threads, 0, s, p);
+        return hipGetLastError() == hipSuccess ? ANSZP_OK : ANSZP_E_HIP;
+    }
     const uint64_t groups = (p.n_chunks + p.chunks_per_group - 1u) / p.chunks_per_group;
     if (groups) hipLaunchKernelGGL(encode_sizes, dim3(uint32_t(groups)), dim3(kThreads), 0, s, p);
     else if (!p.jobs) hipLaunchKernelGGL(encode_nothing, dim3(1), dim3(kWave), 0, s, p);

@@ -257,3 +257,30 @@ def test_a_layer_without_symbols_still_has_its_frequencies_checked():
         g[at] = v
         chunks, hdr, payload, used, status = _pack(empty, g, 10, 64, 4096)
         assert status == (B.ST_BAD_FREQ, 1) and used == 0 and np.all(payload == 0xFFFFFFFF)
+
+
+@pytest.mark.parametrize("polls", [1, 2])
+def test_chunks_whose_place_is_not_known_in_time_are_written_all_the_same(orc, polls):
+    """Workgroups wait for the word counts of the chunks before theirs; with the bound lowered from the host most give up,
+    and the launch behind them writes those chunks."""
+    w = W.tiny(seed=11, n=300 * 4096 + 77, bitwidth=5, n_streams=64, chunk_size=4096, table_log=11, p0=0.6)
+    try:
+        B.lib().anszp_test_set_spin_limit(polls)
+        _compare(orc, w.symbols()[0], 11, 64, 4096)
+    finally:
+        B.lib().anszp_test_set_spin_limit(0)
+    _compare(orc, w.symbols()[0], 11, 64, 4096)
+
+
+@pytest.mark.parametrize("R,N,chunk,n", [(12, 64, 65536, 200000), (8, 64, 36000, 100000), (12, 5, 3000, 40000), (10, 1, 4400, 30000), (9, 1, 200000, 190001)])
+def test_streams_longer_than_their_place_in_lds(orc, R, N, chunk, n):
+    """Up to 8 bits a symbol: chunks with a stream of more words than LDS holds, beside some that fit, are written by the
+    launch behind; 4,400 symbols of one bit are just such a stream, and of half of them not."""
+    rng = np.random.default_rng(n)
+    dense = rng.integers(0, 256 if R >= 8 else 16, n).astype(np.uint8)
+    _compare(orc, dense, R, N, chunk)
+    two = rng.integers(0, 2, n).astype(np.uint8)
+    two[: n // 3] = 1
+    _compare(orc, two, R, N, chunk)
+    thin = np.where(rng.random(n) < 0.97, 1, two).astype(np.uint8)
+    _compare(orc, np.concatenate([thin, dense, two]), R, N, chunk)
