@@ -41,6 +41,11 @@ class DecodeArgs(C.Structure):
                 ("out", C.c_void_p), ("out_elems", C.c_uint64), ("status", C.c_void_p)]
 
 
+class _LayerArg(C.Structure):          # LAYER_DTYPE, for the call that takes one in host memory
+    _fields_ = [("scale", C.c_float), ("zero_point", C.c_uint32), ("bitwidth", C.c_uint32), ("channel_len", C.c_uint32),
+                ("scales_offset", C.c_uint64), ("out_base", C.c_uint64)]
+
+
 class ConvArgs(C.Structure):
     _fields_ = [("tables", C.c_void_p), ("n_tables", C.c_uint32), ("table_log", C.c_uint32),
                 ("n_streams", C.c_uint32), ("layer_id", C.c_uint32),
@@ -250,11 +255,48 @@ def pack_workload(w) -> HostContainer:
 
 
 # --------------------------------------------------------------------------- device entry points
+_torch_with_gpu = None
+
+
 def _torch():
-    import torch
-    if not torch.cuda.is_available():
-        raise RuntimeError("libanszp device entry points need a GPU (torch.cuda.is_available() is False)")
-    return torch
+    global _torch_with_gpu
+    if _torch_with_gpu is None:
+        import torch
+        if not torch.cuda.is_available():
+            raise RuntimeError("libanszp device entry points need a GPU (torch.cuda.is_available() is False)")
+        _torch_with_gpu = torch
+    return _torch_with_gpu
+
+
+# A call of a small layer takes 6 us on the device, so what stands before the launch matters: asking torch for its current
+# stream as an object and entering a device context for the device that is current anyway took 5 of 9 us.
+_index_of_name = {}
+
+
+def _device_index(torch, device) -> int:
+    """The index of a device named in any way torch knows ("cuda": the current one)."""
+    if type(device) is int:
+        return device
+    index = _index_of_name.get(device)
+    if index is None:
+        index = torch.device(device).index
+        if index is None:
+            return torch.cuda.current_device()
+        _index_of_name[device] = index
+    return index
+
+
+def _enqueue(where: str, function, device, *args):
+    """function(*args, stream) with `device` as the current device and its current stream; raises on an error code."""
+    torch = _torch()
+    index = _device_index(torch, device)
+    if index == torch.cuda.current_device():
+        rc = function(*args, torch._C._cuda_getCurrentRawStream(index))
+    else:
+        with torch.cuda.device(index):
+            rc = function(*args, torch._C._cuda_getCurrentRawStream(index))
+    if rc:
+        raise AnszpError(rc, where)
 
 
 def _dev(arr: np.ndarray, device):
@@ -287,11 +329,9 @@ def build_tables_device(freqs_dev, table_log: int, status=None):
     torch = _torch()
     device = freqs_dev.device
     n_tables = freqs_dev.numel() // ALPHABET
-    with torch.cuda.device(device):
-        tables = torch.empty(table_words(n_tables, table_log), dtype=torch.int32, device=device)
-        _check(lib().anszp_build_tables_device(freqs_dev.data_ptr(), n_tables, table_log, tables.data_ptr(),
-                                               status.data_ptr() if status is not None else None,
-                                               _stream_ptr(torch, device)), "anszp_build_tables_device")
+    tables = torch.empty(table_words(n_tables, table_log), dtype=torch.int32, device=device)
+    _enqueue("anszp_build_tables_device", lib().anszp_build_tables_device, device, freqs_dev.data_ptr(), n_tables, table_log,
+             tables.data_ptr(), status.data_ptr() if status is not None else None)
     return tables
 
 
@@ -350,13 +390,10 @@ VARIANT_AUTO, VARIANT_STEPWISE, VARIANT_MERGED, VARIANT_STEPWISE_SHARED, VARIANT
 
 def decode_raw(args: DecodeArgs, device="cuda:0", variant: Optional[int] = None):
     """anszp_decode (or anszp_decode_variant) on torch's current stream of `device`."""
-    torch = _torch()
-    with torch.cuda.device(device):
-        if variant is None:
-            _check(lib().anszp_decode(C.byref(args), _stream_ptr(torch, device)), "anszp_decode")
-        else:
-            _check(lib().anszp_decode_variant(C.byref(args), variant, _stream_ptr(torch, device)),
-                   "anszp_decode_variant")
+    if variant is None:
+        _enqueue("anszp_decode", lib().anszp_decode, device, C.byref(args))
+    else:
+        _enqueue("anszp_decode_variant", lib().anszp_decode_variant, device, C.byref(args), variant)
 
 
 def plan_bytes(n_chunks: int) -> int:
@@ -374,16 +411,12 @@ def plan_decode(args: DecodeArgs, device="cuda:0"):
 
 def decode_planned_raw(args: DecodeArgs, plan, device="cuda:0"):
     """anszp_decode_planned on torch's current stream of `device`."""
-    torch = _torch()
-    with torch.cuda.device(device):
-        _check(lib().anszp_decode_planned(C.byref(args), plan.data_ptr(), plan.numel(), _stream_ptr(torch, device)), "anszp_decode_planned")
+    _enqueue("anszp_decode_planned", lib().anszp_decode_planned, device, C.byref(args), plan.data_ptr(), plan.numel())
 
 
 def decode_static_plan_raw(args: DecodeArgs, replan: bool, device="cuda:0"):
     """anszp_decode_static_plan on torch's current stream of `device`."""
-    torch = _torch()
-    with torch.cuda.device(device):
-        _check(lib().anszp_decode_static_plan(C.byref(args), 1 if replan else 0, _stream_ptr(torch, device)), "anszp_decode_static_plan")
+    _enqueue("anszp_decode_static_plan", lib().anszp_decode_static_plan, device, C.byref(args), 1 if replan else 0)
 
 
 LOOKAHEAD_WINDOW_WORDS = 11096     # stream words of one chunk the look-ahead kernel can hold on chip (a chunk that has a workgroup to itself)
@@ -429,15 +462,14 @@ def dequant_zp(symbols, zero_point: int, scale: float, out_dtype: str = "bf16", 
     n = symbols.numel()
     dev = symbols.device
     out = torch.empty(max(n, 8), dtype=getattr(torch, _TORCH_OUT[out_dtype]), device=dev)
-    lay = np.zeros(1, dtype=LAYER_DTYPE)
-    lay[0] = (scale, zero_point, 8, channel_len, 0, 0)
-    n_sc = 0 if channel_scales is None else channel_scales.numel()
-    with torch.cuda.device(dev):
-        _check(lib().anszp_dequant_zp(symbols.data_ptr(), n, lay.ctypes.data,
-                                      channel_scales.data_ptr() if channel_scales is not None else None, n_sc,
-                                      out.data_ptr(), OUT_CODES[out_dtype], _stream_ptr(torch, dev)),
-               "anszp_dequant_zp")
-    return out[:n]
+    zero_point, channel_len = int(zero_point), int(channel_len)
+    if not (0 <= zero_point < 1 << 32 and 0 <= channel_len < 1 << 32):
+        raise OverflowError("zero_point and channel_len are unsigned 32-bit numbers")
+    lay = _LayerArg(scale, zero_point, 8, channel_len, 0, 0)
+    scales, n_sc = (None, 0) if channel_scales is None else (channel_scales.data_ptr(), channel_scales.numel())
+    _enqueue("anszp_dequant_zp", lib().anszp_dequant_zp, dev, symbols.data_ptr(), n, C.byref(lay), scales, n_sc, out.data_ptr(),
+             OUT_CODES[out_dtype])
+    return out if n >= 8 else out[:n]
 
 
 def bits_of(t) -> np.ndarray:
@@ -542,9 +574,7 @@ def conv_args(d: DeviceContainer, layer: int, first_chunk: int, rows_per_chunk: 
 
 def conv_fused_raw(args: ConvArgs, device="cuda:0"):
     """anszp_conv_fused on torch's current stream of `device`."""
-    torch = _torch()
-    with torch.cuda.device(device):
-        _check(lib().anszp_conv_fused(C.byref(args), _stream_ptr(torch, device)), "anszp_conv_fused")
+    _enqueue("anszp_conv_fused", lib().anszp_conv_fused, device, C.byref(args))
 
 
 def conv_fused(d: DeviceContainer, layer: int, first_chunk: int, rows_per_chunk: int, x, shape: tuple, stride: int,
@@ -581,25 +611,32 @@ def pack_layer_device(symbols_dev, freqs_dev, table_log: int, n_streams: int, ch
     chunks = torch.zeros(max(nc.value, 1) * CHUNK_DTYPE.itemsize, dtype=torch.uint8, device=dev)
     hdr = torch.zeros(max(nc.value * n_streams, 4), dtype=torch.int32, device=dev)
     payload = torch.full((max(cap, 4),), -1, dtype=torch.int32, device=dev)
-    used = torch.zeros(1, dtype=torch.int64, device=dev)
+    used = torch.empty(1, dtype=torch.int64, device=dev)
     status = torch.zeros(2, dtype=torch.int32, device=dev)
-    with torch.cuda.device(dev):
-        _check(lib().anszp_pack_layer_device(symbols_dev.data_ptr(), n, freqs_dev.data_ptr(), table_log, n_streams, chunk_size,
-                                             layer_id, out_offset, payload_word_offset, stream_offset, chunks.data_ptr(),
-                                             hdr.data_ptr(), payload.data_ptr(), cap, used.data_ptr(), status.data_ptr(),
-                                             _stream_ptr(torch, dev)), "anszp_pack_layer_device")
+    _enqueue("anszp_pack_layer_device", lib().anszp_pack_layer_device, dev, symbols_dev.data_ptr(), n, freqs_dev.data_ptr(), table_log,
+             n_streams, chunk_size, layer_id, out_offset, payload_word_offset, stream_offset, chunks.data_ptr(),
+             hdr.data_ptr(), payload.data_ptr(), cap, used.data_ptr(), status.data_ptr())
     return chunks, hdr, payload, used, status
 
 
 def pack_jobs(layer_sizes: Sequence[int], chunk_sizes: Sequence[int]) -> np.ndarray:
     """The anszp_pack_job_t array of a set of layers stored one after the other."""
     jobs = np.zeros(len(layer_sizes), dtype=JOB_DTYPE)
-    first = chunk = 0
-    for i, (n, cs) in enumerate(zip(layer_sizes, chunk_sizes)):
-        jobs[i] = (first, n, cs, chunk, (0, 0))
-        first += n
-        chunk += (n + cs - 1) // cs
+    if len(jobs) == 0:
+        return jobs
+    counts = [(n + cs - 1) // cs for n, cs in zip(layer_sizes, chunk_sizes)]
+    if min(layer_sizes) < 0 or min(chunk_sizes) < 0 or sum(layer_sizes) >= 1 << 63 or max(max(chunk_sizes), sum(counts)) >= 1 << 32:
+        raise OverflowError("layer sizes are unsigned 64-bit numbers, chunk sizes and chunk counts unsigned 32-bit ones")
+    jobs["n_symbols"] = layer_sizes
+    jobs["chunk_size"] = chunk_sizes
+    jobs["first_symbol"][1:] = np.cumsum(jobs["n_symbols"])[:-1]
+    jobs["first_chunk"][1:] = np.cumsum(counts)[:-1]
     return jobs
+
+
+def _pack_bound_words(layer_sizes, chunk_sizes, table_log: int, n_streams: int) -> int:
+    """The payload words anszp_pack_bound gives for each layer, added up."""
+    return sum((n * table_log + 31) // 32 + (n + c - 1) // c * (n_streams + 3) for n, c in zip(layer_sizes, chunk_sizes))
 
 
 def pack_layers_device(symbols_dev, layer_sizes: Sequence[int], freqs_dev, table_log: int, n_streams: int, chunk_size,
@@ -612,25 +649,30 @@ def pack_layers_device(symbols_dev, layer_sizes: Sequence[int], freqs_dev, table
     sizes = [int(n) for n in layer_sizes]
     css = [int(chunk_size)] * len(sizes) if np.isscalar(chunk_size) else [int(c) for c in chunk_size]
     jobs = pack_jobs(sizes, css)
-    n_chunks = int(sum((n + c - 1) // c for n, c in zip(sizes, css)))
-    bound = 0
-    for n, c in zip(sizes, css):
+    n_chunks = sum((n + c - 1) // c for n, c in zip(sizes, css))
+    if sizes:                                             # (refuses what the arguments' ranges refuse)
         nc, b = C.c_uint64(), C.c_uint64()
-        _check(lib().anszp_pack_bound(n, table_log, n_streams, c, C.byref(nc), C.byref(b)), "anszp_pack_bound")
-        bound += b.value
+        _check(lib().anszp_pack_bound(sizes[0], table_log, n_streams, min(css), C.byref(nc), C.byref(b)), "anszp_pack_bound")
+    bound = _pack_bound_words(sizes, css, table_log, n_streams)
     cap = bound if payload_cap_words is None else payload_cap_words
-    jobs_dev = torch.from_numpy(jobs.view(np.uint8).copy()).to(dev)
+    # (through pinned memory, which torch keeps until the copy is done: a copy from pageable memory would wait for the stream)
+    staging = torch.empty(max(jobs.nbytes, 1), dtype=torch.uint8, pin_memory=True)
+    staging.numpy()[:jobs.nbytes] = jobs.view(np.uint8)
+    jobs_dev = staging.to(dev, non_blocking=True)
     if out is None:
         chunks = torch.zeros(max(n_chunks, 1) * CHUNK_DTYPE.itemsize, dtype=torch.uint8, device=dev)
         hdr = torch.zeros(max(n_chunks * n_streams, 4), dtype=torch.int32, device=dev)
         payload = torch.full((max(cap, 4),), -1, dtype=torch.int32, device=dev)
-        used = torch.zeros(1, dtype=torch.int64, device=dev)
+        used = torch.empty(1, dtype=torch.int64, device=dev)
         status = torch.zeros(2, dtype=torch.int32, device=dev)
     else:
         chunks, hdr, payload, used, status = out
-    with torch.cuda.device(dev):
-        _check(lib().anszp_pack_layers_device(symbols_dev.data_ptr(), jobs_dev.data_ptr(), len(sizes), n_chunks, freqs_dev.data_ptr(),
-                                              table_log, n_streams, chunks.data_ptr(), hdr.data_ptr(), payload.data_ptr(), cap,
-                                              used.data_ptr(), status.data_ptr(), _stream_ptr(torch, dev)), "anszp_pack_layers_device")
-        torch.cuda.current_stream(dev).synchronize()      # (jobs_dev must outlive the launches)
+    _enqueue("anszp_pack_layers_device", lib().anszp_pack_layers_device, dev, symbols_dev.data_ptr(), jobs_dev.data_ptr(), len(sizes),
+             n_chunks, freqs_dev.data_ptr(), table_log, n_streams, chunks.data_ptr(), hdr.data_ptr(), payload.data_ptr(), cap,
+             used.data_ptr(), status.data_ptr())
+    # The call returns before the GPU is done.  Its tensors may come from another stream: their memory is not handed out
+    # again before this stream has got here.
+    stream = torch.cuda.current_stream(dev)
+    for t in (symbols_dev, freqs_dev) if out is None else (symbols_dev, freqs_dev, *out):
+        t.record_stream(stream)
     return chunks, hdr, payload, used, status
