@@ -1629,23 +1629,28 @@ __device__ __forceinline__ void decode_lookahead(const DecodeParams& p) {
             uint32_t over_v, next_a, next_b;
             uint2 logged_next;                            // blocks logged, the first expanding wavefront's next block
             uint32_t next_1;
-            asm volatile(                                // the flag first, the positions last
+            asm volatile(                                // the flag first, the positions before the blocks they are those of
                 "ds_read_b32 %[ov], %[ctla] offset:12\n"
-                "ds_read2_b32 %[ln], %[ctla] offset1:1\n"
-                "ds_read_b32 %[n1], %[ctla] offset:8\n"
                 "ds_read_b32 %[na], %[pa]\n"
                 "ds_read_b32 %[nb], %[pa] offset:256\n"
+                "ds_read2_b32 %[ln], %[ctla] offset1:1\n"
+                "ds_read_b32 %[n1], %[ctla] offset:8\n"
                 "s_waitcnt lgkmcnt(0)\n"
                 : [ov] "=&v"(over_v), [ln] "=&v"(logged_next), [n1] "=&v"(next_1), [na] "=&v"(next_a), [nb] "=&v"(next_b)
                 : [ctla] "v"(pipe_off + kCtlOff), [pa] "v"(pipe_off + kProgOff + lane * 4u)
                 : "memory");
             static_assert(kExpanders == 2u && kWave * 4u == 256u, "two rows of positions, 256 bytes apart");
             // A block is expanded once the wavefront whose turn it was has moved past it: every block below both
-            // wavefronts' next one is, and a lane's position after the last of those is the smaller of the two
-            // rows (positions only grow).  Once no more blocks will be logged and all have been expanded, every
-            // stream is complete (the row of the wavefront that did not expand the last block stays behind).
-            const bool last_pass = uniform(over_v) && uniform(logged_next.x) <= min(uniform(logged_next.y), uniform(next_1));
-            const uint32_t next = last_pass ? 0xFFFFFFFFu : min(next_a, next_b);
+            // wavefronts' next one is.  Where those are neighbours, the wavefront with the later one expanded the last of
+            // them, and its row, written behind its number and read before it, holds no more than that block (positions only grow).  Where it has
+            // run further ahead, a lane's position after the last block that is certainly expanded is the smaller of
+            // the two rows.  (The smaller alone is a block late, and a ring of two reaches of a block then waits for itself:
+            // one block can take every lane as far as the ring lets it.)  Once no more blocks will be logged and all have
+            // been expanded, every stream is complete (the row of the wavefront that did not expand the last block stays behind).
+            const uint32_t block_a = uniform(logged_next.y), block_b = uniform(next_1);
+            const bool last_pass = uniform(over_v) && uniform(logged_next.x) <= min(block_a, block_b);
+            const uint32_t newest = block_a > block_b ? next_a : next_b, lesser = min(next_a, next_b);
+            const uint32_t next = last_pass ? 0xFFFFFFFFu : max(block_a, block_b) - min(block_a, block_b) == 1u ? newest : lesser;
             const uint32_t before = mine;
             while (mine + kSlab <= n && __ballot(next < mine + kSlab) == 0) {
                 store_slab(mine);
@@ -1748,10 +1753,11 @@ __device__ __forceinline__ void decode_lookahead(const DecodeParams& p) {
                 }
             }
             block += kExpanders;
-            // publish the lanes' positions, then the next block, issued after the ring writes above (the slot may
-            // be logged over from here on: what follows works on the registers)
-            asm volatile("ds_write_b32 %[pa], %[ne]\n"
-                         "ds_write_b32 %[nxa], %[nx]\n"
+            // publish the next block, then the lanes' positions (who reads them in the other order finds positions no newer
+            // than the block), issued after the ring writes above (the slot may be logged over from here on: what follows works on
+            // the registers)
+            asm volatile("ds_write_b32 %[nxa], %[nx]\n"
+                         "ds_write_b32 %[pa], %[ne]\n"
                          :: [pa] "v"(pipe_off + kProgOff + sub * (kWave * 4u) + lane * 4u), [ne] "v"(ne),
                             [nxa] "v"(pipe_off + kCtlOff + 4u * (kNext0 + sub)), [nx] "v"(block)
                          : "memory");

@@ -329,3 +329,17 @@ def test_corruption_is_flagged_not_fatal(orc, p0):
     h = copy.deepcopy(good); h.chunks["n_symbols"][2] += 1
     st = status_of(h)
     assert st[0] != 0 and st[1] >= 1
+
+
+@pytest.mark.parametrize("p0", [0.9, 0.99])
+@pytest.mark.parametrize("n_streams", [57, 64])
+def test_pairs_of_chunks_whose_entries_nearly_all_stand_for_eight_symbols(orc, n_streams, p0):
+    """Small tables and more chunks than workgroups: pairs, whose rings hold two reaches of a block.  One block then takes
+    every lane as far as the ring lets it, and the next can only follow when what that block left has been stored."""
+    w = W.tiny(seed=8, n=700 * 8192, bitwidth=3, n_streams=n_streams, chunk_size=8192, table_log=10, p0=p0)
+    c = oracle_encode(orc, w)
+    _, expect = oracle_expected(orc, c, w)
+    d = B.to_device(host_from_oracle(c, w))
+    out = B.decode(d, variant=B.VARIANT_MERGED)
+    assert d.read_status() == (0, 0)
+    assert np.array_equal(B.bits_of(out)[:w.numel], expect)
