@@ -24,6 +24,8 @@
 //                          of the ring and store them, 16 bytes per lane.  A workgroup serves one
 //                          chunk or two chunks of one layer; which, and in what order the
 //                          workgroups take them, is found per launch or read from a prepared plan.
+//   decode_waves           many short chunks: a wavefront per chunk, the table shared by a workgroup that
+//                          takes a run of them (anszp_waves.h).
 //   decode_split           one stream per chunk, long enough: the stream cut into segments that a workgroup's
 //                          wavefronts walk side by side from guessed states (anszp_split.h).
 // The look-ahead path needs the chunk's words to fit its LDS window; other chunks take the step-wise path
@@ -1104,6 +1106,7 @@ struct Flusher {
 };
 
 #include "anszp_split.h"
+#include "anszp_waves.h"
 
 // ---------------------------------------------------------------------------------------------
 // Which chunks a workgroup of the look-ahead kernel decodes.  A workgroup that has a CU to itself decodes a
@@ -2194,8 +2197,10 @@ __global__ __launch_bounds__(256) void dequant_runs_kernel(const uint8_t* sym, u
 
 template <int OUT>
 void launch_decode(const DecodeParams& p, uint32_t n_chunks, bool per_channel, bool stepwise, bool shared, bool streaming,
-                   bool small, bool byte_table, bool split, hipStream_t s) {
-    if (split) {
+                   bool small, bool byte_table, bool split, const WavesShape& waves, hipStream_t s) {
+    if (waves.waves) {
+        hipLaunchKernelGGL(decode_waves<OUT>, dim3(std::min(n_chunks, device_cus())), dim3(waves.waves * kWave), 0, s, p, waves.own);
+    } else if (split) {
         hipLaunchKernelGGL(decode_split<OUT>, dim3(n_chunks), dim3(kSplitThreads), 0, s, p);
     } else if (byte_table) {
         hipLaunchKernelGGL(decode_byte_table<OUT>, dim3((n_chunks + kByteWaves - 1) / kByteWaves), dim3(kByteWaves * kWave), 0, s, p);
@@ -2222,7 +2227,7 @@ void launch_decode(const DecodeParams& p, uint32_t n_chunks, bool per_channel, b
 }
 
 // What a launch would be: checks of the arguments, the kernel's parameters, which kernel.
-struct LaunchChoice { bool stepwise, byte_table, shared, streaming, small, per_channel, split; };
+struct LaunchChoice { bool stepwise, byte_table, shared, streaming, small, per_channel, split; WavesShape waves; };
 
 int choose_launch(const anszp_decode_args_t* a, int mode, DecodeParams& p, LaunchChoice& k);
 
@@ -2238,7 +2243,7 @@ int decode_impl(const anszp_decode_args_t* a, int mode, void* hip_stream, uint32
     if (rc != ANSZP_OK) return rc;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const uint32_t nc = static_cast<uint32_t>(a->n_chunks);
-    const bool lookahead = !k.stepwise && !k.byte_table && !k.split;
+    const bool lookahead = !k.stepwise && !k.byte_table && !k.split && !k.waves.waves;
     if (plan || plan_only) {
         if (!plan) return ANSZP_E_NULL;
         if ((reinterpret_cast<uintptr_t>(plan) & 15) || plan_bytes < 2u * uint64_t(mapped_workgroups(nc)) * sizeof(PlanRecord)) return ANSZP_E_RANGE;
@@ -2256,9 +2261,9 @@ int decode_impl(const anszp_decode_args_t* a, int mode, void* hip_stream, uint32
     }
     p.plan = lookahead ? plan : nullptr;
     switch (a->out_dtype) {
-        case ANSZP_OUT_U8: launch_decode<ANSZP_OUT_U8>(p, nc, k.per_channel, k.stepwise, k.shared, k.streaming, k.small, k.byte_table, k.split, s); break;
-        case ANSZP_OUT_F32: launch_decode<ANSZP_OUT_F32>(p, nc, k.per_channel, k.stepwise, k.shared, k.streaming, k.small, k.byte_table, k.split, s); break;
-        default: launch_decode<ANSZP_OUT_BF16>(p, nc, k.per_channel, k.stepwise, k.shared, k.streaming, k.small, k.byte_table, k.split, s); break;
+        case ANSZP_OUT_U8: launch_decode<ANSZP_OUT_U8>(p, nc, k.per_channel, k.stepwise, k.shared, k.streaming, k.small, k.byte_table, k.split, k.waves, s); break;
+        case ANSZP_OUT_F32: launch_decode<ANSZP_OUT_F32>(p, nc, k.per_channel, k.stepwise, k.shared, k.streaming, k.small, k.byte_table, k.split, k.waves, s); break;
+        default: launch_decode<ANSZP_OUT_BF16>(p, nc, k.per_channel, k.stepwise, k.shared, k.streaming, k.small, k.byte_table, k.split, k.waves, s); break;
     }
     return hipGetLastError() == hipSuccess ? ANSZP_OK : ANSZP_E_HIP;
 }
@@ -2305,6 +2310,19 @@ int choose_launch(const anszp_decode_args_t* a, int mode, DecodeParams& p, Launc
               mean_words <= (a->n_chunks == 1 ? kSplitWords : LargeLds::kPayloadWords) &&
               (a->n_chunks <= p.n_cus || bits >= 16384u);
     if (k.split) k.stepwise = k.streaming = false;
+    // More chunks than the look-ahead kernel decodes at once (two per workgroup): a wavefront per chunk and a table staged
+    // once per workgroup and layer, where the chunks' words fit and a layer has chunks enough for a workgroup's share to be of
+    // few layers (24 a layer where only eight wavefronts fit a CU: 130 layers of 12 chunks of 1,600 words 70 us, 84 this way).
+    // From two to four chunks per CU only short ones: 540 to 900 chunks of 367 words, 2^12 states 17 -> 13 us, of 570
+    // words 20 either way; with the small geometry 115 words 10 -> 8, 288 words 11.2 to 12.9 and 11.7 to 12.0, 367 words 12 to 16
+    // and 15.
+    k.waves = WavesShape{0u, 0u};
+    const uint64_t per_layer = a->n_chunks / a->n_tables, cus = p.n_cus;
+    if (mode == 0 && !k.stepwise && !k.split && per_layer >= 8u &&
+        (a->n_chunks > 4u * cus || (a->n_chunks > 2u * cus && mean_words <= (k.small ? 256u : 450u)))) {
+        k.waves = waves_shape(a->table_log, mean_words);
+        if (k.waves.waves == 8u && per_layer < 24u) k.waves.waves = 0u;
+    }
     return ANSZP_OK;
 }
 

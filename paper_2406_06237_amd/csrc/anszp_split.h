@@ -28,6 +28,8 @@
 #ifndef ANSZP_SPLIT_H
 #define ANSZP_SPLIT_H
 
+#include "anszp_walk.h"
+
 constexpr uint32_t kSplitThreads = 1024u;
 constexpr uint32_t kSplitMaxCuts = 64u;
 constexpr uint32_t kSplitParts = 4u;                      // parts of a segment that are written side by side
@@ -50,76 +52,6 @@ struct SplitLds {
 // A node (eleven words, an array of them behind SplitLds): its place and cut, then what its walk found: the symbols, where it
 // ended, the node that is (or kSplitUnknown, kSplitNone), and place and symbols at the ends of its parts but the last.
 enum { kNodePlace, kNodeCut, kNodeCount, kNodeEnd, kNodeLink, kNodePartPlace, kNodePartCount = kNodePartPlace + kSplitParts - 1, kNodeWords = kNodePartCount + kSplitParts - 1 };
-
-// Look-ups of every lane from the entry at LDS address `at` with the stream at bit `q` on.  Entries as staged (see
-// below): low word 31 - T | T << 8 | symbol << 16 | c << 24, high word the address of entry number `base`; T + 1 bits
-// choose the next entry, c symbols are counted.  q is 31 more than the LDS bit address of the next bit (words first bit
-// on top: then ~q is what v_alignbit shifts two words by to bring it to the top).  A lane stops before the first look-up
-// at which q >= q_end (WRITE: n >= n_end) holds; every four look-ups the other bound is looked at too.  WRITE: n is an
-// address in LDS, and the entry's last symbol goes to n after c has been added to it.
-// Bound by one LDS round trip per look-up where a SIMD has one wavefront (two words serve two look-ups, and what does
-// not stand between an entry's arrival and the next read is issued while that is under way: 8.5 vector instructions per
-// look-up in all), by those instructions with four.  As the compiler had it, 20 instructions with the loads at the loop's
-// head, a look-up took twice as long.
-template <bool WRITE>
-__device__ __forceinline__ void split_walk(uint32_t& at, uint32_t& q, uint32_t& n, uint32_t q_end, uint32_t n_end) {
-#define ANSZP_SPLIT_ADD(TO, E, BYTE) "v_add_u32_sdwa " TO ", " TO ", " E " dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:" BYTE "\n"
-#define ANSZP_SPLIT_NEXT(ELO, EHI, FB)                                                                  \
-        "v_lshrrev_b32 v46, " ELO ", v47\n"                                                             \
-        "v_lshl_add_u32 %[at], v46, 3, " EHI "\n"                                                       \
-        "ds_read_b64 " FB ", %[at]\n"                                                                   \
-        ANSZP_SPLIT_ADD("%[q]", ELO, "BYTE_1")
-#define ANSZP_SPLIT_WORDS                                                                               \
-        "v_lshrrev_b32 v49, 3, %[q]\n"                                                                  \
-        "v_and_b32 v49, 0x1ffffffc, v49\n"                                                              \
-        "ds_read2_b32 v[44:45], v49 offset1:1\n"                                                        \
-        "v_not_b32 v48, %[q]\n"
-    // two look-ups from one window; the entry in v[40:41] at the start and the end
-#define ANSZP_SPLIT_TWO(EMIT_A, EMIT_B, WAIT, STOP)                                                      \
-        "v_alignbit_b32 v47, v44, v45, v48\n"                                                           \
-        ANSZP_SPLIT_NEXT("v40", "v41", "v[42:43]")                                                      \
-        ANSZP_SPLIT_ADD("%[n]", "v40", "BYTE_3")                                                        \
-        EMIT_A                                                                                          \
-        "v_lshlrev_b32_sdwa v47, v40, v47 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1 src1_sel:DWORD\n" \
-        STOP                                                                                            \
-        "s_waitcnt lgkmcnt(" WAIT ")\n"                                                                 \
-        ANSZP_SPLIT_NEXT("v42", "v43", "v[40:41]")                                                      \
-        ANSZP_SPLIT_WORDS                                                                               \
-        ANSZP_SPLIT_ADD("%[n]", "v42", "BYTE_3")                                                        \
-        EMIT_B                                                                                          \
-        STOP                                                                                            \
-        "s_waitcnt lgkmcnt(" WAIT ")\n"
-#define ANSZP_SPLIT_WALK(EMIT_A, EMIT_B, WAIT, STOP, BOUND)                                              \
-    asm volatile(                                                                                       \
-        "s_mov_b64 s[40:41], exec\n"                                                                    \
-        "v_cmpx_gt_u32 vcc, %[qe], %[q]\n"                                                              \
-        "v_cmpx_gt_u32 vcc, %[ne], %[n]\n"                                                              \
-        "s_cbranch_execz 2f\n"                                                                          \
-        "ds_read_b64 v[40:41], %[at]\n"                                                                 \
-        ANSZP_SPLIT_WORDS                                                                               \
-        "s_waitcnt lgkmcnt(0)\n"                                                                        \
-        "1:\n"                                                                                          \
-        ANSZP_SPLIT_TWO(EMIT_A, EMIT_B, WAIT, STOP)                                                     \
-        ANSZP_SPLIT_TWO(EMIT_A, EMIT_B, WAIT, STOP)                                                     \
-        BOUND                                                                                           \
-        "s_cbranch_execnz 1b\n"                                                                         \
-        "2:\n"                                                                                          \
-        "s_mov_b64 exec, s[40:41]\n"                                                                    \
-        "s_waitcnt lgkmcnt(0)\n"                                                                        \
-        : [at] "+v"(at), [q] "+v"(q), [n] "+v"(n)                                                       \
-        : [qe] "v"(q_end), [ne] "v"(n_end)                                                              \
-        : "memory", "vcc", "scc", "s40", "s41", "v40", "v41", "v42", "v43", "v44", "v45", "v46", "v47", "v48", "v49")
-    // (the write follows the entry's read and the words' read: with one access more in flight they have arrived)
-    if constexpr (WRITE)
-        ANSZP_SPLIT_WALK("ds_write_b8_d16_hi %[n], v40\n", "ds_write_b8_d16_hi %[n], v42\n", "1", "v_cmpx_gt_u32 vcc, %[ne], %[n]\n", "v_cmpx_gt_u32 vcc, %[qe], %[q]\n");
-    else
-        ANSZP_SPLIT_WALK("", "", "0", "v_cmpx_gt_u32 vcc, %[qe], %[q]\n", "v_cmpx_gt_u32 vcc, %[ne], %[n]\n");
-#undef ANSZP_SPLIT_WALK
-#undef ANSZP_SPLIT_TWO
-#undef ANSZP_SPLIT_WORDS
-#undef ANSZP_SPLIT_NEXT
-#undef ANSZP_SPLIT_ADD
-}
 
 template <int OUT>
 __global__ __launch_bounds__(kSplitThreads) void decode_split(DecodeParams p) {
@@ -159,13 +91,8 @@ __global__ __launch_bounds__(kSplitThreads) void decode_split(DecodeParams p) {
     const uint32_t dominant = src[table_triples_offset(p.table_log) + L - 1u] >> 24;
     {
         const uint4* const entries = reinterpret_cast<const uint4*>(src + table_lookahead_offset(p.table_log));
-        auto low = [](uint32_t e) {
-            const uint32_t T = (e >> 24) & 15u, symbols = ((e >> 28) & 7u) + 1u;
-            return (31u - T) | T << 8 | (e & 0xFF0000u) | symbols << 24;
-        };
         for (uint32_t i = tid; i < L; i += kSplitThreads) {
-            const uint4 e = entries[i];
-            reinterpret_cast<uint4*>(lds)[i] = make_uint4(low(e.x), e.y + table_at, low(e.z), e.w + table_at);
+            reinterpret_cast<uint4*>(lds)[i] = walk_entry_pair(entries[i], table_at);
         }
         const uint32_t* const words = p.payload + c.payload_offset;
         uint32_t* const to = reinterpret_cast<uint32_t*>(lds + words_off);
@@ -199,7 +126,7 @@ __global__ __launch_bounds__(kSplitThreads) void decode_split(DecodeParams p) {
         if (g != 0u || r == 0u) {
             uint32_t at = at_of(g == 0u ? first_place : 2u * (((2u * r + 1u) * L / (2u * per_group)) & (L - 1u)) + next_bit(g * seg));
             uint32_t q = q0 + g * seg, count = 0;
-            split_walk<false>(at, q, count, q0 + (g + 1u) * seg, len);
+            walk_entries<kWalkCount>(at, q, count, q0 + (g + 1u) * seg, len);
             place = place_of(at, q);
         }
         // the different ones among the group's (a group is a part of a wavefront, which reads before it writes)
@@ -245,7 +172,7 @@ __global__ __launch_bounds__(kSplitThreads) void decode_split(DecodeParams p) {
             uint32_t at = at_of(at_node(kNodePlace, id)), q = q_of(at_node(kNodePlace, id)), count = 0;
 #pragma unroll 1
             for (uint32_t m = 0; m < kSplitParts; ++m) {
-                split_walk<false>(at, q, count, q0 + cut * seg + (m + 1u) * seg / kSplitParts, len);
+                walk_entries<kWalkCount>(at, q, count, q0 + cut * seg + (m + 1u) * seg / kSplitParts, len);
                 if (m + 1u < kSplitParts) {
                     at_node(kNodePartPlace + m, id) = place_of(at, q);
                     at_node(kNodePartCount + m, id) = count;
@@ -338,7 +265,7 @@ __global__ __launch_bounds__(kSplitThreads) void decode_split(DecodeParams p) {
         if (count < until && count + skew < first + end) {
             const uint32_t to = lds_address(buf) + skew - first - 1u;      // the symbol that ends a look-up is number count - 1 after it
             uint32_t address = to + count;
-            split_walk<true>(at, q, address, q0 + total + 1u, to + min(until, first + end - skew));
+            walk_entries<kWalkWrite>(at, q, address, q0 + total + 1u, to + min(until, first + end - skew));
             count = address - to;
         }
         __syncthreads();
