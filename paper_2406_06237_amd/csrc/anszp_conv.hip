@@ -18,7 +18,7 @@
 // wavefronts decode the chunks that hold those weight rows, one lane per stream (Sec. II-A, III-B),
 // through the table's look-ahead entries (one look-up per run of up to eight symbols) into a
 // [16 * MR][K] panel in LDS: symbols as bytes, or, where they fit, the bf16 values q - z.  Phase 2, by
-// kind of layer: input channels that are multiples of 32 under 1 x 1 kernels without padding or kernels
+// kind of layer: input channels that are multiples of 8 under 1 x 1 kernels without padding or kernels
 // three taps wide (nearly all layers of a network) have conv_sliced_kernel, which also slices the
 // reduction over the wavefronts; conv_fused_kernel has the others (see the enumeration in front of it).
 // fp32 accumulators; one store of four consecutive output channels per lane, row tile and column tile.
@@ -943,8 +943,12 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
     }
 }
 
-// The convolution of layers whose input channels are a multiple of 32 and whose kernels are 1 x 1 without padding
-// (kPoint) or three taps wide (kRow; stride 1: kShift): nearly all of a network's.
+// The convolution of layers whose input channels are a multiple of 8 and whose kernels are 1 x 1 without padding
+// (kPoint) or three taps wide (kRow; stride 1: kShift): nearly all of a network's.  TAIL: the channels are no multiple of 32,
+// so that the last unit of a kernel row has fewer (a kernel of its own, because the condition on every load is worth a few
+// per cent).  Such layers were left to the loops without slices and rings before: 28 drawn calls of 72 to 1,624 channels 1.0 to
+// 4.2 times as fast (3 x 3 x 496 on two 23 x 23 images 57 -> 17 us, 1 x 1 from 816 channels on one 47 x 47 image 46 -> 19), 8 to 24
+// channels, where most of a unit is empty, 1.02 to 1.8.
 //
 // Phase 2: a step is a kernel tap and 32 input channels, a unit the steps of a kernel row with the same 32 channels.
 // kRow asks for the row's three taps together: they read the same pixels shifted by one, or alternate halves of the
@@ -998,7 +1002,7 @@ __device__ __forceinline__ words4 neighbours(const words4& tile, const words4& b
     return v;
 }
 
-template <uint32_t MR, bool P16, uint32_t MODE, uint32_t QT>
+template <uint32_t MR, bool P16, uint32_t MODE, uint32_t QT, bool TAIL>
 __global__ __launch_bounds__(kThreads) void conv_sliced_kernel(ConvParams p) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     constexpr uint32_t NS = MODE == kPoint ? 1u : 3u;             // steps of a unit
@@ -1078,8 +1082,11 @@ __global__ __launch_bounds__(kThreads) void conv_sliced_kernel(ConvParams p) {
 
     const uint32_t a_at = lds_address(lds) + (P16 ? p.panel_off : 0u) + (col * p.row_stride + 8u * kg) * 2u;
     const uint32_t tile_stride = kRows * p.row_stride * 2u;
-    const uint32_t blocks = p.cin / 32u, units = (MODE != kPoint ? p.kh : 1u) * blocks;
+    const uint32_t blocks = TAIL ? (p.cin + 31u) / 32u : p.cin / 32u, units = (MODE != kPoint ? p.kh : 1u) * blocks;
     const uint32_t u_begin = wk * p.slice_units, n = min(p.slice_units, units - min(u_begin, units));
+    // TAIL: the last block has fewer than 32 channels; the lanes of those that are missing read outside there (the weights they
+    // meet are the next tap's or the row's padding: finite)
+    [[maybe_unused]] const bool beyond_tail = 8u * kg >= p.cin % 32u;
     const uint32_t row0 = MODE != kPoint ? __umulhi(2u * u_begin, p.blocks_magic) >> p.blocks_shift : 0u;
     const __amdgpu_buffer_rsrc_t y_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, p.y_bytes, 0x00020000);
     const bool per_channel = lay.channel_len != 0;
@@ -1119,8 +1126,11 @@ __global__ __launch_bounds__(kThreads) void conv_sliced_kernel(ConvParams p) {
             const uint32_t at = asked < n ? cb * 8u * p.x_block : 0u;      // (an empty buffer's check must not overflow)
             // (what is outside stays beyond the buffer: no row is 2^31 bytes away)
             const uint32_t row_at = MODE == kPoint ? 0u : row * p.in_w * p.x_pixel * 2u;
+            [[maybe_unused]] const bool is_tail = TAIL && cb + 1u == blocks;
             auto in_row = [&](int32_t first_row, uint32_t where) {
-                return MODE == kPoint ? where : uint32_t(first_row + int32_t(row)) < p.in_h ? where + row_at : kOutside;
+                const uint32_t v = MODE == kPoint ? where : uint32_t(first_row + int32_t(row)) < p.in_h ? where + row_at : kOutside;
+                if constexpr (TAIL) return is_tail && beyond_tail ? kOutside : v;
+                return v;
             };
 #pragma unroll
             for (uint32_t q = 0; q < QT; ++q)
@@ -1167,7 +1177,7 @@ __global__ __launch_bounds__(kThreads) void conv_sliced_kernel(ConvParams p) {
             if constexpr (MODE != kPoint) {
                 const bool next_row = use_cb == blocks;
                 use_cb = next_row ? 0u : use_cb;
-                k_use += next_row ? 2u * p.cin : 0u;
+                k_use += next_row ? (TAIL ? NS * p.cin - 32u * blocks : 2u * p.cin) : 0u;
             }
         };
         uint32_t done = 0;
@@ -1223,39 +1233,44 @@ __global__ __launch_bounds__(kThreads) void conv_sliced_kernel(ConvParams p) {
     }
 }
 
-template <uint32_t MR, bool P16, uint32_t MODE>
+template <uint32_t MR, bool P16, uint32_t MODE, bool TAIL>
 void (*sliced_kernel(uint32_t qt))(ConvParams) {
     if constexpr (most_tiles(MR, MODE) == 4u) {
-        if (qt == 4u) return conv_sliced_kernel<MR, P16, MODE, 4>;
+        if (qt == 4u) return conv_sliced_kernel<MR, P16, MODE, 4, TAIL>;
     }
-    return qt == 3u ? conv_sliced_kernel<MR, P16, MODE, 3> : qt == 2u ? conv_sliced_kernel<MR, P16, MODE, 2> : conv_sliced_kernel<MR, P16, MODE, 1>;
+    return qt == 3u ? conv_sliced_kernel<MR, P16, MODE, 3, TAIL> : qt == 2u ? conv_sliced_kernel<MR, P16, MODE, 2, TAIL> : conv_sliced_kernel<MR, P16, MODE, 1, TAIL>;
 }
-template <uint32_t MR, bool P16>
+template <uint32_t MR, bool P16, bool TAIL>
 void (*sliced_kernel(uint32_t mode, uint32_t qt))(ConvParams) {
-    return mode == kPoint ? sliced_kernel<MR, P16, kPoint>(qt) : mode == kShift ? sliced_kernel<MR, P16, kShift>(qt) : sliced_kernel<MR, P16, kRow>(qt);
+    return mode == kPoint ? sliced_kernel<MR, P16, kPoint, TAIL>(qt) : mode == kShift ? sliced_kernel<MR, P16, kShift, TAIL>(qt) : sliced_kernel<MR, P16, kRow, TAIL>(qt);
+}
+template <bool TAIL>
+void (*sliced_kernel(uint32_t mr, bool p16, uint32_t mode, uint32_t qt))(ConvParams) {
+    return p16 ? (mr == 4 ? sliced_kernel<4, true, TAIL>(mode, qt) : mr == 2 ? sliced_kernel<2, true, TAIL>(mode, qt) : sliced_kernel<1, true, TAIL>(mode, qt))
+               : (mr == 4 ? sliced_kernel<4, false, TAIL>(mode, qt) : mr == 2 ? sliced_kernel<2, false, TAIL>(mode, qt) : sliced_kernel<1, false, TAIL>(mode, qt));
 }
 
-template <uint32_t MR, bool P16>
-bool allow_all_lds(uint32_t mode) {
-    for (uint32_t qt = 1; qt <= most_tiles(MR, mode); ++qt)
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(sliced_kernel<MR, P16>(mode, qt)), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
-            return false;
+template <bool TAIL>
+bool allow_all_lds() {
+    for (uint32_t mode = kPoint; mode <= kRow; ++mode)
+        for (const uint32_t mr : {1u, 2u, 4u})
+            for (uint32_t qt = 1; qt <= most_tiles(mr, mode); ++qt)
+                for (const bool p16 : {false, true})
+                    if (hipFuncSetAttribute(reinterpret_cast<const void*>(sliced_kernel<TAIL>(mr, p16, mode, qt)), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+                        return false;
     return true;
 }
 
 int launch_sliced(const ConvParams& p, uint32_t mr, bool p16, uint32_t mode, uint32_t qt, int device, uint32_t groups, uint32_t lds_bytes, hipStream_t s) {
-    void (*const kernel)(ConvParams) =
-        p16 ? (mr == 4 ? sliced_kernel<4, true>(mode, qt) : mr == 2 ? sliced_kernel<2, true>(mode, qt) : sliced_kernel<1, true>(mode, qt))
-            : (mr == 4 ? sliced_kernel<4, false>(mode, qt) : mr == 2 ? sliced_kernel<2, false>(mode, qt) : sliced_kernel<1, false>(mode, qt));
+    const bool tail = p.cin % 32u != 0u;
+    void (*const kernel)(ConvParams) = tail ? sliced_kernel<true>(mr, p16, mode, qt) : sliced_kernel<false>(mr, p16, mode, qt);
     // the kernels may use all of the CU's LDS: said for all of them by a device's first call, because which one a layer gets
     // depends on the batch too, and a call may be captured whose layer ran before with another batch (concurrent first callers
     // at worst both say it)
     static std::atomic<bool> allowed[64];
     if (device < 0 || device >= 64) return ANSZP_E_HIP;
     if (!allowed[device].load(std::memory_order_acquire)) {
-        for (uint32_t every = kPoint; every <= kRow; ++every)
-            if (!allow_all_lds<4, true>(every) || !allow_all_lds<2, true>(every) || !allow_all_lds<1, true>(every) ||
-                !allow_all_lds<4, false>(every) || !allow_all_lds<2, false>(every) || !allow_all_lds<1, false>(every)) return ANSZP_E_HIP;
+        if (!allow_all_lds<false>() || !allow_all_lds<true>()) return ANSZP_E_HIP;
         allowed[device].store(true, std::memory_order_release);
     }
     hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), std::max(lds_bytes, kLeastLds), s, p);
@@ -1273,7 +1288,7 @@ int conv_sliced(ConvParams p, const anszp_conv_args_t& a, uint32_t images, uint3
         m = uint32_t((1ull << (31 + shift)) / d + 1u);
     };
     magic(p.out_h, p.out_h_magic, p.out_h_shift);
-    magic(a.cin / 32u, p.blocks_magic, p.blocks_shift);
+    magic((a.cin + 31u) / 32u, p.blocks_magic, p.blocks_shift);
     for (uint32_t first = 0; first < a.batch; first += images) {
         const uint32_t n = std::min(images, a.batch - first);
         p.x = a.x + uint64_t(first) * p.x_image;
@@ -1368,7 +1383,7 @@ extern "C" int anszp_conv_fused(const anszp_conv_args_t* a, void* stream) {
     const uint32_t cus = device_cus(device);
     const bool generic = (a->cin % 8u) != 0;
     const bool pointwise = !generic && a->kh == 1 && a->kw == 1 && a->pad == 0;
-    if ((a->cin % 32u) == 0 && (pointwise || a->kw == 3)) {
+    if (!generic && (pointwise || a->kw == 3)) {
         // buffer offsets are 31 bits: as many images at a time as x and y of that size allow (all of them, but for very large calls)
         const uint64_t x_image = uint64_t(a->in_h) * a->in_w * a->cin, y_image = uint64_t(out_h) * out_w * a->cout;
         const uint64_t most = ((1ull << 31) - 1u) / std::max(2u * x_image, (p.y_bf16 ? 2u : 4u) * y_image);

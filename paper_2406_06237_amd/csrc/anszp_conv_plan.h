@@ -42,7 +42,7 @@ struct SlicedPlan {
 };
 inline SlicedPlan plan_sliced(const anszp_conv_args_t& a, uint32_t mode, uint32_t K, uint32_t row_stride, uint32_t n_tiles, uint32_t cus) {
     const uint32_t table_bytes = 16u << a.table_log, fixed = kStageBytes + table_bytes + 64u;
-    const uint32_t taps = mode == kPoint ? 1u : 3u, units = (mode == kPoint ? 1u : a.kh) * (a.cin / 32u);
+    const uint32_t taps = mode == kPoint ? 1u : 3u, units = (mode == kPoint ? 1u : a.kh) * ((a.cin + 31u) / 32u);
     SlicedPlan best;
     for (const uint32_t mr : {4u, 2u, 1u}) {
         if (a.cout % (kRows * mr)) continue;

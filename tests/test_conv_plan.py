@@ -56,12 +56,25 @@ int main() {
 """
 
 
-def test_plans_of_every_size(tmp_path):
+def _run(tmp_path, driver):
     if shutil.which("g++") is None:
         pytest.skip("no host compiler")
     src, exe = tmp_path / "plan.cpp", tmp_path / "plan"
-    src.write_text("#include <cmath>\n" + DRIVER)
+    src.write_text("#include <cmath>\n" + driver)
     subprocess.check_call(["g++", "-std=c++17", "-O2", "-Wall", "-I", os.path.join(ROOT, "include"),
                            "-I", os.path.join(ROOT, "paper_2406_06237_amd", "csrc"), str(src), "-o", str(exe)])
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and r.stdout == "ok\n", r.stdout
+
+
+def test_plans_of_every_size(tmp_path):
+    _run(tmp_path, DRIVER)
+
+
+def test_plans_of_channels_that_are_multiples_of_eight(tmp_path):
+    """The last unit of a kernel row has fewer than 32 channels then: units are counted up, rows keep their padding."""
+    driver = DRIVER.replace("a.cin = 32u * upto(kMaxK / (32u * a.kh * a.kw));", "a.cin = 8u * upto(kMaxK / (8u * a.kh * a.kw));")
+    driver = driver.replace("a.cin = kMaxK / (a.kh * a.kw) / 32u * 32u;", "a.cin = kMaxK / (a.kh * a.kw) / 8u * 8u;")
+    driver = driver.replace("a.kh) * (a.cin / 32u);", "a.kh) * ((a.cin + 31u) / 32u);")
+    assert driver.count("8u * upto") == 1 and driver.count("/ 8u * 8u") == 1 and driver.count("+ 31u) / 32u)") >= 1
+    _run(tmp_path, driver)

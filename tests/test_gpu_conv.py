@@ -478,3 +478,27 @@ def test_a_value_that_is_not_finite_reaches_its_own_windows_only(orc, shape, str
     assert d.read_status() == (0, 0)
     reached = torch.nn.functional.conv2d(hit, torch.ones((1, 1, kh, kw), device="cuda:0"), stride=stride, padding=pad)[:, 0, :, :, None] > 0
     assert torch.equal(~torch.isfinite(y), reached.expand_as(y))
+
+
+# Channels that are multiples of 8 and not of 32: the last unit of a kernel row has 8, 16 or 24, alone or behind whole ones;
+# one, two and four row tiles, panels of bf16 and of bytes, slices that begin and end with such units, every way of
+# addressing the activations, the largest panel.
+@pytest.mark.parametrize("shape,B_,H,Wd,stride,pad", [
+    ((64, 8, 1, 1), 2, 9, 17, 1, 0), ((16, 24, 1, 1), 1, 5, 5, 2, 0), ((128, 40, 1, 1), 3, 20, 20, 1, 0), ((48, 504, 1, 1), 4, 9, 9, 1, 0),
+    ((32, 1992, 1, 1), 1, 7, 7, 1, 0), ((64, 4600, 1, 1), 1, 6, 6, 2, 0), ((256, 104, 1, 1), 30, 30, 30, 1, 0),
+    ((64, 8, 3, 3), 2, 9, 17, 1, 1), ((32, 16, 3, 3), 1, 5, 40, 1, 0), ((16, 24, 1, 3), 2, 7, 18, 1, 1), ((128, 40, 3, 3), 9, 20, 20, 1, 1),
+    ((64, 72, 3, 3), 2, 13, 9, 2, 1), ((32, 56, 3, 3), 1, 31, 31, 2, 1), ((16, 504, 3, 3), 2, 7, 7, 1, 1), ((48, 136, 3, 3), 1, 9, 33, 1, 2),
+    ((64, 248, 3, 3), 4, 8, 8, 1, 1), ((16, 88, 5, 3), 1, 12, 12, 3, 2), ((64, 200, 2, 3), 3, 14, 14, 1, 0),
+])
+@pytest.mark.parametrize("layout", ["nhwc", "c8"])
+def test_channels_that_are_no_multiple_of_thirty_two(orc, shape, B_, H, Wd, stride, pad, layout):
+    _check(*_case(orc, shape, B_, H, Wd, stride, pad, x_layout=layout, y_layout=layout))
+
+
+@pytest.mark.parametrize("shape,stride,pad", [
+    ((32, 72, 1, 1), 1, 0), ((32, 48, 1, 1), 2, 0), ((32, 56, 3, 3), 1, 0), ((32, 48, 3, 3), 1, 1), ((32, 88, 3, 3), 2, 1), ((16, 504, 3, 3), 1, 1),
+])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_channels_that_are_missing_let_no_value_through(orc, shape, stride, pad, value):
+    """What lies where a unit's missing channels would be (the next pixel's, the next image's) is not read into a sum."""
+    test_a_value_that_is_not_finite_reaches_its_own_windows_only(orc, shape, stride, pad, value)
