@@ -391,9 +391,9 @@ __global__ __launch_bounds__(kThreads, 4) void encode_write(EncParams p) {
 // ones, which the chip has started before it; it gives up after a bounded number of looks all the same.  The
 // chunks of those that did, and chunks with a stream longer than its place in LDS, are written by the launch behind
 // this one, with a walk of their own.
-// Measured on 369 chunks of 65,536 symbols (2^12 states, 64 streams): 70 us, 11 of them the tables, 40 ns a symbol, and 1.4
-// and 4 us for the launches before and behind; with a pass for the sizes, a scan and a pass that writes 71, 5 and 97.  One
-// layer of 2.4 M symbols in 144 chunks 26 (23, 5, 29).  (A chunk whose streams do not fit is walked twice and costs what it
+// Measured on 369 chunks of 65,536 symbols (2^12 states, 64 streams): 66 us, 7.5 of them the tables, 40 ns a symbol, and 1.4
+// and 4 us for the launches before and behind; with a pass for the sizes, a scan and a pass that writes 71, 5 and 97 (11 of
+// both for the tables then).  One layer of 2.4 M symbols in 144 chunks 24 (23, 5, 29).  (A chunk whose streams do not fit is walked twice and costs what it
 // did: 200 chunks of 65,536 symbols at 4.9 bits 236, 240.)
 constexpr uint32_t kRows = 16u;                             // rows of symbols between two barriers
 constexpr uint32_t kRowsPerLoader = 4u;

@@ -5,19 +5,17 @@
 // occurrence i of a symbol of frequency f sits at (2i + 1) / (2f); all occurrences of all symbols are sorted by that
 // fraction, ties going to the smaller symbol, and an occurrence's rank is its state.
 //
-// The rank is found by a counting sort: occurrence -> one of L buckets by the integer part of L (2i + 1) / (2f)
-// (equal fractions share a bucket and buckets are ordered as the fractions are), a prefix sum over the buckets, and an
-// exact comparison with the other occurrences of the same bucket: one division per state, and as many comparisons as a
-// bucket has members.  On most tables these are a few, compared by their products (below 2^26; all symbols of odd
-// frequency meet in the middle, but one bucket of a dozen is soon done).  Where symbols share a frequency they share all
-// fractions, and every bucket has as many members as there are such symbols: then a second division gives every
-// occurrence a number that orders its bucket by itself.  With r / 2f the place in the bucket, that is the integer part of
-// 2L r / 2f (different fractions, of frequencies f + g <= L, are 1 / 2fg >= 2 / L^2 apart, so 4 apart here), the symbol
-// below it.
-// Counting the occurrences of every other symbol before each occurrence takes a division per state and symbol instead: with
-// 2^12 states a decode table took 57 us that way (16 symbols; 218 us with 256), 36 us (46 us) this way by one workgroup.
-// Flat rows of 2^12 states by several workgroups, by products -> by numbers: 16 symbols 25 -> 16 us, 256 symbols
-// 231 -> 60; tables with a crowded middle only as before.
+// The rank is found by a counting sort with a key per occurrence, floor(L^2 (2i + 1) / (2f)) with the symbol below it: equal
+// fractions have equal first parts, and different ones, of frequencies f + g <= L, are at least 1 / 2fg >= 2 / L^2 apart, so
+// their first parts differ.  The key's upper log2 L bits are a bucket; a prefix sum over the buckets' sizes, and then every
+// occurrence counts the smaller keys among its bucket's, four to an LDS read: a key of a bucket before or behind is smaller
+// or larger by itself, so the reads need neither begin nor end where the bucket does.
+// What bounds it is instructions (a workgroup's wavefronts share the four SIMDs): a quotient takes eight with a reciprocal
+// that is a little too small, a comparison two, and wavefronts whose 64 occurrences are one symbol's search for nothing.
+// A call that builds one table of 2^12 states (several workgroups) with the divisions and the members' products, or second
+// divisions where buckets were large, that stood here before -> now: 16 symbols around a dominant one 12.5 -> 7.8 us (with the
+// shorter chains of the look-ahead entries, which are a third of it), 16 symbols alike 16.3 -> 10.2, 64 alike 28.6 -> 20, 256
+// alike 60 -> 37, 256 of random frequencies 40 -> 22; in the packer (a workgroup of 512 threads, two per CU) 11.2 -> 7.5 us.
 #ifndef ANSZP_SPREAD_H
 #define ANSZP_SPREAD_H
 
@@ -28,16 +26,15 @@
 #include "anszp.h"
 
 constexpr uint32_t kSpreadStates = 1u << ANSZP_MAX_TABLE_LOG;
-constexpr uint32_t kSpreadFew = 8, kSpreadMany = 24;      // crowded: that many lanes of a wavefront have an occurrence that is not
-                                                          // among the first kSpreadFew of its bucket
 
+typedef __attribute__((ext_vector_type(4))) uint32_t spread_words4;
 struct SpreadLds {
     uint32_t f[ANSZP_ALPHABET];
-    uint32_t first[ANSZP_ALPHABET];        // occurrences of smaller symbols: occurrence i of symbol s is number first[s] + i
+    // occurrences of smaller symbols: occurrence i of symbol s is number first[s] + i
+    __attribute__((aligned(16))) uint32_t first[ANSZP_ALPHABET];
+    spread_words4 member[kSpreadStates / 4u];       // keys, bucket after bucket
     uint32_t bucket[kSpreadStates];        // members of each bucket, then where each bucket's members start
-    uint32_t member[kSpreadStates];        // bucket after bucket: f - 1 | i << 12 | symbol << 24 (crowded: order in the bucket << 8 | symbol)
     uint32_t part[16];                     // a wavefront's share of a prefix sum
-    uint32_t crowded;                      // many buckets have many members
 };
 
 // Inclusive prefix sum over the 64 lanes of a wavefront.
@@ -59,7 +56,9 @@ template <uint32_t THREADS, class PLACE>
 __device__ __forceinline__ bool spread_states(const uint32_t* freqs, uint32_t table_log, SpreadLds& t, PLACE&& place) {
     static_assert(THREADS >= ANSZP_ALPHABET && THREADS <= 1024u && kSpreadStates % THREADS == 0, "a thread per symbol, sixteen shares");
     constexpr uint32_t kPerThread = kSpreadStates / THREADS;
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    typedef spread_words4 words4;
+    uint32_t* const members = reinterpret_cast<uint32_t*>(t.member);
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t L = 1u << table_log;
     uint32_t fs = 0, upto = 0;
     if (tid < ANSZP_ALPHABET) {
@@ -68,6 +67,7 @@ __device__ __forceinline__ bool spread_states(const uint32_t* freqs, uint32_t ta
         if (lane == 63u) t.part[wave] = upto;
     }
     for (uint32_t b = tid; b < L; b += THREADS) t.bucket[b] = 0u;
+    if (tid >= L && tid < 4u) members[tid] = 0xFFFFFFFFu;      // (read with the others when L < 4)
     __syncthreads();
     uint32_t total = 0;
 #pragma unroll
@@ -79,34 +79,48 @@ __device__ __forceinline__ bool spread_states(const uint32_t* freqs, uint32_t ta
     if (tid < ANSZP_ALPHABET) {
         t.f[tid] = fs;
         t.first[tid] = upto - fs;
-        t.crowded = 0u;
     }
     __syncthreads();
-    // occurrence g: its symbol, frequency, number among the symbol's, bucket
-    auto occurrence = [&](uint32_t g, uint32_t& sy, uint32_t& f, uint32_t& i) {
-        sy = 0;                                                // the largest symbol with first[sy] <= g (it has a frequency)
-#pragma unroll
-        for (uint32_t step = ANSZP_ALPHABET / 2u; step; step >>= 1)
-            sy += t.first[sy + step] <= g ? step : 0u;
-        f = t.f[sy];
-        i = g - t.first[sy];
-        return ((2u * i + 1u) << table_log) / (2u * f);        // below 2^26; i < f, so below L
+    // symbols whose first occurrence is not beyond g (g alike for all lanes)
+    const words4 firsts = reinterpret_cast<const words4*>(t.first)[lane];
+    auto symbols_upto = [&](uint32_t g) {
+        return static_cast<uint32_t>(__popcll(__ballot(firsts.x <= g)) + __popcll(__ballot(firsts.y <= g)) +
+                                     __popcll(__ballot(firsts.z <= g)) + __popcll(__ballot(firsts.w <= g)));
     };
-    uint32_t mine[kPerThread], at[kPerThread] = {};     // as in `member`; bucket | place within it << 16
-    uint32_t places = 0;
+    uint32_t sy[kPerThread], number[kPerThread], key[kPerThread], at[kPerThread];   // number: f - 1 | i << 12; at: place within the bucket
 #pragma unroll
     for (uint32_t u = 0; u < kPerThread; ++u) {
-        const uint32_t g = tid + u * THREADS;
-        if (g < L) {
-            uint32_t sy, f, i;
-            const uint32_t b = occurrence(g, sy, f, i);
-            mine[u] = (f - 1u) | i << 12 | sy << 24;
-            at[u] = b | atomicAdd(&t.bucket[b], 1u) << 16;     // below 2^12 both
+        const uint32_t g0 = wave * 64u + u * THREADS, g = g0 + lane;
+        if (g0 >= L) break;                                    // (uniform)
+        // the largest symbol with first[symbol] <= g (it has a frequency)
+        uint32_t s = symbols_upto(g0) - 1u;
+        const uint32_t most = symbols_upto(g0 + 63u) - 1u;
+        if (s != most) {                                       // (uniform)
+            for (uint32_t step = 0x80000000u >> __builtin_clz(most - s); step; step >>= 1) {
+                const uint32_t c = min(s + step, most);
+                s = t.first[c] <= g ? c : s;
+            }
         }
-        places |= at[u];
+        if (g >= L) break;                                     // (L < 64: one round)
+        const uint32_t f = t.f[s], i = g - t.first[s];
+        // n / 2f for n < 2^26, n / 2f < 2^12 (i < f): the quotient with the reciprocal, whose and whose product's errors of
+        // less than 2^-22 are made to lie on one side, is right or one too small
+        const float inverse = __builtin_amdgcn_rcpf(static_cast<float>(2u * f)) * (1.0f - 0x1p-20f);
+        auto divide = [&](uint32_t n, uint32_t& rest) {
+            const uint32_t q = static_cast<uint32_t>(static_cast<float>(n) * inverse);
+            rest = n - __umul24(q, 2u * f);
+            const bool more = rest >= 2u * f;
+            rest = more ? rest - 2u * f : rest;
+            return more ? q + 1u : q;
+        };
+        uint32_t rest;
+        const uint32_t b = divide((2u * i + 1u) << table_log, rest);
+        const uint32_t low = divide(rest << table_log, rest);
+        sy[u] = s;
+        number[u] = (f - 1u) | i << 12;
+        key[u] = (b << table_log | low) << 8 | s;
+        at[u] = atomicAdd(&t.bucket[b], 1u);
     }
-    // (kSpreadFew is a power of two: a place beyond it has a bit that high)
-    if (__builtin_expect(__popcll(__ballot((places >> 16) >= kSpreadFew)) >= kSpreadMany, 0)) t.crowded = 1u;
     __syncthreads();
     {                                                          // counts -> starts: neighbouring buckets per thread
         const uint32_t per = max(L / THREADS, 1u), b0 = tid * per;
@@ -128,60 +142,39 @@ __device__ __forceinline__ bool spread_states(const uint32_t* freqs, uint32_t ta
         }
     }
     __syncthreads();
-    uint32_t starts[kPerThread];                               // (asked for together with `crowded`, not behind the branch)
-    const uint32_t crowded = t.crowded;
+    uint32_t starts[kPerThread];
 #pragma unroll
-    for (uint32_t u = 0; u < kPerThread; ++u) starts[u] = t.bucket[at[u] & 0xFFFFu];
-    if (__builtin_expect(__builtin_amdgcn_readfirstlane(crowded), 0)) {        // (uniform)
-        // (loops that work everything out again: less code beside the other tables' than from registers)
-        auto key_of = [&](uint32_t g, uint32_t& sy, uint32_t& f, uint32_t& i, uint32_t& b) {
-            b = occurrence(g, sy, f, i);
-            const uint32_t rest = ((2u * i + 1u) << table_log) - b * 2u * f;             // below 2 f
-            return (rest << (table_log + 1u)) / (2u * f) << 8 | sy;                      // (the division below 2^26)
-        };
-        uint32_t sy, f, i, b;
-#pragma unroll 1
-        for (uint32_t g = tid; g < L; g += THREADS) {
-            const uint32_t key = key_of(g, sy, f, i, b);
-            t.member[atomicAdd(&t.bucket[b], 1u)] = key;       // (behind this loop every bucket's entry is its end)
+    for (uint32_t u = 0; u < kPerThread; ++u) {
+        if (tid + u * THREADS < L) {
+            starts[u] = t.bucket[key[u] >> (table_log + 8u)];
+            members[starts[u] + at[u]] = key[u];
         }
-        __syncthreads();
-#pragma unroll 1
-        for (uint32_t g = tid; g < L; g += THREADS) {
-            const uint32_t key = key_of(g, sy, f, i, b), begin = b ? t.bucket[b - 1u] : 0u, end = t.bucket[b];
-            // (from another member in every lane: occurrences of one symbol are in buckets of like sizes, whose members
-            // in one place would share an LDS bank)
-            uint32_t state = begin, m = begin + lane % (end - begin);
-#pragma unroll 8
-            for (uint32_t n = end - begin; n; --n) {
-                state += t.member[m] < key ? 1u : 0u;
-                m = m + 1u < end ? m + 1u : begin;
-            }
-            place(g, sy, f, i, state);
-        }
-        return true;
     }
-#pragma unroll
-    for (uint32_t u = 0; u < kPerThread; ++u)
-        if (tid + u * THREADS < L) t.member[starts[u] + (at[u] >> 16)] = mine[u];
     __syncthreads();
 #pragma unroll
     for (uint32_t u = 0; u < kPerThread; ++u) {
         const uint32_t g = tid + u * THREADS;
         if (g < L) {
-            const uint32_t b = at[u] & 0xFFFFu;
-            const uint32_t begin = t.bucket[b], end = b + 1u < L ? t.bucket[b + 1u] : L;
-            const uint32_t f = (mine[u] & 0xFFFu) + 1u, i = (mine[u] >> 12) & 0xFFFu, s = mine[u] >> 24;
-            uint32_t state = begin;
-#pragma unroll 4
-            for (uint32_t m = begin; m < end; ++m) {
-                const uint32_t o = t.member[m];
-                const uint32_t fo = (o & 0xFFFu) + 1u, io = (o >> 12) & 0xFFFu, so = o >> 24;
-                // (2 io + 1) / fo against (2 i + 1) / f, ties to the smaller symbol (an occurrence is not before itself)
-                const uint32_t theirs = __umul24(2u * io + 1u, f), ours = __umul24(2u * i + 1u, fo);
-                state += theirs < ours || (theirs == ours && so < s) ? 1u : 0u;
+            const uint32_t b = key[u] >> (table_log + 8u), end = b + 1u < L ? t.bucket[b + 1u] : L;
+            const uint32_t first = starts[u] / 4u, behind = (end + 3u) / 4u;
+            uint32_t state = 4u * first;
+            auto count = [&](const words4 k) {
+                state += (k.x < key[u] ? 1u : 0u) + (k.y < key[u] ? 1u : 0u) + (k.z < key[u] ? 1u : 0u) + (k.w < key[u] ? 1u : 0u);
+            };
+            count(t.member[first]);
+            uint32_t left = behind - first - 1u;
+            if (left) {
+                // the bucket's other reads, from another one in every lane: where symbols share a frequency a wavefront's
+                // buckets are of one size, and reads in one place of each would share an LDS bank
+                uint32_t at = first + 1u + ((lane * 37u & 63u) * left >> 6);
+#pragma unroll 1
+                do {
+                    const words4 k = t.member[at];
+                    at = at + 1u < behind ? at + 1u : first + 1u;
+                    count(k);
+                } while (--left);
             }
-            place(g, s, f, i, state);
+            place(g, sy[u], (number[u] & 0xFFFu) + 1u, number[u] >> 12, state);
         }
     }
     return true;

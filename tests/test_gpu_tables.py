@@ -70,3 +70,19 @@ def test_buckets_of_few_and_of_many_members(kind, k, R):
     rows = np.stack([row, row[::-1]]).astype(np.uint32)
     got = B.build_tables_device(torch.from_numpy(rows.view(np.int32)).to("cuda:0"), R).cpu().numpy().view(np.uint32).reshape(2, -1)
     assert np.array_equal(got, B.build_tables_host(rows, R))
+
+
+# A wavefront's 64 occurrences: one symbol's, or those of symbols that begin, or are one occurrence long, around its edges; in
+# front of them, between them and behind them symbols without any.
+@pytest.mark.parametrize("R,lead", [(R, lead) for R in (6, 7, 11, 12) for lead in (1, 2, 62, 63, 64, 65, 126, 127, 128, 129, 1023, 1024, 1025)
+                                    if lead + 2 <= 1 << R])
+def test_symbols_that_begin_around_a_wavefronts_edge(R, lead):
+    L = 1 << R
+    rows = np.zeros((2, 256), dtype=np.uint32)
+    rows[0, [0, 1, 254]] = lead, 1, L - lead - 1        # the first and nearly the last symbol
+    few = min(60, L - lead - 1)
+    rows[1, 5] = lead
+    rows[1, 9:9 + 3 * few:3] = 1                        # one occurrence each
+    rows[1, 200] = L - lead - few
+    got = B.build_tables_device(torch.from_numpy(rows.view(np.int32)).to("cuda:0"), R).cpu().numpy().view(np.uint32).reshape(2, -1)
+    assert np.array_equal(got, B.build_tables_host(rows, R))
