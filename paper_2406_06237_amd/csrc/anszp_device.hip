@@ -2044,24 +2044,32 @@ void decode_merged_small(DecodeParams p) { decode_lookahead<OUT, PER_CHANNEL, Sm
 // The host merges the per-symbol position sequences with a heap; here a counting sort gives every occurrence of
 // every symbol its state (anszp_spread.h), the occurrence index gives the sub-state f + i, hence nb_bits and newX;
 // the look-ahead entries then follow the step table in LDS.
+//
+// What bounds it is instructions: sixteen wavefronts share the four SIMDs.  An entry is up to seven steps of the dominant symbol
+// without bits, one bit's step among them, and a last one: whether a state's step is of the first or the second kind is worked
+// out once and kept beside its triple, so a step costs a look-up and a test, and the two entries of a state share the steps in
+// front of the bit's.  53 tables of 2^12 states: 2.1 us of the kernel's 8.3, where asking triple and dominant symbol anew
+// at every step of every entry took 6.7.
 constexpr uint32_t kBuildThreads = 1024u;
 
 __global__ __launch_bounds__(kBuildThreads) void build_tables_kernel(const uint32_t* freqs, int table_log, uint32_t* tables,
                                                                      uint32_t* status) {
     constexpr uint32_t kStates = 1u << ANSZP_MAX_TABLE_LOG;
     __shared__ SpreadLds spread;
-    __shared__ uint32_t dominant_sym;
-    __shared__ uint32_t triple[kStates];                // newX | nb_bits << 16 | symbol << 24 of every state
+    __shared__ uint32_t triple[kStates];                // newX | nb_bits << 16 | symbol << 24 of every state, and for the dominant symbol:
+    constexpr uint32_t kDropsNone = 1u << 22, kDropsOne = 1u << 23;      // no bits and a next state other than 0; one bit
     const uint32_t tid = threadIdx.x;
     const uint32_t L = 1u << table_log;
     const uint32_t* f = freqs + size_t(blockIdx.x) * ANSZP_ALPHABET;
     uint32_t* out = tables + size_t(blockIdx.x) * table_stride_words(table_log);
-    if (tid == 0) dominant_sym = 0xFFFFFFFFu;
     const bool ok = spread_states<kBuildThreads>(f, static_cast<uint32_t>(table_log), spread, [&](uint32_t, uint32_t sy, uint32_t fs, uint32_t i, uint32_t rank) {
         // Sec. II-A: sub-state f + i, shifted left until it lies in [L, 2L)
         const uint32_t v = fs + i;
         const uint32_t shift = static_cast<uint32_t>(table_log) - (31u - static_cast<uint32_t>(__clz(v)));
-        triple[rank] = ((v << shift) - L) | shift << 16 | sy << 24;
+        const uint32_t newX = (v << shift) - L;
+        // (the dominant symbol drops no bit or one; at most one symbol is that frequent)
+        const uint32_t flag = fs <= L / 2u ? 0u : shift ? kDropsOne : newX ? kDropsNone : 0u;
+        triple[rank] = newX | shift << 16 | flag | sy << 24;
     });
     // this workgroup's share of the table (gridDim.y of them build it together)
     const uint32_t first = blockIdx.y * kBuildThreads + tid, stride = gridDim.y * kBuildThreads;
@@ -2070,11 +2078,10 @@ __global__ __launch_bounds__(kBuildThreads) void build_tables_kernel(const uint3
         if (first == 0 && status) report(status, ANSZP_ST_BAD_FREQ);
         return;
     }
-    if (tid < ANSZP_ALPHABET && spread.f[tid] > L / 2) dominant_sym = tid;      // at most one
     __syncthreads();
     // every word the planes below do not fill is zero (the byte table fills 3 L of the first L words' bytes)
     for (uint32_t i = first; i < L; i += stride) {
-        const uint32_t t = triple[i];
+        const uint32_t t = triple[i] & ~(kDropsNone | kDropsOne);
         out[table_triples_offset(table_log) + i] = t;
         out[L + i] = 0u;
         out[3u * L + i] = 0u;
@@ -2084,41 +2091,45 @@ __global__ __launch_bounds__(kBuildThreads) void build_tables_kernel(const uint3
             uint32_t word = 0;
             for (uint32_t j = 4u * i; j < 4u * i + 4u && j < 3u * L; ++j) {
                 const uint32_t e = triple[j / 3u], field = j % 3u;
-                word |= (field == 0u ? e >> 24 : field == 1u ? (e >> 16) & 0xFFu : e & 0xFFu) << 8u * (j & 3u);
+                word |= (field == 0u ? e >> 24 : field == 1u ? (e >> 16) & 0xFu : e & 0xFFu) << 8u * (j & 3u);
             }
             out[table_bytes_offset(table_log) + i] = word;
         }
     }
     // look-ahead entries: up to kLookaheadMaxSymbols steps merged into one look-up, indexed by the state and
     // the next bit; a run never passes through state 0 (a stream then always ends where an entry ends)
-    const uint32_t dominant = dominant_sym;
-    uint2* ahead = reinterpret_cast<uint2*>(out + table_lookahead_offset(table_log));
-    for (uint32_t e = first; e < 2u * L; e += stride) {
-        const uint32_t X = e >> 1, b = e & 1u;
-        uint32_t Y = X, count = 0, bits = 0, last_sym = 0, saved_Y = 0, saved_count = 0;
-        bool took_b = false, may_take_b = true;
-        int32_t base = 0;
-        for (;;) {
-            const uint32_t t = triple[Y], n = (t >> 16) & 0xFFu, newX = t & 0xFFFFu;
-            const bool room = count + 1u < kLookaheadMaxSymbols;       // another symbol may follow this one
-            const bool is_dominant = t >> 24 == dominant;
-            if (is_dominant && room && n == 0u && newX != 0u) { ++count; Y = newX; continue; }
-            if (is_dominant && room && n == 1u && !took_b && may_take_b && (newX | b) != 0u) {
-                saved_Y = Y; saved_count = count;
-                took_b = true; ++count; Y = newX | b;
-                continue;
-            }
-            if (took_b && 1u + n > uint32_t(ANSZP_MAX_TABLE_LOG)) {    // too many bits for one look-up: the 1-bit step is the last
-                Y = saved_Y; count = saved_count; took_b = false; may_take_b = false;
-                continue;
-            }
-            bits = (took_b ? 1u : 0u) + n;
-            base = int32_t(2u * newX) - (took_b ? int32_t(b << (n + 1u)) : 0);
-            last_sym = t >> 24;
+    // (the entries of both values of the next bit by one thread: they share the steps in front of it)
+    constexpr uint32_t kMore = kLookaheadMaxSymbols - 1u;
+    auto run = [&](uint32_t& t, uint32_t& count) {             // steps that drop no bits, while another symbol may follow
+        while ((t & kDropsNone) && count < kMore) {
+            t = triple[t & 0xFFFFu];
             ++count;
-            break;
         }
-        ahead[e] = make_uint2(lookahead_first_word(bits, count, last_sym, X == 0u), lookahead_second_word(base));
+    };
+    typedef __attribute__((ext_vector_type(4))) uint32_t words4;
+    words4* ahead = reinterpret_cast<words4*>(out + table_lookahead_offset(table_log));
+    for (uint32_t X = first; X < L; X += stride) {
+        uint32_t t = triple[X], before = 0;
+        run(t, before);
+        uint32_t entry[4];
+#pragma unroll
+        for (uint32_t b = 0; b < 2u; ++b) {
+            uint32_t last = t, count = before, taken = 0;
+            if ((t & kDropsOne) && before < kMore && ((t & 0xFFFFu) | b) != 0u) {
+                last = triple[(t & 0xFFFFu) | b];
+                ++count;
+                run(last, count);
+                taken = 1u;
+                if (((last >> 16) & 0xFu) + 1u > uint32_t(ANSZP_MAX_TABLE_LOG)) {        // too many bits for one look-up: the 1-bit step is the last
+                    last = t; count = before; taken = 0u;
+                }
+            }
+            const uint32_t n = (last >> 16) & 0xFu;
+            const int32_t base = int32_t(2u * (last & 0xFFFFu)) - (taken ? int32_t(b << (n + 1u)) : 0);
+            entry[2u * b] = lookahead_first_word(taken + n, count + 1u, last >> 24, X == 0u);
+            entry[2u * b + 1u] = lookahead_second_word(base);
+        }
+        ahead[X] = words4{entry[0], entry[1], entry[2], entry[3]};
     }
 }
 
@@ -2374,10 +2385,9 @@ int anszp_build_tables_device(const uint32_t* freqs_dev, int n_tables, int table
     if (table_log < 1 || table_log > ANSZP_MAX_TABLE_LOG || n_tables < 1) return ANSZP_E_RANGE;
     if (reinterpret_cast<uintptr_t>(tables_dev) & 15) return ANSZP_E_RANGE;
     // Several workgroups per table while the tables alone do not fill the chip (each works out the states for itself and
-    // writes a share of the table); no more than there are rows of kBuildThreads look-ahead entries.  53 tables of 2^12
-    // states: 19 us with four workgroups each, 41 us with one (most of it the chains of steps an entry merges); one
-    // table: 16 us with eight, 36 us with one.
-    const uint32_t rows = std::max(1u, (2u << table_log) / kBuildThreads);
+    // writes a share of the table); no more than there are rows of kBuildThreads states.  53 tables of 2^12 states, a call: 9 us
+    // with four workgroups each; 300 tables, one each, 19 us.
+    const uint32_t rows = std::max(1u, (1u << table_log) / kBuildThreads);
     const uint32_t shares = std::max(1u, std::min(rows, device_cus() / static_cast<uint32_t>(n_tables)));
     hipLaunchKernelGGL(build_tables_kernel, dim3(static_cast<uint32_t>(n_tables), shares), dim3(kBuildThreads), 0,
                        static_cast<hipStream_t>(hip_stream), freqs_dev, table_log, tables_dev, status_dev);
