@@ -974,9 +974,13 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
 // whose best choice takes 9 to 500 us became 4 to 20 % faster where a wavefront has few units or rounds, none slower; 1 x 1
 // from 32 channels to 592 on eight 59 x 59 images 31 -> 27 us).
 //
+// The first units' activations are asked for before the panel is decoded, behind the loads that decoding waits for, where the
+// registers hold them meanwhile (kEarly: all but 4 row tiles x 3 column tiles of three taps and 4 column tiles of nine
+// vectors): a ResNet-50's convolutions, each repeated, 696 -> 674 us on 16 images and 1286 -> 1263 on 64, 0.1 to 1.2 us a call.
+//
 // Measured against rings of loads without slices (a call among others, MI355X): 3 x 3 x 512 channels, one 7 x 7 image 21.8 ->
-// 13.0 us; 1 x 1 from 1024 channels, 64 14 x 14 images 21.4 -> 17.2; 3 x 3 x 128 channels, 64 28 x 28 images 28.5 -> 26.2; a
-// ResNet-50's 53 convolutions on 16 images, one call each 900 -> 696.
+// 12.4 us; 1 x 1 from 1024 channels, 64 14 x 14 images 21.4 -> 16.8; 3 x 3 x 128 channels, 64 28 x 28 images 28.5 -> 25.5; a
+// ResNet-50's 53 convolutions on 16 images, one call each 900 -> 692.
 // Every lane's neighbour's words within rows of 16 lanes: of the lane before (BEFORE) or after, the first (last) lane's
 // from `beyond`, which holds them in the row's last (first) lane if it is a tile of its own (ROTATE), else in the lane
 // itself; and-ed with `mask`.  (Moves and masks in one: the lane without a source keeps what the first instruction
@@ -1008,6 +1012,8 @@ __global__ __launch_bounds__(kThreads) void conv_sliced_kernel(ConvParams p) {
     constexpr uint32_t NS = MODE == kPoint ? 1u : 3u;             // steps of a unit
     constexpr uint32_t NF = MODE == kRow ? 3u : 1u;               // vectors of a unit that are loaded per column tile
     constexpr uint32_t kSlots = units_in_flight(MR, MODE, QT);
+    // the first round's activations are asked for before the panel is decoded
+    constexpr bool kEarly = MODE == kPoint || (MODE == kShift ? MR * QT < 12u : MR * QT < 12u && QT < 4u);
     constexpr uint32_t kOutside = 0x80000000u;                    // an offset beyond any x or y (the host: fewer than 2^31 bytes)
     const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1043,7 +1049,7 @@ __global__ __launch_bounds__(kThreads) void conv_sliced_kernel(ConvParams p) {
     // a round's tiles dealt evenly: QT or one fewer each
     auto first_tile = [&](uint32_t g) { return g * p.wave_tiles + min(g, p.wave_tiles_rest); };
     const bool has_last = first_tile(wt + 1u) - first_tile(wt) == QT;
-    auto place = [&](uint32_t t0) {                               // of the round from tile t0 on
+    auto place = [&](uint32_t t0) __attribute__((always_inline)) {                               // of the round from tile t0 on
         const uint32_t pix0 = split_begin + 16u * (t0 + first_tile(wt)), end = min(split_begin + 16u * (t0 + first_tile(wt + 1u)), split_end);
 #pragma unroll
         for (uint32_t q = 0; q < QT; ++q) {
@@ -1076,18 +1082,57 @@ __global__ __launch_bounds__(kThreads) void conv_sliced_kernel(ConvParams p) {
                             ? (b * p.x_image + uint32_t(edge_h0 * int32_t(p.in_w) + w0) * p.x_pixel + kg * p.x_block) * 2u : kOutside;
         }
     };
-    const anszp_layer_t lay = decode_panel<MR, P16>(p, lds, mtile, [&] { place(0u); });
-    __syncthreads();
-    if constexpr (!P16) widen_panel<MR>(p, lds, lay);
-
-    const uint32_t a_at = lds_address(lds) + (P16 ? p.panel_off : 0u) + (col * p.row_stride + 8u * kg) * 2u;
-    const uint32_t tile_stride = kRows * p.row_stride * 2u;
     const uint32_t blocks = TAIL ? (p.cin + 31u) / 32u : p.cin / 32u, units = (MODE != kPoint ? p.kh : 1u) * blocks;
     const uint32_t u_begin = wk * p.slice_units, n = min(p.slice_units, units - min(u_begin, units));
     // TAIL: the last block has fewer than 32 channels; the lanes of those that are missing read outside there (the weights they
     // meet are the next tap's or the row's padding: finite)
     [[maybe_unused]] const bool beyond_tail = 8u * kg >= p.cin % 32u;
     const uint32_t row0 = MODE != kPoint ? __umulhi(2u * u_begin, p.blocks_magic) >> p.blocks_shift : 0u;
+    // the cursors of the loads and of the multiplications: kernel row and block of 32 channels of the next unit
+    uint32_t row, cb, use_cb, k_use, asked;
+    words4 ring[kSlots][NF][QT];
+    [[maybe_unused]] words4 edge[kSlots];
+    auto request = [&](uint32_t slot) __attribute__((always_inline)) {
+        const __amdgpu_buffer_rsrc_t x = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.x), 0, asked < n ? p.x_bytes : 0u, 0x00020000);
+        const uint32_t at = asked < n ? cb * 8u * p.x_block : 0u;      // (an empty buffer's check must not overflow)
+        // (what is outside stays beyond the buffer: no row is 2^31 bytes away)
+        const uint32_t row_at = MODE == kPoint ? 0u : row * p.in_w * p.x_pixel * 2u;
+        [[maybe_unused]] const bool is_tail = TAIL && cb + 1u == blocks;
+        auto in_row = [&](int32_t first_row, uint32_t where) {
+            const uint32_t v = MODE == kPoint ? where : uint32_t(first_row + int32_t(row)) < p.in_h ? where + row_at : kOutside;
+            if constexpr (TAIL) return is_tail && beyond_tail ? kOutside : v;
+            return v;
+        };
+#pragma unroll
+        for (uint32_t q = 0; q < QT; ++q)
+#pragma unroll
+            for (uint32_t f = 0; f < NF; ++f) ring[slot][f][q] = __builtin_amdgcn_raw_buffer_load_b128(x, in_row(h0[q], from[f][q]), at, 0);
+        if constexpr (MODE == kShift) edge[slot] = __builtin_amdgcn_raw_buffer_load_b128(x, in_row(edge_h0, edge_from), at, 0);
+        ++asked;
+        ++cb;
+        if constexpr (MODE != kPoint) {
+            const bool next_row = cb == blocks;               // (without a branch)
+            cb = next_row ? 0u : cb;
+            row += next_row ? 1u : 0u;
+        }
+    };
+    auto request_first = [&]() __attribute__((always_inline)) {
+        row = row0;
+        cb = use_cb = u_begin - row0 * blocks;
+        k_use = row0 * NS * p.cin + cb * 32u;
+        asked = 0;
+#pragma unroll
+        for (uint32_t d = 0; d < kSlots; ++d) request(d);
+    };
+    const anszp_layer_t lay = decode_panel<MR, P16>(p, lds, mtile, [&]() __attribute__((always_inline)) {
+        place(0u);
+        if constexpr (kEarly) request_first();
+    });
+    __syncthreads();
+    if constexpr (!P16) widen_panel<MR>(p, lds, lay);
+
+    const uint32_t a_at = lds_address(lds) + (P16 ? p.panel_off : 0u) + (col * p.row_stride + 8u * kg) * 2u;
+    const uint32_t tile_stride = kRows * p.row_stride * 2u;
     const __amdgpu_buffer_rsrc_t y_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, p.y_bytes, 0x00020000);
     const bool per_channel = lay.channel_len != 0;
     auto store = [&](uint32_t m, uint32_t at, const floatx4 sum) {
@@ -1117,36 +1162,7 @@ __global__ __launch_bounds__(kThreads) void conv_sliced_kernel(ConvParams p) {
         for (uint32_t m = 0; m < MR; ++m)
 #pragma unroll
             for (uint32_t q = 0; q < QT; ++q) acc[m][q] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-        // the cursors of the loads and of the multiplications: kernel row and block of 32 channels of the next unit
-        uint32_t row = row0, cb = u_begin - row0 * blocks, use_cb = cb, k_use = row0 * NS * p.cin + cb * 32u, asked = 0;
-        words4 ring[kSlots][NF][QT];
-        [[maybe_unused]] words4 edge[kSlots];
-        auto request = [&](uint32_t slot) {
-            const __amdgpu_buffer_rsrc_t x = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.x), 0, asked < n ? p.x_bytes : 0u, 0x00020000);
-            const uint32_t at = asked < n ? cb * 8u * p.x_block : 0u;      // (an empty buffer's check must not overflow)
-            // (what is outside stays beyond the buffer: no row is 2^31 bytes away)
-            const uint32_t row_at = MODE == kPoint ? 0u : row * p.in_w * p.x_pixel * 2u;
-            [[maybe_unused]] const bool is_tail = TAIL && cb + 1u == blocks;
-            auto in_row = [&](int32_t first_row, uint32_t where) {
-                const uint32_t v = MODE == kPoint ? where : uint32_t(first_row + int32_t(row)) < p.in_h ? where + row_at : kOutside;
-                if constexpr (TAIL) return is_tail && beyond_tail ? kOutside : v;
-                return v;
-            };
-#pragma unroll
-            for (uint32_t q = 0; q < QT; ++q)
-#pragma unroll
-                for (uint32_t f = 0; f < NF; ++f) ring[slot][f][q] = __builtin_amdgcn_raw_buffer_load_b128(x, in_row(h0[q], from[f][q]), at, 0);
-            if constexpr (MODE == kShift) edge[slot] = __builtin_amdgcn_raw_buffer_load_b128(x, in_row(edge_h0, edge_from), at, 0);
-            ++asked;
-            ++cb;
-            if constexpr (MODE != kPoint) {
-                const bool next_row = cb == blocks;               // (without a branch)
-                cb = next_row ? 0u : cb;
-                row += next_row ? 1u : 0u;
-            }
-        };
-#pragma unroll
-        for (uint32_t d = 0; d < kSlots; ++d) request(d);
+        if constexpr (!kEarly) request_first();
         auto use = [&](uint32_t d) {                              // the unit in slot d
             uint32_t a_step = a_at + k_use * 2u;
 #pragma unroll
@@ -1201,6 +1217,7 @@ __global__ __launch_bounds__(kThreads) void conv_sliced_kernel(ConvParams p) {
             t0 += p.round_tiles;
             if (split_begin + 16u * t0 >= split_end) break;
             place(t0);
+            if constexpr (kEarly) request_first();
         } else {
             // One round.  Every wavefront leaves its sums in LDS, 1 KiB per tile and row tile ([slice][tile range][q][m]);
             // the wavefronts then take the blocks in turn, add up the slices' and store.
