@@ -230,7 +230,9 @@ int anszp_decode_variant(const anszp_decode_args_t* args, int variant, void* hip
  * kernels is bounded by a number of polls, after which the chunk is abandoned with ANSZP_ST_INTERNAL and its
  * workgroup drains.  polls >= 1: later launches give up after polls - 1 polls (1: at the first wait that is not
  * satisfied at once, which every launch of the look-ahead and streaming kernels has); 0: back to the default
- * (2^22).  Process-wide, not synchronised with launches in flight. */
+ * (2^22).  The GPU packer's workgroups wait for the sizes of lower-numbered chunks within the same bound (default 2^16
+ * polls); a chunk whose workgroup gives up is written by the launch behind it, with the same words and no status bit.
+ * Process-wide, not synchronised with launches in flight. */
 void anszp_test_set_spin_limit(uint32_t polls);
 
 /* Sec. III-A: the weights of a network are decoded again at every inference, from arrays that do not

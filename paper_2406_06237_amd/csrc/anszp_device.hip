@@ -1644,16 +1644,22 @@ __device__ __forceinline__ void decode_lookahead(const DecodeParams& p) {
                 : "memory");
             static_assert(kExpanders == 2u && kWave * 4u == 256u, "two rows of positions, 256 bytes apart");
             // A block is expanded once the wavefront whose turn it was has moved past it: every block below both
-            // wavefronts' next one is.  Where those are neighbours, the wavefront with the later one expanded the last of
-            // them, and its row, written behind its number and read before it, holds no more than that block (positions only grow).  Where it has
-            // run further ahead, a lane's position after the last block that is certainly expanded is the smaller of
-            // the two rows.  (The smaller alone is a block late, and a ring of two reaches of a block then waits for itself:
-            // one block can take every lane as far as the ring lets it.)  Once no more blocks will be logged and all have
-            // been expanded, every stream is complete (the row of the wavefront that did not expand the last block stays behind).
+            // wavefronts' next one is, and a lane's position after the last of those is at least the smaller of the two
+            // rows (positions only grow).  That is a block late, and a ring of two reaches of a block would wait for itself:
+            // one block can take every lane as far as the ring lets it.  There, where the next blocks are neighbours, the row of
+            // the wavefront with the later one is taken: it expanded the last of them, and its row, written behind its number and
+            // read before it, holds no more than that block.  (Four reaches leave the lane that is furthest behind room for a
+            // block whatever is late; the exact row there cost 0.8 % of a ResNet-50's decoding.)  Once no more blocks will be
+            // logged and all have been expanded, every stream is complete (the row of the wavefront that did not expand the
+            // last block stays behind).
             const uint32_t block_a = uniform(logged_next.y), block_b = uniform(next_1);
             const bool last_pass = uniform(over_v) && uniform(logged_next.x) <= min(block_a, block_b);
-            const uint32_t newest = block_a > block_b ? next_a : next_b, lesser = min(next_a, next_b);
-            const uint32_t next = last_pass ? 0xFFFFFFFFu : max(block_a, block_b) - min(block_a, block_b) == 1u ? newest : lesser;
+            uint32_t next = min(next_a, next_b);
+            if constexpr (kRingElems < 4u * kBlockLookups * kLookaheadMaxSymbols * kWave) {
+                const uint32_t newest = block_a > block_b ? next_a : next_b;
+                next = max(block_a, block_b) - min(block_a, block_b) == 1u ? newest : next;
+            }
+            next = last_pass ? 0xFFFFFFFFu : next;
             const uint32_t before = mine;
             while (mine + kSlab <= n && __ballot(next < mine + kSlab) == 0) {
                 store_slab(mine);

@@ -206,12 +206,12 @@ class Chunk:
         if self.done_s[s]:
             return False
         last_pass = self.over and self.published <= min(self.next)
-        # Neighbouring next blocks: the row of the wavefront that expanded the last block.  A wavefront publishes its next block
+        # A ring of fewer than four reaches of a block and neighbouring next blocks: the row of the wavefront that expanded the last block.  A wavefront publishes its next block
         # before its row, and the kernel reads the rows before the numbers, so a row may be older than the numbers say (here:
         # as old as the last time these were looked at).
         rows = self.prog if self.rng.random() < 0.5 else self.rows_seen[s]
         self.rows_seen[s] = [list(r) for r in self.prog]
-        exact = abs(self.next[0] - self.next[1]) == 1
+        exact = self.ring < 4 * self.reach and abs(self.next[0] - self.next[1]) == 1
         newest = rows[0] if self.next[0] > self.next[1] else rows[1]
         nxt = [0xFFFFFFFF] * self.N if last_pass else newest if exact else [min(a, b) for a, b in zip(*rows)]
         assert all(p <= q for p, q in zip(nxt, self.expanded())) or last_pass, "positions ahead of what is expanded"
@@ -272,6 +272,7 @@ def test_a_ring_of_two_blocks_never_waits_for_itself(p0, seed):
     follow from the block expanded last, whichever wavefront expanded it."""
     w = W.tiny(seed=seed, n=9000, bitwidth=3, n_streams=8, chunk_size=4096, table_log=9, p0=p0)
     assert _run(w, 1024, 128, 4, 3, seed) == 0
+    assert _run(w, 2048, 128, 8, 3, seed) == 0               # the large geometry: four reaches
 
 
 @pytest.mark.parametrize("seed", [1, 2, 3])
