@@ -274,12 +274,16 @@ _index_of_name = {}
 
 
 def _device_index(torch, device) -> int:
-    """The index of a device named in any way torch knows ("cuda": the current one)."""
+    """The index of a GPU named in any way torch.cuda.device takes ("cuda", None: the current one).  ValueError for any other
+    device: what lies in its memory must not reach a kernel."""
     if type(device) is int:
         return device
     index = _index_of_name.get(device)
     if index is None:
-        index = torch.device(device).index
+        named = torch.device("cuda" if device is None else device)
+        if named.type != "cuda":
+            raise ValueError(f"Expected a cuda device, but got: {named}")
+        index = named.index
         if index is None:
             return torch.cuda.current_device()
         _index_of_name[device] = index
@@ -646,6 +650,7 @@ def pack_layers_device(symbols_dev, layer_sizes: Sequence[int], freqs_dev, table
     Returns (chunks, stream_hdr, payload, used, status) as device tensors (out: the same five, to be reused)."""
     torch = _torch()
     dev = symbols_dev.device
+    _device_index(torch, dev)                             # (refused before anything is prepared for it)
     sizes = [int(n) for n in layer_sizes]
     css = [int(chunk_size)] * len(sizes) if np.isscalar(chunk_size) else [int(c) for c in chunk_size]
     jobs = pack_jobs(sizes, css)
