@@ -27,6 +27,11 @@ def test_bounds_and_jobs_of_a_set(table_log, n_streams):
     assert len(B.pack_jobs([], [])) == 0
 
 
+def test_sizes_of_layers_that_are_not_there():
+    assert B.pack_jobs([5, 6], [2, 3, 0, -1]).tobytes() == B.pack_jobs([5, 6], [2, 3]).tobytes()
+    assert len(B.pack_jobs([], [7])) == 0
+
+
 def test_what_a_field_cannot_hold_is_refused():
     for sizes, chunks, error in (([-1], [4], OverflowError), ([4], [-4], OverflowError), ([4], [1 << 32], OverflowError),
                                  ([1 << 33, 1], [1, 1], OverflowError), ([4], [0], ZeroDivisionError)):
