@@ -628,7 +628,7 @@ def pack_jobs(layer_sizes: Sequence[int], chunk_sizes: Sequence[int]) -> np.ndar
     jobs = np.zeros(len(layer_sizes), dtype=JOB_DTYPE)
     if len(jobs) == 0:
         return jobs
-    chunk_sizes = chunk_sizes[:len(jobs)]                 # (sizes of layers that are not there are not looked at)
+    chunk_sizes = list(chunk_sizes)[:len(jobs)]           # (sizes of layers that are not there are not looked at)
     counts = [(n + cs - 1) // cs for n, cs in zip(layer_sizes, chunk_sizes)]
     if min(layer_sizes) < 0 or min(chunk_sizes) < 0 or sum(layer_sizes) >= 1 << 63 or max(max(chunk_sizes), sum(counts)) >= 1 << 32:
         raise OverflowError("layer sizes are unsigned 64-bit numbers, chunk sizes and chunk counts unsigned 32-bit ones")
@@ -653,7 +653,7 @@ def pack_layers_device(symbols_dev, layer_sizes: Sequence[int], freqs_dev, table
     dev = symbols_dev.device
     _device_index(torch, dev)                             # (refused before anything is prepared for it)
     sizes = [int(n) for n in layer_sizes]
-    css = [int(chunk_size)] * len(sizes) if np.isscalar(chunk_size) else [int(c) for c in chunk_size[:len(sizes)]]
+    css = [int(chunk_size)] * len(sizes) if np.isscalar(chunk_size) else [int(c) for c in chunk_size][:len(sizes)]
     jobs = pack_jobs(sizes, css)
     n_chunks = sum((n + c - 1) // c for n, c in zip(sizes, css))
     if sizes:                                             # (refuses what the arguments' ranges refuse)

@@ -29,6 +29,7 @@ def test_bounds_and_jobs_of_a_set(table_log, n_streams):
 
 def test_sizes_of_layers_that_are_not_there():
     assert B.pack_jobs([5, 6], [2, 3, 0, -1]).tobytes() == B.pack_jobs([5, 6], [2, 3]).tobytes()
+    assert B.pack_jobs([5, 6], iter([2, 3])).tobytes() == B.pack_jobs([5, 6], [2, 3]).tobytes()
     assert len(B.pack_jobs([], [7])) == 0
 
 
