@@ -87,9 +87,10 @@ extern "C" {
 #define ANSZP_OUT_BF16        2     /* bfloat16, round-to-nearest-even of the binary32 value    */
 
 /* One chunk (32 bytes).  Arrays of these live in device memory for anszp_decode.  A descriptor
-   names everything its chunk touches, so the array may be in any order: workgroups are handed
-   out in array order, and a launch whose chunks differ much in size ends sooner when the chunks
-   with the most payload words come first. */
+   names everything its chunk touches, so the array may be in any order.  Layer after layer, as the
+   packers leave it, is the order to prefer: the chunks of a layer that stand together share its table.
+   (A launch of few chunks that differ much in size, without a plan, ends sooner when the chunks with
+   the most payload words come first; a plan and the kernel for many short chunks see to that themselves.) */
 typedef struct {
     uint32_t layer_id;        /* selects the table and the anszp_layer_t                       */
     uint32_t n_symbols;       /* symbols in this chunk; stream k holds ceil((n_symbols-k)/N)   */

@@ -2212,16 +2212,19 @@ __global__ __launch_bounds__(256) void dequant_runs_kernel(const uint8_t* sym, u
     }
 }
 
+// What a launch would be: checks of the arguments, the kernel's parameters, which kernel.
+struct LaunchChoice { bool stepwise, byte_table, shared, streaming, small, per_channel, split; WavesShape waves; };
+
 template <int OUT>
-void launch_decode(const DecodeParams& p, uint32_t n_chunks, bool per_channel, bool stepwise, bool shared, bool streaming,
-                   bool small, bool byte_table, bool split, const WavesShape& waves, hipStream_t s) {
-    if (waves.waves) {
-        hipLaunchKernelGGL(decode_waves<OUT>, dim3(std::min(n_chunks, device_cus())), dim3(waves.waves * kWave), 0, s, p, waves.own);
-    } else if (split) {
+void launch_decode(const DecodeParams& p, const LaunchChoice& k, hipStream_t s) {
+    const uint32_t n_chunks = p.n_chunks;
+    if (k.waves.waves) {
+        hipLaunchKernelGGL(decode_waves<OUT>, dim3(std::min(n_chunks, device_cus())), dim3(k.waves.waves * kWave), 0, s, p, k.waves);
+    } else if (k.split) {
         hipLaunchKernelGGL(decode_split<OUT>, dim3(n_chunks), dim3(kSplitThreads), 0, s, p);
-    } else if (byte_table) {
+    } else if (k.byte_table) {
         hipLaunchKernelGGL(decode_byte_table<OUT>, dim3((n_chunks + kByteWaves - 1) / kByteWaves), dim3(kByteWaves * kWave), 0, s, p);
-    } else if (stepwise && streaming) {
+    } else if (k.stepwise && k.streaming) {
         // chunks dealt evenly to as many workgroups as fill whole rounds of the device's CUs
         const uint32_t per_round = device_cus() * uint32_t(kStreamDecoders);
         const uint32_t rounds = (n_chunks + per_round - 1u) / per_round;
@@ -2230,21 +2233,18 @@ void launch_decode(const DecodeParams& p, uint32_t n_chunks, bool per_channel, b
             hipLaunchKernelGGL((decode_streaming<OUT, true>), dim3(groups), dim3(kStreamWaves * kWave), 0, s, p, n_chunks, groups);
         else
             hipLaunchKernelGGL((decode_streaming<OUT, false>), dim3(groups), dim3(kStreamWaves * kWave), 0, s, p, n_chunks, groups);
-    } else if (stepwise && shared)
+    } else if (k.stepwise && k.shared)
         hipLaunchKernelGGL(decode_stepwise_shared<OUT>, dim3((n_chunks + kSharedWaves - 1) / kSharedWaves),
                            dim3(kSharedWaves * kWave), 0, s, p, n_chunks);
-    else if (stepwise) hipLaunchKernelGGL(decode_stepwise<OUT>, dim3(n_chunks), dim3(kWave), 0, s, p);
+    else if (k.stepwise) hipLaunchKernelGGL(decode_stepwise<OUT>, dim3(n_chunks), dim3(kWave), 0, s, p);
     else {
         const dim3 grid(mapped_workgroups(n_chunks));
-        if (small && per_channel) hipLaunchKernelGGL((decode_merged_small<OUT, true>), grid, dim3(kBlock), 0, s, p);
-        else if (small) hipLaunchKernelGGL((decode_merged_small<OUT, false>), grid, dim3(kBlock), 0, s, p);
-        else if (per_channel) hipLaunchKernelGGL((decode_merged<OUT, true>), grid, dim3(kBlock), 0, s, p);
+        if (k.small && k.per_channel) hipLaunchKernelGGL((decode_merged_small<OUT, true>), grid, dim3(kBlock), 0, s, p);
+        else if (k.small) hipLaunchKernelGGL((decode_merged_small<OUT, false>), grid, dim3(kBlock), 0, s, p);
+        else if (k.per_channel) hipLaunchKernelGGL((decode_merged<OUT, true>), grid, dim3(kBlock), 0, s, p);
         else hipLaunchKernelGGL((decode_merged<OUT, false>), grid, dim3(kBlock), 0, s, p);
     }
 }
-
-// What a launch would be: checks of the arguments, the kernel's parameters, which kernel.
-struct LaunchChoice { bool stepwise, byte_table, shared, streaming, small, per_channel, split; WavesShape waves; };
 
 int choose_launch(const anszp_decode_args_t* a, int mode, DecodeParams& p, LaunchChoice& k);
 
@@ -2278,9 +2278,9 @@ int decode_impl(const anszp_decode_args_t* a, int mode, void* hip_stream, uint32
     }
     p.plan = lookahead ? plan : nullptr;
     switch (a->out_dtype) {
-        case ANSZP_OUT_U8: launch_decode<ANSZP_OUT_U8>(p, nc, k.per_channel, k.stepwise, k.shared, k.streaming, k.small, k.byte_table, k.split, k.waves, s); break;
-        case ANSZP_OUT_F32: launch_decode<ANSZP_OUT_F32>(p, nc, k.per_channel, k.stepwise, k.shared, k.streaming, k.small, k.byte_table, k.split, k.waves, s); break;
-        default: launch_decode<ANSZP_OUT_BF16>(p, nc, k.per_channel, k.stepwise, k.shared, k.streaming, k.small, k.byte_table, k.split, k.waves, s); break;
+        case ANSZP_OUT_U8: launch_decode<ANSZP_OUT_U8>(p, k, s); break;
+        case ANSZP_OUT_F32: launch_decode<ANSZP_OUT_F32>(p, k, s); break;
+        default: launch_decode<ANSZP_OUT_BF16>(p, k, s); break;
     }
     return hipGetLastError() == hipSuccess ? ANSZP_OK : ANSZP_E_HIP;
 }
@@ -2333,11 +2333,11 @@ int choose_launch(const anszp_decode_args_t* a, int mode, DecodeParams& p, Launc
     // From two to four chunks per CU only short ones: 540 to 900 chunks of 367 words, 2^12 states 17 -> 13 us, of 570
     // words 20 either way; with the small geometry 115 words 10 -> 8, 288 words 11.2 to 12.9 and 11.7 to 12.0, 367 words 12 to 16
     // and 15.
-    k.waves = WavesShape{0u, 0u};
+    k.waves = WavesShape{};
     const uint64_t per_layer = a->n_chunks / a->n_tables, cus = p.n_cus;
     if (mode == 0 && !k.stepwise && !k.split && per_layer >= 8u &&
         (a->n_chunks > 4u * cus || (a->n_chunks > 2u * cus && mean_words <= (k.small ? 256u : 450u)))) {
-        k.waves = waves_shape(a->table_log, mean_words);
+        k.waves = waves_shape(a->table_log, a->n_streams, mean_words);
         if (k.waves.waves == 8u && per_layer < 24u) k.waves.waves = 0u;
     }
     return ANSZP_OK;

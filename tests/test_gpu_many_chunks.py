@@ -104,3 +104,75 @@ def test_streams_that_do_not_end_where_they_should(orc):
     st = d.read_status()
     assert st[0] & (B.ST_BAD_STATE | B.ST_BAD_LENGTH) and st[1] <= 1100
     assert bool((buf[:64] == 0x5A5A).all()) and bool((buf[64 + n:] == 0x5A5A).all())
+
+
+# ---- descriptors in any order, chunks of any size: shares of equal weight, layer after layer, instead of descriptors in a row
+def _in_order(d, order):
+    c = d.host.chunks
+    if order == "shuffled":
+        idx = np.random.default_rng(len(c)).permutation(len(c))
+    elif order == "most words first":
+        idx = np.argsort(-c["payload_words"].astype(np.int64), kind="stable")
+    else:                                                            # the layers' chunks in turn
+        idx = np.argsort(np.concatenate([np.arange(k) for k in np.bincount(c["layer_id"])]), kind="stable")
+    d.chunks.copy_(torch.from_numpy(np.ascontiguousarray(c[idx]).view(np.uint8).reshape(-1).copy()))
+
+
+def _check_order(orc, w, dtype, order):
+    """Bit for bit; then, with a stream's length wrong in every chunk, every chunk is reported once: none is left out or decoded twice."""
+    c = oracle_encode(orc, w)
+    assert c.n_chunks >= 1025 and c.n_chunks >= 8 * len(w.layers)
+    _, expect = oracle_expected(orc, c, w, dtype)
+    d = B.to_device(host_from_oracle(c, w))
+    _in_order(d, order)
+    out = B.alloc_out(d, dtype)
+    args = B.decode_args(d, out, dtype)
+    out.view(torch.uint8).fill_(0xA5)
+    B.decode_raw(args, d.device)
+    assert d.read_status() == (0, 0)
+    bad = np.nonzero(B.bits_of(out)[:w.numel] != expect)[0]
+    assert len(bad) == 0, f"{len(bad)} mismatches, first at {bad[:5]}"
+    h = d.host.stream_hdr.copy()
+    h[::w.n_streams] += 1 << 16
+    d.stream_hdr.copy_(torch.from_numpy(h.view(np.uint8).copy()))
+    B.decode_raw(args, d.device)
+    st = d.read_status()
+    assert st[1] == c.n_chunks and st[0] & B.ST_BAD_DESC, st[:2]
+
+
+@pytest.mark.parametrize("order", ["shuffled", "most words first", "in turn"])
+@pytest.mark.parametrize("table_log,n_streams,chunk,n_layers,chunks,p0", [
+    (12, 64, 1024, 48, 23, 0.6),              # few chunks a workgroup
+    (9, 17, 100, 7, 1290, 0.5),               # more than are sorted at once
+    (12, 64, 4096, 130, 9, 0.8), (10, 33, 1000, 2, 600, 0.7), (11, 1, 500, 48, 30, 0.6),
+])
+def test_descriptors_in_any_order(orc, order, table_log, n_streams, chunk, n_layers, chunks, p0):
+    layers = [W.Layer(f"l{i}", ((chunks - i % 3) * chunk - (i * 37) % 99,), 4, 8, 0.01 + 0.001 * i, W.peaked_geometric_pmf(16, 8, p0 + 0.39 * (i % 7) / 7), 5 + i)
+              for i in range(n_layers)]
+    w = W.Workload("order", layers, table_log, n_streams, chunk, "bf16")
+    _check_order(orc, w, ("bf16", "u8", "f32")[chunk % 3], order)
+
+
+@pytest.mark.parametrize("order", ["shuffled", "most words first", "in turn"])
+@pytest.mark.parametrize("table_log,n_streams,chunk", [(12, 64, 8192), (10, 16, 16384), (12, 8, 5000)])
+def test_long_chunks_among_short_ones(orc, order, table_log, n_streams, chunk):
+    """8 bits a symbol beside a tenth: the long ones take a turn of their own, several at a time."""
+    pmfs = [W.peaked_geometric_pmf(16, 8, 0.985)] * 2 + [np.ones(256) / 256, W.laplace_pmf(256, 128, 7.0)] + [W.peaked_geometric_pmf(16, 8, 0.97)] * 2
+    sizes = [300 * chunk, 250 * chunk - 5, 40 * chunk, 30 * chunk - 77, 400 * chunk, 100 * chunk]
+    layers = [W.Layer(f"l{i}", (n,), 8, 8, 0.02, pmf, 5 + i) for i, (n, pmf) in enumerate(zip(sizes, pmfs))]
+    _check_order(orc, W.Workload("long", layers, table_log, n_streams, chunk, "bf16"), "bf16", order)
+
+
+def test_chunks_of_more_words_than_a_workgroup_holds(orc):
+    """32,768 words: one symbol at a time from memory, as in every kernel whose window they exceed; 16,384: alone in LDS."""
+    chunk = 131072
+    layers = [W.Layer("thin", (1030 * chunk,), 8, 8, 0.02, W.peaked_geometric_pmf(16, 8, 0.998), 5), W.Layer("long", (2 * chunk,), 8, 8, 0.02, np.ones(256) / 256, 6),
+              W.Layer("half", (2 * chunk,), 8, 8, 0.02, W.laplace_pmf(16, 8, 4.0), 7)]
+    _check_order(orc, W.Workload("window", layers, 12, 64, chunk, "u8"), "u8", "most words first")
+
+
+@pytest.mark.parametrize("singles,rest", [(150, 1200), (11, 1100)])
+def test_layers_of_one_chunk_in_a_row(orc, singles, rest):
+    sizes = [rest // 2 * 1024] + [1024 - i % 7 for i in range(singles)] + [rest // 2 * 1024 - 3]
+    layers = [W.Layer(f"l{i}", (n,), 4, 8, 0.01 + 0.001 * i, W.peaked_geometric_pmf(16, 8, 0.5 + 0.003 * (i % 99)), 5 + i) for i, n in enumerate(sizes)]
+    _check(orc, W.Workload("singles", layers, 12, 64, 1024, "bf16"), "bf16")
