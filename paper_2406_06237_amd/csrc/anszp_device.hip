@@ -2246,7 +2246,7 @@ void launch_decode(const DecodeParams& p, const LaunchChoice& k, hipStream_t s) 
     }
 }
 
-int choose_launch(const anszp_decode_args_t* a, int mode, DecodeParams& p, LaunchChoice& k);
+int choose_launch(const anszp_decode_args_t* a, int mode, bool planned, DecodeParams& p, LaunchChoice& k);
 
 // plan: null, or device memory written by plan_units for these arrays (used by the look-ahead kernel only);
 // plan_only: write the plan instead of decoding
@@ -2256,7 +2256,7 @@ int decode_impl(const anszp_decode_args_t* a, int mode, void* hip_stream, uint32
     if (a->n_chunks == 0) return ANSZP_OK;
     DecodeParams p;
     LaunchChoice k;
-    const int rc = choose_launch(a, mode, p, k);
+    const int rc = choose_launch(a, mode, plan || plan_only, p, k);
     if (rc != ANSZP_OK) return rc;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const uint32_t nc = static_cast<uint32_t>(a->n_chunks);
@@ -2285,7 +2285,7 @@ int decode_impl(const anszp_decode_args_t* a, int mode, void* hip_stream, uint32
     return hipGetLastError() == hipSuccess ? ANSZP_OK : ANSZP_E_HIP;
 }
 
-int choose_launch(const anszp_decode_args_t* a, int mode, DecodeParams& p, LaunchChoice& k) {
+int choose_launch(const anszp_decode_args_t* a, int mode, bool planned, DecodeParams& p, LaunchChoice& k) {
     if (!a->tables || !a->chunks || !a->stream_hdr || !a->layers || !a->out || !a->status) return ANSZP_E_NULL;
     if (!a->payload && a->payload_words) return ANSZP_E_NULL;
     if (a->table_log < 1 || a->table_log > ANSZP_MAX_TABLE_LOG || a->n_streams < 1 ||
@@ -2328,15 +2328,23 @@ int choose_launch(const anszp_decode_args_t* a, int mode, DecodeParams& p, Launc
               (a->n_chunks <= p.n_cus || bits >= 16384u);
     if (k.split) k.stepwise = k.streaming = false;
     // More chunks than the look-ahead kernel decodes at once (two per workgroup): a wavefront per chunk and a table staged
-    // once per workgroup and layer, where the chunks' words fit and a layer has chunks enough for a workgroup's share to be of
+    // once per workgroup and layer, where the chunks' words fit and there are chunks enough for a workgroup's share to be of
     // few layers (24 a layer where only eight wavefronts fit a CU: 130 layers of 12 chunks of 1,600 words 70 us, 84 this way).
-    // From two to four chunks per CU only short ones: 540 to 900 chunks of 367 words, 2^12 states 17 -> 13 us, of 570
-    // words 20 either way; with the small geometry 115 words 10 -> 8, 288 words 11.2 to 12.9 and 11.7 to 12.0, 367 words 12 to 16
-    // and 15.
+    // Up to four chunks per CU only short ones, and with a plan, which spares the look-ahead kernel its search, fewer still.
+    // 16 layers of 544 to 992 chunks, layers in a row and descriptors in any order, times as fast as the look-ahead kernel:
+    //   2^12 states, without a plan                  1.4 to 3.4 (few streams or 65,536 symbols 1.0 to 1.6)     1.3 to 2.4 (1.0)
+    //   2^12 states, with one, up to 480 bits a stream    1.1 to 1.8 (once 0.91)      1.04 to 1.9
+    //     more bits or more than 8,192 symbols       0.72 to 1.4                      0.72 to 2
+    //   small geometry, without, up to 512 bits and symbols a stream     1.2 to 2.4   1.04 to 1.6
+    //     longer streams                             0.72 to 1.3                      0.9 to 1.5
+    //   small geometry, with one                     0.68 to 1.3                      0.67 to 1.2 (so: never)
+    // 1,120 chunks: 0.96 to 2 but for 1,870 bits a stream with a plan in the small geometry, 0.77.
     k.waves = WavesShape{};
-    const uint64_t per_layer = a->n_chunks / a->n_tables, cus = p.n_cus;
-    if (mode == 0 && !k.stepwise && !k.split && per_layer >= 8u &&
-        (a->n_chunks > 4u * cus || (a->n_chunks > 2u * cus && mean_words <= (k.small ? 256u : 450u)))) {
+    const uint64_t per_layer = a->n_chunks / a->n_tables, cus = p.n_cus, N = a->n_streams, symbols = a->out_elems / a->n_chunks;
+    const bool short_enough = a->n_chunks > 4u * cus ? !(planned && k.small && a->n_chunks <= 6u * cus && bits > 1024u * N)
+                              : k.small              ? !planned && mean_words <= 256u && bits <= 512u * N && symbols <= 512u * N
+                                                     : mean_words <= 450u && (!planned || (bits <= 480u * N && symbols <= 8192u));
+    if (mode == 0 && !k.stepwise && !k.split && per_layer >= 8u && a->n_chunks > 2u * cus && short_enough) {
         k.waves = waves_shape(a->table_log, a->n_streams, mean_words);
         if (k.waves.waves == 8u && per_layer < 24u) k.waves.waves = 0u;
     }
