@@ -9,7 +9,7 @@
 // started together in different states the true one meets some after about 2 L / G bits, so a few dozen starts
 // hit within a fraction of that.  So:
 //   1  The stream is cut into `cuts` segments of equal length in bits and a short last one.  At every cut, a group of
-//      1024 / cuts threads starts in as many states and walks one segment.  Where the group stands at the next cut
+//      1024 / cuts threads starts in as many places and walks one segment.  Where the group stands at the next cut
 //      (its first look-up at or behind it: state and bit) are the places, mostly two to ten different ones, at which
 //      the true walk is expected there.  They are the nodes of a graph.
 //   2  Every node is walked through its segment once more, which leads to a node of the next cut, or to a place that is
@@ -21,10 +21,12 @@
 //      are walked again from states noted on the way, into a buffer in LDS, which leaves in 16-byte stores.
 // The first walk is bound by the instructions of sixteen wavefronts, the others by one LDS round trip per look-up.
 // Everything is held together by barriers: no wavefront waits for another's progress.
-// Measured (one chunk, fp32 out, as one chain in the look-ahead kernel -> here): 36,864 symbols of 1.2 bits, 2^10 states
-// 504 -> 52 us (first walk 16, walks of the nodes 11 + 12 in two rounds, following the links 2, writing 4, storing 2);
-// 2^12 states 500 -> 101 (six rounds); 2.8 bits, 2^12 states 1429 -> 147; 9,000 symbols of 1.2 bits, 2^10 states 129 -> 33;
-// 2,500 of them 41 -> 21.
+// Measured (one chunk, fp32 out, as one chain in the look-ahead kernel -> here, the mean of twelve): 36,864 symbols of 1.2 bits,
+// 2^10 states 504 -> 51 us (42 to 60; 16 of them the first walk, about 10 a round, mostly two), 2^12 states 500 -> 75; 2.8 bits,
+// 2^12 states 1430 -> 120; 12,000 symbols of 1.2 bits, 2^10 states 171 -> 34; 2,500 of them 41 -> 21.
+// Where walks hardly meet, frequencies of (nearly) powers of two, 2^12 states: 64 chunks of 12,000 symbols, 2 of them alike 320 -> 411,
+// 16 alike 474 -> 448 (471 and 610 with all starts in spread states and the walk that is short of instructions); 200 chunks of
+// half, quarter, quarter 323 -> 477 (563), which is the worst there is; 64 alike 473 -> 230, 2^9 states 16 alike 473 -> 65.
 #ifndef ANSZP_SPLIT_H
 #define ANSZP_SPLIT_H
 
@@ -38,7 +40,7 @@ constexpr uint32_t kSplitMaxNodes = 1600u;                // no more, and as man
 constexpr uint32_t kSplitUnknown = 0xFFFFFFFFu, kSplitNone = 0xFFFFFFFEu;
 constexpr uint32_t kSplitMinBits = 2048u;
 constexpr uint32_t kSplitPad = 10u;                       // words beside the stream's: one before it, zeros behind (a walk that must stop
-                                                          // at the stream's end may make four look-ups more and read two words there)
+                                                          // at the stream's end may make four look-ups more and read three words there)
 
 // A place in a stream: the next look-ahead entry (13 bits) and the bit it stands at, plus 31 (19 bits).
 static_assert(kSplitWords * 32u + 31u + 32u < (1u << 19) && ANSZP_MAX_TABLE_LOG + 1 <= 13, "a place is one word");
@@ -124,8 +126,13 @@ __global__ __launch_bounds__(kSplitThreads) void decode_split(DecodeParams p) {
         const uint32_t g = tid / per_group, r = tid % per_group;
         uint32_t place = kSplitUnknown;
         if (g != 0u || r == 0u) {
-            uint32_t at = at_of(g == 0u ? first_place : 2u * (((2u * r + 1u) * L / (2u * per_group)) & (L - 1u)) + next_bit(g * seg));
-            uint32_t q = q0 + g * seg, count = 0;
+            // The first eight start in the stream's own initial state at eight bits in a row, the others in states spread evenly: with
+            // frequencies that are powers of two, or nearly, a state keeps its upper bits for ever, or long, and every symbol takes as many bits.
+            const bool own = r < 8u;
+            const uint32_t state = own ? hdr & (L - 1u) : ((2u * r + 1u) * L / (2u * per_group)) & (L - 1u);
+            const uint32_t b = g * seg + (own ? r : 0u);
+            uint32_t at = at_of(g == 0u ? first_place : 2u * state + next_bit(b));
+            uint32_t q = q0 + b, count = 0;
             walk_entries<kWalkCount>(at, q, count, q0 + (g + 1u) * seg, len);
             place = place_of(at, q);
         }
@@ -172,7 +179,7 @@ __global__ __launch_bounds__(kSplitThreads) void decode_split(DecodeParams p) {
             uint32_t at = at_of(at_node(kNodePlace, id)), q = q_of(at_node(kNodePlace, id)), count = 0;
 #pragma unroll 1
             for (uint32_t m = 0; m < kSplitParts; ++m) {
-                walk_entries<kWalkCount>(at, q, count, q0 + cut * seg + (m + 1u) * seg / kSplitParts, len);
+                walk_entries<kWalkCount, true>(at, q, count, q0 + cut * seg + (m + 1u) * seg / kSplitParts, len);
                 if (m + 1u < kSplitParts) {
                     at_node(kNodePartPlace + m, id) = place_of(at, q);
                     at_node(kNodePartCount + m, id) = count;
@@ -183,8 +190,15 @@ __global__ __launch_bounds__(kSplitThreads) void decode_split(DecodeParams p) {
             at_node(kNodeCount, id) = count;
             uint32_t link = kSplitNone;
             const uint32_t size = S.group_size[cut];
-            for (uint32_t j = 0; j < size; ++j)
-                if (S.group[cut * per_group + j] == place) { link = S.group_first[cut] + j; break; }
+            // (four at a time and without a way out, so that the reads do not wait for each other; behind `size` lies what was there)
+            const uint4* const known = reinterpret_cast<const uint4*>(&S.group[cut * per_group]);
+            uint32_t found = size;
+#pragma unroll 4
+            for (uint32_t j = 0; j < size; j += 4u) {
+                const uint4 o = known[j / 4u];
+                found = min(found, o.x == place ? j : o.y == place ? j + 1u : o.z == place ? j + 2u : o.w == place ? j + 3u : size);
+            }
+            if (found < size) link = S.group_first[cut] + found;
             if (link == kSplitNone) {
                 const uint32_t fresh = atomicAdd(&S.n_nodes, 1u);
                 if (fresh < n_shared) {
@@ -265,7 +279,7 @@ __global__ __launch_bounds__(kSplitThreads) void decode_split(DecodeParams p) {
         if (count < until && count + skew < first + end) {
             const uint32_t to = lds_address(buf) + skew - first - 1u;      // the symbol that ends a look-up is number count - 1 after it
             uint32_t address = to + count;
-            walk_entries<kWalkWrite>(at, q, address, q0 + total + 1u, to + min(until, first + end - skew));
+            walk_entries<kWalkWrite, true>(at, q, address, q0 + total + 1u, to + min(until, first + end - skew));
             count = address - to;
         }
         __syncthreads();

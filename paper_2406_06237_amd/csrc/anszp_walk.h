@@ -23,9 +23,9 @@ __device__ __forceinline__ uint4 walk_entry_pair(const uint4& e, uint32_t table_
 // look-up in all), by those instructions with four.  As the compiler had it, 20 instructions with the loads at the loop's
 // head, a look-up took twice as long.
 // ALONE: for a wavefront that has its SIMD to itself, or nearly.  There the words stand between the second look-up of a window and
-// the next (they are asked for where that look-up's bits are known): 50 ns a look-up.  With a window of two registers that lasts for
-// four, and the next one asked for a look-up early and shifted by what that one reads, only the entry's round trip is left, for
-// one instruction and a half more a look-up.
+// the next (they are asked for where that look-up's bits are known): 50 ns a look-up.  A window of two registers lasts for four,
+// and the next one is asked for a look-up early and shifted by what that one reads: 45 ns, for one instruction and a half more a
+// look-up, which four wavefronts on a SIMD would feel.
 enum { kWalkCount, kWalkWrite, kWalkSpread };
 template <int MODE, bool ALONE = false>
 __device__ __forceinline__ void walk_entries(uint32_t& at, uint32_t& q, uint32_t& n, uint32_t q_end, uint32_t n_end, uint32_t step = 1u) {

@@ -52,6 +52,22 @@ def test_long_streams_and_odd_distributions(orc, dtype, table_log, n, pmf):
     _decode(orc, [W.Layer("one", (n,), 8, 8, 0.02, np.asarray(pmf), 11)], table_log, 1 << 20, dtype)
 
 
+class _Exact(W.Layer):
+    """Every symbol exactly as often as its share says, so that frequencies which are powers of two stay that."""
+    def symbols(self):
+        sym = np.repeat(np.arange(len(self.pmf)), (np.asarray(self.pmf) * self.numel).astype(int)).astype(np.uint8)
+        assert len(sym) == self.numel
+        return np.random.default_rng(self.seed).permutation(sym)
+
+
+@pytest.mark.parametrize("table_log,pmf", [(r, q) for r in (5, 9, 12) for q in ([0.5, 0.5], [0.25] * 4, [1 / 16] * 16, [0.5, 0.25, 0.25],
+                                                                             [0.25, 0.25] + [1 / 16] * 8, [1 / 256] * 256) if len(q) <= 1 << r])
+def test_states_that_never_meet(orc, table_log, pmf):
+    """A state keeps its upper bits: walks meet in the stream's own class of states and at its own bits, or not at all."""
+    for n, chunk in ((12288, 1 << 20), (5 * 12288, 12288)):
+        _decode(orc, [_Exact("one", (n,), 8, 0, 0.02, np.asarray(pmf), 11)], table_log, chunk, "f32")
+
+
 @pytest.mark.parametrize("planned", [False, True])
 @pytest.mark.parametrize("dtype", ["u8", "f32", "bf16"])
 def test_several_chunks_at_odd_offsets(orc, dtype, planned):
