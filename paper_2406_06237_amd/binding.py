@@ -648,7 +648,10 @@ def pack_layers_device(symbols_dev, layer_sizes: Sequence[int], freqs_dev, table
                        payload_cap_words: Optional[int] = None, out=None):
     """anszp_pack_layers_device on torch's current stream: symbols_dev a uint8 tensor holding the layers one after the
     other, freqs_dev an int32 tensor [n_layers, 256], both on the GPU; chunk_size: one for all layers or one per layer.
-    Returns (chunks, stream_hdr, payload, used, status) as device tensors (out: the same five, to be reused)."""
+    Returns (chunks, stream_hdr, payload, used, status) as device tensors (out: the same five, to be reused).
+
+    Like every call here it returns before the GPU is done: what it returns is valid in order on the current stream, another
+    stream has to wait for it first (an event, a synchronisation), and so has whoever overwrites the symbols or frequencies there."""
     torch = _torch()
     dev = symbols_dev.device
     _device_index(torch, dev)                             # (refused before anything is prepared for it)

@@ -135,6 +135,41 @@ def test_whole_sets_in_one_call_equal_the_oracles_container(orc, name):
     assert np.all(payload[used:] == 0xFFFFFFFF)
 
 
+def _same(c, w, out):
+    chunks, hdr, payload, used, status = (t.cpu().numpy() for t in out)
+    nc = c.n_chunks
+    assert tuple(status) == (0, 0) and int(used[0]) == len(c.payload)
+    assert np.array_equal(payload.view(np.uint32)[:len(c.payload)], c.payload) and np.array_equal(hdr.view(np.uint32)[:nc * w.n_streams], c.stream_hdr)
+    assert np.array_equal(chunks.view(B.CHUNK_DTYPE)["payload_offset"][:nc], c.chunk_payload_off)
+    assert np.array_equal(chunks.view(B.CHUNK_DTYPE)["out_offset"][:nc], c.chunk_out_off)
+
+
+def test_a_whole_set_is_packed_in_order_on_its_stream(orc):
+    """The call does not wait: another stream that waits for an event behind it reads the whole container, and what stands behind
+    the call on its own stream may overwrite the symbols."""
+    w = W.config2()
+    from helpers import oracle_encode
+    c = oracle_encode(orc, w)
+    syms = w.symbols()
+    host = torch.from_numpy(np.concatenate(syms)).pin_memory()
+    f = torch.from_numpy(np.ascontiguousarray(c.freqs, dtype=np.uint32).view(np.int32)).to("cuda:0")
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for _ in range(5):
+        with torch.cuda.stream(a):
+            s = host.to("cuda:0", non_blocking=True)
+            out = B.pack_layers_device(s, [len(x) for x in syms], f, w.table_log, w.n_streams, w.chunk_size)
+            done = torch.cuda.Event()
+            done.record()
+            s.zero_()
+        with torch.cuda.stream(b):
+            b.wait_event(done)
+            copies = [t.clone() for t in out]
+        b.synchronize()
+        _same(c, w, copies)
+    torch.cuda.synchronize()
+
+
 def test_whole_set_error_bits_and_rate(orc):
     w = W.config3()
     syms = w.symbols()
