@@ -387,10 +387,12 @@ __global__ __launch_bounds__(kThreads, 4) void encode_write(EncParams p) {
 // What stands between two states is then all the walking wavefront does (one LDS read, three instructions: 40 ns a
 // symbol; 83 with the bits laid down in between, after 54 for a walk that only counts them).  A stream's bits stay in LDS
 // until it is known how many there are and where the chunk's words begin: every workgroup publishes its chunk's words
-// in the chunk's descriptor and adds up those of the chunks before it (the field reads kUnknown until then).  A workgroup only ever waits for lower-numbered
-// ones, which the chip has started before it; it gives up after a bounded number of looks all the same.  The
-// chunks of those that did, and chunks with a stream longer than its place in LDS, are written by the launch behind
-// this one, with a walk of their own.
+// in the chunk's descriptor and adds up those of the chunks before it (the field reads kUnknown until then).  A workgroup only
+// ever waits for lower-numbered ones, which have usually been started before it.  That is not certain: each of the chip's dies
+// starts its own share in order, and another stream's kernels may hold places on some of them.  So a wait ends after a bounded
+// number of looks (about 25 ms), and the chunks of workgroups that gave up, like chunks with a stream longer than its place in
+// LDS, are written by the launch behind this one, with a walk of their own.  (Three streams that pack beside each other, or a
+// matrix product beside one, never got there: 55 us a pack of 369 chunks of 65,536 symbols, 81 on one stream.)
 // Measured on 369 chunks of 65,536 symbols (2^12 states, 64 streams): 66 us, 7.5 of them the tables, 40 ns a symbol, and 1.4
 // and 4 us for the launches before and behind; with a pass for the sizes, a scan and a pass that writes 71, 5 and 97 (11 of
 // both for the tables then).  One layer of 2.4 M symbols in 144 chunks 24 (23, 5, 29).  (A chunk whose streams do not fit is walked twice and costs what it
@@ -456,7 +458,7 @@ __device__ __forceinline__ bool words_before(const EncParams& p, uint64_t c, uin
     }
     if (sum) atomicAdd(&before, sum);
     __syncthreads();
-    out = before;                                           // (at most 2^9 chunks of at most 2^21 words)
+    out = before;                                           // (at most 2^9 chunks of less than 2^22 words each)
     return gave_up == 0u;
 }
 

@@ -170,6 +170,26 @@ def test_a_whole_set_is_packed_in_order_on_its_stream(orc):
     torch.cuda.synchronize()
 
 
+def test_packing_on_three_streams_beside_each_other(orc):
+    """Workgroups of several packs share the chip: each waits for lower-numbered ones of its own, and every container is whole."""
+    from helpers import oracle_encode
+    jobs = []
+    for i, w in enumerate((W.config2(), W.config3(), W.tiny(seed=5, n=700001, n_streams=48, chunk_size=1400, table_log=11))):
+        c = oracle_encode(orc, w)
+        s = torch.from_numpy(np.concatenate(w.symbols())).to("cuda:0")
+        f = torch.from_numpy(np.ascontiguousarray(c.freqs, dtype=np.uint32).view(np.int32)).to("cuda:0")
+        jobs.append((w, c, s, f, torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    for _ in range(4):
+        outs = []
+        for w, c, s, f, stream in jobs:
+            with torch.cuda.stream(stream):
+                outs.append(B.pack_layers_device(s, [len(x) for x in w.symbols()], f, w.table_log, w.n_streams, w.chunk_size))
+        torch.cuda.synchronize()
+        for (w, c, *_), out in zip(jobs, outs):
+            _same(c, w, out)
+
+
 def test_whole_set_error_bits_and_rate(orc):
     w = W.config3()
     syms = w.symbols()
