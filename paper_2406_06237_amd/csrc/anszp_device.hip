@@ -1097,6 +1097,22 @@ struct Flusher {
             }
         }
     }
+    // The same for 4 symbols (ANSZP_OUT_F32: 16 bytes, so that the lanes' stores lie one behind the other).
+    static __device__ __forceinline__ void store4(const DecodeParams& p, const anszp_layer_t& lay, uint64_t g, uint64_t layer_elem, uint32_t s) {
+        static_assert(OUT == ANSZP_OUT_F32, "16 bytes");
+        float sc[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sc[i] = lay.scale;
+        if constexpr (PER_CHANNEL) {
+            const bool one = lay.channel_len - static_cast<uint32_t>(layer_elem) % lay.channel_len >= 4u;
+            sc[0] = channel_scale(p, lay, layer_elem);
+#pragma unroll
+            for (int i = 1; i < 4; ++i) sc[i] = one ? sc[0] : channel_scale(p, lay, layer_elem + i);
+        }
+        __builtin_nontemporal_store(floats4{dequant(s & 0xFFu, lay.zero_point, sc[0]), dequant((s >> 8) & 0xFFu, lay.zero_point, sc[1]),
+                                            dequant((s >> 16) & 0xFFu, lay.zero_point, sc[2]), dequant(s >> 24, lay.zero_point, sc[3])},
+                                    reinterpret_cast<floats4*>(static_cast<float*>(p.out) + g));
+    }
     // One element (tail of a chunk).
     static __device__ __forceinline__ void store1(const DecodeParams& p, const anszp_layer_t& lay, uint64_t g,
                                                   uint64_t layer_elem, uint32_t sym) {
