@@ -22,11 +22,12 @@
 // The first walk is bound by the instructions of sixteen wavefronts, the others by one LDS round trip per look-up.
 // Everything is held together by barriers: no wavefront waits for another's progress.
 // Measured (one chunk, fp32 out, as one chain in the look-ahead kernel -> here, the mean of twelve): 36,864 symbols of 1.2 bits,
-// 2^10 states 504 -> 51 us (42 to 60; 16 of them the first walk, about 10 a round, mostly two), 2^12 states 500 -> 75; 2.8 bits,
-// 2^12 states 1430 -> 120; 12,000 symbols of 1.2 bits, 2^10 states 171 -> 34; 2,500 of them 41 -> 21.
-// Where walks hardly meet, frequencies of (nearly) powers of two, 2^12 states: 64 chunks of 12,000 symbols, 2 of them alike 320 -> 411,
-// 16 alike 474 -> 448 (471 and 610 with all starts in spread states and the walk that is short of instructions); 200 chunks of
-// half, quarter, quarter 323 -> 477 (563), which is the worst there is; 64 alike 473 -> 230, 2^9 states 16 alike 473 -> 65.
+// 2^10 states 500 -> 50 us (42 to 60; 16 of them the first walk, about 10 a round, mostly two), 2^12 states 496 -> 80; 2.8 bits,
+// 2^12 states 1424 -> 134; 12,000 symbols of 1.2 bits, 2^10 states 169 -> 36; 2,500 of them 41 -> 21.
+// Where a state keeps its upper bits: half, quarter, quarter, 36,864 symbols, 2^9 states 1146 -> 154 (305 at worst; 426 and 1,872 with all
+// starts in spread states).  Where it keeps them for a while, 2^12 states and short streams, the kernel may lose: 64 chunks of 12,000
+// symbols, 2 alike 319 -> 445, 16 alike 472 -> 543, 200 of half, quarter, quarter 322 -> 495, the worst there is (walks that wait for their
+// windows took another 10 %); 64 alike 472 -> 249, 2^9 states 16 alike 472 -> 98.
 #ifndef ANSZP_SPLIT_H
 #define ANSZP_SPLIT_H
 
@@ -47,7 +48,7 @@ static_assert(kSplitWords * 32u + 31u + 32u < (1u << 19) && ANSZP_MAX_TABLE_LOG 
 
 struct SplitLds {
     uint32_t path[kSplitMaxCuts + 1u], start[kSplitMaxCuts + 2u];
-    uint32_t n_nodes, path_cut, forced, err, pad;
+    uint32_t n_nodes, path_cut, forced, err, kept;
     __attribute__((aligned(16))) uint32_t group[kSplitThreads];         // a cut's places, then the different ones among them
     uint32_t group_size[kSplitMaxCuts], group_first[kSplitMaxCuts];
 };
@@ -120,22 +121,32 @@ __global__ __launch_bounds__(kSplitThreads) void decode_split(DecodeParams p) {
     if (tid == 0) {
         at_node(kNodePlace, 0) = first_place; at_node(kNodeCut, 0) = 0u; at_node(kNodeLink, 0) = kSplitUnknown;
         S.n_nodes = 1u;
+        S.kept = 0u;
     }
     __syncthreads();
     if (cuts) {
         const uint32_t g = tid / per_group, r = tid % per_group;
         uint32_t place = kSplitUnknown;
-        if (g != 0u || r == 0u) {
-            // The first eight start in the stream's own initial state at eight bits in a row, the others in states spread evenly: with
-            // frequencies that are powers of two, or nearly, a state keeps its upper bits for ever, or long, and every symbol takes as many bits.
-            const bool own = r < 8u;
-            const uint32_t state = own ? hdr & (L - 1u) : ((2u * r + 1u) * L / (2u * per_group)) & (L - 1u);
-            const uint32_t b = g * seg + (own ? r : 0u);
-            uint32_t at = at_of(g == 0u ? first_place : 2u * state + next_bit(b));
-            uint32_t q = q0 + b, count = 0;
+        const bool walks = g != 0u || r == 0u;
+        auto walk = [&](uint32_t state, uint32_t b) {     // from that state at that bit to the next cut; returns the state there
+            uint32_t at = at_of(g == 0u ? first_place : 2u * state + next_bit(b)), q = q0 + b, count = 0;
             walk_entries<kWalkCount>(at, q, count, q0 + (g + 1u) * seg, len);
             place = place_of(at, q);
+            return (at - table_at) >> 4;
+        };
+        bool kept = false;
+        if (walks) {
+            const uint32_t state = g == 0u ? hdr & (L - 1u) : ((2u * r + 1u) * L / (2u * per_group)) & (L - 1u);
+            const uint32_t end = walk(state, g * seg);
+            kept = max(end, state) - min(end, state) <= L / 8u;
         }
+        // With frequencies that are powers of two, or nearly, a state keeps its upper bits (a quarter of the states come as close by
+        // chance) and walks started in other states never meet the true one: eight of them are started again, in the stream's own
+        // initial state, at eight bits in a row (a symbol may take as many).
+        const uint64_t n_kept = __ballot(kept);
+        if (lane == 0) atomicAdd(&S.kept, static_cast<uint32_t>(__popcll(n_kept)));
+        __syncthreads();
+        if (S.kept > kSplitThreads / 2u && g != 0u && r < 8u) walk(hdr & (L - 1u), g * seg + r);
         // the different ones among the group's (a group is a part of a wavefront, which reads before it writes)
         S.group[tid] = place;
         bool again = place == kSplitUnknown;

@@ -63,7 +63,8 @@ class _Exact(W.Layer):
 @pytest.mark.parametrize("table_log,pmf", [(r, q) for r in (5, 9, 12) for q in ([0.5, 0.5], [0.25] * 4, [1 / 16] * 16, [0.5, 0.25, 0.25],
                                                                              [0.25, 0.25] + [1 / 16] * 8, [1 / 256] * 256) if len(q) <= 1 << r])
 def test_states_that_never_meet(orc, table_log, pmf):
-    """A state keeps its upper bits: walks meet in the stream's own class of states and at its own bits, or not at all."""
+    """A state keeps its upper bits: walks meet in the stream's own class of states and at its own bits, or not at all (and are
+    started a second time there)."""
     for n, chunk in ((12288, 1 << 20), (5 * 12288, 12288)):
         _decode(orc, [_Exact("one", (n,), 8, 0, 0.02, np.asarray(pmf), 11)], table_log, chunk, "f32")
 
