@@ -2353,12 +2353,14 @@ int choose_launch(const anszp_decode_args_t* a, int mode, bool planned, DecodePa
     //     more bits or more than 8,192 symbols       0.72 to 1.4                      0.72 to 2
     //   small geometry, without, up to 512 bits and symbols a stream     1.2 to 2.4   1.04 to 1.6
     //     longer streams                             0.72 to 1.3                      0.9 to 1.5
-    //   small geometry, with one                     0.68 to 1.3                      0.67 to 1.2 (so: never)
+    //   small geometry, with one, more than three chunks per CU of up to 240 bits and 256 symbols a stream     0.98 to 1.3   0.86 to 1
+    //     others                                     0.68 to 1.25                     0.67 to 1.2
     // 1,120 chunks: 0.96 to 2 but for 1,870 bits a stream with a plan in the small geometry, 0.77.
     k.waves = WavesShape{};
     const uint64_t per_layer = a->n_chunks / a->n_tables, cus = p.n_cus, N = a->n_streams, symbols = a->out_elems / a->n_chunks;
     const bool short_enough = a->n_chunks > 4u * cus ? !(planned && k.small && a->n_chunks <= 6u * cus && bits > 1024u * N)
-                              : k.small              ? !planned && mean_words <= 256u && bits <= 512u * N && symbols <= 512u * N
+                              : k.small              ? mean_words <= 256u && (planned ? a->n_chunks > 3u * cus && bits <= 240u * N && symbols <= 256u * N
+                                                                                      : bits <= 512u * N && symbols <= 512u * N)
                                                      : mean_words <= 450u && (!planned || (bits <= 480u * N && symbols <= 8192u));
     if (mode == 0 && !k.stepwise && !k.split && per_layer >= 8u && a->n_chunks > 2u * cus && short_enough) {
         k.waves = waves_shape(a->table_log, a->n_streams, mean_words);
