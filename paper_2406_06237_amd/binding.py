@@ -655,6 +655,8 @@ def pack_layers_device(symbols_dev, layer_sizes: Sequence[int], freqs_dev, table
     torch = _torch()
     dev = symbols_dev.device
     _device_index(torch, dev)                             # (refused before anything is prepared for it)
+    if torch.cuda.is_current_stream_capturing():
+        raise RuntimeError("pack_layers_device cannot be captured: its jobs are copied from host memory of this call")
     sizes = [int(n) for n in layer_sizes]
     css = [int(chunk_size)] * len(sizes) if np.isscalar(chunk_size) else [int(c) for c in chunk_size][:len(sizes)]
     jobs = pack_jobs(sizes, css)

@@ -51,3 +51,12 @@ def test_every_name_of_a_gpu_is_accepted(calls, device):
     for _ in range(2):
         B.decode_raw(B.DecodeArgs(), device)
     assert calls == ["anszp_decode"] * 2
+
+
+def test_a_set_is_not_packed_under_capture(calls, monkeypatch):
+    """The jobs come from pinned memory that is free again when the call returns: a graph would copy whatever lies there later."""
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: True)
+    monkeypatch.setattr(B, "_device_index", lambda torch, device: 0)
+    with pytest.raises(RuntimeError, match="captur"):
+        B.pack_layers_device(torch.zeros(64, dtype=torch.uint8), [64], torch.zeros(256, dtype=torch.int32), 12, 64, 64)
+    assert calls == []

@@ -170,6 +170,23 @@ def test_a_whole_set_is_packed_in_order_on_its_stream(orc):
     torch.cuda.synchronize()
 
 
+def test_a_whole_set_is_refused_under_capture(orc):
+    w = W.config2()
+    from helpers import oracle_encode
+    c = oracle_encode(orc, w)
+    s = torch.from_numpy(np.concatenate(w.symbols())).to("cuda:0")
+    f = torch.from_numpy(np.ascontiguousarray(c.freqs, dtype=np.uint32).view(np.int32)).to("cuda:0")
+    sizes = [len(x) for x in w.symbols()]
+    out = B.pack_layers_device(s, sizes, f, w.table_log, w.n_streams, w.chunk_size)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(torch.cuda.CUDAGraph()):
+        with pytest.raises(RuntimeError, match="captur"):
+            B.pack_layers_device(s, sizes, f, w.table_log, w.n_streams, w.chunk_size, out=out)
+    out = B.pack_layers_device(s, sizes, f, w.table_log, w.n_streams, w.chunk_size)
+    torch.cuda.synchronize()
+    _same(c, w, out)
+
+
 def test_packing_on_three_streams_beside_each_other(orc):
     """Workgroups of several packs share the chip: each waits for lower-numbered ones of its own, and every container is whole."""
     from helpers import oracle_encode
