@@ -176,3 +176,11 @@ def test_layers_of_one_chunk_in_a_row(orc, singles, rest):
     sizes = [rest // 2 * 1024] + [1024 - i % 7 for i in range(singles)] + [rest // 2 * 1024 - 3]
     layers = [W.Layer(f"l{i}", (n,), 4, 8, 0.01 + 0.001 * i, W.peaked_geometric_pmf(16, 8, 0.5 + 0.003 * (i % 99)), 5 + i) for i, n in enumerate(sizes)]
     _check(orc, W.Workload("singles", layers, 12, 64, 1024, "bf16"), "bf16")
+
+
+def test_a_share_of_several_windows(orc):
+    """8,200 single streams of 1,000 words before 150,000 of ten: a share of the first descriptors sorted at once is longer than its list."""
+    pmf = np.ones(256) / 256
+    w = W.Workload("windows", [W.Layer("long", (8200 * 4000,), 8, 128, 0.02, pmf, 5), W.Layer("short", (150000 * 40,), 8, 128, 0.03, pmf, 6)], 9, 1, 4000, "u8")
+    w.chunk_sizes = [4000, 40]
+    _check_order(orc, w, "u8", "most words first")
