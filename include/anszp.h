@@ -320,6 +320,34 @@ int anszp_pack_layers_device(const uint8_t* symbols_dev, const anszp_pack_job_t*
                              uint64_t payload_cap_words, uint64_t* payload_words_used_dev,
                              uint32_t* status_dev, void* hip_stream);
 
+/* What anszp_pack_layers_device or, with `single`, anszp_pack_layer_device writes, for callers that bring
+ * scratch memory and have their layers' sizes on the host: the encoding tables are worked out once per layer instead of once
+ * per workgroup, the jobs travel with the launches, and with `clear` the call itself clears the results, so that they may come
+ * from memory with any contents.  The struct and its host arrays are read before the call returns. */
+typedef struct {
+    const uint8_t*  symbols;               /* [device] the layers' symbols, one layer behind the other      */
+    const uint32_t* freqs;                 /* [device] n_layers rows of 256 frequencies                     */
+    const uint64_t* layer_symbols;         /* [host] n_layers counts                                        */
+    const uint32_t* chunk_sizes;           /* [host] n_layers sizes, each >= 1                              */
+    uint32_t        n_layers, table_log, n_streams;
+    uint32_t        single;                /* not 0: n_layers is 1, with the offsets and the treatment of bad frequencies of anszp_pack_layer_device */
+    uint32_t        layer_id, stream_offset;             /* with `single` only (else 0)                     */
+    uint32_t        clear;                 /* descriptors, headers and status to 0, payload to 0xFFFFFFFF, over the sizes below */
+    uint64_t        out_offset, payload_word_offset;     /* with `single` only (else 0)                     */
+    anszp_chunk_t*  chunks;                /* [device] with `clear` 16-byte aligned, as stream_hdr and payload */
+    uint32_t*       stream_hdr;            /* [device]                                                      */
+    uint32_t*       payload;               /* [device]                                                      */
+    uint64_t        payload_cap_words;
+    uint64_t        clear_chunks, clear_stream_hdr, clear_payload_words;   /* descriptors, headers, words there are */
+    uint64_t*       payload_words_used;    /* [device]                                                      */
+    uint32_t*       status;                /* [device] 2 words                                              */
+    void*           scratch;               /* [device] 16-byte aligned, anszp_pack_scratch_bytes; in use until the launches are done */
+    uint64_t        scratch_bytes;
+} anszp_pack_set_t;
+/* [host only] 32 + 16 + 2048 + 2 * max(2^table_log, 8) bytes a layer (0 for a table_log out of range). */
+uint64_t anszp_pack_scratch_bytes(uint32_t n_layers, int table_log);
+int anszp_pack_set_device(const anszp_pack_set_t* set, void* hip_stream);
+
 /* activation layouts of anszp_conv_fused */
 #define ANSZP_ACT_NHWC        0     /* [batch][h][w][channels]                                    */
 #define ANSZP_ACT_C8          1     /* [batch][channels / 8][h][w][8]: blocks of 8 channels, so that

@@ -60,6 +60,16 @@ class ConvArgs(C.Structure):
                 ("y_layout", C.c_uint32), ("status", C.c_void_p)]
 
 
+class PackSet(C.Structure):
+    _fields_ = [("symbols", C.c_void_p), ("freqs", C.c_void_p), ("layer_symbols", C.c_void_p), ("chunk_sizes", C.c_void_p),
+                ("n_layers", C.c_uint32), ("table_log", C.c_uint32), ("n_streams", C.c_uint32),
+                ("single", C.c_uint32), ("layer_id", C.c_uint32), ("stream_offset", C.c_uint32), ("clear", C.c_uint32),
+                ("out_offset", C.c_uint64), ("payload_word_offset", C.c_uint64),
+                ("chunks", C.c_void_p), ("stream_hdr", C.c_void_p), ("payload", C.c_void_p), ("payload_cap_words", C.c_uint64),
+                ("clear_chunks", C.c_uint64), ("clear_stream_hdr", C.c_uint64), ("clear_payload_words", C.c_uint64),
+                ("payload_words_used", C.c_void_p), ("status", C.c_void_p), ("scratch", C.c_void_p), ("scratch_bytes", C.c_uint64)]
+
+
 class AnszpError(RuntimeError):
     def __init__(self, code: int, where: str):
         self.code = code
@@ -71,7 +81,7 @@ EXPORTS = ["anszp_version", "anszp_strerror", "anszp_normalize_freqs", "anszp_bu
            "anszp_build_tables", "anszp_build_tables_device", "anszp_pack_bound", "anszp_pack_layer", "anszp_decode", "anszp_decode_variant",
            "anszp_dequant_zp", "anszp_conv_fused", "anszp_pack_layer_device",
            "anszp_plan_bytes", "anszp_plan_decode", "anszp_decode_planned", "anszp_decode_static_plan",
-           "anszp_pack_layers_device", "anszp_test_set_spin_limit"]
+           "anszp_pack_layers_device", "anszp_pack_scratch_bytes", "anszp_pack_set_device", "anszp_test_set_spin_limit"]
 
 
 def lib():
@@ -112,6 +122,9 @@ def lib():
                                               C.c_uint64, C.c_void_p, C.c_void_p, C.c_void_p]
         L.anszp_pack_layers_device.argtypes = [C.c_void_p, C.c_void_p, C.c_uint32, C.c_uint64, C.c_void_p, C.c_int, C.c_int,
                                                C.c_void_p, C.c_void_p, C.c_void_p, C.c_uint64, C.c_void_p, C.c_void_p, C.c_void_p]
+        L.anszp_pack_scratch_bytes.argtypes = [C.c_uint32, C.c_int]
+        L.anszp_pack_scratch_bytes.restype = C.c_uint64
+        L.anszp_pack_set_device.argtypes = [C.c_void_p, C.c_void_p]
         L.anszp_test_set_spin_limit.argtypes = [C.c_uint32]
         L.anszp_test_set_spin_limit.restype = None
         _lib = L
@@ -600,27 +613,64 @@ def conv_fused(d: DeviceContainer, layer: int, first_chunk: int, rows_per_chunk:
 
 
 # --------------------------------------------------------------------------- packing on the GPU
+def _pack_scratch_bytes(n_layers: int, table_log: int) -> int:
+    """What anszp_pack_scratch_bytes gives."""
+    return n_layers * (2096 + 2 * max(1 << table_log, 8))
+
+
+def _pack_set(torch, dev, symbols_dev, freqs_dev, sizes, chunk_sizes, n_chunks: int, table_log: int, n_streams: int, cap: int, out=None,
+              single: int = 0, layer_id: int = 0, out_offset: int = 0, payload_word_offset: int = 0, stream_offset: int = 0):
+    """anszp_pack_set_device into `out`, or into new tensors, which the call clears.  The arguments have been checked."""
+    n = len(sizes)
+    scratch_bytes = _pack_scratch_bytes(n, table_log)
+    empty, int32, uint8 = torch.empty, torch.int32, torch.uint8
+    scratch = empty(max(scratch_bytes, 1), dtype=uint8, device=dev)
+    if out is None:
+        out = (empty(max(n_chunks, 1) * CHUNK_DTYPE.itemsize, dtype=uint8, device=dev), empty(max(n_chunks * n_streams, 4), dtype=int32, device=dev),
+               empty(max(cap, 4), dtype=int32, device=dev), empty(1, dtype=torch.int64, device=dev), empty(2, dtype=int32, device=dev))
+        cleared = (1, max(n_chunks, 1), max(n_chunks * n_streams, 4), max(cap, 4))
+    else:
+        cleared = (0, 0, 0, 0)
+    chunks, hdr, payload, used, status = out
+    host_sizes, host_chunk_sizes = (C.c_uint64 * n)(*sizes), (C.c_uint32 * n)(*chunk_sizes)
+    a = PackSet(symbols_dev.data_ptr(), freqs_dev.data_ptr(), C.addressof(host_sizes), C.addressof(host_chunk_sizes),
+                n, table_log, n_streams, single, layer_id, stream_offset, cleared[0], out_offset, payload_word_offset,
+                chunks.data_ptr(), hdr.data_ptr(), payload.data_ptr(), cap, cleared[1], cleared[2], cleared[3],
+                used.data_ptr(), status.data_ptr(), scratch.data_ptr(), scratch_bytes)
+    _enqueue("anszp_pack_set_device", lib().anszp_pack_set_device, dev, C.addressof(a))
+    return out
+
+
+def _check_pack_ranges(n: int, table_log: int, n_streams: int, chunk_size: int):
+    """Raises what anszp_pack_bound refuses."""
+    if not (1 <= table_log <= MAX_TABLE_LOG and 1 <= n_streams <= MAX_STREAMS and 1 <= chunk_size < 1 << 32):
+        nc, bound = C.c_uint64(), C.c_uint64()
+        _check(lib().anszp_pack_bound(n, table_log, n_streams, chunk_size, C.byref(nc), C.byref(bound)), "anszp_pack_bound")
+
+
 def pack_layer_device(symbols_dev, freqs_dev, table_log: int, n_streams: int, chunk_size: int, layer_id: int = 0,
                       out_offset: int = 0, payload_word_offset: int = 0, stream_offset: int = 0,
                       payload_cap_words: Optional[int] = None):
-    """anszp_pack_layer_device on torch's current stream: symbols_dev a uint8 tensor, freqs_dev an int32 tensor of
-    256 frequencies, both on the GPU.  Returns (chunks, stream_hdr, payload, used, status) as device tensors
-    (chunks as raw bytes of anszp_chunk_t; used: one int64; status: two int32)."""
+    """One layer packed on torch's current stream (anszp_pack_set_device, which writes what anszp_pack_layer_device does):
+    symbols_dev a uint8 tensor, freqs_dev an int32 tensor of 256 frequencies, both on the GPU.  Returns (chunks, stream_hdr,
+    payload, used, status) as device tensors (chunks as raw bytes of anszp_chunk_t; used: one int64; status: two int32)."""
     torch = _torch()
     dev = symbols_dev.device
+    _device_index(torch, dev)                             # (refused before anything is prepared for it)
     n = symbols_dev.numel()
-    nc = C.c_uint64(); bound = C.c_uint64()
-    _check(lib().anszp_pack_bound(n, table_log, n_streams, chunk_size, C.byref(nc), C.byref(bound)), "anszp_pack_bound")
-    cap = bound.value if payload_cap_words is None else payload_cap_words
-    chunks = torch.zeros(max(nc.value, 1) * CHUNK_DTYPE.itemsize, dtype=torch.uint8, device=dev)
-    hdr = torch.zeros(max(nc.value * n_streams, 4), dtype=torch.int32, device=dev)
-    payload = torch.full((max(cap, 4),), -1, dtype=torch.int32, device=dev)
-    used = torch.empty(1, dtype=torch.int64, device=dev)
-    status = torch.zeros(2, dtype=torch.int32, device=dev)
-    _enqueue("anszp_pack_layer_device", lib().anszp_pack_layer_device, dev, symbols_dev.data_ptr(), n, freqs_dev.data_ptr(), table_log,
-             n_streams, chunk_size, layer_id, out_offset, payload_word_offset, stream_offset, chunks.data_ptr(),
-             hdr.data_ptr(), payload.data_ptr(), cap, used.data_ptr(), status.data_ptr())
-    return chunks, hdr, payload, used, status
+    _check_pack_ranges(n, table_log, n_streams, chunk_size)
+    n_chunks = -(-n // chunk_size)
+    cap = _pack_bound_words((n,), (chunk_size,), table_log, n_streams) if payload_cap_words is None else payload_cap_words
+    return _pack_set(torch, dev, symbols_dev, freqs_dev, (n,), (chunk_size,), n_chunks, table_log, n_streams, cap, None,
+                     1, layer_id, out_offset, payload_word_offset, stream_offset)
+
+
+def _chunk_counts(layer_sizes, chunk_sizes) -> List[int]:
+    """Chunks of each layer; raises for what the fields of a job cannot hold."""
+    counts = [(n + cs - 1) // cs for n, cs in zip(layer_sizes, chunk_sizes)]
+    if counts and (min(layer_sizes) < 0 or min(chunk_sizes) < 0 or sum(layer_sizes) >= 1 << 63 or max(max(chunk_sizes), sum(counts)) >= 1 << 32):
+        raise OverflowError("layer sizes are unsigned 64-bit numbers, chunk sizes and chunk counts unsigned 32-bit ones")
+    return counts
 
 
 def pack_jobs(layer_sizes: Sequence[int], chunk_sizes: Sequence[int]) -> np.ndarray:
@@ -629,9 +679,7 @@ def pack_jobs(layer_sizes: Sequence[int], chunk_sizes: Sequence[int]) -> np.ndar
     if len(jobs) == 0:
         return jobs
     chunk_sizes = list(chunk_sizes)[:len(jobs)]           # (sizes of layers that are not there are not looked at)
-    counts = [(n + cs - 1) // cs for n, cs in zip(layer_sizes, chunk_sizes)]
-    if min(layer_sizes) < 0 or min(chunk_sizes) < 0 or sum(layer_sizes) >= 1 << 63 or max(max(chunk_sizes), sum(counts)) >= 1 << 32:
-        raise OverflowError("layer sizes are unsigned 64-bit numbers, chunk sizes and chunk counts unsigned 32-bit ones")
+    counts = _chunk_counts(layer_sizes, chunk_sizes)
     jobs["n_symbols"] = layer_sizes
     jobs["chunk_size"] = chunk_sizes
     jobs["first_symbol"][1:] = np.cumsum(jobs["n_symbols"])[:-1]
@@ -646,44 +694,27 @@ def _pack_bound_words(layer_sizes, chunk_sizes, table_log: int, n_streams: int) 
 
 def pack_layers_device(symbols_dev, layer_sizes: Sequence[int], freqs_dev, table_log: int, n_streams: int, chunk_size,
                        payload_cap_words: Optional[int] = None, out=None):
-    """anszp_pack_layers_device on torch's current stream: symbols_dev a uint8 tensor holding the layers one after the
-    other, freqs_dev an int32 tensor [n_layers, 256], both on the GPU; chunk_size: one for all layers or one per layer.
+    """A set of layers packed on torch's current stream (anszp_pack_set_device): symbols_dev a uint8 tensor holding the layers one
+    after the other, freqs_dev an int32 tensor [n_layers, 256], both on the GPU; chunk_size: one for all layers or one per layer.
     Returns (chunks, stream_hdr, payload, used, status) as device tensors (out: the same five, to be reused).
 
     Like every call here it returns before the GPU is done: what it returns is valid in order on the current stream, another
     stream has to wait for it first (an event, a synchronisation), and so has whoever overwrites the symbols or frequencies there."""
     torch = _torch()
     dev = symbols_dev.device
-    _device_index(torch, dev)                             # (refused before anything is prepared for it)
+    index = _device_index(torch, dev)                     # (refused before anything is prepared for it)
     if torch.cuda.is_current_stream_capturing():
-        raise RuntimeError("pack_layers_device cannot be captured: its jobs are copied from host memory of this call")
+        raise RuntimeError("pack_layers_device cannot be captured")
     sizes = [int(n) for n in layer_sizes]
     css = [int(chunk_size)] * len(sizes) if np.isscalar(chunk_size) else [int(c) for c in chunk_size][:len(sizes)]
-    jobs = pack_jobs(sizes, css)
-    n_chunks = sum((n + c - 1) // c for n, c in zip(sizes, css))
-    if sizes:                                             # (refuses what the arguments' ranges refuse)
-        nc, b = C.c_uint64(), C.c_uint64()
-        _check(lib().anszp_pack_bound(sizes[0], table_log, n_streams, min(css), C.byref(nc), C.byref(b)), "anszp_pack_bound")
-    bound = _pack_bound_words(sizes, css, table_log, n_streams)
-    cap = bound if payload_cap_words is None else payload_cap_words
-    # (through pinned memory, which torch keeps until the copy is done: a copy from pageable memory would wait for the stream)
-    staging = torch.empty(max(jobs.nbytes, 1), dtype=torch.uint8, pin_memory=True)
-    staging.numpy()[:jobs.nbytes] = jobs.view(np.uint8)
-    jobs_dev = staging.to(dev, non_blocking=True)
-    if out is None:
-        chunks = torch.zeros(max(n_chunks, 1) * CHUNK_DTYPE.itemsize, dtype=torch.uint8, device=dev)
-        hdr = torch.zeros(max(n_chunks * n_streams, 4), dtype=torch.int32, device=dev)
-        payload = torch.full((max(cap, 4),), -1, dtype=torch.int32, device=dev)
-        used = torch.empty(1, dtype=torch.int64, device=dev)
-        status = torch.zeros(2, dtype=torch.int32, device=dev)
-    else:
-        chunks, hdr, payload, used, status = out
-    _enqueue("anszp_pack_layers_device", lib().anszp_pack_layers_device, dev, symbols_dev.data_ptr(), jobs_dev.data_ptr(), len(sizes),
-             n_chunks, freqs_dev.data_ptr(), table_log, n_streams, chunks.data_ptr(), hdr.data_ptr(), payload.data_ptr(), cap,
-             used.data_ptr(), status.data_ptr())
+    n_chunks = sum(_chunk_counts(sizes, css))
+    if sizes:
+        _check_pack_ranges(sizes[0], table_log, n_streams, min(css))
+    cap = _pack_bound_words(sizes, css, table_log, n_streams) if payload_cap_words is None else payload_cap_words
+    results = _pack_set(torch, dev, symbols_dev, freqs_dev, sizes, css, n_chunks, table_log, n_streams, cap, out)
     # The call returns before the GPU is done.  Its tensors may come from another stream: their memory is not handed out
     # again before this stream has got here.
-    stream = torch.cuda.current_stream(dev)
+    stream = torch.cuda.current_stream(index)
     for t in (symbols_dev, freqs_dev) if out is None else (symbols_dev, freqs_dev, *out):
         t.record_stream(stream)
-    return chunks, hdr, payload, used, status
+    return results

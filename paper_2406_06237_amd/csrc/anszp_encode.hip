@@ -53,6 +53,7 @@ struct EncParams {
     uint32_t* payload;
     unsigned long long* used;
     uint32_t* status;
+    const uint32_t* prepared;               // null, or a record of encoding tables per layer (encode_prepare)
     uint64_t n_chunks, out_offset, payload_word_offset, payload_cap_words;
     uint32_t n_layers, table_log, n_streams, layer_id, stream_offset, chunks_per_group, spin_limit;
 };
@@ -61,8 +62,8 @@ struct EncParams {
 // in state x; 2 * (x >> that) + info.y is the byte of `next` that holds the new state plus L.  A symbol without a
 // frequency has info.x = 0 (no other symbol has), drops nothing and leads to some state.
 struct EncTables {
-    uint2 info[ANSZP_ALPHABET];
-    uint16_t next[kSpreadStates];
+    __attribute__((aligned(16))) uint2 info[ANSZP_ALPHABET];
+    __attribute__((aligned(16))) uint16_t next[kSpreadStates];
 };
 struct EncLds : EncTables {
     SpreadLds spread;
@@ -73,6 +74,13 @@ __device__ __forceinline__ void report(uint32_t* status, uint32_t bits) {
     atomicAdd(&status[1], 1u);
 }
 
+// f: the symbol's frequency, first: the occurrences of smaller symbols.
+__device__ __forceinline__ uint2 symbol_info(uint32_t f, uint32_t first, uint32_t table_log) {
+    // x in [L, 2L) drops k or k - 1 bits, k = table_log - floor(log2 f): k when x >= f << k
+    const uint32_t k = f ? table_log - (31u - static_cast<uint32_t>(__clz(f))) : 0u;
+    return f ? make_uint2((k << 16) - (f << k), 2u * (first - f)) : make_uint2(0u, 0u - (2u << table_log));
+}
+
 // The workgroup's encoding tables.  False (for every thread) when the frequencies do not sum to L.
 __device__ __forceinline__ bool build_tables(const uint32_t* freqs, uint32_t table_log, EncTables& t, SpreadLds& spread) {
     const uint32_t tid = threadIdx.x, L = 1u << table_log;
@@ -80,14 +88,36 @@ __device__ __forceinline__ bool build_tables(const uint32_t* freqs, uint32_t tab
         t.next[g] = static_cast<uint16_t>(L + state);
     });
     if (!ok) return false;
-    if (tid < ANSZP_ALPHABET) {
-        const uint32_t f = spread.f[tid];
-        // x in [L, 2L) drops k or k - 1 bits, k = table_log - floor(log2 f): k when x >= f << k
-        const uint32_t k = f ? table_log - (31u - static_cast<uint32_t>(__clz(f))) : 0u;
-        t.info[tid] = f ? make_uint2((k << 16) - (f << k), 2u * (spread.first[tid] - f)) : make_uint2(0u, 0u - 2u * L);
-    }
+    if (tid < ANSZP_ALPHABET) t.info[tid] = symbol_info(spread.f[tid], spread.first[tid], table_log);
     __syncthreads();
     return true;
+}
+
+// A layer's record of encode_prepare: four words, the first of them whether the frequencies sum to L, then `info` and the
+// first L states of `next`.
+constexpr uint32_t kRecordInfo = 4u, kRecordNext = kRecordInfo + 2u * ANSZP_ALPHABET;
+__host__ __device__ constexpr uint32_t record_words(uint32_t table_log) { return kRecordNext + (table_log > 3u ? (1u << table_log) / 2u : 4u); }
+
+// The workgroup's encoding tables, built or taken from the layer's record.
+__device__ __forceinline__ bool layer_tables(const EncParams& p, uint32_t layer, EncTables& t, SpreadLds& spread) {
+    if (!p.prepared) return build_tables(p.freqs + size_t(layer) * ANSZP_ALPHABET, p.table_log, t, spread);
+    typedef spread_words4 words4;
+    const words4* const record = reinterpret_cast<const words4*>(p.prepared + size_t(layer) * record_words(p.table_log));
+    const uint32_t units = record_words(p.table_log) / 4u;
+    constexpr uint32_t kMost = (record_words(ANSZP_MAX_TABLE_LOG) / 4u + kThreads - 1u) / kThreads, kInfo = kRecordNext / 4u;
+    words4 v[kMost];
+    const uint32_t ok = __builtin_amdgcn_readfirstlane(record[0].x);
+#pragma unroll
+    for (uint32_t u = 0; u < kMost; ++u) v[u] = record[min(threadIdx.x + u * kThreads, units - 1u)];
+#pragma unroll
+    for (uint32_t u = 0; u < kMost; ++u) {
+        const uint32_t i = threadIdx.x + u * kThreads;
+        if (i >= units || i == 0u) continue;
+        if (i < kInfo) reinterpret_cast<words4*>(t.info)[i - 1u] = v[u];
+        else reinterpret_cast<words4*>(t.next)[i - kInfo] = v[u];
+    }
+    __syncthreads();
+    return ok != 0u;
 }
 
 // A chunk's streams as its wavefront walks them: symbol number r of this lane's stream is chunk[r * n_streams + lane_off].
@@ -236,7 +266,7 @@ __device__ __forceinline__ void for_each_chunk(const EncParams& p, EncLds& t, CH
         uint64_t run = (job.n_symbols + job.chunk_size - 1) / job.chunk_size - local;   // chunks of this layer from c on
         if (p.jobs && layer + 1u < p.n_layers && p.jobs[layer + 1u].first_chunk > c) run = min(run, (unsigned long long)(p.jobs[layer + 1u].first_chunk - c));
         run = min(run, (unsigned long long)(end - c));
-        const bool ok = build_tables(p.freqs + size_t(layer) * ANSZP_ALPHABET, p.table_log, t, t.spread);
+        const bool ok = layer_tables(p, layer, t, t.spread);
         for (uint64_t i = wave; i < run; i += kWaves) chunk(job, layer, local + i, c + i, ok);
         c += run;
         // (behind the last run a wavefront is done as soon as its own chunks are: the registers of the idle ones let the
@@ -441,6 +471,151 @@ __global__ __launch_bounds__(kThreads) void encode_begin(EncParams p) {
     for (uint64_t c = threadIdx.x; c < p.n_chunks; c += kThreads) p.chunks[c].payload_words = kUnknown;
 }
 
+// ---- Before a packer whose caller brings scratch memory (anszp_pack_set_device): one launch for what does not depend on the symbols.
+//
+// The first workgroups work out the layers' encoding tables, once for all chunks: 512 occurrences each, a thread's occurrence
+// against every symbol there is.  Occurrence i of symbol s has, of symbol t's, those before it whose (2j + 1) / 2g, g = t's
+// frequency, is smaller than (2i + 1) / 2f (or equal, t < s): the odd numbers up to ((2i + 1) g - (t >= s)) / f.  That is a
+// dozen instructions per symbol without a barrier or a look-up, 16 symbols 1 us, where every workgroup of the packer needed
+// 7.5 us for a counting sort of its own.  Beyond kDirectSymbols symbols the sort is the faster one; one workgroup then does it.
+// The others clear what the packer's callers find cleared (a fill per buffer took a launch each) and mark all chunks as
+// unpublished; they are at work beside the former.  4.0 us for one table of 2^11 states and 3 MB of results, 8 for 53 of 2^12
+// and 35 MB; packing a set with build_tables_device before it, results allocated by the caller of the binding: 369 chunks of
+// 65,536 symbols 98 -> 79 us, 144 of 16,384 43 -> 35, two layers of 11,792 symbols 64 -> 31.
+constexpr uint32_t kDirectSymbols = 128u;
+constexpr uint32_t kClearUnits = 8u * kThreads;             // of 16 bytes, per workgroup
+constexpr uint32_t kJobsPerLaunch = 64u;
+struct JobsArg { anszp_pack_job_t job[kJobsPerLaunch]; };
+struct PrepareParams {
+    anszp_pack_job_t* jobs;                                 // null: one layer, of `n_jobs` 0
+    uint32_t* records;
+    uint32_t n_jobs, first_job;                             // in this launch
+    uint32_t shares, table_groups, clear;                   // workgroups per table, of all tables; whether the results are cleared
+    uint64_t chunk_units, hdr_words, payload_words;         // sizes of what is cleared
+};
+struct PrepareLds {
+    SpreadLds spread;
+    __attribute__((aligned(16))) uint32_t list[ANSZP_ALPHABET];     // the symbols there are: frequency, first occurrence << 16
+};
+
+// `words` words from `to`, a multiple of 16 bytes, on; this workgroup's share: units of 16 bytes [first, end).
+__device__ __forceinline__ void fill_words(uint32_t* to, uint64_t words, uint32_t value, uint64_t first, uint64_t end) {
+    const spread_words4 v = {value, value, value, value};
+    const uint64_t whole = words / 4u;
+    for (uint64_t i = first + threadIdx.x; i < min(end, whole); i += kThreads) reinterpret_cast<spread_words4*>(to)[i] = v;
+    if (first <= whole && whole < end && threadIdx.x < words % 4u) to[4u * whole + threadIdx.x] = value;
+}
+
+__device__ __forceinline__ void store_jobs(const PrepareParams& q, const JobsArg& jobs) {
+    if (threadIdx.x < q.n_jobs) q.jobs[q.first_job + threadIdx.x] = jobs.job[threadIdx.x];
+}
+
+__global__ __launch_bounds__(kJobsPerLaunch) void encode_jobs(PrepareParams q, JobsArg jobs) { store_jobs(q, jobs); }
+
+__global__ __launch_bounds__(kThreads, 4) void encode_prepare(EncParams p, PrepareParams q, JobsArg jobs) {
+    __shared__ PrepareLds t;
+    const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1u), wave = __builtin_amdgcn_readfirstlane(tid >> 6), L = 1u << p.table_log;
+    if (blockIdx.x >= q.table_groups) {
+        const uint64_t share = blockIdx.x - q.table_groups;
+        if (share == 0u) {
+            store_jobs(q, jobs);
+            if (q.clear && tid < 2u) p.status[tid] = 0u;
+        }
+        uint64_t first = share * kClearUnits, end = first + kClearUnits;        // among the units of all buffers, one behind the other
+        if (q.clear) {
+            const uint64_t payload_units = (q.payload_words + 3u) / 4u, hdr_units = (q.hdr_words + 3u) / 4u;
+            fill_words(p.payload, q.payload_words, 0xFFFFFFFFu, first, end);
+            if (end <= payload_units) return;
+            first = first > payload_units ? first - payload_units : 0u;
+            end -= payload_units;
+            fill_words(p.stream_hdr, q.hdr_words, 0u, first, end);
+            if (end <= hdr_units) return;
+            first = first > hdr_units ? first - hdr_units : 0u;
+            end -= hdr_units;
+        }
+        // (one layer of bad frequencies: nothing is written at all)
+        const bool mark = p.jobs || one_layer_ok(p);
+        end = min(end, (unsigned long long)q.chunk_units);
+        for (uint64_t i = first + tid; i < end; i += kThreads) {
+            uint32_t* const at = reinterpret_cast<uint32_t*>(p.chunks) + 4u * i;
+            const uint32_t words = mark && (i & 1u) && i / 2u < p.n_chunks ? kUnknown : 0u;
+            if (q.clear) *reinterpret_cast<spread_words4*>(at) = spread_words4{0u, 0u, words, 0u};
+            else if (words) at[2] = words;
+        }
+        return;
+    }
+    static_assert(sizeof(anszp_chunk_t) == 32 && offsetof(anszp_chunk_t, payload_words) == 24, "two units a descriptor");
+    const uint32_t layer = blockIdx.x / q.shares, share = blockIdx.x % q.shares;
+    const uint32_t* const freqs = p.freqs + size_t(layer) * ANSZP_ALPHABET;
+    uint32_t* const record = q.records + size_t(layer) * record_words(p.table_log);
+    uint16_t* const next = reinterpret_cast<uint16_t*>(record + kRecordNext);
+    uint32_t fs = 0, upto = 0, place = 0;
+    if (tid < ANSZP_ALPHABET) {
+        fs = freqs[tid];
+        const uint64_t there = __ballot(fs != 0u);
+        upto = spread_wave_sum(min(fs, L + 1u));                // (as in spread_states)
+        place = static_cast<uint32_t>(__popcll(there & ((1ull << lane) - 1ull)));
+        if (lane == kWave - 1u) {
+            t.spread.part[wave] = upto;
+            t.spread.part[8u + wave] = static_cast<uint32_t>(__popcll(there));
+        }
+    }
+    __syncthreads();
+    uint32_t total = 0, symbols = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < ANSZP_ALPHABET / kWave; ++w) {
+        if (w == wave) {
+            upto += total;
+            place += symbols;
+        }
+        total += t.spread.part[w];
+        symbols += t.spread.part[8u + w];
+    }
+    const bool ok = total == L;
+    if (share == 0u) {
+        if (tid == 0u) record[0] = ok ? 1u : 0u;
+        if (ok && tid < ANSZP_ALPHABET) reinterpret_cast<uint2*>(record + kRecordInfo)[tid] = symbol_info(fs, upto - fs, p.table_log);
+    }
+    if (!ok) return;
+    if (symbols > kDirectSymbols) {
+        if (share) return;
+        __syncthreads();                                        // (`part` has been read)
+        spread_states<kThreads>(freqs, p.table_log, t.spread, [&](uint32_t g, uint32_t, uint32_t, uint32_t, uint32_t state) {
+            next[g] = static_cast<uint16_t>(L + state);
+        });
+        return;
+    }
+    if (fs) t.list[place] = fs | (upto - fs) << 16;             // (fs <= 2^12, upto - fs < 2^12)
+    if (tid >= symbols && tid < ((symbols + 3u) & ~3u)) t.list[tid] = 0u;       // up to a multiple of four: counted, and nothing
+    __syncthreads();
+    const uint32_t g = share * kThreads + tid;
+    if (g >= L) return;
+    uint32_t mine = 0;                                          // the last symbol whose first occurrence is not beyond g
+    for (uint32_t step = 0x80000000u >> __builtin_clz(symbols); step; step >>= 1) {
+        const uint32_t c = mine + step;
+        if (c < symbols && (t.list[c] >> 16) <= g) mine = c;
+    }
+    const uint32_t f = t.list[mine] & 0xFFFFu, odd = 2u * (g - (t.list[mine] >> 16)) + 1u;
+    // n / f for n < 2^25, n / f < 2^13 (odd < 2f): the quotient with the reciprocal, whose and whose product's errors of less than
+    // 2^-22 are made to lie on one side, is right or one too small
+    const float inverse = __builtin_amdgcn_rcpf(static_cast<float>(f)) * (1.0f - 0x1p-20f);
+    uint32_t state = L;
+    auto count = [&](uint32_t j, uint32_t entry) {
+        const uint32_t n = __umul24(odd, entry & 0xFFFFu) - (j >= mine ? 1u : 0u);
+        uint32_t q0 = static_cast<uint32_t>(static_cast<float>(n) * inverse);
+        q0 += n - __umul24(q0, f) >= f ? 1u : 0u;
+        state += (q0 + 1u) >> 1;
+    };
+    for (uint32_t j = 0; j < symbols; j += 4u) {
+        const spread_words4 e = *reinterpret_cast<const spread_words4*>(&t.list[j]);
+        count(j, e.x);
+        if (e.y) count(j + 1u, e.y);                            // (uniform; behind the last symbol nothing)
+        if (e.z) count(j + 2u, e.z);
+        if (e.w) count(j + 3u, e.w);
+    }
+    next[g] = static_cast<uint16_t>(state);
+}
+
 // Words of the chunks before c (each a multiple of four), once all are published.  False for every thread when one of
 // them was not by the `looks`-th look.
 __device__ __forceinline__ bool words_before(const EncParams& p, uint64_t c, uint32_t looks, uint32_t& before, uint32_t& gave_up, uint64_t& out) {
@@ -483,7 +658,7 @@ __global__ __launch_bounds__(kThreads, 4) void encode_once(EncParams p) {
         if (tid < N) p.stream_hdr[c * N + tid] = 0u;
         return;
     }
-    const bool ok = build_tables(p.freqs + size_t(layer) * ANSZP_ALPHABET, p.table_log, t.tables, t.spread);
+    const bool ok = layer_tables(p, layer, t.tables, t.spread);
     const uint64_t out_offset = p.out_offset + job.first_symbol + local * job.chunk_size;
     auto describe = [&](uint32_t n_symbols, bool later) {
         anszp_chunk_t* const d = &p.chunks[c];
@@ -716,7 +891,7 @@ __global__ __launch_bounds__(kThreads, 4) void encode_rest(EncParams p) {
         }
         return;
     }
-    if (!build_tables(p.freqs + size_t(layer) * ANSZP_ALPHABET, p.table_log, t, t.spread)) return;      // (they were there: the chunk has symbols)
+    if (!layer_tables(p, layer, t, t.spread)) return;      // (they were there: the chunk has symbols)
     if (tid >= kWave) return;
     if (tid == 0) p.chunks[c].payload_offset = p.payload_word_offset + sum;
     write_chunk(p, t, job, local, c, d.payload_words, p.payload_word_offset + sum, d.payload_offset);
@@ -739,7 +914,7 @@ int launch(EncParams& p, hipStream_t s) {
         const uint32_t looks = spin_limit_for_tests().load(std::memory_order_relaxed);
         p.spin_limit = looks ? looks - 1u : 1u << 16;
         const dim3 groups(uint32_t(p.n_chunks)), threads(kThreads);
-        hipLaunchKernelGGL(encode_begin, dim3(1), threads, 0, s, p);
+        if (!p.prepared) hipLaunchKernelGGL(encode_begin, dim3(1), threads, 0, s, p);
         hipLaunchKernelGGL(encode_once, groups, threads, 0, s, p);
         hipLaunchKernelGGL(encode_rest, groups, threads, 0, s, p);
         return hipGetLastError() == hipSuccess ? ANSZP_OK : ANSZP_E_HIP;
@@ -753,6 +928,73 @@ int launch(EncParams& p, hipStream_t s) {
 }
 
 }  // namespace
+
+extern "C" uint64_t anszp_pack_scratch_bytes(uint32_t n_layers, int table_log) {
+    if (table_log < 1 || table_log > ANSZP_MAX_TABLE_LOG) return 0;
+    return uint64_t(n_layers) * (sizeof(anszp_pack_job_t) + 4u * record_words(uint32_t(table_log)));
+}
+
+extern "C" int anszp_pack_set_device(const anszp_pack_set_t* a, void* stream) {
+    if (!a || !a->payload_words_used || !a->status || (a->n_layers && (!a->layer_symbols || !a->chunk_sizes || !a->freqs || !a->scratch))) return ANSZP_E_NULL;
+    if (a->table_log < 1 || a->table_log > ANSZP_MAX_TABLE_LOG || a->n_streams < 1 || a->n_streams > ANSZP_MAX_STREAMS || (a->payload_word_offset & 3) ||
+        (a->single && a->n_layers != 1u) || a->n_layers >= (1u << 27) || a->scratch_bytes < anszp_pack_scratch_bytes(a->n_layers, int(a->table_log)) ||
+        (reinterpret_cast<uintptr_t>(a->scratch) & 15) ||
+        (a->clear && ((reinterpret_cast<uintptr_t>(a->chunks) | reinterpret_cast<uintptr_t>(a->stream_hdr) | reinterpret_cast<uintptr_t>(a->payload)) & 15)))
+        return ANSZP_E_RANGE;
+    uint64_t n_chunks = 0, n_symbols = 0;
+    for (uint32_t l = 0; l < a->n_layers; ++l) {
+        if (!a->chunk_sizes[l] || a->layer_symbols[l] >= (1ull << 63)) return ANSZP_E_RANGE;
+        n_chunks += (a->layer_symbols[l] + a->chunk_sizes[l] - 1u) / a->chunk_sizes[l];
+        n_symbols += a->layer_symbols[l];
+        if (n_chunks >= (1ull << 32) || n_symbols >= (1ull << 63)) return ANSZP_E_RANGE;
+    }
+    if (!a->single && (n_chunks >= (1ull << 31) || n_chunks * a->n_streams >= (1ull << 32))) return ANSZP_E_RANGE;
+    if (n_chunks && (!a->symbols || !a->chunks || !a->stream_hdr)) return ANSZP_E_NULL;
+    if (!a->payload && a->payload_cap_words) return ANSZP_E_NULL;
+    if (a->clear && ((a->clear_chunks && !a->chunks) || (a->clear_stream_hdr && !a->stream_hdr) || (a->clear_payload_words && !a->payload))) return ANSZP_E_NULL;
+    if (a->clear && a->clear_chunks < n_chunks) return ANSZP_E_RANGE;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    EncParams p{};
+    p.symbols = a->symbols; p.freqs = a->freqs; p.chunks = a->chunks; p.stream_hdr = a->stream_hdr; p.payload = a->payload;
+    p.used = reinterpret_cast<unsigned long long*>(a->payload_words_used); p.status = a->status;
+    p.n_chunks = n_chunks; p.payload_word_offset = a->payload_word_offset; p.payload_cap_words = a->payload_cap_words;
+    p.out_offset = a->out_offset; p.n_layers = a->n_layers; p.table_log = a->table_log; p.n_streams = a->n_streams;
+    p.layer_id = a->layer_id; p.stream_offset = a->stream_offset;
+    if (!a->single && (a->layer_id || a->stream_offset || a->out_offset || a->payload_word_offset)) return ANSZP_E_RANGE;
+    PrepareParams q{};
+    JobsArg jobs;
+    anszp_pack_job_t* const jobs_dev = static_cast<anszp_pack_job_t*>(a->scratch);
+    q.records = reinterpret_cast<uint32_t*>(jobs_dev + a->n_layers);
+    if (!a->single) {
+        p.jobs = q.jobs = jobs_dev;
+    } else {
+        p.one.n_symbols = a->layer_symbols[0]; p.one.chunk_size = a->chunk_sizes[0];
+    }
+    if (q.jobs) {                                           // by the kernels' arguments: no copy from host memory
+        uint64_t symbol = 0, chunk = 0;
+        for (uint32_t l = 0; l < a->n_layers; ++l) {
+            if (q.n_jobs == kJobsPerLaunch) {
+                hipLaunchKernelGGL(encode_jobs, dim3(1), dim3(kJobsPerLaunch), 0, s, q, jobs);
+                q.first_job = l;
+                q.n_jobs = 0;
+            }
+            jobs.job[q.n_jobs++] = anszp_pack_job_t{symbol, a->layer_symbols[l], a->chunk_sizes[l], uint32_t(chunk), {0u, 0u}};
+            symbol += a->layer_symbols[l];
+            chunk += (a->layer_symbols[l] + a->chunk_sizes[l] - 1u) / a->chunk_sizes[l];
+        }
+    }
+    q.clear = a->clear ? 1u : 0u;
+    q.shares = std::max(1u, (1u << p.table_log) / kThreads);
+    q.table_groups = n_chunks ? a->n_layers * q.shares : 0u;    // (without chunks nobody reads them)
+    q.chunk_units = 2u * (a->clear ? a->clear_chunks : n_chunks);
+    q.hdr_words = a->clear_stream_hdr; q.payload_words = a->clear_payload_words;
+    const uint64_t units = q.chunk_units + (a->clear ? (q.hdr_words + 3u) / 4u + (q.payload_words + 3u) / 4u : 0u);
+    const uint64_t groups = q.table_groups + std::max<uint64_t>(1u, (units + kClearUnits - 1u) / kClearUnits);
+    if (groups >= (1ull << 31)) return ANSZP_E_RANGE;
+    hipLaunchKernelGGL(encode_prepare, dim3(uint32_t(groups)), dim3(kThreads), 0, s, p, q, jobs);
+    p.prepared = n_chunks ? q.records : nullptr;
+    return launch(p, s);
+}
 
 extern "C" int anszp_pack_layers_device(const uint8_t* symbols_dev, const anszp_pack_job_t* jobs_dev, uint32_t n_layers,
                                         uint64_t n_chunks, const uint32_t* freqs_dev, int table_log, int n_streams,

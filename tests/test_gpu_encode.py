@@ -356,3 +356,65 @@ def test_streams_longer_than_their_place_in_lds(orc, R, N, chunk, n):
     _compare(orc, two, R, N, chunk)
     thin = np.where(rng.random(n) < 0.97, 1, two).astype(np.uint8)
     _compare(orc, np.concatenate([thin, dense, two]), R, N, chunk)
+
+
+# ---- tables worked out by the launch before the packer (anszp_pack_set_device, behind every call above): occurrences are counted
+# against each symbol up to 128 symbols and sorted beyond; 512 of them a workgroup; 64 jobs a launch.
+@pytest.mark.parametrize("symbols", [1, 2, 3, 4, 5, 63, 127, 128, 129, 256])
+def test_tables_of_any_alphabet(orc, symbols):
+    rng = np.random.default_rng(symbols)
+    for R in (1, 3, 8, 9, 10, 12):
+        if symbols > 1 << R:
+            continue
+        names = np.sort(rng.choice(256, symbols, replace=False)).astype(np.uint8)
+        for weights in (np.ones(symbols), rng.random(symbols) ** 4 + 1e-4):
+            sym = np.concatenate([names, rng.choice(names, 3000, p=weights / weights.sum())]).astype(np.uint8)
+            _compare(orc, sym, R, 17, 700)
+
+
+@pytest.mark.parametrize("n_layers", [1, 2, 63, 64, 65, 130])
+def test_jobs_by_the_launches_arguments(orc, n_layers):
+    layers = [W.tiny(seed=s, n=300 + 17 * s % 500, bitwidth=1 + s % 8, n_streams=32, chunk_size=256, table_log=9, p0=0.6).layers[0] for s in range(n_layers)]
+    w = W.Workload("many", layers, 9, 32, 256, "bf16")
+    from helpers import oracle_encode
+    c = oracle_encode(orc, w)
+    chunks, hdr, payload, used, status = _pack_set(w, c)
+    assert status == (0, 0) and used == len(c.payload)
+    assert np.array_equal(chunks["out_offset"], c.chunk_out_off) and np.array_equal(chunks["payload_offset"], c.chunk_payload_off)
+    assert np.array_equal(hdr, c.stream_hdr) and np.array_equal(payload[:used], c.payload) and np.all(payload[used:] == 0xFFFFFFFF)
+
+
+def _pack_without_scratch(w, c):
+    """anszp_pack_layers_device: nothing but the results."""
+    syms = w.symbols()
+    s = torch.from_numpy(np.concatenate(syms)).to("cuda:0")
+    f = torch.from_numpy(np.ascontiguousarray(c.freqs, dtype=np.uint32).view(np.int32)).to("cuda:0")
+    jobs = torch.from_numpy(B.pack_jobs([len(x) for x in syms], [w.chunk_size] * len(syms)).view(np.uint8)).to("cuda:0")
+    nc, cap = c.n_chunks, len(c.payload) + 100
+    chunks = torch.zeros(nc * B.CHUNK_DTYPE.itemsize, dtype=torch.uint8, device="cuda:0")
+    hdr = torch.zeros(nc * w.n_streams, dtype=torch.int32, device="cuda:0")
+    payload = torch.full((cap,), -1, dtype=torch.int32, device="cuda:0")
+    used, status = torch.zeros(1, dtype=torch.int64, device="cuda:0"), torch.zeros(2, dtype=torch.int32, device="cuda:0")
+    assert B.lib().anszp_pack_layers_device(s.data_ptr(), jobs.data_ptr(), len(syms), nc, f.data_ptr(), w.table_log, w.n_streams, chunks.data_ptr(),
+                                            hdr.data_ptr(), payload.data_ptr(), cap, used.data_ptr(), status.data_ptr(),
+                                            torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    return chunks, hdr, payload, used, status
+
+
+@pytest.mark.parametrize("chunk,N", [(5000, 64), (300, 17)])             # few chunks, and more than two per CU
+def test_the_entry_points_without_scratch_memory(orc, chunk, N):
+    from helpers import oracle_encode
+    layers = [W.tiny(seed=s, n=40000 + 17 * s, bitwidth=2 + s, n_streams=N, chunk_size=chunk, table_log=11, p0=0.6).layers[0] for s in range(6)]
+    w = W.Workload("raw", layers, 11, N, chunk, "bf16")
+    c = oracle_encode(orc, w)
+    _same(c, w, _pack_without_scratch(w, c))
+    sym, f = w.symbols()[1], torch.from_numpy(c.freqs[1].astype(np.uint32).view(np.int32)).to("cuda:0")
+    s = torch.from_numpy(sym).to("cuda:0")
+    chunks, hdr, payload, used, status = B.pack_layer_device(s, f, 11, N, chunk, 3, 64, 8, 5)
+    again = [torch.zeros_like(chunks), torch.zeros_like(hdr), torch.full_like(payload, -1), torch.zeros_like(used), torch.zeros_like(status)]
+    assert B.lib().anszp_pack_layer_device(s.data_ptr(), len(sym), f.data_ptr(), 11, N, chunk, 3, 64, 8, 5, again[0].data_ptr(), again[1].data_ptr(),
+                                           again[2].data_ptr(), payload.numel(), again[3].data_ptr(), again[4].data_ptr(),
+                                           torch.cuda.current_stream().cuda_stream) == 0
+    for a, b in zip((chunks, hdr, payload, used, status), again):
+        assert torch.equal(a, b)
