@@ -13,7 +13,7 @@
 // the blocked layout the 16 lanes that hold the same 8 k of 16 neighbouring pixels read 256 contiguous
 // bytes, where NHWC makes them read 16 pieces a whole pixel apart.
 //
-// One workgroup owns a panel of 16 * MR output channels (MR = 4, 2 or 1 row tiles of
+// One workgroup owns a panel of 16 * MR output channels (MR = 4, 2 or 1 row tiles, conv_sliced_kernel also half a one, of
 // v_mfma_f32_16x16x32_bf16: as many as fit in LDS) and a range of output pixels.  Phase 1: its twelve
 // wavefronts decode the chunks that hold those weight rows, one lane per stream (Sec. II-A, III-B),
 // through the table's look-ahead entries (one look-up per run of up to eight symbols) into a
@@ -341,9 +341,9 @@ __device__ __forceinline__ uint32_t unit_of_workgroup() {
     return die * per_die + min(die, extra) + blockIdx.x / kDies;
 }
 
-// Phase 1: panel `mtile` (16 * MR weight rows) into LDS; the caller's barrier follows.  meanwhile(): called while the
+// Phase 1: panel `mtile` (ROWS weight rows) into LDS; the caller's barrier follows.  meanwhile(): called while the
 // first loads are on their way.  Returns the layer's quantizer.
-template <uint32_t MR, bool P16, class MEANWHILE>
+template <uint32_t ROWS, bool P16, class MEANWHILE>
 __device__ __forceinline__ anszp_layer_t decode_panel(const ConvParams& p, uint8_t* lds, uint32_t mtile, MEANWHILE&& meanwhile) {
     const uint32_t L = 1u << p.table_log;
     const uint32_t ahead_bytes = 16u * L;                         // 2 L look-ahead entries of two words
@@ -353,7 +353,7 @@ __device__ __forceinline__ anszp_layer_t decode_panel(const ConvParams& p, uint8
     constexpr uint32_t kElem = P16 ? 2u : 1u;                     // bytes per panel element
     const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // ---- phase 1: the layer's look-ahead entries into LDS, then this workgroup's 16 * MR weight rows.
+    // ---- phase 1: the layer's look-ahead entries into LDS, then this workgroup's weight rows.
     // Every global read that depends only on the kernel's arguments is issued before any is waited for: the
     // descriptors of this wavefront's chunks (lane i: its i-th chunk, panel chunk wave + i * kWaves), the layer's
     // quantizer, the triple of the last state (it carries the layer's dominant symbol if there is one), the
@@ -421,7 +421,7 @@ __device__ __forceinline__ anszp_layer_t decode_panel(const ConvParams& p, uint8
             const uint32_t h = __float_as_uint(static_cast<float>(int32_t(dominant) - int32_t(lay.zero_point))) >> 16;
             fill = h | h << 16;
         }
-        const uint32_t panel_quads = (kRows * MR * p.row_stride * kElem + 64u) / 16u;
+        const uint32_t panel_quads = (ROWS * p.row_stride * kElem + 64u) / 16u;
         for (uint32_t i = tid; i < panel_quads; i += kThreads) reinterpret_cast<words4*>(panel)[i] = words4{fill, fill, fill, fill};
     }
 #pragma unroll
@@ -493,7 +493,7 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
     const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t unit = unit_of_workgroup(), mtile = unit % p.n_mtiles, split = unit / p.n_mtiles;
-    const anszp_layer_t lay = decode_panel<MR, P16>(p, lds, mtile, [] {});
+    const anszp_layer_t lay = decode_panel<kRows * MR, P16>(p, lds, mtile, [] {});
     __syncthreads();
     // kGeneric: what every k of the reduction means, worked out once (the table and the staging room are free now):
     // two words per k, the offset of its activation from the one under the first tap's first channel, and its
@@ -1006,9 +1006,11 @@ __device__ __forceinline__ words4 neighbours(const words4& tile, const words4& b
     return v;
 }
 
-template <uint32_t MR, bool P16, uint32_t MODE, uint32_t QT, bool TAIL>
+template <uint32_t ROWS, bool P16, uint32_t MODE, uint32_t QT, bool TAIL>
 __global__ __launch_bounds__(kThreads) void conv_sliced_kernel(ConvParams p) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    constexpr uint32_t MR = ROWS < kRows ? 1u : ROWS / kRows;     // row tiles
+    constexpr bool kHalf = ROWS < kRows;                          // half a row tile: its lower rows are the upper ones again, and not stored
     constexpr uint32_t NS = MODE == kPoint ? 1u : 3u;             // steps of a unit
     constexpr uint32_t NF = MODE == kRow ? 3u : 1u;               // vectors of a unit that are loaded per column tile
     constexpr uint32_t kSlots = units_in_flight(MR, MODE, QT);
@@ -1040,11 +1042,11 @@ __global__ __launch_bounds__(kThreads) void conv_sliced_kernel(ConvParams p) {
         if constexpr (MODE == kShift) {
             const uint32_t w = wo - p.first_column;
             const uint32_t at = (b * p.y_image + (ho * p.out_w + w) * p.y_pixel + (kg >> 1) * p.y_block + 4u * (kg & 1u)) << y_elem;
-            return ((pix < end) & (w < p.out_w)) ? at : kOutside;
+            return ((pix < end) & (w < p.out_w) & (!kHalf || kg < 2u)) ? at : kOutside;
         }
         // D: lane holds column lane % 16, rows 4 * (lane / 16) + 0..3 of a row tile
         const uint32_t at = (b * p.y_image + (ho * p.out_w + wo) * p.y_pixel + (kg >> 1) * p.y_block + 4u * (kg & 1u)) << y_elem;
-        return pix < end ? at : kOutside;
+        return ((pix < end) & (!kHalf || kg < 2u)) ? at : kOutside;
     };
     // a round's tiles dealt evenly: QT or one fewer each
     auto first_tile = [&](uint32_t g) { return g * p.wave_tiles + min(g, p.wave_tiles_rest); };
@@ -1124,30 +1126,30 @@ __global__ __launch_bounds__(kThreads) void conv_sliced_kernel(ConvParams p) {
 #pragma unroll
         for (uint32_t d = 0; d < kSlots; ++d) request(d);
     };
-    const anszp_layer_t lay = decode_panel<MR, P16>(p, lds, mtile, [&]() __attribute__((always_inline)) {
+    const anszp_layer_t lay = decode_panel<ROWS, P16>(p, lds, mtile, [&]() __attribute__((always_inline)) {
         place(0u);
         if constexpr (kEarly) request_first();
     });
     __syncthreads();
     if constexpr (!P16) widen_panel<MR>(p, lds, lay);
 
-    const uint32_t a_at = lds_address(lds) + (P16 ? p.panel_off : 0u) + (col * p.row_stride + 8u * kg) * 2u;
+    const uint32_t a_at = lds_address(lds) + (P16 ? p.panel_off : 0u) + ((kHalf ? col & 7u : col) * p.row_stride + 8u * kg) * 2u;
     const uint32_t tile_stride = kRows * p.row_stride * 2u;
     const __amdgpu_buffer_rsrc_t y_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, p.y_bytes, 0x00020000);
     const bool per_channel = lay.channel_len != 0;
     auto store = [&](uint32_t m, uint32_t at, const floatx4 sum) {
-        const uint32_t tile = mtile * MR + m;                     // (o = 16 * tile + 4 * kg + i)
+        const uint32_t tile = mtile * MR + m;                     // (o = 16 * tile + 4 * kg + i, of half a row tile 8 * tile + ..)
         float sc[4] = {lay.scale, lay.scale, lay.scale, lay.scale};
         if (per_channel) {
 #pragma unroll 1
             for (uint32_t i = 0; i < 4; ++i) {
-                const uint64_t ch = lay.scales_offset + tile * kRows + 4u * kg + i;
+                const uint64_t ch = lay.scales_offset + tile * (kHalf ? ROWS : kRows) + 4u * kg + i;
                 const float v = ch < p.n_scales ? p.scales[ch] : 0.0f;
                 sc[0] = i == 0u ? v : sc[0]; sc[1] = i == 1u ? v : sc[1]; sc[2] = i == 2u ? v : sc[2]; sc[3] = i == 3u ? v : sc[3];
             }
         }
         const floatx4 out = {sum[0] * sc[0], sum[1] * sc[1], sum[2] * sc[2], sum[3] * sc[3]};
-        const uint32_t tile_at = (2u * tile * p.y_block) << y_elem;
+        const uint32_t tile_at = ((kHalf ? 1u : 2u) * tile * p.y_block) << y_elem;
         if (p.y_bf16) {                                           // round to nearest even (v_cvt_pk_bf16_f32)
             typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
             const bf16x4 r = {static_cast<__bf16>(out[0]), static_cast<__bf16>(out[1]), static_cast<__bf16>(out[2]), static_cast<__bf16>(out[3])};
@@ -1250,37 +1252,39 @@ __global__ __launch_bounds__(kThreads) void conv_sliced_kernel(ConvParams p) {
     }
 }
 
-template <uint32_t MR, bool P16, uint32_t MODE, bool TAIL>
-void (*sliced_kernel(uint32_t qt))(ConvParams) {
-    if constexpr (most_tiles(MR, MODE) == 4u) {
-        if (qt == 4u) return conv_sliced_kernel<MR, P16, MODE, 4, TAIL>;
+typedef void (*ConvKernel)(ConvParams);
+template <uint32_t ROWS, bool P16, uint32_t MODE, bool TAIL>
+ConvKernel sliced_kernel(uint32_t qt) {
+    if constexpr (most_tiles(ROWS < kRows ? 1u : ROWS / kRows, MODE) == 4u) {
+        if (qt == 4u) return conv_sliced_kernel<ROWS, P16, MODE, 4, TAIL>;
     }
-    return qt == 3u ? conv_sliced_kernel<MR, P16, MODE, 3, TAIL> : qt == 2u ? conv_sliced_kernel<MR, P16, MODE, 2, TAIL> : conv_sliced_kernel<MR, P16, MODE, 1, TAIL>;
+    return qt == 3u ? conv_sliced_kernel<ROWS, P16, MODE, 3, TAIL> : qt == 2u ? conv_sliced_kernel<ROWS, P16, MODE, 2, TAIL> : conv_sliced_kernel<ROWS, P16, MODE, 1, TAIL>;
 }
-template <uint32_t MR, bool P16, bool TAIL>
-void (*sliced_kernel(uint32_t mode, uint32_t qt))(ConvParams) {
-    return mode == kPoint ? sliced_kernel<MR, P16, kPoint, TAIL>(qt) : mode == kShift ? sliced_kernel<MR, P16, kShift, TAIL>(qt) : sliced_kernel<MR, P16, kRow, TAIL>(qt);
+template <uint32_t ROWS, bool P16, bool TAIL>
+ConvKernel sliced_kernel(uint32_t mode, uint32_t qt) {
+    return mode == kPoint ? sliced_kernel<ROWS, P16, kPoint, TAIL>(qt) : mode == kShift ? sliced_kernel<ROWS, P16, kShift, TAIL>(qt) : sliced_kernel<ROWS, P16, kRow, TAIL>(qt);
 }
 template <bool TAIL>
-void (*sliced_kernel(uint32_t mr, bool p16, uint32_t mode, uint32_t qt))(ConvParams) {
-    return p16 ? (mr == 4 ? sliced_kernel<4, true, TAIL>(mode, qt) : mr == 2 ? sliced_kernel<2, true, TAIL>(mode, qt) : sliced_kernel<1, true, TAIL>(mode, qt))
-               : (mr == 4 ? sliced_kernel<4, false, TAIL>(mode, qt) : mr == 2 ? sliced_kernel<2, false, TAIL>(mode, qt) : sliced_kernel<1, false, TAIL>(mode, qt));
+ConvKernel sliced_kernel(uint32_t rows, bool p16, uint32_t mode, uint32_t qt) {
+    if (rows < kRows) return sliced_kernel<kRows / 2u, true, TAIL>(mode, qt);
+    return p16 ? (rows == 64u ? sliced_kernel<64, true, TAIL>(mode, qt) : rows == 32u ? sliced_kernel<32, true, TAIL>(mode, qt) : sliced_kernel<16, true, TAIL>(mode, qt))
+               : (rows == 64u ? sliced_kernel<64, false, TAIL>(mode, qt) : rows == 32u ? sliced_kernel<32, false, TAIL>(mode, qt) : sliced_kernel<16, false, TAIL>(mode, qt));
 }
 
 template <bool TAIL>
 bool allow_all_lds() {
     for (uint32_t mode = kPoint; mode <= kRow; ++mode)
-        for (const uint32_t mr : {1u, 2u, 4u})
-            for (uint32_t qt = 1; qt <= most_tiles(mr, mode); ++qt)
+        for (const uint32_t rows : {8u, 16u, 32u, 64u})
+            for (uint32_t qt = 1; qt <= most_tiles(std::max(1u, rows / kRows), mode); ++qt)
                 for (const bool p16 : {false, true})
-                    if (hipFuncSetAttribute(reinterpret_cast<const void*>(sliced_kernel<TAIL>(mr, p16, mode, qt)), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+                    if (hipFuncSetAttribute(reinterpret_cast<const void*>(sliced_kernel<TAIL>(rows, p16, mode, qt)), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
                         return false;
     return true;
 }
 
-int launch_sliced(const ConvParams& p, uint32_t mr, bool p16, uint32_t mode, uint32_t qt, int device, uint32_t groups, uint32_t lds_bytes, hipStream_t s) {
+int launch_sliced(const ConvParams& p, uint32_t rows, bool p16, uint32_t mode, uint32_t qt, int device, uint32_t groups, uint32_t lds_bytes, hipStream_t s) {
     const bool tail = p.cin % 32u != 0u;
-    void (*const kernel)(ConvParams) = tail ? sliced_kernel<true>(mr, p16, mode, qt) : sliced_kernel<false>(mr, p16, mode, qt);
+    const ConvKernel kernel = tail ? sliced_kernel<true>(rows, p16, mode, qt) : sliced_kernel<false>(rows, p16, mode, qt);
     // the kernels may use all of the CU's LDS: said for all of them by a device's first call, because which one a layer gets
     // depends on the batch too, and a call may be captured whose layer ran before with another batch (concurrent first callers
     // at worst both say it)
@@ -1315,7 +1319,7 @@ int conv_sliced(ConvParams p, const anszp_conv_args_t& a, uint32_t images, uint3
         // (without padding kShift takes two pixels more per row: narrow images are better off with kRow)
         auto plan_of = [&](uint32_t mode) {
             const uint32_t columns = p.out_w + (mode == kShift && a.pad == 0u ? 2u : 0u);
-            return plan_sliced(a, mode, p.K, p.row_stride, (n * p.out_h * columns + 15u) / 16u, cus);
+            return plan_half_tile(a, mode, p.K, p.row_stride, (n * p.out_h * columns + 15u) / 16u, cus);
         };
         uint32_t mode = widest;
         SlicedPlan plan = plan_of(mode);
@@ -1328,9 +1332,9 @@ int conv_sliced(ConvParams p, const anszp_conv_args_t& a, uint32_t images, uint3
         p.columns = p.out_w + 2u * p.first_column;
         magic(p.columns, p.columns_magic, p.columns_shift);
         p.n_pixels = n * p.out_h * p.columns;
-        p.n_mtiles = a.cout / (kRows * plan.mr);
+        p.n_mtiles = a.cout / plan.rows;
         magic(p.n_mtiles, p.n_mtiles_magic, p.n_mtiles_shift);
-        p.chunks_per_panel = kRows * plan.mr / a.rows_per_chunk;
+        p.chunks_per_panel = plan.rows / a.rows_per_chunk;
         p.pixels_per_split = 16u * plan.tiles_per_split;
         p.k_groups = plan.k_groups;
         p.t_groups = kWaves / plan.k_groups;
@@ -1339,7 +1343,7 @@ int conv_sliced(ConvParams p, const anszp_conv_args_t& a, uint32_t images, uint3
         p.wave_tiles_rest = plan.round_tiles % p.t_groups;
         p.round_tiles = plan.round_tiles;
         p.slice_units = plan.slice_units;
-        const int rc = launch_sliced(p, plan.mr, plan.p16, mode, plan.qt, device, p.n_mtiles * plan.splits, plan.lds_bytes, s);
+        const int rc = launch_sliced(p, plan.rows, plan.p16, mode, plan.qt, device, p.n_mtiles * plan.splits, plan.lds_bytes, s);
         if (rc != ANSZP_OK) return rc;
     }
     return ANSZP_OK;

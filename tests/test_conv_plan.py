@@ -78,3 +78,13 @@ def test_plans_of_channels_that_are_multiples_of_eight(tmp_path):
     driver = driver.replace("a.kh) * (a.cin / 32u);", "a.kh) * ((a.cin + 31u) / 32u);")
     assert driver.count("8u * upto") == 1 and driver.count("/ 8u * 8u") == 1 and driver.count("+ 31u) / 32u)") >= 1
     _run(tmp_path, driver)
+
+
+def test_plans_of_half_a_row_tile(tmp_path):
+    """What holds for whole row tiles holds for panels of eight channels, which are of bf16 values always."""
+    driver = DRIVER.replace("plan_sliced(a, mode,", "plan_half_tile(a, mode,").replace("p.mr == 1u || p.mr == 2u || p.mr == 4u", "p.rows == (p.rows == 8u ? 8u : 16u * p.mr)")
+    driver = driver.replace("a.cout % (kRows * p.mr) == 0u", "a.cout % p.rows == 0u && p.rows % a.rows_per_chunk == 0u && (p.rows > 8u || (p.p16 && ++halves))")
+    driver = driver.replace("a.cout / (kRows * p.mr), elems = kRows * p.mr * row_stride", "a.cout / p.rows, elems = p.rows * row_stride")
+    driver = driver.replace("std::mt19937 rng(1);", "std::mt19937 rng(1); uint32_t halves = 0;").replace("std::puts", "if (halves > 2000u) std::puts")
+    assert driver.count("halves") == 3 and driver.count("p.rows") >= 6
+    _run(tmp_path, driver)
