@@ -344,7 +344,7 @@ typedef struct {
     void*           scratch;               /* [device] 16-byte aligned, anszp_pack_scratch_bytes; in use until the launches are done */
     uint64_t        scratch_bytes;
 } anszp_pack_set_t;
-/* [host only] 32 + 16 + 2048 + 2 * max(2^table_log, 8) bytes a layer (0 for a table_log out of range). */
+/* [host only] 32 + 16 + 2048 + 2 * max(2^table_log, 8) bytes a layer and 272 (0 for a table_log out of range). */
 uint64_t anszp_pack_scratch_bytes(uint32_t n_layers, int table_log);
 int anszp_pack_set_device(const anszp_pack_set_t* set, void* hip_stream);
 

@@ -615,7 +615,7 @@ def conv_fused(d: DeviceContainer, layer: int, first_chunk: int, rows_per_chunk:
 # --------------------------------------------------------------------------- packing on the GPU
 def _pack_scratch_bytes(n_layers: int, table_log: int) -> int:
     """What anszp_pack_scratch_bytes gives."""
-    return n_layers * (2096 + 2 * max(1 << table_log, 8))
+    return n_layers * (2096 + 2 * max(1 << table_log, 8)) + 272
 
 
 def _pack_set(torch, dev, symbols_dev, freqs_dev, sizes, chunk_sizes, n_chunks: int, table_log: int, n_streams: int, cap: int, out=None,
@@ -624,7 +624,7 @@ def _pack_set(torch, dev, symbols_dev, freqs_dev, sizes, chunk_sizes, n_chunks: 
     n = len(sizes)
     scratch_bytes = _pack_scratch_bytes(n, table_log)
     empty, int32, uint8 = torch.empty, torch.int32, torch.uint8
-    scratch = empty(max(scratch_bytes, 1), dtype=uint8, device=dev)
+    scratch = empty(scratch_bytes, dtype=uint8, device=dev)
     if out is None:
         out = (empty(max(n_chunks, 1) * CHUNK_DTYPE.itemsize, dtype=uint8, device=dev), empty(max(n_chunks * n_streams, 4), dtype=int32, device=dev),
                empty(max(cap, 4), dtype=int32, device=dev), empty(1, dtype=torch.int64, device=dev), empty(2, dtype=int32, device=dev))

@@ -54,8 +54,10 @@ struct EncParams {
     unsigned long long* used;
     uint32_t* status;
     const uint32_t* prepared;               // null, or a record of encoding tables per layer (encode_prepare)
+    uint32_t* finish;                       // with `prepared`: workgroups that are done, then a bit per chunk that was not written
     uint64_t n_chunks, out_offset, payload_word_offset, payload_cap_words;
     uint32_t n_layers, table_log, n_streams, layer_id, stream_offset, chunks_per_group, spin_limit;
+    uint32_t longest_chunk;                 // with `prepared`: symbols
 };
 
 // A layer's encoding tables.  info[s]: what x + info.x has in its upper half is the number of bits symbol s drops
@@ -485,6 +487,7 @@ __global__ __launch_bounds__(kThreads) void encode_begin(EncParams p) {
 constexpr uint32_t kDirectSymbols = 128u;
 constexpr uint32_t kClearUnits = 8u * kThreads;             // of 16 bytes, per workgroup
 constexpr uint32_t kJobsPerLaunch = 64u;
+constexpr uint32_t kFinishWords = 1u + 64u;                 // EncParams::finish: up to 2,048 chunks are packed at once
 struct JobsArg { anszp_pack_job_t job[kJobsPerLaunch]; };
 struct PrepareParams {
     anszp_pack_job_t* jobs;                                 // null: one layer, of `n_jobs` 0
@@ -519,6 +522,7 @@ __global__ __launch_bounds__(kThreads, 4) void encode_prepare(EncParams p, Prepa
         const uint64_t share = blockIdx.x - q.table_groups;
         if (share == 0u) {
             store_jobs(q, jobs);
+            if (tid < kFinishWords) p.finish[tid] = 0u;
             if (q.clear && tid < 2u) p.status[tid] = 0u;
         }
         uint64_t first = share * kClearUnits, end = first + kClearUnits;        // among the units of all buffers, one behind the other
@@ -637,13 +641,26 @@ __device__ __forceinline__ bool words_before(const EncParams& p, uint64_t c, uin
     return gave_up == 0u;
 }
 
-__global__ __launch_bounds__(kThreads, 4) void encode_once(EncParams p) {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[kOnceLds];
-    OnceLds& t = *reinterpret_cast<OnceLds*>(lds);
+// Chunk c.  FINISH: its descriptor and words are complete where this returns true; false: its words before are not known.
+template <bool FINISH>
+__device__ __forceinline__ bool encode_chunk(const EncParams& p, OnceLds& t, uint64_t c) {
     const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t N = p.n_streams, L = 1u << p.table_log;
-    const uint64_t c = blockIdx.x;
     auto publish = [&](uint32_t words) { __hip_atomic_store(&p.chunks[c].payload_words, words, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    // FINISH: where the chunk's words begin; the last chunk knows the total
+    auto settle = [&](uint64_t before, uint64_t padded) {
+        if (tid != 0) return;
+        p.chunks[c].payload_offset = p.payload_word_offset + before;
+        if (c + 1u < p.n_chunks) return;
+        *p.used = before + padded;
+        if (before + padded > p.payload_cap_words) report(p.status, ANSZP_ST_NO_SPACE);
+    };
+    auto settle_empty = [&]() {
+        uint64_t before = 0;
+        const bool known = words_before(p, c, p.spin_limit, t.before, t.gave_up, before);
+        if (known) settle(before, 0u);
+        return known;
+    };
     uint32_t layer;
     anszp_pack_job_t job;
     uint64_t local;
@@ -652,11 +669,11 @@ __global__ __launch_bounds__(kThreads, 4) void encode_once(EncParams p) {
             report(p.status, ANSZP_ST_BAD_DESC);
             anszp_chunk_t* const d = &p.chunks[c];
             d->layer_id = d->n_symbols = d->stream_offset = 0u;
-            d->out_offset = kNotWritten;
+            d->out_offset = FINISH ? 0u : kNotWritten;
             publish(0u);
         }
         if (tid < N) p.stream_hdr[c * N + tid] = 0u;
-        return;
+        return FINISH ? settle_empty() : true;
     }
     const bool ok = layer_tables(p, layer, t.tables, t.spread);
     const uint64_t out_offset = p.out_offset + job.first_symbol + local * job.chunk_size;
@@ -664,18 +681,21 @@ __global__ __launch_bounds__(kThreads, 4) void encode_once(EncParams p) {
         anszp_chunk_t* const d = &p.chunks[c];
         d->layer_id = p.jobs ? layer : p.layer_id;
         d->n_symbols = n_symbols;
-        d->out_offset = out_offset | (later ? kNotWritten : 0u);
+        d->out_offset = out_offset | (later && !FINISH ? kNotWritten : 0u);
         d->stream_offset = p.stream_offset + static_cast<uint32_t>(c) * N;
     };
     if (!ok) {
         if (tid == 0 && local == 0) report(p.status, ANSZP_ST_BAD_FREQ);
-        if (!p.jobs) return;                                // (one layer: nothing is written)
+        if (!p.jobs) {                                      // (one layer: nothing is written)
+            if (FINISH && tid == 0 && c + 1u == p.n_chunks) *p.used = 0ull;
+            return true;
+        }
         if (tid < N) p.stream_hdr[c * N + tid] = 0u;
         if (tid == 0) {
             describe(0u, true);
             publish(0u);
         }
-        return;
+        return FINISH ? settle_empty() : true;
     }
     const ChunkStreams s = streams_of(p, job, local, lane);
     if (tid == 0) t.bad = t.over = 0u;
@@ -825,20 +845,25 @@ __global__ __launch_bounds__(kThreads, 4) void encode_once(EncParams p) {
     if (tid == 0 && t.bad) report(p.status, ANSZP_ST_BAD_SYMBOL);
     const bool over = t.over != 0u;
     uint64_t before = 0;
-    const bool known = !over && words_before(p, c, p.spin_limit, t.before, t.gave_up, before);
+    const bool known = (FINISH || !over) && words_before(p, c, p.spin_limit, t.before, t.gave_up, before);
     const uint32_t nw = t.n_words[lane], n_words = __builtin_amdgcn_readlane(t.first[lane] + nw, kWave - 1);
     const uint64_t padded = (uint64_t(n_words) + 3ull) & ~3ull;
     if (wave == 0u && lane < N)
-        p.stream_hdr[c * N + lane] = t.x[lane] | (known ? 0u : ((32u - t.pad[lane]) & 15u) << 12) | nw << 16;
-    if (!known) {
-        if (tid == 0) {
-            p.chunks[c].payload_offset = t.fifth;
-            p.chunks[c].out_offset = out_offset | kNotWritten;
+        p.stream_hdr[c * N + lane] = t.x[lane] | (FINISH || known ? 0u : ((32u - t.pad[lane]) & 15u) << 12) | nw << 16;
+    if constexpr (FINISH) {
+        if (!known) return false;
+        settle(before, padded);
+    } else {
+        if (!known) {
+            if (tid == 0) {
+                p.chunks[c].payload_offset = t.fifth;
+                p.chunks[c].out_offset = out_offset | kNotWritten;
+            }
+            return true;
         }
-        return;
+        if (tid == 0) p.chunks[c].payload_offset = p.payload_word_offset + before;
     }
-    if (tid == 0) p.chunks[c].payload_offset = p.payload_word_offset + before;
-    if (before > p.payload_cap_words || padded > p.payload_cap_words - before) return;    // no room: reported by the launch behind this one
+    if (before > p.payload_cap_words || padded > p.payload_cap_words - before) return true;    // no room: reported with the total
     uint32_t* const out = p.payload + before;
     // A wavefront takes a stream at a time, a lane every 64th word: the bits as laid down, moved up by the zero bits behind
     // the stream's last one, are whole words of the stream from its last to its first, bit-reversed.
@@ -851,6 +876,93 @@ __global__ __launch_bounds__(kThreads, 4) void encode_once(EncParams p) {
         }
     }
     if (tid < padded - n_words) out[n_words + tid] = 0u;        // up to three pad words
+    return true;
+}
+
+// Without scratch memory: encode_rest behind it.
+__global__ __launch_bounds__(kThreads, 4) void encode_once(EncParams p) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kOnceLds];
+    encode_chunk<false>(p, *reinterpret_cast<OnceLds*>(lds), blockIdx.x);
+}
+
+// A stream's words symbol by symbol, nothing asked for ahead: for the few chunks the last workgroup writes, in little code.
+__device__ __forceinline__ uint32_t walk_plain(const EncTables& t, const ChunkStreams& s, uint32_t N, uint32_t L, uint32_t* words, uint32_t n_words, uint32_t pad) {
+    uint32_t x = L, bits = 0, cnt = pad, at = n_words;
+    uint64_t acc = 0;
+#pragma unroll 1
+    for (uint32_t row = s.max_len; row-- > 0u;) {
+        if (row + 1u == s.max_len && !s.has_last) continue;
+        const uint2 i = t.info[(s.chunk + uint64_t(row) * N)[s.lane_off]];
+        const uint32_t nb = (x + i.x) >> 16;
+        acc |= uint64_t(__builtin_amdgcn_ubfe(x, 0u, nb)) << cnt;
+        cnt += nb;
+        bits += nb;
+        if (cnt >= 32u) {
+            if (at) words[--at] = __brev(static_cast<uint32_t>(acc));
+            acc >>= 32;
+            cnt -= 32u;
+        }
+        x = *reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(t.next) + (2u * (x >> nb) + i.y));
+    }
+    return bits;
+}
+
+// With it, and with streams that fit LDS whatever their symbols: the last workgroup to be done writes the chunks of those that
+// gave up waiting (all chunks' words are published by then), and no launch is needed behind this one: 144 chunks of 16,384
+// symbols with their tables 34.6 -> 32.8 us, three layers of 533,769 30.5 -> 29.8.  (Writing chunks that do not fit here too took
+// the kernel 85 KB of code and registers to scratch memory: 69 us.)
+__global__ __launch_bounds__(kThreads, 4) void encode_all(EncParams p) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kOnceLds];
+    OnceLds& t = *reinterpret_cast<OnceLds*>(lds);
+    const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1u);
+    uint32_t* const left = p.finish + 1;
+    const bool done = encode_chunk<true>(p, t, blockIdx.x);
+    __syncthreads();
+    if (tid == 0) {
+        if (!done) {
+            atomicOr(&left[blockIdx.x / 32u], 1u << blockIdx.x % 32u);
+            __threadfence();                                // (before it is counted as done)
+        }
+        t.over = atomicAdd(&p.finish[0], 1u) + 1u == gridDim.x ? 1u : 0u;
+    }
+    __syncthreads();
+    if (!t.over) return;
+    __threadfence();
+    const uint32_t marks = __hip_atomic_load(&left[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    static_assert(kFinishWords == 1u + kWave, "a lane a word");
+    for (uint64_t c = 0; c < p.n_chunks; ++c) {             // (alike for every thread)
+        const uint32_t word = __builtin_amdgcn_readlane(marks, uint32_t(c) / 32u);
+        if (!word) c |= 31u;                                // none of the word's
+        if (!(word >> c % 32u & 1u)) continue;
+        __syncthreads();                                    // (what words_before and the tables use is free)
+        uint64_t before = 0;
+        const bool known = words_before(p, c, 1u << 16, t.before, t.gave_up, before);
+        uint32_t layer, nw = 0, bits = 0;
+        anszp_pack_job_t job;
+        uint64_t local;
+        const bool ok = layer_of_chunk(p, c, layer, job, local) && layer_tables(p, layer, t.tables, t.spread);
+        if (tid >= kWave) continue;
+        ChunkStreams s{};
+        if (ok) {
+            s = streams_of(p, job, local, lane);
+            bits = s.has_any ? walk_plain(t.tables, s, p.n_streams, 1u << p.table_log, nullptr, 0u, 0u) : 0u;
+            nw = (bits + 31u) >> 5;
+        }
+        const uint32_t upto = spread_wave_sum(nw), words = __builtin_amdgcn_readlane(upto, kWave - 1u);
+        const uint64_t padded = (uint64_t(words) + 3ull) & ~3ull;
+        const bool room = before <= p.payload_cap_words && padded <= p.payload_cap_words - before;
+        if (tid == 0) {
+            p.chunks[c].payload_offset = p.payload_word_offset + before;
+            if (!known) report(p.status, ANSZP_ST_INTERNAL);
+            if (c + 1u == p.n_chunks) {
+                *p.used = before + padded;
+                if (!room) report(p.status, ANSZP_ST_NO_SPACE);
+            }
+        }
+        if (!ok || !known || !room) continue;
+        walk_plain(t.tables, s, p.n_streams, 1u << p.table_log, p.payload + before + (upto - nw), nw, (32u - bits) & 31u);
+        if (lane < padded - words) p.payload[before + words + lane] = 0u;       // up to three pad words
+    }
 }
 
 // Behind it: the total, and the chunks that were not written.
@@ -914,6 +1026,12 @@ int launch(EncParams& p, hipStream_t s) {
         const uint32_t looks = spin_limit_for_tests().load(std::memory_order_relaxed);
         p.spin_limit = looks ? looks - 1u : 1u << 16;
         const dim3 groups(uint32_t(p.n_chunks)), threads(kThreads);
+        // (a symbol has at most table_log bits)
+        const uint64_t rows = (uint64_t(p.longest_chunk) + p.n_streams - 1u) / p.n_streams;
+        if (p.prepared && p.n_chunks <= 32u * (kFinishWords - 1u) && rows * p.table_log <= 32u * kBitRows) {
+            hipLaunchKernelGGL(encode_all, groups, threads, 0, s, p);
+            return hipGetLastError() == hipSuccess ? ANSZP_OK : ANSZP_E_HIP;
+        }
         if (!p.prepared) hipLaunchKernelGGL(encode_begin, dim3(1), threads, 0, s, p);
         hipLaunchKernelGGL(encode_once, groups, threads, 0, s, p);
         hipLaunchKernelGGL(encode_rest, groups, threads, 0, s, p);
@@ -931,21 +1049,22 @@ int launch(EncParams& p, hipStream_t s) {
 
 extern "C" uint64_t anszp_pack_scratch_bytes(uint32_t n_layers, int table_log) {
     if (table_log < 1 || table_log > ANSZP_MAX_TABLE_LOG) return 0;
-    return uint64_t(n_layers) * (sizeof(anszp_pack_job_t) + 4u * record_words(uint32_t(table_log)));
+    return uint64_t(n_layers) * (sizeof(anszp_pack_job_t) + 4u * record_words(uint32_t(table_log))) + (4u * kFinishWords + 15u) / 16u * 16u;
 }
 
 extern "C" int anszp_pack_set_device(const anszp_pack_set_t* a, void* stream) {
-    if (!a || !a->payload_words_used || !a->status || (a->n_layers && (!a->layer_symbols || !a->chunk_sizes || !a->freqs || !a->scratch))) return ANSZP_E_NULL;
+    if (!a || !a->payload_words_used || !a->status || !a->scratch || (a->n_layers && (!a->layer_symbols || !a->chunk_sizes || !a->freqs))) return ANSZP_E_NULL;
     if (a->table_log < 1 || a->table_log > ANSZP_MAX_TABLE_LOG || a->n_streams < 1 || a->n_streams > ANSZP_MAX_STREAMS || (a->payload_word_offset & 3) ||
         (a->single && a->n_layers != 1u) || a->n_layers >= (1u << 27) || a->scratch_bytes < anszp_pack_scratch_bytes(a->n_layers, int(a->table_log)) ||
         (reinterpret_cast<uintptr_t>(a->scratch) & 15) ||
         (a->clear && ((reinterpret_cast<uintptr_t>(a->chunks) | reinterpret_cast<uintptr_t>(a->stream_hdr) | reinterpret_cast<uintptr_t>(a->payload)) & 15)))
         return ANSZP_E_RANGE;
-    uint64_t n_chunks = 0, n_symbols = 0;
+    uint64_t n_chunks = 0, n_symbols = 0, longest = 0;
     for (uint32_t l = 0; l < a->n_layers; ++l) {
         if (!a->chunk_sizes[l] || a->layer_symbols[l] >= (1ull << 63)) return ANSZP_E_RANGE;
         n_chunks += (a->layer_symbols[l] + a->chunk_sizes[l] - 1u) / a->chunk_sizes[l];
         n_symbols += a->layer_symbols[l];
+        longest = std::max(longest, std::min<uint64_t>(a->layer_symbols[l], a->chunk_sizes[l]));
         if (n_chunks >= (1ull << 32) || n_symbols >= (1ull << 63)) return ANSZP_E_RANGE;
     }
     if (!a->single && (n_chunks >= (1ull << 31) || n_chunks * a->n_streams >= (1ull << 32))) return ANSZP_E_RANGE;
@@ -959,12 +1078,13 @@ extern "C" int anszp_pack_set_device(const anszp_pack_set_t* a, void* stream) {
     p.used = reinterpret_cast<unsigned long long*>(a->payload_words_used); p.status = a->status;
     p.n_chunks = n_chunks; p.payload_word_offset = a->payload_word_offset; p.payload_cap_words = a->payload_cap_words;
     p.out_offset = a->out_offset; p.n_layers = a->n_layers; p.table_log = a->table_log; p.n_streams = a->n_streams;
-    p.layer_id = a->layer_id; p.stream_offset = a->stream_offset;
+    p.layer_id = a->layer_id; p.stream_offset = a->stream_offset; p.longest_chunk = uint32_t(longest);
     if (!a->single && (a->layer_id || a->stream_offset || a->out_offset || a->payload_word_offset)) return ANSZP_E_RANGE;
     PrepareParams q{};
     JobsArg jobs;
     anszp_pack_job_t* const jobs_dev = static_cast<anszp_pack_job_t*>(a->scratch);
     q.records = reinterpret_cast<uint32_t*>(jobs_dev + a->n_layers);
+    p.finish = q.records + size_t(a->n_layers) * record_words(p.table_log);
     if (!a->single) {
         p.jobs = q.jobs = jobs_dev;
     } else {
