@@ -200,29 +200,46 @@ __device__ uint32_t decode_chunk_to_panel(const ConvParams& p, const ChunkDesc& 
             const uint32_t end = kOneRow ? rows + n * kElem : n;
             uint32_t pos = kOneRow ? rows + lane * kElem : lane;
             const uint32_t gap = (p.row_stride - p.K) * kElem;
-            auto look_up = [&](uint32_t window, words2 e) {          // returns the bits it consumed
+            auto advance = [&](uint32_t window, words2 e) {          // to the next entry; returns the bits consumed
                 const uint32_t v = window >> (e.x & 31u);            // the next T + 1 stream bits
-                const uint32_t T = (e.x >> 24) & 15u;
                 at = (e.y + 8u * v) & ahead_mask;
-                pos = __umul24((e.x >> 28) & 7u, step) + pos;        // past the entry's dominant symbols
+                const uint32_t T = (e.x >> 24) & 15u;
+                left -= T;
+                return T;
+            };
+            auto place = [&](uint32_t entry) {                       // the entry's symbols
+                pos = __umul24((entry >> 28) & 7u, step) + pos;      // past its dominant ones
                 uint32_t where = pos;
                 if constexpr (!kOneRow) {
                     uint32_t row;                                    // pos / K (anszp_panel.h)
-                    asm("v_mul_hi_u32_u24 %0, %1, %2" : "=v"(row) : "v"(pos << p.row_of.shift), "v"(p.row_of.magic));
-                    where = __umul24(row, gap) + pos * kElem + rows;
+                    asm("v_mul_hi_u32_u24 %0, %2, %1" : "=v"(row) : "v"(pos << p.row_of.shift), "s"(p.row_of.magic));
+                    where = __umul24(row, gap) + (pos * kElem + rows);
                 }
-                put(min(where, beyond), e.x);
+                put(min(where, beyond), entry);
                 pos += step;
-                return T;
             };
-            while (pos < end) {
-                const uint32_t word = stage_address(left);
-                const uint32_t lo = lds_load<uint32_t>(word), hi = lds_load<uint32_t>(word + 4u);
-                const words2 e = lds_load<words2>(ahead + at);
-                const uint32_t window = __builtin_amdgcn_alignbit(hi, lo, left);
-                const uint32_t T = look_up(window, e);
-                left -= T;
-                if (pos < end) left -= look_up(window << T, lds_load<words2>(ahead + at));
+            // The next entry (and, every second time, the next window's words) is asked for as soon as its index is known, and the
+            // symbols of the one at hand are placed while it is on its way: what a stream's end leaves asked for is not used.
+            if (pos < end) {
+                words2 e = lds_load<words2>(ahead + at);
+                uint32_t word = stage_address(left);
+                uint32_t lo = lds_load<uint32_t>(word), hi = lds_load<uint32_t>(word + 4u);
+                do {
+                    const uint32_t window = __builtin_amdgcn_alignbit(hi, lo, left);
+                    const uint32_t T = advance(window, e);
+                    const words2 second = lds_load<words2>(ahead + at);
+                    __builtin_amdgcn_sched_barrier(0);
+                    place(e.x);
+                    if (pos < end) {
+                        advance(window << T, second);
+                        e = lds_load<words2>(ahead + at);
+                        word = stage_address(left);
+                        lo = lds_load<uint32_t>(word);
+                        hi = lds_load<uint32_t>(word + 4u);
+                        __builtin_amdgcn_sched_barrier(0);
+                        place(second.x);
+                    }
+                } while (pos < end);
             }
             ended_at = kOneRow ? (pos - rows) / kElem : pos;
         };
@@ -349,7 +366,6 @@ __device__ __forceinline__ anszp_layer_t decode_panel(const ConvParams& p, uint8
     const uint32_t ahead_bytes = 16u * L;                         // 2 L look-ahead entries of two words
     uint8_t* ahead = lds + kStageBytes;
     uint8_t* panel = lds + p.panel_off;
-    const uint32_t lds_at = lds_address(lds);                     // 0
     constexpr uint32_t kElem = P16 ? 2u : 1u;                     // bytes per panel element
     const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -439,8 +455,8 @@ __device__ __forceinline__ anszp_layer_t decode_panel(const ConvParams& p, uint8
         }
         const uint32_t j = wave + i * kWaves;
         if (!cur.ok) err |= ANSZP_ST_BAD_DESC;                    // its rows stay the dominant symbol
-        else err |= decode_chunk_to_panel<P16>(p, cur, cur_data, lds_at + kStageBytes, ahead_bytes - 8u, lds_at + wave * (kStageWords * 4u),
-                                               lds_at + p.panel_off + j * p.rows_per_chunk * p.row_stride * kElem, lane, int32_t(lay.zero_point));
+        else err |= decode_chunk_to_panel<P16>(p, cur, cur_data, kStageBytes, ahead_bytes - 8u, wave * (kStageWords * 4u),
+                                               p.panel_off + j * p.rows_per_chunk * p.row_stride * kElem, lane, int32_t(lay.zero_point));
         cur = nxt;
         cur_data = nxt_data;
     }
