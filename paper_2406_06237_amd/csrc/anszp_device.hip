@@ -1123,6 +1123,7 @@ struct Flusher {
 
 #include "anszp_split.h"
 #include "anszp_waves.h"
+#include "anszp_few.h"
 
 // ---------------------------------------------------------------------------------------------
 // Which chunks a workgroup of the look-ahead kernel decodes.  A workgroup that has a CU to itself decodes a
@@ -2229,13 +2230,19 @@ __global__ __launch_bounds__(256) void dequant_runs_kernel(const uint8_t* sym, u
 }
 
 // What a launch would be: checks of the arguments, the kernel's parameters, which kernel.
-struct LaunchChoice { bool stepwise, byte_table, shared, streaming, small, per_channel, split; WavesShape waves; };
+struct LaunchChoice { bool stepwise, byte_table, shared, streaming, small, per_channel, split; uint32_t few; WavesShape waves; };
 
 template <int OUT>
 void launch_decode(const DecodeParams& p, const LaunchChoice& k, hipStream_t s) {
     const uint32_t n_chunks = p.n_chunks;
     if (k.waves.waves) {
         hipLaunchKernelGGL(decode_waves<OUT>, dim3(std::min(n_chunks, device_cus())), dim3(k.waves.waves * kWave), 0, s, p, k.waves);
+    } else if (k.few) {
+        const dim3 grid(mapped_workgroups(n_chunks));
+        if (k.few == 1u) hipLaunchKernelGGL((decode_few<OUT, few_lds(1)>), grid, dim3(kFewThreads), 0, s, p);
+        else if (k.few == 2u) hipLaunchKernelGGL((decode_few<OUT, few_lds(2)>), grid, dim3(kFewThreads), 0, s, p);
+        else if (k.few == 3u) hipLaunchKernelGGL((decode_few<OUT, few_lds(3)>), grid, dim3(kFewThreads), 0, s, p);
+        else hipLaunchKernelGGL((decode_few<OUT, few_lds(4)>), grid, dim3(kFewThreads), 0, s, p);
     } else if (k.split) {
         hipLaunchKernelGGL(decode_split<OUT>, dim3(n_chunks), dim3(kSplitThreads), 0, s, p);
     } else if (k.byte_table) {
@@ -2276,7 +2283,7 @@ int decode_impl(const anszp_decode_args_t* a, int mode, void* hip_stream, uint32
     if (rc != ANSZP_OK) return rc;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const uint32_t nc = static_cast<uint32_t>(a->n_chunks);
-    const bool lookahead = !k.stepwise && !k.byte_table && !k.split && !k.waves.waves;
+    const bool lookahead = !k.stepwise && !k.byte_table && !k.split && !k.waves.waves && !k.few;
     if (plan || plan_only) {
         if (!plan) return ANSZP_E_NULL;
         if ((reinterpret_cast<uintptr_t>(plan) & 15) || plan_bytes < 2u * uint64_t(mapped_workgroups(nc)) * sizeof(PlanRecord)) return ANSZP_E_RANGE;
@@ -2366,6 +2373,20 @@ int choose_launch(const anszp_decode_args_t* a, int mode, bool planned, DecodePa
         k.waves = waves_shape(a->table_log, a->n_streams, mean_words);
         if (k.waves.waves == 8u && per_layer < 24u) k.waves.waves = 0u;
     }
+    // Few chunks: a workgroup per chunk that stages, walks and stores one after the other (decode_few), as many on a CU as there are
+    // chunks for it and LDS for. It starts 1.5 to 2 us earlier than the look-ahead kernel and takes 5 ns a look-up and the
+    // stores behind the last one longer, so the line is a stream's length and a chunk's bytes: 64 streams, bf16, look-ahead
+    // kernel with a plan -> here, chunks of 2,048 / 8,192 / 16,384 / 32,768 / 65,536 symbols (2^12 states, 2.2 bits; 24 of them)
+    // 7.3 / 11.1 / 16.4 / 26.5 / 52.2 -> 5.9 / 10.3 / 15.5 / 25.6 / 52.2; (2^12 states, mostly dominant; 249) 7.0 / 8.5 / 10.0 / 12.3 / 17.3
+    // -> 5.6 / 7.7 / 9.5 / 12.4 / 20.5, as fp32 (99) 6.8 / 8.2 / 9.9 / 12.7 / 17.3 -> 5.7 / 7.4 / 9.7 / 13.6 / 20.2; (2^10 states, 1.2 bits;
+    // 499, two on a CU) 8.8 / 11.0 / 12.9 / 16.4 / 24.2 -> 6.2 / 8.7 / 10.9 / 18.6 / 32.9.  Without a plan 0.4 us more are saved.  Three and
+    // four on a CU without a plan only, 1.0 to 2.1 times as fast (with one 0.68 to 1.4).  Twice the mean chunk has to fit LDS whole.
+    k.few = 0u;
+    const uint64_t per_cu = (a->n_chunks + cus - 1u) / cus;
+    if (mode == 0 && !k.stepwise && !k.split && !k.waves.waves && per_cu <= (planned ? 2u : kFewMostPerCu) && symbols <= 512u * N &&
+        symbols <= (a->out_dtype == ANSZP_OUT_F32 ? 12288u : 20480u) &&
+        (16ull << a->table_log) + 8u * mean_words + 2u * symbols + kFewLeastRoom <= few_lds(uint32_t(per_cu)))
+        k.few = uint32_t(per_cu);
     return ANSZP_OK;
 }
 

@@ -1,0 +1,146 @@
+// Few chunks: a workgroup per chunk, one thing after the other (internal to the library; included by the decode kernels'
+// source, whose names it uses).
+//
+// The look-ahead kernel lets a chunk's walk, the placing of its symbols and the stores run beside each other, which takes
+// hand-overs through LDS, blocks with a boundary between them and a start that deals out tasks.  A call of few short chunks is over
+// before that pays: here all wavefronts stage the table and the words, one walks the streams from end to end
+// (walk_entries) into a buffer that holds the whole chunk, and all convert and store it.  A chunk longer than the buffer
+// comes in windows of the buffer's length, as in decode_waves.
+// What bounds it: memory's latency three times in a row (arguments, descriptor, table and words: about 2 us with the launch),
+// 45 ns a look-up, and the stores at the end.  One chunk of 4,096 symbols (2^10 states) 6.7 -> 4.7 us, 249 of 8,192 (2^12) 8.5 -> 7.7;
+// choose_launch has the line between this kernel and the look-ahead kernel, with both sides.
+#ifndef ANSZP_FEW_H
+#define ANSZP_FEW_H
+
+#include "anszp_walk.h"
+
+constexpr uint32_t kFewThreads = 512u;
+constexpr uint32_t kFewMostPerCu = 4u;
+constexpr uint32_t few_lds(uint32_t per_cu) { return (160u * 1024u / per_cu - 64u) & ~15u; }   // for so many workgroups per CU
+constexpr uint32_t kFewTableLoads = (1u << ANSZP_MAX_TABLE_LOG) / kFewThreads;          // 16-byte loads per thread
+constexpr uint32_t kFewLeastRoom = 2048u;                  // symbols in the buffer
+
+template <int OUT, uint32_t LDS>
+__global__ __launch_bounds__(kFewThreads) void decode_few(DecodeParams p) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[LDS];
+    const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wave = uniform(tid >> 6);
+    const uint32_t number = unit_of_workgroup(blockIdx.x);
+    if (number >= p.n_chunks) return;
+    const anszp_chunk_t c = p.chunks[number];
+    if (!chunk_in_bounds(p, c)) {
+        if (tid == 0) report(p.status, ANSZP_ST_BAD_DESC);
+        return;
+    }
+    const uint32_t L = 1u << p.table_log, N = p.n_streams, table_bytes = 16u << p.table_log, table_at = lds_address(lds);
+    const uint32_t total = c.payload_words, quads = total / 4u;
+    const uint32_t* const src = p.tables + c.layer_id * table_stride_words(p.table_log);
+    const uint32_t* const payload = p.payload + c.payload_offset;
+    // everything that depends on the descriptor alone is asked for at once
+    const uint4* const entries = reinterpret_cast<const uint4*>(src + table_lookahead_offset(p.table_log));
+    uint4 tv[kFewTableLoads];
+#pragma unroll
+    for (uint32_t u = 0; u < kFewTableLoads; ++u)
+        if (u * kFewThreads < L) tv[u] = entries[min(tid + u * kFewThreads, L - 1u)];
+    constexpr uint32_t kWordLoads = 2u;
+    uint4 wv[kWordLoads];
+    const uint4* const rows = quads ? reinterpret_cast<const uint4*>(payload) : entries;
+#pragma unroll
+    for (uint32_t u = 0; u < kWordLoads; ++u) wv[u] = rows[quads ? min(tid + u * kFewThreads, quads - 1u) : 0u];
+    const uint32_t last_at = 4u * quads + tid;              // the last words, and zeros
+    const uint32_t last = last_at < total ? payload[last_at] : 0u;
+    const uint32_t hdr = wave == 0u && lane < N ? p.stream_hdr[c.stream_offset + lane] : 0u;
+    const anszp_layer_t lay = p.layers[c.layer_id];
+    const uint32_t bg = (src[table_triples_offset(p.table_log) + L - 1u] >> 24) * 0x01010101u;     // four times the dominant symbol
+    if (!scales_in_bounds(p, lay, c)) {
+        if (tid == 0) report(p.status, ANSZP_ST_BAD_DESC);
+        return;
+    }
+    // LDS: table | a zero word, the chunk's words from a multiple of 16 bytes on, zeros | buffer
+    const uint32_t skew = static_cast<uint32_t>(c.out_offset) & 7u, n = c.n_symbols + skew;        // (see decode_waves)
+    const uint32_t area = LDS - table_bytes, words_bytes = (4u * (min(total, LDS) + kWavesPad) + 15u) & ~15u;
+    if (c.n_symbols > (1u << 24) || words_bytes + kWavesBehind + kFewLeastRoom > area) {           // the plain loop, like any chunk beyond its kernel's reach
+        if (wave) return;
+        const uint32_t err = decode_chunk_stepwise<OUT>(p, c, lay, WordTable{src + table_triples_offset(p.table_log)}, lane);
+        if (err && lane == 0) report(p.status, err);
+        return;
+    }
+    uint32_t* const words = reinterpret_cast<uint32_t*>(lds + table_bytes) + 3;
+    uint8_t* const buf = lds + table_bytes + words_bytes;
+    const uint32_t buf_at = lds_address(buf), room = min((area - words_bytes - kWavesBehind) & ~15u, (n + 15u) & ~15u);
+    const bool per_channel = lay.channel_len != 0u;
+    auto reversed = [](const uint4& v) { return make_uint4(__brev(v.x), __brev(v.y), __brev(v.z), __brev(v.w)); };
+#pragma unroll
+    for (uint32_t u = 0; u < kFewTableLoads; ++u)
+        if (tid + u * kFewThreads < L) reinterpret_cast<uint4*>(lds)[tid + u * kFewThreads] = walk_entry_pair(tv[u], table_at);
+#pragma unroll
+    for (uint32_t u = 0; u < kWordLoads; ++u)
+        if (tid + u * kFewThreads < quads) reinterpret_cast<uint4*>(words + 1)[tid + u * kFewThreads] = reversed(wv[u]);
+    for (uint32_t i = tid + kWordLoads * kFewThreads; i < quads; i += kFewThreads) reinterpret_cast<uint4*>(words + 1)[i] = reversed(rows[i]);
+    if (last_at < total + kWavesPad - 4u) words[1u + last_at] = __brev(last);
+    if (tid == 0) words[0] = 0u;
+    for (uint32_t i = tid * 16u; i < room + kWavesBehind; i += kFewThreads * 16u) *reinterpret_cast<uint4*>(buf + i) = make_uint4(bg, bg, bg, bg);
+    uint32_t all_words;
+    const uint32_t first_word = wave_exclusive_sum(hdr >> 16, &all_words), first_bit = 32u * min(first_word, total);
+    uint32_t err = all_words != total ? ANSZP_ST_BAD_DESC : 0u;
+    const uint32_t len = (lane < N && c.n_symbols > lane) ? (c.n_symbols - lane + N - 1u) / N : 0u;
+    const uint64_t out_elem0 = c.out_offset - skew, layer_elem0 = out_elem0 - lay.out_base;
+    const bool wide = per_channel && c.out_offset - lay.out_base + c.n_symbols >= (1ull << 32);    // (store8 numbers a layer's elements in 32 bits)
+    __syncthreads();
+    // The walking wavefront's lanes: entry, bit, and the next symbol's position (as in decode_waves).
+    const uint32_t q0 = 8u * lds_address(words) + 31u, q_end = q0 + 32u * total + 1u;
+    uint32_t q = q0 + first_bit, at = table_at + 8u * (2u * (hdr & (L - 1u)) + (words[1u + (first_bit >> 5)] >> 31));
+    uint32_t next = len ? skew + lane : n;
+    for (uint32_t from = 0; from < n; from += room) {
+        const uint32_t end = min(n - from, room);
+        const bool is_last = from + room >= n;
+        if (wave == 0u) {
+            uint32_t to = buf_at + next - from - N;        // an entry's last symbol is N positions before the stream's next
+            __builtin_amdgcn_s_setprio(3);
+            walk_entries<kWalkSpread, true>(at, q, to, q_end, buf_at + end - N, N);
+            __builtin_amdgcn_s_setprio(0);
+            next = to + N + from - buf_at;
+        }
+        __syncthreads();
+        constexpr uint32_t kStore = OUT == ANSZP_OUT_F32 ? 4u : 8u;
+        typedef typename std::conditional<OUT == ANSZP_OUT_F32, uint32_t, uint2>::type symbols_t;
+        for (uint32_t i = tid * kStore; i < end; i += kFewThreads * kStore) {
+            const symbols_t s = *reinterpret_cast<const symbols_t*>(buf + i);
+            const uint32_t pos = from + i;
+            if (__builtin_expect(pos >= skew && i + kStore <= end && !wide, 1)) {
+                if constexpr (OUT == ANSZP_OUT_F32) {
+                    if (per_channel) Flusher<OUT, true>::store4(p, lay, out_elem0 + pos, layer_elem0 + pos, s);
+                    else Flusher<OUT, false>::store4(p, lay, out_elem0 + pos, layer_elem0 + pos, s);
+                } else {
+                    if (per_channel) Flusher<OUT, true>::store8(p, lay, out_elem0 + pos, layer_elem0 + pos, s);
+                    else Flusher<OUT, false>::store8(p, lay, out_elem0 + pos, layer_elem0 + pos, s);
+                }
+            } else {
+#pragma unroll 1
+                for (uint32_t j = pos < skew ? skew - pos : 0u; j < kStore && i + j < end; ++j) {
+                    const uint32_t sym = buf[i + j];
+                    if (per_channel) Flusher<OUT, true>::store1(p, lay, out_elem0 + pos + j, layer_elem0 + pos + j, sym);
+                    else Flusher<OUT, false>::store1(p, lay, out_elem0 + pos + j, layer_elem0 + pos + j, sym);
+                }
+            }
+        }
+        if (is_last) break;
+        // what last look-ups wrote behind the window begins the next one
+        uint2 behind = make_uint2(bg, bg);
+        if (wave == 0u) behind = *reinterpret_cast<const uint2*>(buf + end + lane * 8u);           // (end == room, a multiple of 16)
+        __syncthreads();
+        for (uint32_t i = tid * 16u; i < room + kWavesBehind; i += kFewThreads * 16u) *reinterpret_cast<uint4*>(buf + i) = make_uint4(bg, bg, bg, bg);
+        __syncthreads();
+        if (wave == 0u) *reinterpret_cast<uint2*>(buf + lane * 8u) = behind;
+        __syncthreads();
+    }
+    if (wave) return;
+    // Every stream ends with an entry, in state 0, its words read and no more.
+    if (lane < N) {
+        if (next != (len ? skew + lane + len * N : n) || at - table_at >= 16u) err |= ANSZP_ST_BAD_STATE;
+        if (((q - q0 - first_bit + 31u) >> 5) != hdr >> 16) err |= ANSZP_ST_BAD_LENGTH;
+    }
+    err = wave_or(err);
+    if (err && lane == 0) report(p.status, err);
+}
+
+#endif

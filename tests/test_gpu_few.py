@@ -1,0 +1,109 @@
+"""GPU parity of decode_few (a workgroup per chunk, csrc/anszp_few.h) against the oracle, bit for bit: the calls anszp_decode
+sends there by itself, at the sizes where it can go wrong."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2406_06237_amd import binding as B
+from paper_2406_06237_amd import workloads as W
+
+from helpers import host_from_oracle, oracle_encode, oracle_expected
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(orc, w, planned=False, out_dtype=None):
+    c = oracle_encode(orc, w)
+    if out_dtype:
+        w.out_dtype = out_dtype
+    _, expect = oracle_expected(orc, c, w)
+    d = B.to_device(host_from_oracle(c, w))
+    guard = 4096
+    dt = getattr(torch, {"u8": "uint8", "f32": "float32", "bf16": "bfloat16"}[w.out_dtype])
+    buf = torch.full((w.numel + 2 * guard,), 77, dtype=dt, device="cuda:0")
+    out = buf[guard:guard + w.numel]
+    args = B.decode_args(d, out)
+    if planned:
+        B.decode_planned_raw(args, B.plan_decode(args))
+    else:
+        B.decode_raw(args)
+    assert d.read_status() == (0, 0)
+    assert np.array_equal(B.bits_of(out), expect)
+    assert bool((buf[:guard] == 77).all()) and bool((buf[guard + w.numel:] == 77).all())
+    return d, out, expect
+
+
+def _set(sizes, table_log, n_streams, chunk, dtype="bf16", b=4, p0=0.6):
+    layers = [W.tiny(seed=s, n=n, bitwidth=b, n_streams=n_streams, chunk_size=chunk, table_log=table_log, p0=p0).layers[0] for s, n in enumerate(sizes)]
+    return W.Workload("few", layers, table_log, n_streams, chunk, dtype)
+
+
+@pytest.mark.parametrize("dtype", ["u8", "f32", "bf16"])
+@pytest.mark.parametrize("table_log,N", [(1, 64), (4, 7), (8, 64), (9, 17), (10, 64), (11, 33), (12, 64), (12, 1)])
+def test_tables_streams_and_types(orc, table_log, N, dtype):
+    sizes = [1, 15, 64 * N + 3, 700, 8 * N]                        # chunks at odd offsets, fewer symbols than streams
+    _check(orc, _set(sizes, table_log, N, 1000, dtype, b=1 if table_log == 1 else 4 if table_log >= 5 else 2), planned=table_log % 2 == 0)
+
+
+# one, two, three and four workgroups per CU (of 256): the last with one, the first with two of them
+@pytest.mark.parametrize("n_chunks", [1, 2, 255, 256, 257, 511, 512, 513, 768, 769, 1024, 1025])
+@pytest.mark.parametrize("table_log", [9, 12])
+def test_numbers_of_chunks(orc, n_chunks, table_log):
+    _check(orc, _set([300 * n_chunks - 7], table_log, 64, 300))
+
+
+@pytest.mark.parametrize("table_log,sizes,chunk,dtype", [
+    (12, [20480], 20480, "bf16"), (12, [12288, 5], 12288, "f32"), (12, [24575] + [64] * 40, 65536, "u8"),
+    (12, [150000] + [640] * 60, 200000, "bf16"),                    # a chunk of two windows among short ones
+    (10, [400001, 17] + [640] * 200, 500000, "f32"),                # four windows
+    (9, [70000] + [128] * 300, 80000, "bf16"),                      # two workgroups per CU, two windows
+])
+def test_long_chunks_among_short_ones(orc, table_log, sizes, chunk, dtype):
+    _check(orc, _set(sizes, table_log, 64, chunk, dtype))
+
+
+def test_a_chunk_whose_words_do_not_fit(orc):
+    layers = [W.Layer("dense", (1, 1, 1, 150000), 8, 128, 0.02, np.full(256, 1 / 256), 5)]
+    layers += [W.tiny(seed=s, n=640, bitwidth=3, n_streams=64, chunk_size=640, table_log=12, p0=0.8).layers[0] for s in range(100)]
+    _check(orc, W.Workload("dense", layers, 12, 64, 150000, "bf16"))
+
+
+def test_a_scale_per_channel(orc):
+    for clen in (1, 7, 9 * 64, 100000):
+        n = 5003
+        lay = W.tiny(seed=clen, n=n, bitwidth=5, n_streams=64, chunk_size=2000, table_log=11, p0=0.5).layers[0]
+        lay.channel_len = clen
+        lay.channel_scales = (0.01 + 0.001 * np.arange(-(-n // clen))).astype(np.float32)
+        for dtype in ("bf16", "f32"):
+            _check(orc, W.Workload("channels", [lay], 11, 64, 2000, dtype))
+
+
+def test_corrupt_words_are_reported_and_stay_inside(orc):
+    w = _set([8000, 3001], 11, 64, 4000)
+    d, out, expect = _check(orc, w)
+    rng = np.random.default_rng(3)
+    for _ in range(6):
+        h = d.host
+        bad = h.payload.copy()
+        at = rng.integers(0, len(bad), 20)
+        bad[at] ^= rng.integers(1, 1 << 32, 20, dtype=np.uint64).astype(np.uint32)
+        d.payload.copy_(torch.from_numpy(bad.view(np.uint8)).to("cuda:0"))
+        buf = torch.full((w.numel + 8192,), 77, dtype=torch.bfloat16, device="cuda:0")
+        d.status.zero_()
+        B.decode(d, out=buf[4096:4096 + w.numel])
+        assert d.read_status()[0] & (B.ST_BAD_STATE | B.ST_BAD_LENGTH)
+        assert bool((buf[:4096] == 77).all()) and bool((buf[4096 + w.numel:] == 77).all())
+
+
+def test_replayed_from_a_captured_graph(orc):
+    w = _set([9000, 777], 10, 64, 3000)
+    d, out, expect = _check(orc, w)
+    args = B.decode_args(d, out)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        B.decode_raw(args)
+    for _ in range(4):
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(B.bits_of(out), expect) and d.read_status() == (0, 0)
