@@ -316,6 +316,36 @@ def _enqueue(where: str, function, device, *args):
         raise AnszpError(rc, where)
 
 
+_host = None
+
+
+def _host_calls():
+    """The native calls (csrc/anszp_torch.cpp)."""
+    global _host
+    if _host is None:
+        lib()
+        from paper_2406_06237_amd import _anszp_torch
+        _host = _anszp_torch
+    return _host
+
+
+def _call(where: str, function, device, *args):
+    """_enqueue for a native call: its result, or None where the binding's own path has to take over."""
+    torch = _torch()
+    index = _device_index(torch, device)
+    try:
+        if index == torch.cuda.current_device():
+            r = function(*args, torch._C._cuda_getCurrentRawStream(index))
+        else:
+            with torch.cuda.device(index):
+                r = function(*args, torch._C._cuda_getCurrentRawStream(index))
+    except TypeError:                                     # (an argument of a type or size that it does not take)
+        return None
+    if type(r) is int:
+        raise AnszpError(r, where)
+    return r
+
+
 def _dev(arr: np.ndarray, device):
     """Copy a numpy array to the device as raw bytes (at least 16 bytes so the pointer is valid)."""
     torch = _torch()
@@ -346,6 +376,11 @@ def build_tables_device(freqs_dev, table_log: int, status=None):
     torch = _torch()
     device = freqs_dev.device
     n_tables = freqs_dev.numel() // ALPHABET
+    if device.type == "cuda" and type(table_log) is int and 1 <= table_log <= MAX_TABLE_LOG:
+        tables = _call("anszp_build_tables_device", _host_calls().build_tables_device, device, freqs_dev, n_tables, table_log,
+                       table_words(n_tables, table_log), status)
+        if tables is not None:
+            return tables
     tables = torch.empty(table_words(n_tables, table_log), dtype=torch.int32, device=device)
     _enqueue("anszp_build_tables_device", lib().anszp_build_tables_device, device, freqs_dev.data_ptr(), n_tables, table_log,
              tables.data_ptr(), status.data_ptr() if status is not None else None)
@@ -478,10 +513,14 @@ def dequant_zp(symbols, zero_point: int, scale: float, out_dtype: str = "bf16", 
     torch = _torch()
     n = symbols.numel()
     dev = symbols.device
-    out = torch.empty(max(n, 8), dtype=getattr(torch, _TORCH_OUT[out_dtype]), device=dev)
     zero_point, channel_len = int(zero_point), int(channel_len)
     if not (0 <= zero_point < 1 << 32 and 0 <= channel_len < 1 << 32):
         raise OverflowError("zero_point and channel_len are unsigned 32-bit numbers")
+    if dev.type == "cuda" and type(scale) is float:
+        out = _call("anszp_dequant_zp", _host_calls().dequant_zp, dev, symbols, zero_point, scale, OUT_CODES[out_dtype], channel_len, channel_scales)
+        if out is not None:
+            return out
+    out = torch.empty(max(n, 8), dtype=getattr(torch, _TORCH_OUT[out_dtype]), device=dev)
     lay = _LayerArg(scale, zero_point, 8, channel_len, 0, 0)
     scales, n_sc = (None, 0) if channel_scales is None else (channel_scales.data_ptr(), channel_scales.numel())
     _enqueue("anszp_dequant_zp", lib().anszp_dequant_zp, dev, symbols.data_ptr(), n, C.byref(lay), scales, n_sc, out.data_ptr(),
@@ -659,6 +698,11 @@ def pack_layer_device(symbols_dev, freqs_dev, table_log: int, n_streams: int, ch
     _device_index(torch, dev)                             # (refused before anything is prepared for it)
     n = symbols_dev.numel()
     _check_pack_ranges(n, table_log, n_streams, chunk_size)
+    if payload_cap_words is None:
+        packed = _call("anszp_pack_set_device", _host_calls().pack_set, dev, symbols_dev, freqs_dev, (n,), chunk_size, table_log, n_streams, -1,
+                       1, layer_id, out_offset, payload_word_offset, stream_offset, False)
+        if packed is not None:
+            return packed
     n_chunks = -(-n // chunk_size)
     cap = _pack_bound_words((n,), (chunk_size,), table_log, n_streams) if payload_cap_words is None else payload_cap_words
     return _pack_set(torch, dev, symbols_dev, freqs_dev, (n,), (chunk_size,), n_chunks, table_log, n_streams, cap, None,
@@ -705,6 +749,12 @@ def pack_layers_device(symbols_dev, layer_sizes: Sequence[int], freqs_dev, table
     index = _device_index(torch, dev)                     # (refused before anything is prepared for it)
     if torch.cuda.is_current_stream_capturing():
         raise RuntimeError("pack_layers_device cannot be captured")
+    if out is None and payload_cap_words is None and type(table_log) is int and 1 <= table_log <= MAX_TABLE_LOG and type(n_streams) is int and \
+            1 <= n_streams <= MAX_STREAMS:
+        packed = _call("anszp_pack_set_device", _host_calls().pack_set, dev, symbols_dev, freqs_dev, layer_sizes, chunk_size, table_log, n_streams, -1,
+                       0, 0, 0, 0, 0, True)
+        if packed is not None:
+            return packed
     sizes = [int(n) for n in layer_sizes]
     css = [int(chunk_size)] * len(sizes) if np.isscalar(chunk_size) else [int(c) for c in chunk_size][:len(sizes)]
     n_chunks = sum(_chunk_counts(sizes, css))

@@ -30,6 +30,26 @@ def build_test_helpers(verbose: bool = False) -> str:
     return TEST_HELPER_LIB
 
 
+HOST_SRC = os.path.join(CSRC, "anszp_torch.cpp")
+HOST_LIB = os.path.join(HERE, "_anszp_torch.so")
+
+
+def build_host_calls(verbose: bool = False) -> str:
+    """The binding's native calls (host code, against torch's headers and the library), in-tree like the library."""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(ROOT, "include"), *[f for d in include_paths() + [sysconfig.get_paths()["include"]] for f in ("-isystem", d)],
+           "-o", HOST_LIB, HOST_SRC, "-L", HERE, "-l:" + os.path.basename(LIB), "-L", lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    return HOST_LIB
+
+
 def build_library(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     cmd = [hipcc] + FLAGS + ["-o", LIB] + SOURCES
@@ -41,4 +61,5 @@ def build_library(verbose: bool = False) -> str:
 
 if __name__ == "__main__":
     print(build_library(verbose=True))
+    print(build_host_calls(verbose=True))
     print(build_test_helpers(verbose=True))
