@@ -46,6 +46,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float floatx4;
 typedef __attribute__((ext_vector_type(4))) uint32_t words4;
 typedef __attribute__((ext_vector_type(2))) uint32_t words2;
+typedef words4 __attribute__((aligned(4))) words4_word_aligned;
 
 struct ConvParams {
     const uint32_t* tables;
@@ -500,7 +501,7 @@ enum { kTaps = 0,        // input channels a multiple of 8: a lane's 8 consecuti
        kPointwise = 1,   // as kTaps with a 1 x 1 kernel and no padding: one pixel per column, nothing outside the image
        kGeneric = 2,     // any number of input channels (NHWC): every activation is addressed on its own
        kTapsRing = 3,          // as kTaps with input channels a multiple of 32 * D: D steps' activations in flight
-       kGenericPatch = 4 };    // as kGeneric when whole image rows are multiples of 16 bytes: the image rows under a round
+       kGenericPatch = 4 };    // as kGeneric when image rows are whole words, 16 bytes or more: the image rows under a round
                                // of pixels are staged in LDS, zero padding included, and gathered from there
 // D (kTapsRing only): steps of 32 input channels whose activation loads are in flight at any time.
 template <int KIND, uint32_t MR, bool P16, uint32_t D>
@@ -528,7 +529,7 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
     }
 
     if constexpr (KIND == kGenericPatch) {
-        // ---- phase 2 for any number of input channels (NHWC) when an image row is a multiple of 16 bytes: the
+        // ---- phase 2 for any number of input channels (NHWC) when an image row is a number of words: the
         // workgroup's column tiles are taken in rounds of up to four per wavefront, dealt out evenly; the image rows under a
         // round's pixels go to LDS as they are, 16 bytes at a time, each behind 32 bytes whose upper part is the
         // left zero padding, followed by the right one; rows above and below an image are zeros.  A lane then
@@ -540,8 +541,9 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
         const float zf = static_cast<float>(lay.zero_point);
         const uint32_t S = p.stride, Hp = p.in_h + 2u * p.pad;
         const uint32_t Kp = (p.K + 31u) & ~31u;
-        const uint32_t row_bytes = p.in_w * p.cin * 2u, pieces_per_row = row_bytes / 16u;
-        const uint32_t edge_pieces = 2u + (p.row_pitch - 32u - row_bytes) / 16u;   // the 16-byte pieces of a row that hold no image
+        // (a row is a whole number of words, its last piece may repeat some of the one before)
+        const uint32_t row_bytes = p.in_w * p.cin * 2u, pieces_per_row = (row_bytes + 15u) / 16u;
+        const uint32_t edge_words = (p.row_pitch - row_bytes) / 4u;        // the words of a row that hold no image: eight in front, the others behind
         uint32_t* k_offset = reinterpret_cast<uint32_t*>(lds);    // [Kp]: bytes from a pixel's first tap, first channel, to k's activation
         uint8_t* rows_at = lds + p.patch_off;
         for (uint32_t k = tid; k < Kp; k += kThreads) {
@@ -582,18 +584,18 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
                     const uint32_t piece = i % pieces_per_row, row = i / pieces_per_row;
                     const uint32_t pra = pr0 + row;
                     const uint32_t b = pra / Hp, h = pra % Hp - p.pad;                      // unsigned: above the image wraps around
-                    dst[u] = row * p.row_pitch + 32u + piece * 16u;
-                    if (h < p.in_h) held_x[u] = reinterpret_cast<const words4*>(p.x + (b * p.in_h + h) * p.in_w * p.cin)[piece];
+                    const uint32_t in_row = min(piece * 16u, row_bytes - 16u);
+                    dst[u] = row * p.row_pitch + 32u + in_row;
+                    if (h < p.in_h) held_x[u] = *reinterpret_cast<const words4_word_aligned*>(p.x + (b * p.in_h + h) * p.in_w * p.cin + in_row / 2u);
                 }
             }
-            for (uint32_t i = tid; i < n_rows * edge_pieces; i += kThreads) {
-                const uint32_t e = i % edge_pieces, row = i / edge_pieces;
-                const uint32_t at = row * p.row_pitch + (e < 2u ? e * 16u : 32u + row_bytes + (e - 2u) * 16u);
-                *reinterpret_cast<words4*>(rows_at + at) = words4{0u, 0u, 0u, 0u};
+            for (uint32_t i = tid; i < n_rows * edge_words; i += kThreads) {
+                const uint32_t e = i % edge_words, row = i / edge_words;
+                *reinterpret_cast<uint32_t*>(rows_at + row * p.row_pitch + e * 4u + (e < 8u ? 0u : row_bytes)) = 0u;
             }
 #pragma unroll
             for (uint32_t u = 0; u < kPieces; ++u)
-                if (dst[u] != 0xFFFFFFFFu) *reinterpret_cast<words4*>(rows_at + dst[u]) = held_x[u];
+                if (dst[u] != 0xFFFFFFFFu) *reinterpret_cast<words4_word_aligned*>(rows_at + dst[u]) = held_x[u];
             __syncthreads();
 
             const uint32_t w_begin = t0 + tn * wave / kWaves, w_end = t0 + tn * (wave + 1u) / kWaves;   // this wavefront's tiles
@@ -1459,12 +1461,15 @@ extern "C" int anszp_conv_fused(const anszp_conv_args_t* a, void* stream) {
     p.panel_off = kStageBytes + table_bytes;
     bool generic_patch = false;
     if (generic) {
-        // image rows that are multiples of 16 bytes (NHWC): the rows under a round of pixels staged in LDS, if the most
+        // image rows that are multiples of 16 bytes, or of whole words where the reduction is more than one step of 32 k (NHWC; with every
+        // activation on its own and from LDS, us: 64 x 3 x 7 x 7 on 60 212 x 212 images 91.5, 47.0, on one of 134 x 134 12.1, 8.1; of 50
+        // calls with 1 to 60 channels and kernels of 1 to 7 the 18 of at most 32 k that could change took 0.1 to 0.6 longer, but for three,
+        // the 20 others went 1.07 to 2.1 times as fast, one 1.00): the rows under a round of pixels staged in LDS, if the most
         // rows a round can need fit below the panel (after the table of k offsets) and in pieces per thread
         const uint32_t Kp = (uint32_t(K) + 31u) & ~31u;
         const uint64_t row_bytes = uint64_t(a->in_w) * a->cin * 2u;
         const uint64_t row_pitch = (32u + row_bytes + uint64_t(a->pad) * a->cin * 2u + 15u) & ~uint64_t(15);
-        if (a->x_layout == ANSZP_ACT_NHWC && row_bytes % 16u == 0 && uint64_t(a->pad) * a->cin * 2u <= 32u && row_pitch < (1u << 20)) {
+        if (a->x_layout == ANSZP_ACT_NHWC && (row_bytes % 16u == 0 || (row_bytes % 4u == 0 && row_bytes >= 16u && K > 32u)) && uint64_t(a->pad) * a->cin * 2u <= 32u && row_pitch < (1u << 20)) {
             const uint32_t S = a->stride, Hp = a->in_h + 2u * a->pad;
             const int64_t gap = int64_t(Hp) - int64_t(out_h) * S;
             const uint64_t tiles = (p.pixels_per_split + 15u) / 16u;
@@ -1475,7 +1480,7 @@ extern "C" int anszp_conv_fused(const anszp_conv_args_t* a, void* stream) {
             const uint64_t rows = (rows_out - 1u) * S + a->kh + crossings * uint64_t(gap > 0 ? gap : 0);
             const uint64_t k_table_bytes = (uint64_t(Kp) * 4u + 63u) & ~uint64_t(63);
             const uint64_t below = std::max<uint64_t>(p.panel_off, k_table_bytes + rows * row_pitch);
-            if (rows * (row_bytes / 16u) <= kPatchPieces * kThreads && below + panel_bytes + 64u <= kLdsLimit) {
+            if (rows * ((row_bytes + 15u) / 16u) <= kPatchPieces * kThreads && below + panel_bytes + 64u <= kLdsLimit) {
                 generic_patch = true;
                 p.row_pitch = uint32_t(row_pitch);
                 p.patch_off = uint32_t(k_table_bytes);

@@ -520,3 +520,23 @@ def test_panels_of_half_a_row_tile(orc, shape, B_, H, Wd, stride, pad, layout):
     one and must reach no output: neighbouring panels write the channels beside theirs."""
     _check(*_case(orc, shape, B_, H, Wd, stride, pad, bitwidth=5, p0=0.6, seed=shape[1] + H, x_layout=layout, y_layout=layout))
     _check(*_case(orc, shape, B_, H, Wd, stride, pad, seed=shape[1], per_channel=True, x_layout=layout, y_layout=layout))
+
+
+@pytest.mark.parametrize("shape,B_,H,Wd,stride,pad", [
+    ((64, 3, 7, 7), 2, 18, 18, 2, 3),             # rows of 108 bytes: seven pieces, the last one four bytes behind the sixth's start
+    ((64, 3, 7, 7), 9, 62, 62, 2, 3),             # 372 bytes, rounds that span images
+    ((16, 4, 3, 3), 1, 5, 2, 1, 1),               # 16 bytes: one piece
+    ((16, 10, 3, 3), 3, 4, 1, 1, 1),              # 20 bytes, images of one column
+    ((32, 3, 5, 5), 2, 9, 6, 1, 4),               # 36 bytes, padding of 24
+    ((32, 5, 3, 3), 2, 11, 22, 1, 3),             # 220 bytes, padding of 30
+    ((48, 36, 1, 1), 5, 7, 7, 1, 0),              # 504 bytes, without padding
+    ((16, 6, 3, 2), 4, 10, 9, 3, 0),              # 108 bytes, stride 3, no column of zeros
+    ((16, 3, 3, 3), 2, 7, 9, 1, 1),               # 54 bytes: no whole words, every activation on its own
+    ((16, 6, 3, 3), 2, 7, 1, 1, 1),               # 12 bytes: shorter than a piece, likewise
+    ((16, 2, 4, 4), 2, 9, 6, 1, 1),               # 24 bytes, a reduction of one step, likewise
+    ((16, 11, 3, 1), 2, 9, 6, 1, 0),              # 132 bytes, one k more
+])
+def test_image_rows_of_whole_words(orc, shape, B_, H, Wd, stride, pad):
+    """Channels that are no multiple of 8, rows that end inside a 16-byte piece: nothing of the next row is taken for padding."""
+    _check(*_case(orc, shape, B_, H, Wd, stride, pad, seed=shape[1] + Wd))
+    _check(*_case(orc, shape, B_, H, Wd, stride, pad, bitwidth=6, seed=Wd, per_channel=True))
