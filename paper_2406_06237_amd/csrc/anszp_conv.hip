@@ -48,6 +48,14 @@ typedef __attribute__((ext_vector_type(4))) uint32_t words4;
 typedef __attribute__((ext_vector_type(2))) uint32_t words2;
 typedef words4 __attribute__((aligned(4))) words4_word_aligned;
 
+// n / d for n < 2^31: no division in the kernels, whose code mostly runs once (a division is some 150 bytes of it, and code that runs
+// for the first time costs about 85 ns per 64 bytes; some twenty of them a call of conv_fused_kernel: first layers 0.4 to 1.5 us a
+// call, 64 x 3 x 7 x 7 on 16 224 x 224 images 20.7 -> 19.7, two of 104 x 104 8.6 -> 8.1; other channel counts 0.2 to 0.9 us).
+struct Reciprocal {
+    uint32_t magic, shift;
+    __device__ __forceinline__ uint32_t operator()(uint32_t n) const { return __umulhi(2u * n, magic) >> shift; }
+};
+
 struct ConvParams {
     const uint32_t* tables;
     const anszp_chunk_t* chunks;        // the layer's first chunk
@@ -82,6 +90,9 @@ struct ConvParams {
     // n / d = mulhi(2 n, magic) >> shift for n < 2^31 (d: columns, output rows, panels, blocks of 32 input channels)
     uint32_t columns_magic, columns_shift, out_h_magic, out_h_shift, n_mtiles_magic, n_mtiles_shift, blocks_magic, blocks_shift;
     __device__ __forceinline__ uint32_t n_mtiles_by(uint32_t n) const { return __umulhi(2u * n, n_mtiles_magic) >> n_mtiles_shift; }
+    // conv_fused_kernel's: by output columns and rows; by channels and kernel columns (a k's tap and row), kGenericPatch: by pieces of
+    // an image row, words of its edges, padded rows of an image
+    Reciprocal by_out_w, by_out_h, by_cin, by_kw, by_pieces, by_edges, by_padded_h;
     uint32_t pixels_per_split, block_pixels;              // multiples of 16: the pixels of a workgroup; of one block (<= 64)
 };
 
@@ -511,7 +522,7 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
     constexpr uint32_t kElem = P16 ? 2u : 1u;                     // bytes per panel element
     const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t unit = unit_of_workgroup(), mtile = unit % p.n_mtiles, split = unit / p.n_mtiles;
+    const uint32_t unit = unit_of_workgroup(), split = p.n_mtiles_by(unit), mtile = unit - split * p.n_mtiles;
     const anszp_layer_t lay = decode_panel<kRows * MR, P16>(p, lds, mtile, [] {});
     __syncthreads();
     // kGeneric: what every k of the reduction means, worked out once (the table and the staging room are free now):
@@ -520,8 +531,8 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
     [[maybe_unused]] uint32_t* k_table = reinterpret_cast<uint32_t*>(lds);
     if constexpr (KIND == kGeneric) {
         for (uint32_t k = tid; k < ((p.K + 31u) & ~31u); k += kThreads) {
-            const uint32_t tap = k / p.cin, c = k % p.cin;
-            const uint32_t r = tap / p.kw, sx = tap % p.kw;
+            const uint32_t tap = p.by_cin(k), c = k - tap * p.cin;
+            const uint32_t r = p.by_kw(tap), sx = tap - r * p.kw;
             k_table[2u * k] = (r * p.in_w + sx) * p.cin + c;
             k_table[2u * k + 1u] = k < p.K ? (r | sx << 8) : 0xFFFFFF00u;
         }
@@ -547,8 +558,8 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
         uint32_t* k_offset = reinterpret_cast<uint32_t*>(lds);    // [Kp]: bytes from a pixel's first tap, first channel, to k's activation
         uint8_t* rows_at = lds + p.patch_off;
         for (uint32_t k = tid; k < Kp; k += kThreads) {
-            const uint32_t tap = k / p.cin, c = k % p.cin;
-            const uint32_t r = tap / p.kw, sx = tap % p.kw;
+            const uint32_t tap = p.by_cin(k), c = k - tap * p.cin;
+            const uint32_t r = p.by_kw(tap), sx = tap - r * p.kw;
             k_offset[k] = k < p.K ? r * p.row_pitch + (sx * p.cin + c) * 2u : 0u;
         }
         const uint32_t split_begin = split * p.pixels_per_split;
@@ -563,9 +574,11 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
             const uint32_t tn = min(round_tiles, tiles - t0);
             const uint32_t round0 = split_begin + 16u * t0, round_end = min(round0 + 16u * tn, split_end);
             // the staged rows: flat index b * Hp + padded row, from the first pixel's first tap to the last pixel's last
-            const uint32_t first_row = round0 / p.out_w, last_row = (round_end - 1u) / p.out_w;   // flat output rows b * out_h + ho
-            const uint32_t pr0 = (first_row / p.out_h) * Hp + (first_row % p.out_h) * S;
-            const uint32_t pr_last = (last_row / p.out_h) * Hp + (last_row % p.out_h) * S + p.kh - 1u;
+            auto row_under = [&](uint32_t pix) {                  // (flat output row b * out_h + ho)
+                const uint32_t row = p.by_out_w(pix), b = p.by_out_h(row);
+                return b * Hp + (row - b * p.out_h) * S;
+            };
+            const uint32_t pr0 = row_under(round0), pr_last = row_under(round_end - 1u) + p.kh - 1u;
             const uint32_t n_rows = pr_last - pr0 + 1u;
             const uint32_t n_pieces = n_rows * pieces_per_row;
             if (n_pieces > kPieces * kThreads) {                  // the host sized the rounds so that this cannot happen
@@ -581,16 +594,16 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
                 held_x[u] = words4{0u, 0u, 0u, 0u};
                 dst[u] = 0xFFFFFFFFu;
                 if (i < n_pieces) {
-                    const uint32_t piece = i % pieces_per_row, row = i / pieces_per_row;
+                    const uint32_t row = p.by_pieces(i), piece = i - row * pieces_per_row;
                     const uint32_t pra = pr0 + row;
-                    const uint32_t b = pra / Hp, h = pra % Hp - p.pad;                      // unsigned: above the image wraps around
+                    const uint32_t b = p.by_padded_h(pra), h = pra - b * Hp - p.pad;         // unsigned: above the image wraps around
                     const uint32_t in_row = min(piece * 16u, row_bytes - 16u);
                     dst[u] = row * p.row_pitch + 32u + in_row;
                     if (h < p.in_h) held_x[u] = *reinterpret_cast<const words4_word_aligned*>(p.x + (b * p.in_h + h) * p.in_w * p.cin + in_row / 2u);
                 }
             }
             for (uint32_t i = tid; i < n_rows * edge_words; i += kThreads) {
-                const uint32_t e = i % edge_words, row = i / edge_words;
+                const uint32_t row = p.by_edges(i), e = i - row * edge_words;
                 *reinterpret_cast<uint32_t*>(rows_at + row * p.row_pitch + e * 4u + (e < 8u ? 0u : row_bytes)) = 0u;
             }
 #pragma unroll
@@ -610,8 +623,8 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
                     const uint32_t pix = pix0 + q * 16u + col;
                     valid[q] = pix < block_end;
                     const uint32_t n = valid[q] ? pix : pix0;     // a column beyond the block stands on its first pixel
-                    const uint32_t wo = n % p.out_w, t = n / p.out_w;
-                    const uint32_t ho = t % p.out_h, b = t / p.out_h;
+                    const uint32_t t = p.by_out_w(n), wo = n - t * p.out_w;
+                    const uint32_t b = p.by_out_h(t), ho = t - b * p.out_h;
                     at_rows[q] = (b * Hp + ho * S - pr0) * p.row_pitch + 32u + (wo * S * p.cin) * 2u - p.pad * p.cin * 2u;
                     out_at[q] = b * p.out_h * p.out_w * p.cout + (ho * p.out_w + wo) * p.y_pixel;
                 }
@@ -687,8 +700,8 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
                 const uint32_t pix = pix0 + q * 16u + col;
                 valid[q] = pix < block_end;
                 const uint32_t n = valid[q] ? pix : pix0;         // a column beyond the block stands on its first pixel
-                const uint32_t wo = n % p.out_w, t = n / p.out_w;
-                const uint32_t ho = t % p.out_h, b = t / p.out_h;
+                const uint32_t t = p.by_out_w(n), wo = n - t * p.out_w;
+                const uint32_t b = p.by_out_h(t), ho = t - b * p.out_h;
                 h0[q] = int32_t(ho * p.stride) - int32_t(p.pad);
                 w0[q] = int32_t(wo * p.stride) - int32_t(p.pad);
                 img[q] = b * p.in_h * p.in_w * p.cin;
@@ -704,7 +717,7 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
             const uint16_t* tap_ptr[QT];
             uint32_t tap_step[QT];
             auto enter_tap = [&](uint32_t tap) {
-                const uint32_t r = tap / p.kw, sx = tap % p.kw;
+                const uint32_t r = p.by_kw(tap), sx = tap - r * p.kw;
 #pragma unroll
                 for (uint32_t q = 0; q < QT; ++q) {
                     const int32_t h = h0[q] + int32_t(r), w = w0[q] + int32_t(sx);
@@ -814,8 +827,8 @@ __global__ __launch_bounds__(kThreads) void conv_fused_kernel(ConvParams p) {
             pix[q] = pix0 + q * 16u + col;
             valid[q] = pix[q] < block_end;
             const uint32_t n = valid[q] ? pix[q] : 0u;
-            const uint32_t wo = n % p.out_w, t = n / p.out_w;
-            const uint32_t ho = t % p.out_h, b = t / p.out_h;
+            const uint32_t t = p.by_out_w(n), wo = n - t * p.out_w;
+            const uint32_t b = p.by_out_h(t), ho = t - b * p.out_h;
             h0[q] = int32_t(ho * p.stride) - int32_t(p.pad);
             w0[q] = int32_t(wo * p.stride) - int32_t(p.pad);
             img[q] = b * p.in_h * p.in_w * p.cin;
@@ -1318,6 +1331,11 @@ int launch_sliced(const ConvParams& p, uint32_t rows, bool p16, uint32_t mode, u
     return hipGetLastError() == hipSuccess ? ANSZP_OK : ANSZP_E_HIP;
 }
 
+Reciprocal reciprocal(uint32_t d) {
+    const uint32_t shift = d > 1u ? 32u - uint32_t(__builtin_clz(d - 1u)) : 0u;
+    return {uint32_t((1ull << (31 + shift)) / d + 1u), shift};
+}
+
 // The whole call in launches of at most `images` images.
 int conv_sliced(ConvParams p, const anszp_conv_args_t& a, uint32_t images, uint32_t cus, int device, hipStream_t s) {
     const uint32_t widest = a.kw != 3 ? kPoint : a.stride == 1 ? kShift : kRow;
@@ -1325,8 +1343,9 @@ int conv_sliced(ConvParams p, const anszp_conv_args_t& a, uint32_t images, uint3
     p.y_image = p.out_h * p.out_w * a.cout;
     p.panel_off = kStageBytes + (16u << a.table_log);
     auto magic = [](uint32_t d, uint32_t& m, uint32_t& shift) {
-        shift = d > 1u ? 32u - uint32_t(__builtin_clz(d - 1u)) : 0u;
-        m = uint32_t((1ull << (31 + shift)) / d + 1u);
+        const Reciprocal r = reciprocal(d);
+        m = r.magic;
+        shift = r.shift;
     };
     magic(p.out_h, p.out_h_magic, p.out_h_shift);
     magic((a.cin + 31u) / 32u, p.blocks_magic, p.blocks_shift);
@@ -1440,6 +1459,13 @@ extern "C" int anszp_conv_fused(const anszp_conv_args_t* a, void* stream) {
     const uint32_t n_mtiles = a->cout / (kRows * mr);
     p.chunks_per_panel = kRows * mr / R;
     p.n_mtiles = n_mtiles;
+    const Reciprocal by_panels = reciprocal(n_mtiles);
+    p.n_mtiles_magic = by_panels.magic;
+    p.n_mtiles_shift = by_panels.shift;
+    p.by_out_w = reciprocal(out_w);
+    p.by_out_h = reciprocal(out_h);
+    p.by_cin = reciprocal(a->cin);
+    p.by_kw = reciprocal(a->kw);
     // Every workgroup decodes its panel once, so few, long-lived workgroups: as many as are resident at once,
     // which is one per CU (twelve wavefronts of more than 128 VGPRs fill a CU's four SIMDs whatever the LDS
     // would allow).  A panel's pixels are dealt out in column tiles of 16, evenly over the workgroups that
@@ -1462,14 +1488,14 @@ extern "C" int anszp_conv_fused(const anszp_conv_args_t* a, void* stream) {
     bool generic_patch = false;
     if (generic) {
         // image rows that are multiples of 16 bytes, or of whole words where the reduction is more than one step of 32 k (NHWC; with every
-        // activation on its own and from LDS, us: 64 x 3 x 7 x 7 on 60 212 x 212 images 91.5, 47.0, on one of 134 x 134 12.1, 8.1; of 50
+        // activation on its own and from LDS, us, both with the divisions that are reciprocals now: 64 x 3 x 7 x 7 on 60 212 x 212 images 91.5, 47.0, on one of 134 x 134 12.1, 8.1; of 50
         // calls with 1 to 60 channels and kernels of 1 to 7 the 18 of at most 32 k that could change took 0.1 to 0.6 longer, but for three,
         // the 20 others went 1.07 to 2.1 times as fast, one 1.00): the rows under a round of pixels staged in LDS, if the most
         // rows a round can need fit below the panel (after the table of k offsets) and in pieces per thread
         const uint32_t Kp = (uint32_t(K) + 31u) & ~31u;
         const uint64_t row_bytes = uint64_t(a->in_w) * a->cin * 2u;
         const uint64_t row_pitch = (32u + row_bytes + uint64_t(a->pad) * a->cin * 2u + 15u) & ~uint64_t(15);
-        if (a->x_layout == ANSZP_ACT_NHWC && (row_bytes % 16u == 0 || (row_bytes % 4u == 0 && row_bytes >= 16u && K > 32u)) && uint64_t(a->pad) * a->cin * 2u <= 32u && row_pitch < (1u << 20)) {
+        if (a->x_layout == ANSZP_ACT_NHWC && (row_bytes % 16u == 0 || (row_bytes % 4u == 0 && row_bytes >= 16u && K > 32u)) && uint64_t(a->pad) * a->cin * 2u <= 32u && row_pitch < (1u << 20) && uint64_t(a->batch) * (a->in_h + 2u * a->pad) < (1ull << 31)) {
             const uint32_t S = a->stride, Hp = a->in_h + 2u * a->pad;
             const int64_t gap = int64_t(Hp) - int64_t(out_h) * S;
             const uint64_t tiles = (p.pixels_per_split + 15u) / 16u;
@@ -1483,6 +1509,9 @@ extern "C" int anszp_conv_fused(const anszp_conv_args_t* a, void* stream) {
             if (rows * ((row_bytes + 15u) / 16u) <= kPatchPieces * kThreads && below + panel_bytes + 64u <= kLdsLimit) {
                 generic_patch = true;
                 p.row_pitch = uint32_t(row_pitch);
+                p.by_pieces = reciprocal(uint32_t((row_bytes + 15u) / 16u));
+                p.by_edges = reciprocal(uint32_t((row_pitch - row_bytes) / 4u));
+                p.by_padded_h = reciprocal(Hp);
                 p.patch_off = uint32_t(k_table_bytes);
                 p.panel_off = uint32_t((below + 15u) & ~uint64_t(15));
                 lds_total = p.panel_off + panel_bytes + 64u;
