@@ -31,6 +31,7 @@
 // The look-ahead path needs the chunk's words to fit its LDS window; other chunks take the step-wise path
 // inside the same launch.
 #include "anszp.h"
+#include "anszp_choose.h"
 #include "anszp_cus.h"
 #include "anszp_layout.h"
 #include "anszp_spread.h"
@@ -47,22 +48,9 @@ namespace {
 constexpr int kWave = 64;
 constexpr int kBlock = 768;                    // twelve wavefronts stage; up to seven per chunk stay for the decode
 constexpr uint32_t kSlab = 1024u;              // elements that leave the ring together (two runs of 8 per lane)
-constexpr uint32_t kBlockLookups = 8u;         // look-ups a lane makes per block of the look-ahead kernel
 constexpr uint32_t kLogSlotBytes = (kBlockLookups + 1u) * kWave * 2u + 2u * kWave * 4u;   // nine rows of 16 bits per lane, two of 32
 constexpr uint32_t kExpanders = 2u;            // expanding wavefronts per chunk: they take the logged blocks in turn
 constexpr uint32_t kSpinLimit = 1u << 22;       // polls before a hand-over between wavefronts is declared stuck
-
-// LDS geometry of the look-ahead kernel.  The large one takes tables of up to 2^12 states (64 KiB of
-// look-ahead entries) and two chunks of a layer per workgroup, one workgroup per CU; the small one (tables
-// of up to 2^11 states, shorter windows) leaves room for two workgroups per CU.
-struct LargeLds {
-    static constexpr uint32_t kTableLog = ANSZP_MAX_TABLE_LOG, kPayloadWords = 4096u, kRingElems = 16u * 1024u;
-    static constexpr uint32_t kLogSlots = 8u, kWorkgroupsPerCu = 1u, kTag = 1u;
-};
-struct SmallLds {
-    static constexpr uint32_t kTableLog = 11u, kPayloadWords = 2048u, kRingElems = 8u * 1024u;
-    static constexpr uint32_t kLogSlots = 4u, kWorkgroupsPerCu = 2u, kTag = 2u;
-};
 
 struct DecodeParams {
     const uint32_t* tables;
@@ -1404,7 +1392,7 @@ __device__ __forceinline__ void decode_lookahead(const DecodeParams& p) {
     static_assert(kExpanders == 2u, "hand-over words 1 and 2");
     constexpr uint32_t kTableLoads = ((2u << G::kTableLog) / 2u + kBlock - 1u) / kBlock;          // 16-byte loads per thread
     constexpr uint32_t kWordLoads = (kPayloadWords / 4u + kBlock - 1u) / kBlock;                  // per chunk
-    static_assert(kSoloWords <= 2u * kWordLoads * 4u * kBlock, "a single chunk's words are loaded by both chunks' loads");
+    static_assert(kSoloWords == G::kSoloWords && kSoloWords <= 2u * kWordLoads * 4u * kBlock, "a single chunk's words are loaded by both chunks' loads");
 
     const uint32_t tid = threadIdx.x;
     const uint32_t lane = tid & (kWave - 1);
@@ -2230,7 +2218,6 @@ __global__ __launch_bounds__(256) void dequant_runs_kernel(const uint8_t* sym, u
 }
 
 // What a launch would be: checks of the arguments, the kernel's parameters, which kernel.
-struct LaunchChoice { bool stepwise, byte_table, shared, streaming, small, per_channel, split; uint32_t few; WavesShape waves; };
 
 template <int OUT>
 void launch_decode(const DecodeParams& p, const LaunchChoice& k, hipStream_t s) {
@@ -2327,66 +2314,7 @@ int choose_launch(const anszp_decode_args_t* a, int mode, bool planned, DecodePa
     p.plan = nullptr;
     const uint32_t polls = spin_limit_for_tests().load(std::memory_order_relaxed);
     p.spin_limit = polls ? polls - 1u : kSpinLimit;
-    // chunks whose compressed words cannot fit the look-ahead kernel's LDS window would all take its
-    // fallback: they go to the streaming kernel, whatever their number (measured on 772 to 24,704
-    // chunks of 82 KB of words: 5 to 7 times faster than one step-wise wavefront per chunk)
-    const uint64_t mean_words = a->payload_words / a->n_chunks;
-    k.stepwise = mode == 1 || mode == 3 || mode == 4 || (mode == 0 && mean_words > LargeLds::kPayloadWords);
-    k.byte_table = mode == 5;
-    k.shared = mode == 3;
-    k.streaming = mode == 4 || (mode == 0 && k.stepwise);
-    // small tables and short chunks: the variant that fits two workgroups on a CU
-    k.small = a->table_log <= SmallLds::kTableLog && 2u * mean_words <= SmallLds::kPayloadWords &&
-              kBlockLookups * kLookaheadMaxSymbols * a->n_streams < SmallLds::kRingElems;     // a block must fit its ring
-    k.per_channel = a->scales != nullptr && a->n_scales != 0;
-    // One stream per chunk: its chain split over a workgroup where the stream is long enough for walks started anywhere
-    // to meet it, i.e. as many bits as the table has states and 3,072, or twice as many and 2,048 (2^11 states: 2,048 bits
-    // 28.6 us as one chain, 32.0 split; 3,072 bits 40.7 and 28.9; 2^10 states: 2,048 bits 28.2 and 18.6), and either the
-    // chunks leave CUs idle otherwise or a chain is so long that four chunks at once on a CU do not make up for it (600
-    // chunks of 11,000 bits 148 us as chains, of 17,000 bits 146 split).  Longer than the kernel can hold: as before (the
-    // mean is exact for one chunk; several may differ, then the bound is the look-ahead kernel's).
-    const uint64_t bits = 32u * mean_words, states = 1ull << a->table_log;
-    k.split = mode == 0 && a->n_streams == 1 && bits >= kSplitMinBits && bits >= states && (bits >= 3072u || bits >= 2u * states) &&
-              mean_words <= (a->n_chunks == 1 ? kSplitWords : LargeLds::kPayloadWords) &&
-              (a->n_chunks <= p.n_cus || bits >= 16384u);
-    if (k.split) k.stepwise = k.streaming = false;
-    // More chunks than the look-ahead kernel decodes at once (two per workgroup): a wavefront per chunk and a table staged
-    // once per workgroup and layer, where the chunks' words fit and there are chunks enough for a workgroup's share to be of
-    // few layers (24 a layer where only eight wavefronts fit a CU: 130 layers of 12 chunks of 1,600 words 70 us, 84 this way).
-    // Up to four chunks per CU only short ones, and with a plan, which spares the look-ahead kernel its search, fewer still.
-    // 16 layers of 544 to 992 chunks, layers in a row and descriptors in any order, times as fast as the look-ahead kernel:
-    //   2^12 states, without a plan                  1.4 to 3.4 (few streams or 65,536 symbols 1.0 to 1.6)     1.3 to 2.4 (1.0)
-    //   2^12 states, with one, up to 480 bits a stream    1.1 to 1.8 (once 0.91)      1.04 to 1.9
-    //     more bits or more than 8,192 symbols       0.72 to 1.4                      0.72 to 2
-    //   small geometry, without, up to 512 bits and symbols a stream     1.2 to 2.4   1.04 to 1.6
-    //     longer streams                             0.72 to 1.3                      0.9 to 1.5
-    //   small geometry, with one, more than three chunks per CU of up to 240 bits and 256 symbols a stream     0.98 to 1.3   0.86 to 1
-    //     others                                     0.68 to 1.25                     0.67 to 1.2
-    // 1,120 chunks: 0.96 to 2 but for 1,870 bits a stream with a plan in the small geometry, 0.77.
-    k.waves = WavesShape{};
-    const uint64_t per_layer = a->n_chunks / a->n_tables, cus = p.n_cus, N = a->n_streams, symbols = a->out_elems / a->n_chunks;
-    const bool short_enough = a->n_chunks > 4u * cus ? !(planned && k.small && a->n_chunks <= 6u * cus && bits > 1024u * N)
-                              : k.small              ? mean_words <= 256u && (planned ? a->n_chunks > 3u * cus && bits <= 240u * N && symbols <= 256u * N
-                                                                                      : bits <= 512u * N && symbols <= 512u * N)
-                                                     : mean_words <= 450u && (!planned || (bits <= 480u * N && symbols <= 8192u));
-    if (mode == 0 && !k.stepwise && !k.split && per_layer >= 8u && a->n_chunks > 2u * cus && short_enough) {
-        k.waves = waves_shape(a->table_log, a->n_streams, mean_words);
-        if (k.waves.waves == 8u && per_layer < 24u) k.waves.waves = 0u;
-    }
-    // Few chunks: a workgroup per chunk that stages, walks and stores one after the other (decode_few), as many on a CU as there are
-    // chunks for it and LDS for. It starts 1.5 to 2 us earlier than the look-ahead kernel and takes 5 ns a look-up and the
-    // stores behind the last one longer, so the line is a stream's length and a chunk's bytes: 64 streams, bf16, look-ahead
-    // kernel with a plan -> here, chunks of 2,048 / 8,192 / 16,384 / 32,768 / 65,536 symbols (2^12 states, 2.2 bits; 24 of them)
-    // 7.3 / 11.1 / 16.4 / 26.5 / 52.2 -> 5.9 / 10.3 / 15.5 / 25.6 / 52.2; (2^12 states, mostly dominant; 249) 7.0 / 8.5 / 10.0 / 12.3 / 17.3
-    // -> 5.6 / 7.7 / 9.5 / 12.4 / 20.5, as fp32 (99) 6.8 / 8.2 / 9.9 / 12.7 / 17.3 -> 5.7 / 7.4 / 9.7 / 13.6 / 20.2; (2^10 states, 1.2 bits;
-    // 499, two on a CU) 8.8 / 11.0 / 12.9 / 16.4 / 24.2 -> 6.2 / 8.7 / 10.9 / 18.6 / 32.9.  Without a plan 0.4 us more are saved.  Three and
-    // four on a CU without a plan only, 1.0 to 2.1 times as fast (with one 0.68 to 1.4).  Twice the mean chunk has to fit LDS whole.
-    k.few = 0u;
-    const uint64_t per_cu = (a->n_chunks + cus - 1u) / cus;
-    if (mode == 0 && !k.stepwise && !k.split && !k.waves.waves && per_cu <= (planned ? 2u : kFewMostPerCu) && symbols <= 512u * N &&
-        symbols <= (a->out_dtype == ANSZP_OUT_F32 ? 12288u : 20480u) &&
-        (16ull << a->table_log) + 8u * mean_words + 2u * symbols + kFewLeastRoom <= few_lds(uint32_t(per_cu)))
-        k.few = uint32_t(per_cu);
+    k = choose_kernel(*a, mode, planned, p.n_cus);
     return ANSZP_OK;
 }
 

@@ -15,10 +15,7 @@
 #include "anszp_walk.h"
 
 constexpr uint32_t kFewThreads = 512u;
-constexpr uint32_t kFewMostPerCu = 4u;
-constexpr uint32_t few_lds(uint32_t per_cu) { return (160u * 1024u / per_cu - 64u) & ~15u; }   // for so many workgroups per CU
 constexpr uint32_t kFewTableLoads = (1u << ANSZP_MAX_TABLE_LOG) / kFewThreads;          // 16-byte loads per thread
-constexpr uint32_t kFewLeastRoom = 2048u;                  // symbols in the buffer
 
 template <int OUT, uint32_t LDS>
 __global__ __launch_bounds__(kFewThreads) void decode_few(DecodeParams p) {

@@ -36,10 +36,8 @@
 constexpr uint32_t kSplitThreads = 1024u;
 constexpr uint32_t kSplitMaxCuts = 64u;
 constexpr uint32_t kSplitParts = 4u;                      // parts of a segment that are written side by side
-constexpr uint32_t kSplitWords = 11096u;                  // longest stream (what the look-ahead kernel can hold)
 constexpr uint32_t kSplitMaxNodes = 1600u;                // no more, and as many as LDS has room for
 constexpr uint32_t kSplitUnknown = 0xFFFFFFFFu, kSplitNone = 0xFFFFFFFEu;
-constexpr uint32_t kSplitMinBits = 2048u;
 constexpr uint32_t kSplitPad = 10u;                       // words beside the stream's: one before it, zeros behind (a walk that must stop
                                                           // at the stream's end may make four look-ups more and read three words there)
 

@@ -30,30 +30,6 @@
 
 #include "anszp_walk.h"
 
-constexpr uint32_t kWavesLds = 160u * 1024u - 64u;
-constexpr uint32_t kWavesCtl = 64u;                        // behind the table: what the wavefronts of a run share
-constexpr uint32_t kWavesPad = 16u;                        // words beside a chunk's: four before, zeros behind (see kSplitPad)
-constexpr uint32_t kWavesBehind = kLookaheadMaxSymbols * ANSZP_MAX_STREAMS + 16u;      // bytes behind the buffer
-constexpr uint32_t kWavesRoom = 2048u, kWavesLeastRoom = 512u;    // symbols in the buffer beside a mean chunk's words; beside any chunk's
-
-// Wavefronts per workgroup and the LDS each has for a chunk's words and the buffer (waves == 0: not a launch for this
-// kernel).  As many wavefronts as leave room for a quarter more words than the mean chunk has beside kWavesRoom
-// symbols; chunks of up to a good deal more still fit, with a shorter buffer.
-// What a chunk costs counts as its words and `fixed` (a chunk without words takes about as long as two words a stream do),
-// in units of which the mean chunk has 32 (unit_scale / 2^16 units a word); staging a layer's table counts as stage_units.
-struct WavesShape { uint32_t waves, own, mean, fixed, unit_scale, stage_units; };
-inline WavesShape waves_shape(uint32_t table_log, uint32_t n_streams, uint64_t mean_words) {
-    for (uint32_t waves : {16u, 12u, 8u}) {
-        if (table_log == ANSZP_MAX_TABLE_LOG && waves == 16u) continue;
-        const uint32_t own = (kWavesLds - (16u << table_log) - kWavesCtl) / waves & ~15u;
-        if (4u * (mean_words * 5u / 4u + 16u + kWavesPad) + kWavesRoom + kWavesBehind > own) continue;
-        const uint32_t mean = static_cast<uint32_t>(mean_words), fixed = 2u * n_streams;
-        // (4 us for a table of 2^12 states; a chunk's words and `fixed` take 0.87 us for each word of a stream, `waves` of them at once)
-        return WavesShape{waves, own, mean, fixed, (32u << 16) / (mean + fixed), (147u * waves * n_streams >> (ANSZP_MAX_TABLE_LOG - table_log)) / (mean + fixed)};
-    }
-    return WavesShape{0u, 0u, 0u, 0u, 0u, 0u};
-}
-
 constexpr uint32_t kWavesLookers = 4u;                     // wavefronts that look at a sample of the descriptors
 constexpr uint32_t kWavesKeys = 1024u;                     // layers are told apart by so many of their number's values while they are sorted
 constexpr uint32_t kWavesList = 1024u;                     // chunks of a share that are listed at once

@@ -68,6 +68,25 @@ def test_a_chunk_whose_words_do_not_fit(orc):
     _check(orc, W.Workload("dense", layers, 12, 64, 150000, "bf16"))
 
 
+# table_log, short chunks, symbols of the long one, and the kernel (the dispatch is looked at in test_decode_choice.py)
+MANY_WORDS = [
+    (12, 300, 40000, "few 1"),                                     # 10,000 words: two workgroups per CU would have room for 3,400
+    (12, 300, 46400, "few 1"), (11, 300, 22200, "few 2"),          # about the longest the look-ahead kernel holds
+    (11, 600, 22200, "few 2"), (10, 600, 22200, "few 3"), (9, 900, 22200, "few 4"),
+]
+
+
+def many_words(table_log, n_short, long):
+    layers = [W.Layer("dense", (1, 1, 1, long), 8, 128, 0.02, np.full(256, 1 / 256), 5)]
+    layers += [W.tiny(seed=s, n=200, bitwidth=3, n_streams=64, chunk_size=200, table_log=table_log, p0=0.8).layers[0] for s in range(n_short)]
+    return W.Workload("dense", layers, table_log, 64, 150000, "bf16")
+
+
+@pytest.mark.parametrize("table_log,n_short,long,kernel", MANY_WORDS)
+def test_a_chunk_of_many_words_among_short_ones(orc, table_log, n_short, long, kernel):
+    _check(orc, many_words(table_log, n_short, long))
+
+
 def test_a_scale_per_channel(orc):
     for clen in (1, 7, 9 * 64, 100000):
         n = 5003
