@@ -54,10 +54,10 @@ constexpr uint32_t kSplitMinBits = 2048u;
 
 constexpr uint32_t kFewMostPerCu = 4u;
 constexpr uint32_t few_lds(uint32_t per_cu) { return (160u * 1024u / per_cu - 64u) & ~15u; }   // for so many workgroups per CU
-constexpr uint32_t kFewLeastRoom = 2048u;                  // symbols in the buffer
-// Words of a chunk that fit beside table and buffer in `lds` bytes (negative: not even those do).
+constexpr uint32_t kFewLeastRoom = 2048u;                  // symbols in each of two buffers
+// Words of a chunk that fit beside table and buffers in `lds` bytes (negative: not even those do).
 constexpr int32_t few_words(uint32_t lds, uint32_t table_log) {
-    return (int32_t(lds) - int32_t(16u << table_log) - int32_t(kFewLeastRoom + kWavesBehind) - 16) / 4 - int32_t(kWavesPad);
+    return (int32_t(lds) - int32_t(16u << table_log) - 2 * int32_t(kFewLeastRoom + kWavesBehind) - 16) / 4 - int32_t(kWavesPad);
 }
 
 // few: workgroups of decode_few on a CU, or 0
@@ -112,18 +112,19 @@ inline LaunchChoice choose_kernel(const anszp_decode_args_t& a, int mode, bool p
         k.waves = waves_shape(a.table_log, a.n_streams, mean_words);
         if (k.waves.waves == 8u && per_layer < 24u) k.waves.waves = 0u;
     }
-    // Few chunks: a workgroup per chunk that stages, walks and stores one after the other (decode_few), as many on a CU as there are
-    // chunks for it and LDS for. It starts 1.5 to 2 us earlier than the look-ahead kernel and takes 5 ns a look-up and the
-    // stores behind the last one longer, so the line is a stream's length and a chunk's bytes: 64 streams, bf16, look-ahead
-    // kernel with a plan -> here, chunks of 2,048 / 8,192 / 16,384 / 32,768 / 65,536 symbols (2^12 states, 2.2 bits; 24 of them)
-    // 7.3 / 11.1 / 16.4 / 26.5 / 52.2 -> 5.9 / 10.3 / 15.5 / 25.6 / 52.2; (2^12 states, mostly dominant; 249) 7.0 / 8.5 / 10.0 / 12.3 / 17.3
-    // -> 5.6 / 7.7 / 9.5 / 12.4 / 20.5, as fp32 (99) 6.8 / 8.2 / 9.9 / 12.7 / 17.3 -> 5.7 / 7.4 / 9.7 / 13.6 / 20.2; (2^10 states, 1.2 bits;
-    // 499, two on a CU) 8.8 / 11.0 / 12.9 / 16.4 / 24.2 -> 6.2 / 8.7 / 10.9 / 18.6 / 32.9.  Without a plan 0.4 us more are saved.  Three and
-    // four on a CU without a plan only, 1.0 to 2.1 times as fast (with one 0.68 to 1.4).  Twice the mean chunk has to fit LDS whole.
+    // Few chunks: a workgroup per chunk that stages and walks, and stores behind the walk or a window later (decode_few), as many on a
+    // CU as there are chunks for it and LDS for.  It starts 1.5 to 2 us earlier than the look-ahead kernel and takes 5 ns a look-up
+    // longer.  64 streams, bf16, look-ahead kernel with a plan -> here, equal chunks of 2,048 / 8,192 / 16,384 / 32,768 / 65,536 symbols:
+    // (2^12 states, 2.2 bits; 24 of them) 7.2 / 10.9 / 16.2 / 26.2 / 89 -> 5.5 / 9.2 / 14.4 / 24.1 / 44; (2^12 states, mostly dominant; 249)
+    // 6.8 / 8.2 / 9.4 / 11.9 / 16.8 -> 5.0 / 6.2 / 7.9 / 10.7 / 16.6, as fp32 (99) 6.8 / 8.0 / 9.4 / 12.0 / 16.8 -> 4.9 / 6.4 / 8.3 / 11.3 /
+    // 17.0; (2^10 states, 1.2 bits; 499, two on a CU) 8.5 / 10.4 / 12.3 / 27 / 42 -> 5.3 / 7.2 / 9.7 / 14.8 / 24.8.  Without a plan 0.4 us
+    // more are saved.  Three and four on a CU without a plan only: 700 and 1,000 of 2,048 to 16,384 1.5 to 2.7 times as fast.  The
+    // line lies where a kernel that stored nothing before a chunk was walked to its end became the slower one; longer chunks
+    // are for the look-ahead kernel, up to twice the mean chunk has to fit LDS whole.  Chunks much longer than their set's mean: see anszp_few.h.
     // The host knows the mean chunk only: a workgroup gets LDS for the longest the look-ahead kernel would decode, and where that
     // leaves fewer of them on a CU than there are chunks, some wait for a CU.  (440 chunks of 2,000 symbols and 20 of 65,536, 1.8 bits,
     // 2^12 states: the look-ahead kernel 41 us, with a plan 30; here 262 where two workgroups were to share a CU and the long chunks'
-    // words, which did not fit, were walked in memory, 34 with one.  500 of 3,000: 19 and 14, here 7 with two, 10 with one.)
+    // words, which did not fit, were walked in memory, 33 with one.  500 of 3,000: 19 and 14, here 7 with two, 10 with one.)
     k.few = 0u;
     const uint64_t per_cu = (a.n_chunks + cus - 1u) / cus;
     if (mode == 0 && !k.stepwise && !k.split && !k.waves.waves && per_cu <= (planned ? 2u : kFewMostPerCu) && symbols <= 512u * N &&
