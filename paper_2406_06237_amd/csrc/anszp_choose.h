@@ -53,7 +53,11 @@ constexpr uint32_t kSplitWords = 11096u;                  // longest stream deco
 constexpr uint32_t kSplitMinBits = 2048u;
 
 constexpr uint32_t kFewMostPerCu = 4u;
-constexpr uint32_t few_lds(uint32_t per_cu) { return (160u * 1024u / per_cu - 64u) & ~15u; }   // for so many workgroups per CU
+// LDS of a workgroup of which so many are to fit a CU, which gives it out in pieces of 1,280 bytes (a third of it all, 54,613 bytes, would be
+// given 55,040, and two workgroups fit: 700 chunks of 8,192 symbols, 2^10 states, 11.3 us, 8.1 with three)
+constexpr uint32_t kLdsPiece = 1280u;
+constexpr uint32_t few_lds(uint32_t per_cu) { return 160u * 1024u / per_cu / kLdsPiece * kLdsPiece - 64u; }
+static_assert(few_lds(3u) % 16u == 0u && 3u * ((few_lds(3u) + kLdsPiece - 1u) / kLdsPiece * kLdsPiece) <= 160u * 1024u, "three fit");
 constexpr uint32_t kFewLeastRoom = 2048u;                  // symbols in each of two buffers
 // Words of a chunk that fit beside table and buffers in `lds` bytes (negative: not even those do).
 constexpr int32_t few_words(uint32_t lds, uint32_t table_log) {
@@ -118,7 +122,7 @@ inline LaunchChoice choose_kernel(const anszp_decode_args_t& a, int mode, bool p
     // (2^12 states, 2.2 bits; 24 of them) 7.2 / 10.9 / 16.2 / 26.2 / 89 -> 5.5 / 9.2 / 14.4 / 24.1 / 44; (2^12 states, mostly dominant; 249)
     // 6.8 / 8.2 / 9.4 / 11.9 / 16.8 -> 5.0 / 6.2 / 7.9 / 10.7 / 16.6, as fp32 (99) 6.8 / 8.0 / 9.4 / 12.0 / 16.8 -> 4.9 / 6.4 / 8.3 / 11.3 /
     // 17.0; (2^10 states, 1.2 bits; 499, two on a CU) 8.5 / 10.4 / 12.3 / 27 / 42 -> 5.3 / 7.2 / 9.7 / 14.8 / 24.8.  Without a plan 0.4 us
-    // more are saved.  Three and four on a CU without a plan only: 700 and 1,000 of 2,048 to 16,384 1.5 to 2.7 times as fast.  The
+    // more are saved.  Three and four on a CU without a plan only: 700 and 1,000 of 2,048 to 16,384 1.8 to 2.7 times as fast.  The
     // line lies where a kernel that stored nothing before a chunk was walked to its end became the slower one; longer chunks
     // are for the look-ahead kernel, up to twice the mean chunk has to fit LDS whole.  Chunks much longer than their set's mean: see anszp_few.h.
     // The host knows the mean chunk only: a workgroup gets LDS for the longest the look-ahead kernel would decode, and where that

@@ -34,6 +34,8 @@ int main() {
         if (!k.few || k.waves.waves) continue;
         ++taken[k.few <= 4u ? k.few : 0u];
         REQUIRE(!k.split && !k.stepwise && k.few <= kFewMostPerCu && k.few <= (a.n_chunks + cus - 1u) / cus);
+        // so many workgroups are resident on a CU: LDS is given out in pieces of 1,280 bytes
+        REQUIRE(k.few * ((few_lds(k.few) + 1279u) / 1280u * 1280u) <= 160u * 1024u && few_lds(k.few) % 16u == 0u);
         // the mean is all the rule sees of the chunks: any that the look-ahead kernel would hold has to fit
         REQUIRE(few_words(few_lds(k.few), a.table_log) >= int32_t(k.small ? SmallLds::kSoloWords : LargeLds::kSoloWords));
     }
