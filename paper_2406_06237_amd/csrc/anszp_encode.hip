@@ -483,7 +483,8 @@ __global__ __launch_bounds__(kThreads) void encode_begin(EncParams p) {
 // The others clear what the packer's callers find cleared (a fill per buffer took a launch each) and mark all chunks as
 // unpublished; they are at work beside the former.  4.0 us for one table of 2^11 states and 3 MB of results, 8 for 53 of 2^12
 // and 35 MB; packing a set with build_tables_device before it, results allocated by the caller of the binding: 369 chunks of
-// 65,536 symbols 98 -> 79 us, 144 of 16,384 43 -> 35, two layers of 11,792 symbols 64 -> 31.
+// 65,536 symbols 98 -> 79 us, 144 of 16,384 43 -> 35, two layers of 11,792 symbols 64 -> 31; 300 layers of 300 symbols, 2^12 states, 256
+// symbols in each 123 -> 80 (215 with all of the workgroups that sort on one die), 16 symbols 124 -> 37.
 constexpr uint32_t kDirectSymbols = 128u;
 constexpr uint32_t kClearUnits = 8u * kThreads;             // of 16 bytes, per workgroup
 constexpr uint32_t kJobsPerLaunch = 64u;
@@ -549,7 +550,8 @@ __global__ __launch_bounds__(kThreads, 4) void encode_prepare(EncParams p, Prepa
         return;
     }
     static_assert(sizeof(anszp_chunk_t) == 32 && offsetof(anszp_chunk_t, payload_words) == 24, "two units a descriptor");
-    const uint32_t layer = blockIdx.x / q.shares, share = blockIdx.x % q.shares;
+    // (share by share: a layer's first share may be the one that sorts, and consecutive workgroups go to the eight dies in turn)
+    const uint32_t share = blockIdx.x / p.n_layers, layer = blockIdx.x - share * p.n_layers;
     const uint32_t* const freqs = p.freqs + size_t(layer) * ANSZP_ALPHABET;
     uint32_t* const record = q.records + size_t(layer) * record_words(p.table_log);
     uint16_t* const next = reinterpret_cast<uint16_t*>(record + kRecordNext);
