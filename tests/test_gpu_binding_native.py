@@ -79,3 +79,28 @@ def test_tables_and_their_status(without):
         call = lambda: B.build_tables_device(freqs, 10, st)
         _same((call(),), (without(call),))
         assert st is None or st.tolist() == [B.ST_BAD_FREQ, 2]
+
+
+def test_threads_with_streams_of_their_own():
+    import threading
+    sizes = [[4000, 300], [70001], [512] * 20, [9, 5000, 31]]
+    inputs = [_inputs(s, seed) for seed, s in enumerate(sizes)]
+    pack = lambda k: B.pack_layers_device(inputs[k][0], sizes[k], inputs[k][1], 10, 32, 1000)
+    expect = [(pack(k), B.dequant_zp(inputs[k][0], 2, 0.5)) for k in range(4)]
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(k):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            got = [(pack(k), B.dequant_zp(inputs[k][0], 2, 0.5)) for _ in range(25)]
+            torch.cuda.current_stream().synchronize()
+        for packed, weights in got:
+            if not (all(torch.equal(a, b) for a, b in zip(packed, expect[k][0])) and torch.equal(weights, expect[k][1])):
+                wrong.append(k)
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
