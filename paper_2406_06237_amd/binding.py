@@ -320,17 +320,26 @@ _host = None
 
 
 def _host_calls():
-    """The native calls (csrc/anszp_torch.cpp)."""
+    """The native calls (csrc/anszp_torch.cpp), or False where they are not built or are for another torch: the binding's own
+    path then does the same with the same library, a little slower."""
     global _host
     if _host is None:
         lib()
-        from paper_2406_06237_amd import _anszp_torch
-        _host = _anszp_torch
+        try:
+            from paper_2406_06237_amd import _anszp_torch
+            _host = _anszp_torch
+        except ImportError as e:
+            import warnings
+            warnings.warn(f"the binding's native calls cannot be loaded, its Python path is used ({e}); run __graft_entry__.build()")
+            _host = False
     return _host
 
 
-def _call(where: str, function, device, *args):
+def _call(where: str, name: str, device, *args):
     """_enqueue for a native call: its result, or None where the binding's own path has to take over."""
+    function = getattr(_host_calls(), name, None)
+    if function is None:
+        return None
     torch = _torch()
     index = _device_index(torch, device)
     try:
@@ -377,7 +386,7 @@ def build_tables_device(freqs_dev, table_log: int, status=None):
     device = freqs_dev.device
     n_tables = freqs_dev.numel() // ALPHABET
     if device.type == "cuda" and type(table_log) is int and 1 <= table_log <= MAX_TABLE_LOG:
-        tables = _call("anszp_build_tables_device", _host_calls().build_tables_device, device, freqs_dev, n_tables, table_log,
+        tables = _call("anszp_build_tables_device", "build_tables_device", device, freqs_dev, n_tables, table_log,
                        table_words(n_tables, table_log), status)
         if tables is not None:
             return tables
@@ -517,7 +526,7 @@ def dequant_zp(symbols, zero_point: int, scale: float, out_dtype: str = "bf16", 
     if not (0 <= zero_point < 1 << 32 and 0 <= channel_len < 1 << 32):
         raise OverflowError("zero_point and channel_len are unsigned 32-bit numbers")
     if dev.type == "cuda" and type(scale) is float:
-        out = _call("anszp_dequant_zp", _host_calls().dequant_zp, dev, symbols, zero_point, scale, OUT_CODES[out_dtype], channel_len, channel_scales)
+        out = _call("anszp_dequant_zp", "dequant_zp", dev, symbols, zero_point, scale, OUT_CODES[out_dtype], channel_len, channel_scales)
         if out is not None:
             return out
     out = torch.empty(max(n, 8), dtype=getattr(torch, _TORCH_OUT[out_dtype]), device=dev)
@@ -699,7 +708,7 @@ def pack_layer_device(symbols_dev, freqs_dev, table_log: int, n_streams: int, ch
     n = symbols_dev.numel()
     _check_pack_ranges(n, table_log, n_streams, chunk_size)
     if payload_cap_words is None:
-        packed = _call("anszp_pack_set_device", _host_calls().pack_set, dev, symbols_dev, freqs_dev, (n,), chunk_size, table_log, n_streams, -1,
+        packed = _call("anszp_pack_set_device", "pack_set", dev, symbols_dev, freqs_dev, (n,), chunk_size, table_log, n_streams, -1,
                        1, layer_id, out_offset, payload_word_offset, stream_offset, False)
         if packed is not None:
             return packed
@@ -751,7 +760,7 @@ def pack_layers_device(symbols_dev, layer_sizes: Sequence[int], freqs_dev, table
         raise RuntimeError("pack_layers_device cannot be captured")
     if out is None and payload_cap_words is None and type(table_log) is int and 1 <= table_log <= MAX_TABLE_LOG and type(n_streams) is int and \
             1 <= n_streams <= MAX_STREAMS:
-        packed = _call("anszp_pack_set_device", _host_calls().pack_set, dev, symbols_dev, freqs_dev, layer_sizes, chunk_size, table_log, n_streams, -1,
+        packed = _call("anszp_pack_set_device", "pack_set", dev, symbols_dev, freqs_dev, layer_sizes, chunk_size, table_log, n_streams, -1,
                        0, 0, 0, 0, 0, True)
         if packed is not None:
             return packed

@@ -48,3 +48,15 @@ def test_the_interpreter_lock_is_free_while_the_library_is_called(tmp_path):
     script = CALLS.replace("PACK_ARGS", "-1, 0, 0, 0, 0, 0, False,")
     r = subprocess.run([sys.executable, "-c", script, str(tmp_path)], capture_output=True, text=True, timeout=300, cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
     assert r.returncode == 0, r.stderr[-2000:]
+
+
+def test_without_them_the_binding_takes_its_own_path(monkeypatch):
+    """Not built, or built against another torch: the calls answer None once and for all, with a warning, and raise nothing."""
+    from paper_2406_06237_amd import binding as B
+    monkeypatch.setattr(B, "_host", None)
+    monkeypatch.setitem(sys.modules, "paper_2406_06237_amd._anszp_torch", None)
+    monkeypatch.delattr("paper_2406_06237_amd._anszp_torch", raising=False)
+    with pytest.warns(UserWarning, match="native calls"):
+        assert B._call("anszp_dequant_zp", "dequant_zp", "cuda:0") is None
+    for name in ("build_tables_device", "pack_set"):
+        assert B._call("", name, "cuda:0") is None

@@ -104,3 +104,13 @@ def test_threads_with_streams_of_their_own():
     for t in threads:
         t.join()
     assert not wrong
+
+
+def test_without_the_module(monkeypatch):
+    sym, freqs = _inputs([3000, 700])
+    calls = (lambda: B.pack_layers_device(sym, [3000, 700], freqs, 10, 32, 512), lambda: B.pack_layer_device(sym, freqs[:1], 10, 32, 512),
+             lambda: (B.dequant_zp(sym, 2, 0.5),), lambda: (B.build_tables_device(freqs, 10),))
+    expect = [call() for call in calls]
+    monkeypatch.setattr(B, "_host", False)                # (what a failed import leaves)
+    for call, e in zip(calls, expect):
+        _same(call(), e)
