@@ -488,7 +488,7 @@ __global__ __launch_bounds__(kThreads) void encode_begin(EncParams p) {
 constexpr uint32_t kDirectSymbols = 128u;
 constexpr uint32_t kClearUnits = 8u * kThreads;             // of 16 bytes, per workgroup
 constexpr uint32_t kJobsPerLaunch = 64u;
-constexpr uint32_t kFinishWords = 1u + 64u;                 // EncParams::finish: up to 2,048 chunks are packed at once
+constexpr uint32_t kFinishWords = 1u + kWave;               // EncParams::finish: a bit per chunk (chunks_per_group)
 struct JobsArg { anszp_pack_job_t job[kJobsPerLaunch]; };
 struct PrepareParams {
     anszp_pack_job_t* jobs;                                 // null: one layer, of `n_jobs` 0
@@ -1017,7 +1017,7 @@ __global__ __launch_bounds__(kThreads, 4) void encode_rest(EncParams p) {
 // 100,000 chunks of 2,048 symbols paid for tables of their own: 1,092 us, 438 with this; 20,000 chunks 233, 122;
 // the 369 chunks of a ResNet-50-shaped set as before.)
 uint32_t chunks_per_group(uint64_t n_chunks) {
-    const uint64_t resident = 2u * device_cus();
+    const uint64_t resident = std::min(2u * device_cus(), 32u * (kFinishWords - 1u));
     return uint32_t(std::max<uint64_t>(1u, (n_chunks + resident - 1u) / resident));
 }
 
@@ -1030,7 +1030,7 @@ int launch(EncParams& p, hipStream_t s) {
         const dim3 groups(uint32_t(p.n_chunks)), threads(kThreads);
         // (a symbol has at most table_log bits)
         const uint64_t rows = (uint64_t(p.longest_chunk) + p.n_streams - 1u) / p.n_streams;
-        if (p.prepared && p.n_chunks <= 32u * (kFinishWords - 1u) && rows * p.table_log <= 32u * kBitRows) {
+        if (p.prepared && rows * p.table_log <= 32u * kBitRows) {
             hipLaunchKernelGGL(encode_all, groups, threads, 0, s, p);
             return hipGetLastError() == hipSuccess ? ANSZP_OK : ANSZP_E_HIP;
         }

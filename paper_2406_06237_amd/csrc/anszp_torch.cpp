@@ -92,9 +92,9 @@ bool integers(py::handle from, size_t count, long long least, long long most, st
     return true;
 }
 
-// cap: words of the payload, or -1 for as many as the set can need; record: the inputs' memory is kept for this stream.
+// The payload is as long as the set can need; record: the inputs' memory is kept for this stream.
 py::object pack_set(const at::Tensor& symbols, const at::Tensor& freqs, py::handle layer_symbols, py::handle chunk_sizes, uint32_t table_log, uint32_t n_streams,
-                    int64_t cap, uint32_t single, uint32_t layer_id, uint64_t out_offset, uint64_t payload_word_offset, uint32_t stream_offset, bool record,
+                    uint32_t single, uint32_t layer_id, uint64_t out_offset, uint64_t payload_word_offset, uint32_t stream_offset, bool record,
                     uint64_t stream) {
     PyObject* const o = layer_symbols.ptr();
     if (!PyList_Check(o) && !PyTuple_Check(o)) return none();
@@ -111,8 +111,7 @@ py::object pack_set(const at::Tensor& symbols, const at::Tensor& freqs, py::hand
         bound += words;
         if (n_chunks >= (1ull << 31)) return none();
     }
-    const uint64_t words = cap < 0 ? bound : uint64_t(cap);
-    const uint64_t chunk_count = std::max<uint64_t>(n_chunks, 1u), hdr_words = std::max<uint64_t>(n_chunks * n_streams, 4u), payload_words = std::max<uint64_t>(words, 4u);
+    const uint64_t chunk_count = std::max<uint64_t>(n_chunks, 1u), hdr_words = std::max<uint64_t>(n_chunks * n_streams, 4u), payload_words = std::max<uint64_t>(bound, 4u);
     const uint64_t scratch_bytes = anszp_pack_scratch_bytes(uint32_t(count), int(table_log));
     at::Tensor chunks, hdr, payload, used, status, scratch;
     int rc = 0;
@@ -140,7 +139,7 @@ py::object pack_set(const at::Tensor& symbols, const at::Tensor& freqs, py::hand
             a.n_layers = uint32_t(count); a.table_log = table_log; a.n_streams = n_streams;
             a.single = single; a.layer_id = layer_id; a.stream_offset = stream_offset; a.clear = 1u;
             a.out_offset = out_offset; a.payload_word_offset = payload_word_offset;
-            a.chunks = data<anszp_chunk_t>(chunks); a.stream_hdr = data<uint32_t>(hdr); a.payload = data<uint32_t>(payload); a.payload_cap_words = words;
+            a.chunks = data<anszp_chunk_t>(chunks); a.stream_hdr = data<uint32_t>(hdr); a.payload = data<uint32_t>(payload); a.payload_cap_words = bound;
             a.clear_chunks = chunk_count; a.clear_stream_hdr = hdr_words; a.clear_payload_words = payload_words;
             a.payload_words_used = data<uint64_t>(used); a.status = data<uint32_t>(status); a.scratch = scratch.data_ptr(); a.scratch_bytes = scratch_bytes;
             rc = anszp_pack_set_device(&a, stream_of(stream));

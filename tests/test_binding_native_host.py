@@ -33,7 +33,7 @@ seen = ctypes.CDLL(sys.argv[1] + "/libanszp.so").anszp_calls_seen
 bytes_, ints = torch.zeros(64, dtype=torch.uint8), torch.zeros(256, dtype=torch.int32)
 assert N.dequant_zp(bytes_, 3, 0.5, 1, 0, None, 0).shape == (64,)
 assert N.build_tables_device(ints, 1, 4, 128, None, 0).shape == (128,)
-assert len(N.pack_set(bytes_, ints, [30, 34], 16, 4, 8, PACK_ARGS 0)) == 5
+assert len(N.pack_set(bytes_, ints, [30, 34], 16, 4, 8, 0, 0, 0, 0, 0, False, 0)) == 5
 assert seen() == 300, seen()
 """
 
@@ -45,8 +45,7 @@ def test_the_interpreter_lock_is_free_while_the_library_is_called(tmp_path):
     (tmp_path / "stand_in.cpp").write_text(STAND_IN)
     subprocess.check_call(["g++", "-O1", "-fPIC", "-shared", "-o", str(tmp_path / "libanszp.so"), str(tmp_path / "stand_in.cpp")])
     shutil.copy(libbuild.HOST_LIB, tmp_path)
-    script = CALLS.replace("PACK_ARGS", "-1, 0, 0, 0, 0, 0, False,")
-    r = subprocess.run([sys.executable, "-c", script, str(tmp_path)], capture_output=True, text=True, timeout=300, cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    r = subprocess.run([sys.executable, "-c", CALLS, str(tmp_path)], capture_output=True, text=True, timeout=300, cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
     assert r.returncode == 0, r.stderr[-2000:]
 
 
