@@ -333,8 +333,8 @@ def test_a_layer_without_symbols_still_has_its_frequencies_checked():
 
 @pytest.mark.parametrize("polls", [1, 2])
 def test_chunks_whose_place_is_not_known_in_time_are_written_all_the_same(orc, polls):
-    """Workgroups wait for the word counts of the chunks before theirs; with the bound lowered from the host most give up,
-    and the launch behind them writes those chunks."""
+    """Workgroups wait for the word counts of the chunks before theirs; with the bound lowered from the host most give up, and
+    where all streams fit LDS (64 rows of at most 11 bits do) the last workgroup to be done writes those chunks."""
     w = W.tiny(seed=11, n=300 * 4096 + 77, bitwidth=5, n_streams=64, chunk_size=4096, table_log=11, p0=0.6)
     try:
         B.lib().anszp_test_set_spin_limit(polls)
@@ -384,6 +384,18 @@ def test_jobs_by_the_launches_arguments(orc, n_layers):
     assert np.array_equal(hdr, c.stream_hdr) and np.array_equal(payload[:used], c.payload) and np.all(payload[used:] == 0xFFFFFFFF)
 
 
+def _pack_layer_without_scratch(sym, freqs, R, N, chunk, cap, layer_id=0, out_offset=0, payload_word_offset=0, stream_offset=0):
+    """anszp_pack_layer_device into cleared results; sym, freqs on the GPU."""
+    nc = -(-sym.numel() // chunk)
+    out = (torch.zeros(nc * B.CHUNK_DTYPE.itemsize, dtype=torch.uint8, device="cuda:0"), torch.zeros(nc * N, dtype=torch.int32, device="cuda:0"),
+           torch.full((cap,), -1, dtype=torch.int32, device="cuda:0"), torch.zeros(1, dtype=torch.int64, device="cuda:0"), torch.zeros(2, dtype=torch.int32, device="cuda:0"))
+    assert B.lib().anszp_pack_layer_device(sym.data_ptr(), sym.numel(), freqs.data_ptr(), R, N, chunk, layer_id, out_offset, payload_word_offset, stream_offset,
+                                           out[0].data_ptr(), out[1].data_ptr(), out[2].data_ptr(), cap, out[3].data_ptr(), out[4].data_ptr(),
+                                           torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    return out
+
+
 def _pack_without_scratch(w, c):
     """anszp_pack_layers_device: nothing but the results."""
     syms = w.symbols()
@@ -412,10 +424,7 @@ def test_the_entry_points_without_scratch_memory(orc, chunk, N):
     sym, f = w.symbols()[1], torch.from_numpy(c.freqs[1].astype(np.uint32).view(np.int32)).to("cuda:0")
     s = torch.from_numpy(sym).to("cuda:0")
     chunks, hdr, payload, used, status = B.pack_layer_device(s, f, 11, N, chunk, 3, 64, 8, 5)
-    again = [torch.zeros_like(chunks), torch.zeros_like(hdr), torch.full_like(payload, -1), torch.zeros_like(used), torch.zeros_like(status)]
-    assert B.lib().anszp_pack_layer_device(s.data_ptr(), len(sym), f.data_ptr(), 11, N, chunk, 3, 64, 8, 5, again[0].data_ptr(), again[1].data_ptr(),
-                                           again[2].data_ptr(), payload.numel(), again[3].data_ptr(), again[4].data_ptr(),
-                                           torch.cuda.current_stream().cuda_stream) == 0
+    again = _pack_layer_without_scratch(s, f, 11, N, chunk, payload.numel(), 3, 64, 8, 5)
     for a, b in zip((chunks, hdr, payload, used, status), again):
         assert torch.equal(a, b)
 
@@ -453,3 +462,58 @@ def test_many_tables_of_many_symbols_are_worked_out_by_the_whole_chip():
     for a, b in zip((chunks, hdr, payload, used, status), again):
         assert torch.equal(a, b)
     assert here < 1.8 * there, (here, there)
+
+
+# ---- Given-up waits where some stream may not fit LDS, or there is no scratch memory: the launch behind (encode_rest) writes the chunks
+# that were given up, those that fitted LDS among them, and those with a stream that did not fit.
+def _long_streams():
+    """1,024 rows a chunk at 2^12 states: mostly dominant layers, whose streams fit, around a dense one, whose streams do not."""
+    dense = W.Layer("dense", (1, 1, 1, 65536 + 3000), 8, 128, 0.02, np.full(256, 1 / 256), 5)
+    thin = [W.tiny(seed=s, n=n, bitwidth=3, n_streams=64, chunk_size=65536, table_log=12, p0=0.95).layers[0] for s, n in enumerate((12 * 65536 + 5, 9 * 65536))]
+    return W.Workload("long", [thin[0], dense, thin[1]], 12, 64, 65536, "bf16")
+
+
+@pytest.mark.parametrize("polls", [1, 2, 0])
+def test_given_up_chunks_are_written_by_the_launch_behind(orc, polls):
+    from helpers import oracle_encode
+    w = _long_streams()
+    c = oracle_encode(orc, w)
+    fits = 32 * 138                                                # bits of a stream that LDS holds
+    bits = (c.stream_hdr >> 16).reshape(-1, 64).max(axis=1) * 32
+    assert (bits < fits).sum() > 20 and (bits > fits).sum() >= 1
+    syms = [torch.from_numpy(x).to("cuda:0") for x in w.symbols()]
+    f = torch.from_numpy(c.freqs.astype(np.uint32).view(np.int32)).to("cuda:0")
+    one = orc.encode_layers([w.symbols()[0]], 12, 64, 65536)
+    single = W.Workload("one", w.layers[:1], 12, 64, 65536, "bf16")
+    try:
+        B.lib().anszp_test_set_spin_limit(polls)
+        _same(c, w, B.pack_layers_device(torch.cat(syms), [t.numel() for t in syms], f, 12, 64, 65536))
+        _same(c, w, _pack_without_scratch(w, c))
+        _same(one, single, B.pack_layer_device(syms[0], f[0], 12, 64, 65536))
+        _same(one, single, _pack_layer_without_scratch(syms[0], f[0], 12, 64, 65536, len(one.payload) + 8))
+    finally:
+        B.lib().anszp_test_set_spin_limit(0)
+
+
+@pytest.mark.parametrize("table_log,chunk", [(10, 1000), (12, 65536)])       # the last workgroup; the launch behind
+def test_a_layer_of_bad_frequencies_in_front_of_given_up_chunks(orc, table_log, chunk):
+    """Its chunks have no words but a place, which is not known in time either."""
+    from helpers import oracle_encode
+    layers = [W.tiny(seed=s, n=9 * chunk + 17 * s, bitwidth=4, n_streams=64, chunk_size=chunk, table_log=table_log, p0=0.9).layers[0] for s in range(5)]
+    w = W.Workload("bad", layers, table_log, 64, chunk, "bf16")
+    c = oracle_encode(orc, w)
+    syms = w.symbols()
+    s = torch.from_numpy(np.concatenate(syms)).to("cuda:0")
+    for bad in ([1], [0, 1], [3, 4], [0, 4]):
+        f = torch.from_numpy(c.freqs.astype(np.uint32).view(np.int32)).to("cuda:0").clone()
+        f[bad, 0] += 1
+        pack = lambda: B.pack_layers_device(s, [len(x) for x in syms], f, table_log, 64, chunk)
+        expect = pack()
+        assert expect[4].tolist() == [B.ST_BAD_FREQ, len(bad)] and 0 < int(expect[3].item()) < len(c.payload)
+        try:
+            B.lib().anszp_test_set_spin_limit(1)
+            for _ in range(3):
+                for a, b in zip(pack(), expect):
+                    assert torch.equal(a, b)
+        finally:
+            B.lib().anszp_test_set_spin_limit(0)
