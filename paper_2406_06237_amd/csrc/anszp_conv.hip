@@ -468,6 +468,7 @@ __device__ __forceinline__ anszp_layer_t decode_panel(const ConvParams& p, uint8
             fetch(nxt, nxt_data);
         }
         const uint32_t j = wave + i * kWaves;
+        // (LDS addresses count from 0: the kernels' only LDS is what their launch asks for, which begins there)
         if (!cur.ok) err |= ANSZP_ST_BAD_DESC;                    // its rows stay the dominant symbol
         else err |= decode_chunk_to_panel<P16>(p, cur, cur_data, kStageBytes, ahead_bytes - 8u, wave * (kStageWords * 4u),
                                                p.panel_off + j * p.rows_per_chunk * p.row_stride * kElem, lane, int32_t(lay.zero_point));

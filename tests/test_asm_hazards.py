@@ -1,6 +1,7 @@
 """Hand-written gfx950 code is not seen by the compiler's hazard recogniser.  On this chip a lane read
 (v_readfirstlane / v_readlane) must not directly follow the VALU instruction that writes the register it
-reads (one wait state); this test reads the inline assembly of the HIP sources and checks that rule."""
+reads (one wait state); this test reads the inline assembly of the HIP sources and checks that rule.
+Another reads where the fused convolution's LDS begins, which its kernels take to be address 0."""
 import os
 import re
 
@@ -47,3 +48,19 @@ def test_no_lane_read_directly_behind_the_write_of_its_register():
                 written = _vgprs(prev_args.split(",")[0])
                 assert not (written & read), f"{name}:{no}: {op} {args} directly behind {prev_op} {prev_args}"
     assert checked >= 4                       # the look-ahead kernel's block reads lanes in its loop and its wait
+
+
+def test_the_fused_convolution_has_no_lds_but_what_its_launch_asks_for():
+    """Its panels are decoded to LDS addresses that count from 0.  LDS asked for at launch begins behind all that a kernel declares
+    itself, so a single __shared__ variable of the kernels' own would move it."""
+    seen, todo, declared = set(), ["anszp_conv.hip"], []
+    while todo:
+        name = todo.pop()
+        if name in seen or not os.path.exists(os.path.join(CSRC, name)):
+            continue
+        seen.add(name)
+        text = open(os.path.join(CSRC, name)).read()
+        todo += re.findall(r'#include "([^"]+)"', text)
+        declared += [line.strip() for line in re.sub(r"//.*", "", text).splitlines() if "__shared__" in line]
+    assert len(seen) >= 4 and len(declared) == 2
+    assert all(re.fullmatch(r"extern __shared__ __attribute__\(\(aligned\(16\)\)\) uint8_t lds\[\];", d) for d in declared), declared
