@@ -1339,7 +1339,6 @@ Reciprocal reciprocal(uint32_t d) {
 
 // The whole call in launches of at most `images` images.
 int conv_sliced(ConvParams p, const anszp_conv_args_t& a, uint32_t images, uint32_t cus, int device, hipStream_t s) {
-    const uint32_t widest = a.kw != 3 ? kPoint : a.stride == 1 ? kShift : kRow;
     p.x_image = a.in_h * a.in_w * a.cin;
     p.y_image = p.out_h * p.out_w * a.cout;
     p.panel_off = kStageBytes + (16u << a.table_log);
@@ -1356,20 +1355,11 @@ int conv_sliced(ConvParams p, const anszp_conv_args_t& a, uint32_t images, uint3
         p.y = static_cast<uint8_t*>(a.y) + uint64_t(first) * p.y_image * (p.y_bf16 ? 2u : 4u);
         p.x_bytes = uint32_t(uint64_t(n) * p.x_image * 2u);
         p.y_bytes = uint32_t(uint64_t(n) * p.y_image * (p.y_bf16 ? 2u : 4u));
-        // (without padding kShift takes two pixels more per row: narrow images are better off with kRow)
-        auto plan_of = [&](uint32_t mode) {
-            const uint32_t columns = p.out_w + (mode == kShift && a.pad == 0u ? 2u : 0u);
-            return plan_half_tile(a, mode, p.K, p.row_stride, (n * p.out_h * columns + 15u) / 16u, cus);
-        };
-        uint32_t mode = widest;
-        SlicedPlan plan = plan_of(mode);
-        if (mode == kShift && a.pad == 0u) {
-            const SlicedPlan by_row = plan_of(kRow);
-            if (by_row.clocks < plan.clocks) { plan = by_row; mode = kRow; }
-        }
+        const CallPlan call = plan_call(a, p.K, p.row_stride, p.out_h, p.out_w, n, cus);
+        const SlicedPlan& plan = call.plan;
         if (!plan.mr) return ANSZP_E_RANGE;
-        p.first_column = mode == kShift && a.pad == 0u ? 1u : 0u;
-        p.columns = p.out_w + 2u * p.first_column;
+        p.first_column = call.first_column;
+        p.columns = call.columns;
         magic(p.columns, p.columns_magic, p.columns_shift);
         p.n_pixels = n * p.out_h * p.columns;
         p.n_mtiles = a.cout / plan.rows;
@@ -1383,7 +1373,7 @@ int conv_sliced(ConvParams p, const anszp_conv_args_t& a, uint32_t images, uint3
         p.wave_tiles_rest = plan.round_tiles % p.t_groups;
         p.round_tiles = plan.round_tiles;
         p.slice_units = plan.slice_units;
-        const int rc = launch_sliced(p, plan.rows, plan.p16, mode, plan.qt, device, p.n_mtiles * plan.splits, plan.lds_bytes, s);
+        const int rc = launch_sliced(p, plan.rows, plan.p16, call.mode, plan.qt, device, p.n_mtiles * plan.splits, plan.lds_bytes, s);
         if (rc != ANSZP_OK) return rc;
     }
     return ANSZP_OK;

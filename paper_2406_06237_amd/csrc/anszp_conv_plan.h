@@ -101,4 +101,19 @@ inline SlicedPlan plan_half_tile(const anszp_conv_args_t& a, uint32_t mode, uint
     return half.rows && half.clocks + (best.p16 ? 0u : half.clocks / 5u) < best.clocks ? half : best;
 }
 
+// How `images` images are convolved: the way a unit's vectors are loaded, and the plan.  The columns of an output row that are
+// gone through begin first_column before it.
+struct CallPlan { uint32_t mode, first_column, columns; SlicedPlan plan; };
+inline CallPlan plan_call(const anszp_conv_args_t& a, uint32_t K, uint32_t row_stride, uint32_t out_h, uint32_t out_w, uint32_t images, uint32_t cus) {
+    // (without padding kShift takes two pixels more per row: narrow images are better off with kRow)
+    auto plan_of = [&](uint32_t mode) {
+        const uint32_t first = mode == kShift && a.pad == 0u ? 1u : 0u, columns = out_w + 2u * first;
+        return CallPlan{mode, first, columns, plan_half_tile(a, mode, K, row_stride, (images * out_h * columns + 15u) / 16u, cus)};
+    };
+    const CallPlan best = plan_of(a.kw != 3 ? kPoint : a.stride == 1 ? kShift : kRow);
+    if (!best.first_column) return best;
+    const CallPlan by_row = plan_of(kRow);
+    return by_row.plan.clocks < best.plan.clocks ? by_row : best;
+}
+
 #endif

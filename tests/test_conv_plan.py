@@ -6,6 +6,8 @@ import subprocess
 
 import pytest
 
+from decode_choice import compile_host
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 DRIVER = r"""
@@ -88,3 +90,30 @@ def test_plans_of_half_a_row_tile(tmp_path):
     driver = driver.replace("std::mt19937 rng(1);", "std::mt19937 rng(1); uint32_t halves = 0;").replace("std::puts", "if (halves > 2000u) std::puts")
     assert driver.count("halves") == 3 and driver.count("p.rows") >= 6
     _run(tmp_path, driver)
+
+
+CALLS = r"""
+#include <cmath>
+#include <cstdio>
+#include "anszp_conv_plan.h"
+int main() {
+    anszp_conv_args_t a{};
+    while (std::scanf("%u %u %u %u %u %u %u %u %u %u %u", &a.cout, &a.cin, &a.kh, &a.kw, &a.batch, &a.in_h, &a.in_w, &a.stride, &a.pad, &a.rows_per_chunk, &a.x_layout) == 11) {
+        a.y_layout = a.x_layout; a.y_dtype = ANSZP_OUT_F32; a.table_log = 12u;
+        const uint32_t K = a.cin * a.kh * a.kw, out_h = (a.in_h + 2u * a.pad - a.kh) / a.stride + 1u, out_w = (a.in_w + 2u * a.pad - a.kw) / a.stride + 1u;
+        std::printf("%u\n", plan_call(a, K, ((K + 31u) & ~31u) + kRowPad, out_h, out_w, a.batch, 256u).plan.rows);
+    }
+    return 0;
+}
+"""
+
+
+def test_the_gpu_tests_of_half_a_row_tile_run_panels_of_eight_rows(tmp_path):
+    import test_gpu_conv
+    if shutil.which("g++") is None:
+        pytest.skip("no host compiler")
+    exe = compile_host(CALLS, str(tmp_path), "calls")
+    calls = [(*shape, *rest, layout) for shape, *rest in test_gpu_conv.HALF_TILES for layout in (0, 1)]
+    r = subprocess.run([exe], input="\n".join(" ".join(map(str, c)) for c in calls), capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0 and r.stdout.split() == ["8"] * len(calls)
+    assert {c[9] for c in calls} == {1, 2, 4, 8}

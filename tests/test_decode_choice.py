@@ -5,6 +5,7 @@ import subprocess
 import pytest
 
 import test_gpu_few as few
+import test_gpu_plan as plan
 from decode_choice import compile_host, kernel_of
 from helpers import host_from_oracle, oracle_encode
 
@@ -56,3 +57,22 @@ def test_the_gpu_tests_of_many_words_run_what_they_name(orc, table_log, n_short,
     h = host_from_oracle(oracle_encode(orc, w), w)
     words = int(h.chunks["payload_words"].max())
     assert kernel_of(h) == kernel and (9000 < words <= 11672 if table_log == 12 else 5500 < words <= 5912)
+
+
+def _kernel(orc, w, planned=False):
+    return kernel_of(host_from_oracle(oracle_encode(orc, w), w), planned)
+
+
+@pytest.mark.parametrize("n_chunks,table_log,kernel", few.NUMBERS)
+def test_numbers_of_chunks(orc, n_chunks, table_log, kernel):
+    assert _kernel(orc, few.numbers_of_chunks(n_chunks, table_log)) == kernel
+
+
+@pytest.mark.parametrize("n_layers,chunks,table_log,dtype,kernel", few.LAYERS)
+def test_layers_of_few_chunks(orc, n_layers, chunks, table_log, dtype, kernel):
+    assert _kernel(orc, few.layers_of_few_chunks(n_layers, chunks, table_log, dtype)) == kernel
+
+
+def test_planned_calls(orc):
+    workloads = plan._workloads()
+    assert {name: _kernel(orc, workloads[name], True) for name in plan.KERNELS} == plan.KERNELS

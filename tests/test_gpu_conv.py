@@ -25,10 +25,10 @@ def _layer(shape, bitwidth, p0, seed, scale=0.03125, channel_scales=None):
 
 
 def _case(orc, shape, B_, H, Wd, stride, pad, bitwidth=4, p0=0.7, n_streams=64, table_log=12, seed=1, per_channel=False,
-          x_layout="nhwc", y_layout="nhwc"):
+          x_layout="nhwc", y_layout="nhwc", rows=None):
     cout, cin, kh, kw = shape
     K = cin * kh * kw
-    rows = B.conv_rows_per_chunk(K)
+    rows = rows or B.conv_rows_per_chunk(K)
     cs = None
     if per_channel:
         cs = (0.01 + 0.002 * np.arange(cout)).astype(np.float32)
@@ -504,22 +504,29 @@ def test_channels_that_are_missing_let_no_value_through(orc, shape, stride, pad,
     test_a_value_that_is_not_finite_reaches_its_own_windows_only(orc, shape, stride, pad, value)
 
 
-@pytest.mark.parametrize("shape,B_,H,Wd,stride,pad", [
-    ((16, 512, 3, 3), 1, 7, 7, 1, 1),             # K = 4608: two panels of half a row tile, the reduction in slices
-    ((48, 512, 3, 3), 1, 1, 1, 1, 1),             # one pixel
-    ((32, 448, 3, 3), 3, 9, 9, 2, 1),             # stride 2: three loads a unit
-    ((16, 344, 3, 3), 2, 13, 5, 1, 1),            # channels that are no multiple of 32, images narrower than a column tile
-    ((32, 256, 3, 3), 1, 56, 56, 2, 1),           # K = 2304, 784 pixels
-    ((32, 504, 3, 3), 2, 17, 16, 1, 0),           # without padding
-    ((16, 4608, 1, 1), 1, 9, 9, 1, 0),            # 1 x 1 with the longest rows
-    ((32, 2048, 1, 1), 4, 7, 7, 2, 0),            # two rows a chunk
-])
+# (the last number: weight rows a chunk.  That these are panels of eight rows is looked at in test_conv_plan.py)
+HALF_TILES = [
+    ((16, 512, 3, 3), 1, 7, 7, 1, 1, 1),          # K = 4608: two panels of half a row tile, the reduction in slices
+    ((48, 512, 3, 3), 1, 1, 1, 1, 1, 1),          # one pixel
+    ((32, 448, 3, 3), 3, 9, 9, 2, 1, 1),          # stride 2: three loads a unit
+    ((16, 344, 3, 3), 2, 13, 5, 1, 1, 1),         # channels that are no multiple of 32, images narrower than a column tile
+    ((32, 256, 3, 3), 1, 56, 56, 2, 1, 1),        # K = 2304, 784 pixels
+    ((32, 504, 3, 3), 2, 17, 16, 1, 0, 1),        # without padding
+    ((16, 4608, 1, 1), 1, 9, 9, 1, 0, 1),         # 1 x 1 with the longest rows
+    ((32, 2048, 1, 1), 4, 7, 7, 2, 0, 1),
+    ((32, 512, 3, 3), 1, 7, 7, 1, 1, 2),          # two, four and eight rows a chunk: a chunk the whole panel
+    ((32, 504, 3, 3), 2, 9, 9, 2, 1, 4),
+    ((16, 4608, 1, 1), 1, 14, 14, 1, 0, 8),
+]
+
+
+@pytest.mark.parametrize("shape,B_,H,Wd,stride,pad,rows", HALF_TILES)
 @pytest.mark.parametrize("layout", ["nhwc", "c8"])
-def test_panels_of_half_a_row_tile(orc, shape, B_, H, Wd, stride, pad, layout):
+def test_panels_of_half_a_row_tile(orc, shape, B_, H, Wd, stride, pad, rows, layout):
     """Long rows and few pixels: eight output channels a workgroup.  The lower half of a matrix instruction's rows repeats the upper
     one and must reach no output: neighbouring panels write the channels beside theirs."""
-    _check(*_case(orc, shape, B_, H, Wd, stride, pad, bitwidth=5, p0=0.6, seed=shape[1] + H, x_layout=layout, y_layout=layout))
-    _check(*_case(orc, shape, B_, H, Wd, stride, pad, seed=shape[1], per_channel=True, x_layout=layout, y_layout=layout))
+    _check(*_case(orc, shape, B_, H, Wd, stride, pad, bitwidth=5, p0=0.6, seed=shape[1] + H, x_layout=layout, y_layout=layout, rows=rows))
+    _check(*_case(orc, shape, B_, H, Wd, stride, pad, seed=shape[1], per_channel=True, x_layout=layout, y_layout=layout, rows=rows))
 
 
 @pytest.mark.parametrize("shape,B_,H,Wd,stride,pad", [

@@ -45,11 +45,34 @@ def test_tables_streams_and_types(orc, table_log, N, dtype):
     _check(orc, _set(sizes, table_log, N, 1000, dtype, b=1 if table_log == 1 else 4 if table_log >= 5 else 2), planned=table_log % 2 == 0)
 
 
-# one, two, three and four workgroups per CU (of 256): the last with one, the first with two of them
-@pytest.mark.parametrize("n_chunks", [1, 2, 255, 256, 257, 511, 512, 513, 768, 769, 1024, 1025])
-@pytest.mark.parametrize("table_log", [9, 12])
-def test_numbers_of_chunks(orc, n_chunks, table_log):
-    _check(orc, _set([300 * n_chunks - 7], table_log, 64, 300))
+# (which kernel each of these goes to is looked at in test_decode_choice.py)
+def numbers_of_chunks(n_chunks, table_log):
+    return _set([300 * n_chunks - 7], table_log, 64, 300)
+
+
+NUMBERS = [(n, t, ("few 1" if n <= 256 or t == 12 else "few 2") if n <= 512 else "waves")
+           for t in (9, 12) for n in (1, 2, 255, 256, 257, 511, 512, 513, 768, 769, 1024, 1025)]
+
+
+@pytest.mark.parametrize("n_chunks,table_log,kernel", NUMBERS)
+def test_numbers_of_chunks(orc, n_chunks, table_log, kernel):
+    _check(orc, numbers_of_chunks(n_chunks, table_log))
+
+
+# Layers of fewer than eight chunks each, which decode_waves does not take: up to four workgroups per CU
+def layers_of_few_chunks(n_layers, chunks, table_log, dtype):
+    w = _set([190 * chunks - s % 61 for s in range(n_layers)] + [70000], table_log, 64, 190, dtype)
+    w.chunk_sizes = [190] * n_layers + [70000]                      # the last layer: one chunk of several windows
+    return w
+
+
+LAYERS = [(130, 4, 10, "u8", "few 3"), (130, 5, 10, "f32", "few 3"), (130, 5, 10, "bf16", "few 3"), (255, 3, 9, "bf16", "few 3"),
+          (192, 4, 9, "u8", "few 4"), (130, 7, 9, "f32", "few 4"), (146, 7, 8, "bf16", "few 4"), (130, 7, 10, "bf16", "few 3"), (60, 5, 12, "bf16", "few 1")]
+
+
+@pytest.mark.parametrize("n_layers,chunks,table_log,dtype,kernel", LAYERS)
+def test_layers_of_few_chunks(orc, n_layers, chunks, table_log, dtype, kernel):
+    _check(orc, layers_of_few_chunks(n_layers, chunks, table_log, dtype))
 
 
 @pytest.mark.parametrize("table_log,sizes,chunk,dtype", [

@@ -16,10 +16,19 @@ pytestmark = pytest.mark.gpu
 
 def _workloads():
     return {"tiny": W.tiny(), "config1": W.config1(), "config2": W.config2(), "config3": W.config3(),
-            "channel_grouped": W.channel_grouped(), "ragged": W.tiny(seed=11, n=70001, bitwidth=3, n_streams=48)}
+            "channel_grouped": W.channel_grouped(), "ragged": W.tiny(seed=11, n=70001, bitwidth=3, n_streams=48),
+            "one_chunk": W.tiny(seed=4, n=60000, chunk_size=65536, table_log=12),
+            "small_one_chunk": W.tiny(seed=5, n=25001, n_streams=32, chunk_size=32768, table_log=10, p0=0.9),
+            "small_ragged": W.tiny(seed=6, n=700001, bitwidth=3, n_streams=48, chunk_size=25000, table_log=11, p0=0.9),
+            "few_streams": W.tiny(seed=7, n=40001, bitwidth=3, n_streams=7, chunk_size=4000, table_log=9)}
 
 
-@pytest.mark.parametrize("name", ["tiny", "config1", "config2", "config3", "channel_grouped", "ragged"])
+# What the planned call goes to (looked at in test_decode_choice.py): a plan is made and read by the look-ahead kernel only
+KERNELS = {"tiny": "few 1", "config1": "split", "config2": "look-ahead small", "config3": "look-ahead large", "channel_grouped": "look-ahead large", "ragged": "few 1",
+           "one_chunk": "look-ahead large", "small_one_chunk": "look-ahead small", "small_ragged": "look-ahead small", "few_streams": "look-ahead small"}
+
+
+@pytest.mark.parametrize("name", list(KERNELS))
 def test_planned_decode_equals_the_oracle(orc, name):
     w = _workloads()[name]
     c = oracle_encode(orc, w)
