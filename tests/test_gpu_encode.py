@@ -517,3 +517,26 @@ def test_a_layer_of_bad_frequencies_in_front_of_given_up_chunks(orc, table_log, 
                     assert torch.equal(a, b)
         finally:
             B.lib().anszp_test_set_spin_limit(0)
+
+
+def test_a_layer_packed_in_a_captured_graph(orc):
+    """Scratch memory, counters and results belong to the graph: every replay packs the symbols that are there then."""
+    sets = [W.tiny(seed=s, n=90001, bitwidth=4, n_streams=64, chunk_size=4096, table_log=11, p0=0.6).symbols()[0] for s in range(4)]
+    freqs = B.normalize_freqs(np.bincount(np.concatenate(sets), minlength=256), 11)
+    f = torch.from_numpy(freqs.astype(np.int32)).to("cuda:0")
+    s = torch.from_numpy(sets[0]).to("cuda:0")
+    expect = []
+    for x in sets:
+        expect.append([t.clone() for t in B.pack_layer_device(torch.from_numpy(x).to("cuda:0"), f, 11, 64, 4096)])
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        out = B.pack_layer_device(s, f, 11, 64, 4096)
+    for k in (0, 1, 2, 3, 1, 0):
+        s.copy_(torch.from_numpy(sets[k]).to("cuda:0"))
+        g.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(out, expect[k]):
+            assert torch.equal(a, b), k
+        B.pack_layer_device(s, f, 11, 64, 4096)                    # (eager work between the replays)
+    assert tuple(expect[0][4].tolist()) == (0, 0)
