@@ -209,8 +209,9 @@ int anszp_pack_layer(const uint8_t* symbols, uint64_t n_symbols, const uint32_t*
 int anszp_decode(const anszp_decode_args_t* args, void* hip_stream);
 
 /* The same call with the kernel chosen by hand; results are identical for every variant.
- *   0  automatic (what anszp_decode does): 2 or 4; for more short chunks than the chip decodes at once, a kernel
- *      with a wavefront per chunk and the table shared by a workgroup; for long enough chunks of a single stream, a kernel that
+ *   0  automatic (what anszp_decode does): 2 or 4; for few short chunks, a kernel with a workgroup per chunk that does one
+ *      thing after the other; for more short chunks than the chip decodes at once, a kernel with a wavefront per chunk and
+ *      the table shared by a workgroup; for long enough chunks of a single stream, a kernel that
  *      decodes a stream from many places at once, started in guessed states and joined where they meet
  *   1  step-wise kernel: one look-up per symbol, exactly the loop of Sec. II-A / III-B; also the
  *      path any chunk takes whose compressed words exceed the on-chip window

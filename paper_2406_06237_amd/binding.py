@@ -1,4 +1,4 @@
-"""Thin ctypes binding of libanszp.so (declared in include/anszp.h).
+"""Binding of libanszp.so (declared in include/anszp.h): ctypes, and for short calls native code (csrc/anszp_torch.cpp).
 
 Argument marshalling only: every step of the decode path (table staging, tANS decode,
 dequantisation, stores) runs in the library's HIP kernels, and the container is built by the

@@ -39,7 +39,7 @@ constexpr uint32_t most_tiles(uint32_t mr, uint32_t mode) { return mode == kRow 
 // Rows: a panel of 16, 32 or 64 output channels, or (plan_half_tile) of half a row tile, 8 of them, whose matrix instructions
 // multiply every row twice and store one.  Long rows are worth that where there are few pixels: a panel of 16 x 4608 is sixteen
 // chunks, two rounds of decoding, and of bytes, since as bf16 values it does not fit LDS beside the table; half of it is one round
-// and needs no widening.  512 x 4608 weights on one 7 x 7 image 12.3 -> 8.6 us.
+// and needs no widening.  512 x 4608 weights on one 7 x 7 image 12.4 -> 8.4 us.
 struct SlicedPlan {
     uint32_t mr = 0, qt = 0, k_groups = 0, round_tiles = 0, slice_units = 0, splits = 0, tiles_per_split = 0, lds_bytes = 0;
     uint32_t rows = 0;                                            // of a panel: 16 per row tile, or 8

@@ -26,6 +26,7 @@
 //                          workgroups take them, is found per launch or read from a prepared plan.
 //   decode_waves           many short chunks: a wavefront per chunk, the table shared by a workgroup that
 //                          takes a run of them (anszp_waves.h).
+//   decode_few             few short chunks: a workgroup per chunk, staging, walk and stores (anszp_few.h).
 //   decode_split           one stream per chunk, long enough: the stream cut into segments that a workgroup's
 //                          wavefronts walk side by side from guessed states (anszp_split.h).
 // The look-ahead path needs the chunk's words to fit its LDS window; other chunks take the step-wise path

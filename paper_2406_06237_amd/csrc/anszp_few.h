@@ -1,4 +1,4 @@
-// Few chunks: a workgroup per chunk, one thing after the other (internal to the library; included by the decode kernels'
+// Few chunks: a workgroup per chunk (internal to the library; included by the decode kernels'
 // source, whose names it uses).
 //
 // The look-ahead kernel lets a chunk's walk, the placing of its symbols and the stores run beside each other, which takes
@@ -7,7 +7,7 @@
 // (walk_entries) into a buffer that holds the whole chunk, and all convert and store it.  A longer chunk comes in windows, in two
 // buffers in turn: while one wavefront walks a window the others store the one before and fill its buffer with the background.
 // What bounds it: memory's latency three times in a row (arguments, descriptor, table and words: about 2 us with the launch),
-// 45 ns a look-up, and the stores at the end.  One chunk of 4,096 symbols (2^10 states) 6.7 -> 4.7 us, 249 of 8,192 (2^12) 8.2 -> 6.2;
+// 45 ns a look-up, and the stores at the end.  One chunk of 4,096 symbols (2^10 states) 6.7 -> 4.6 us, 249 of 8,192 (2^12) 8.2 -> 6.2;
 // choose_kernel (anszp_choose.h) has the line between this kernel and the look-ahead kernel, with both sides.
 // Windows: lanes meet at a window's end, the fastest wait for the slowest (windows of 16,384 symbols: 15 % of a walk of 1.5 bits), so
 // they are few and long, and the last one, whose stores nothing hides, is a quarter of the chunk where LDS allows.  Sets that hold chunks
